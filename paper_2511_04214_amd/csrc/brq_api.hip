@@ -25,6 +25,7 @@ hipError_t device_cus(int* cus) {
         if (hipError_t e = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess) return e;
         if (v <= 0) return hipErrorInvalidDevice;
         if (hipError_t e = setup_gemm_tiled(); e != hipSuccess) return e;
+        if (hipError_t e = setup_gemm_mid(); e != hipSuccess) return e;
         if (hipError_t e = setup_gemm_smallm(); e != hipSuccess) return e;
         if (hipError_t e = setup_matrix_rotate(); e != hipSuccess) return e;
         if (hipError_t e = setup_gemm_decode_fused(); e != hipSuccess) return e;
@@ -267,7 +268,11 @@ brq_status brq_diag_mxfp4_gemm_clock(const uint8_t* aq, const uint8_t* as, brq_l
     const bool both = a_layout == BRQ_LAYOUT_TILED && w_layout == BRQ_LAYOUT_TILED;
     if (M <= 128 || !brq::tiled_gemm_supported(M, N, K, ydt == BRQ_BF16, ldy, both)) return BRQ_ERR_SHAPE;
     const brq::Operand a{aq, as, a_layout == BRQ_LAYOUT_TILED}, w{wq, ws, w_layout == BRQ_LAYOUT_TILED};
-    return launched(brq::launch_gemm_tiled(a, w, M, N, K, y, ydt == BRQ_BF16, ldy, static_cast<hipStream_t>(stream),
+    int cus = 0;
+    if (brq::device_cus(&cus) != hipSuccess) return BRQ_ERR_LAUNCH;
+    // 256 x 256 tiles unless there are too few of them to give every CU one: then 128 x 256
+    const bool half = ((M + 255) / 256) * ((N + 255) / 256) < cus;
+    return launched(brq::launch_gemm_tiled(a, w, M, N, K, y, ydt == BRQ_BF16, ldy, static_cast<hipStream_t>(stream), half,
                                            reinterpret_cast<unsigned long long*>(clock)));
 }
 
@@ -283,7 +288,7 @@ brq_status brq_diag_mxfp4_gemm_no_loads(const uint8_t* aq, const uint8_t* as, br
     if (ydt != BRQ_BF16 || M <= 128 || !brq::tiled_gemm_supported(M, N, K, true, ldy, both) ||
         ((M + 255) / 256) * ((N + 255) / 256) < 1024) return BRQ_ERR_SHAPE;
     const brq::Operand a{aq, as, a_layout == BRQ_LAYOUT_TILED}, w{wq, ws, w_layout == BRQ_LAYOUT_TILED};
-    return launched(brq::launch_gemm_tiled(a, w, M, N, K, y, true, ldy, static_cast<hipStream_t>(stream),
+    return launched(brq::launch_gemm_tiled(a, w, M, N, K, y, true, ldy, static_cast<hipStream_t>(stream), false,
                                            reinterpret_cast<unsigned long long*>(clock), true));
 }
 

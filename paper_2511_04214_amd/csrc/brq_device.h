@@ -259,7 +259,15 @@ __device__ __forceinline__ void dma16(uint32_t lds_base, const uint8_t* base, ui
                  : "memory", "scc", "m0");
 }
 
-// The same with the non-temporal hint, for data that is read once.
+// The same for the lanes of `mask` only (uniform); every lane of the wavefront is active around it.
+template <int LDS_OFF>
+__device__ __forceinline__ void dma16_masked(uint32_t lds_base, const uint8_t* base, uint32_t voff, uint64_t mask) {
+    asm volatile("s_mov_b64 exec, %4\n\ts_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1\n\t"
+                 :: "s"(lds_base), "v"(voff), "s"(base), "n"(LDS_OFF), "s"(mask)
+                 : "memory", "scc", "m0");
+}
+
+// dma16 with the non-temporal hint, for data that is read once.
 template <int LDS_OFF>
 __device__ __forceinline__ void dma16_stream(uint32_t lds_base, const uint8_t* base, uint32_t voff) {
     asm volatile("s_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\t"

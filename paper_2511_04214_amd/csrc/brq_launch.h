@@ -12,6 +12,7 @@ namespace brq {
 // brq_init() is that call made ahead of time.  Nothing else in the library outlives a call.
 hipError_t device_cus(int* cus);
 hipError_t setup_gemm_tiled();     // mxfp4_gemm_tiled.hip
+hipError_t setup_gemm_mid();       // mxfp4_gemm_mid.hip
 hipError_t setup_gemm_smallm();    // mxfp4_gemm.hip
 hipError_t setup_matrix_rotate();  // matrix_rotate_quant.hip
 hipError_t setup_gemm_decode_fused();   // mxfp4_gemm.hip
@@ -73,15 +74,21 @@ constexpr int64_t DECODE_FUSED_MAX_K = 16384;
 hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int64_t K, int64_t ldx, const int8_t* signs,
                                     const Operand& w, int64_t N, void* y, bool out_bf16, int64_t ldy, hipStream_t s);
 
-// Persistent LDS-staged kernel for large shapes (N a multiple of 256, any M; K a multiple of 512,
-// or any K when both operands are tiled, whose K padding is zero).
+// Persistent LDS-staged kernel for large shapes (K a multiple of 512, or any K when both operands are tiled,
+// whose K padding is zero; output rows in whole 16-byte chunks).
 bool tiled_gemm_supported(int64_t M, int64_t N, int64_t K, bool out_bf16, int64_t ldy, bool both_tiled);
 // clk (optional, device): receives the clock read-out of workgroup 0's first wavefront (brq_diag.h).
 // no_loads: the measurement variant without refill loads (needs clk, bf16 out and 256 x 256 tiles).
-// True if the launcher would take 256 x 256 tiles for this shape on the current device.
+// half: 128 x 256 tiles.
 hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
-                             bool out_bf16, int64_t ldy, hipStream_t s, unsigned long long* clk = nullptr,
+                             bool out_bf16, int64_t ldy, hipStream_t s, bool half, unsigned long long* clk = nullptr,
                              bool no_loads = false);
+
+// One output tile per workgroup, the tile one of a family (mxfp4_gemm_mid.hip): any M, N and pitch.
+constexpr int MID_TILES = 4;
+bool mid_gemm_supported(int64_t M, int64_t N, int64_t K, bool a_tiled, bool w_tiled);
+hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
+                           bool out_bf16, int64_t ldy, hipStream_t s);
 
 // Tiled -> row-major copy of a quantized operand.
 hipError_t launch_to_rowmajor(const uint8_t* codes_t, const uint8_t* scales_t, int64_t rows, int64_t K,

@@ -8,13 +8,10 @@
 // (row 8*(i/4) + 4*(l>>5) + i%4, column l & 31).  The 16x16x128 form: row (l & 15), group
 // (l >> 4); accumulator i is (row 4*(l>>4) + i, column l & 15).
 #include <type_traits>
-#include "brq_device.h"
+#include "mfma_fp4.h"
 #include "brq_launch.h"
 
 namespace brq {
-
-template <int V>
-struct IC { static constexpr int value = V; };
 
 // Addressing of one row of a quantized operand, valid for both layouts: the 16 code bytes of
 // group g sit at codes + (g >> 2) * cstep + (g & 3) * 16 and its scale at scales + (g >> 4) * sstep
@@ -48,6 +45,8 @@ __device__ __forceinline__ void store_out(void* y, bool out_bf16, int64_t idx, f
 }
 
 // ---- general shapes: one 32x32 output tile per wavefront, operands straight from global ----
+// The K groups are taken in the order of the LDS-staged kernels (step j of a 128-element stage: groups j and 2 + j),
+// so that a product does not depend on which of them it runs on.
 __global__ void __launch_bounds__(256) k_gemm_direct(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as,
                                                      int a_tiled, const uint8_t* __restrict__ wq,
                                                      const uint8_t* __restrict__ ws, int w_tiled, int M, int N, int K,
@@ -60,11 +59,11 @@ __global__ void __launch_bounds__(256) k_gemm_direct(const uint8_t* __restrict__
     const int groups = K / 32;
     const RowView va(aq, as, a_tiled != 0, ra, K), vw(wq, ws, w_tiled != 0, rw, K);
     v16f acc = {};
-    for (int g0 = 0; g0 < groups; g0 += 2) {
-        int g = g0 + h;
+    for (int g0 = 0; g0 < groups; g0 += (g0 & 1) ? 3 : 1) {   // step j = g0 & 1 of a stage
+        int g = g0 + 2 * h;
         v8i a = {}, b = {};
         int sca = 0, scb = 0;
-        if (g < groups) {   // odd group count: the last step's second half contributes zeros
+        if (g < groups) {   // past the last group: zeros
             v4i ta = va.group(g);
             v4i tb = vw.group(g);
             a[0] = ta[0]; a[1] = ta[1]; a[2] = ta[2]; a[3] = ta[3];
@@ -537,6 +536,50 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
     return hipGetLastError();
 }
 
+// ---- which LDS-staged kernel and output tile -------------------------------------------------
+// The candidates: the persistent kernel with its 256 x 256 and 128 x 256 tiles, and the one-tile-per-workgroup
+// kernel's family.  They are told apart by an estimate of the time, in microseconds:
+//     fixed + max(stages * alone * ceil(tiles / places), stages * full * tiles / CUs * filled + output)
+// `alone`: a stage of a tile while the chip is not full (the issue, load and LDS bound of one workgroup, at the
+// full clock); `full`: a stage's share of a chip full of them, which is what its energy costs (the chip holds 1.6
+// to 1.8 GHz of 2.4 with every CU multiplying); places = CUs x workgroups that fit one; filled: rows past M
+// are zeros in the one-tile kernel and cost half; output: 0.3 us per MB of bf16.  The constants are fitted to the six candidates'
+// times on 64 shapes (M 129 .. 8192, N 256 .. 28672, K 512 .. 11264) in each layout; there the choice is within
+// 1.3 % (tiled) and 0.8 % (row-major) of the best of the six on average, 17 % and 13 % at worst.  What it gives over
+// the rule it replaces (256 x 256, or 128 x 256 where the former do not fill the chip), tiled, us:
+// 300 x 28672 x 8192 54.3 -> 42.7; 1000 x 4096 x 11008 30.3 -> 26.6; 192 x 256 x 4096 12.6 -> 6.7.
+struct TileCost { float fixed, alone, full; };
+struct Tile { int na, mb, per_cu, mid; TileCost tiled, rowmajor; };      // 64 mb x 64 na; mid: its number there, -1 = persistent
+static const Tile TILES[2 + MID_TILES] = {
+    {4, 4, 1, -1, {6.29f, 0.487f, 0.630f}, {6.33f, 0.521f, 0.838f}},
+    {4, 2, 1, -1, {4.19f, 0.266f, 0.393f}, {4.09f, 0.342f, 0.512f}},
+    {2, 1, 2, 0, {2.90f, 0.152f, 0.152f}, {2.36f, 0.193f, 0.221f}},
+    {2, 2, 2, 1, {3.31f, 0.188f, 0.237f}, {3.04f, 0.253f, 0.330f}},
+    {2, 3, 1, 2, {4.78f, 0.216f, 0.390f}, {4.09f, 0.300f, 0.501f}},
+    {4, 3, 1, 3, {6.55f, 0.382f, 0.610f}, {6.22f, 0.441f, 0.810f}},
+};
+
+// Index into TILES, or -1 where no LDS-staged kernel takes the shape.
+static int pick_tile(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, bool out_bf16, int64_t ldy, int cus) {
+    const bool persistent = tiled_gemm_supported(M, N, K, out_bf16, ldy, a.tiled && w.tiled);
+    const bool one_tile = mid_gemm_supported(M, N, K, a.tiled, w.tiled);
+    const float stages = (float)((K + 511) / 512 * 4), output = 0.6e-6f * (float)M * (float)N * (out_bf16 ? 1.0f : 2.0f);
+    int best = -1;
+    float least = 0.0f;
+    for (int i = 0; i < 2 + MID_TILES; ++i) {
+        const Tile& t = TILES[i];
+        if (!(t.mid < 0 ? persistent : one_tile)) continue;
+        const TileCost& c = a.tiled && w.tiled ? t.tiled : t.rowmajor;
+        const int64_t tm = (M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * t.per_cu;
+        const float filled = t.mid < 0 ? 1.0f : 0.5f + 0.5f * (float)M / (float)(64 * t.mb * tm);
+        const float alone = stages * c.alone * (float)((T + places - 1) / places);
+        const float full = stages * c.full * (float)T / (float)cus * filled + output;
+        const float cost = c.fixed + (alone > full ? alone : full);
+        if (best < 0 || cost < least) { best = i; least = cost; }
+    }
+    return best;
+}
+
 hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                              bool out_bf16, int64_t ldy, hipStream_t s) {
     const int64_t Kp = (K + 511) / 512 * 512;
@@ -551,8 +594,11 @@ hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, int64_t M, int6
                            w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy);
         return hipGetLastError();
     }
-    if (M > 16 && tiled_gemm_supported(M, N, K, out_bf16, ldy, a.tiled && w.tiled)) {
-        return launch_gemm_tiled(a, w, M, N, K, y, out_bf16, ldy, s);
+    const int t = M > 16 ? pick_tile(a, w, M, N, K, out_bf16, ldy, cus) : -1;
+    if (t >= 0) {
+        const int mid = TILES[t].mid;
+        return mid < 0 ? launch_gemm_tiled(a, w, M, N, K, y, out_bf16, ldy, s, TILES[t].mb == 2)
+                       : launch_gemm_mid(mid, a, w, M, N, K, y, out_bf16, ldy, s);
     } else if (M <= 16) {
         dim3 grid((uint32_t)((N + 15) / 16));
         hipLaunchKernelGGL(k_gemm_skinny, grid, dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales,

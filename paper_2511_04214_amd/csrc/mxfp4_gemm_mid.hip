@@ -1,0 +1,337 @@
+// Medium-shape W4A4 MXFP4 product for gfx950: one output tile per workgroup, the tile chosen from a family
+// (64 MB rows x 64 NA columns) so that the shape fills the chip (the product of Sec. 2 on the MXFP4 operands
+// of Sec. 4.1).  The persistent 256 x 256 kernel is the better one where there are many tiles; here are the
+// shapes in between: a chunk of a prompt, a few hundred rows against wide weights, a projection with few columns.
+//
+// Workgroup = 4 wavefronts (2 x 2), each with NA x MB MFMA tiles of 32 x 32.  As in the persistent kernel the
+// weights are the MFMA's row operand, K is consumed in stages of 128 elements, within a stage lane half h owns
+// groups 2h and 2h + 1, and operands travel HBM -> LDS by LDS-DMA into a ring of 4 stages whose 64-byte rows
+// have their 16-byte chunks XOR-swizzled by (row >> 2) & 3.
+//
+// What differs is the fragment schedule.  A stage of these tiles is 8 to 24 MFMAs (264 to 800 cycles) long,
+// too short to hide an LDS read between its barrier and its use.  The register file has room (64 to 192
+// accumulators of 512 registers), so ALL fragments of stage t + 1 are read while stage t multiplies:
+//   start of stage t   stage t + 1 has landed, everyone's reads of stage t's buffer are done: one barrier
+//   during stage t     2 (NA + MB) fragment reads of stage t + 1, the loads of stage t + 4 into stage t's
+//                      buffer, and the MFMAs of stage t from registers filled a stage ago.
+// Nothing between the barrier and the MFMAs waits for LDS.
+//
+// K: whole superstages of 4 stages.  Tiled operands are zero-padded to that.  Row-major operands with
+// K % 512 != 0 (K % 128 == 0, K >= 512) take as their last superstage the window [K - 512, K): every load is in
+// bounds, and the stages that the window shares with the superstage before get scale bytes 0 in BOTH operands
+// (2^-127 * 2^-127 times at most 36 * 32 vanishes in an fp32 sum).
+//
+// LDS map (bytes), S = NA + MB: [0, 16K S) 4 stages x (W rows 4K NA | A rows 4K MB); then 2 scale buffers x
+// (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the ring.
+#include "mfma_fp4.h"
+#include "brq_launch.h"
+
+namespace brq {
+namespace mid {
+
+constexpr int stage_bytes(int NA, int MB) { return 4096 * (NA + MB); }
+constexpr int lds_bytes(int NA, int MB) { return 4 * stage_bytes(NA, MB) + 2 * 1024 * (NA + MB); }
+
+// VEC: every 16-byte chunk of an output row is aligned and either wholly inside or outside N (N and ldy multiples
+// of 16 / sizeof(out)); otherwise elements are stored one by one.
+template <bool OUT_BF16, int NA, int MB>
+__global__ void __launch_bounds__(256, (lds_bytes(NA, MB) <= 81920 ? 2 : 1))
+k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const uint8_t* __restrict__ wq,
+           const uint8_t* __restrict__ ws, int M, int N, int K, void* __restrict__ y, int64_t ldy, int a_tiled,
+           int w_tiled, int vec) {
+    constexpr int S = NA + MB, NM = NA * MB, NS = 2 * NM;      // MFMAs per step and per stage
+    constexpr int TM = 64 * MB, TN = 64 * NA, STAGE = stage_bytes(NA, MB), OPER = 4096 * NA;
+    constexpr int SCALE_BASE = 4 * STAGE, SCALE_BUF = 1024 * S;
+    constexpr int SPW = (S + 3) / 4;                           // scale loads per wavefront and superstage
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int wn = wave >> 1, wm = wave & 1;
+
+    TileWalk tw;
+    tw.tiles_m = (M + TM - 1) / TM;
+    tw.tiles_n = (N + TN - 1) / TN;
+    {
+        const int T = tw.tiles_m * tw.tiles_n, per_xcd = (T + 7) / 8;
+        tw.first = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+        tw.end = min(((int)(blockIdx.x & 7) + 1) * per_xcd, T);
+        tw.stride = 1;
+    }
+    if (tw.first >= tw.end) return;                            // uniform over the workgroup
+    int tm, tn;
+    tw.tile(0, tm, tn);
+    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+    const int KQ = (K + 511) / 512;
+    const int64_t Kp = (int64_t)KQ * 512;
+    const int ovd = (K == Kp || w_tiled) ? 0 : (int)((Kp - K) / 128);   // stages the last window shares with the one before
+
+    // ---- loads.  A wavefront brings 16 NA rows of W and 16 MB rows of A per stage, 16 rows x 64 bytes per
+    // instruction (lane i: chunk (i & 3) ^ ((i >> 4) & 3) of row i >> 2), and its share of the scale rows, 64
+    // rows x 16 bytes per instruction, once per superstage (wavefronts without a share repeat the last one, so that
+    // all count the same).  Every per-lane offset is relative to one uniform base per operand that moves along
+    // K; rows past the last one are clamped to it and never stored.
+    const uint32_t swz16 = (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+    auto code_off = [&](int64_t row, int64_t rows, bool tiled) -> uint32_t {
+        row = min(row, rows - 1);
+        return (tiled ? (uint32_t)((row >> 6) * (Kp / 128) * 4096 + (row & 63) * 64) : (uint32_t)(row * (K / 2))) + swz16;
+    };
+    auto scale_off = [&](int64_t row, int64_t rows, bool tiled) -> uint32_t {
+        row = min(row, rows - 1);
+        return tiled ? (uint32_t)((row >> 6) * (Kp / 512) * 1024 + (row & 63) * 16) : (uint32_t)(row * (K / 32));
+    };
+    // (bases moved to the tile's first row, so that the offsets stay below 2^32 for any M and N)
+    const int64_t wslab = n0 >> 6, aslab = m0 >> 6;            // TM and TN are multiples of 64
+    const uint8_t* const wbase = uniform_ptr(wq + (w_tiled ? wslab * (Kp / 128) * 4096 : n0 * (K / 2)));
+    const uint8_t* const abase = uniform_ptr(aq + (a_tiled ? aslab * (Kp / 128) * 4096 : m0 * (K / 2)));
+    const int64_t nrows = N - n0, mrows = M - m0;
+    uint32_t vw[NA], va[MB], vsc[SPW];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) vw[q] = code_off(wave * 16 * NA + 16 * q + (lane >> 2), nrows, w_tiled != 0);
+#pragma unroll
+    for (int q = 0; q < MB; ++q) va[q] = code_off(wave * 16 * MB + 16 * q + (lane >> 2), mrows, a_tiled != 0);
+    // Rows of A past M: their lanes' loads are masked off and their LDS rows are zero in all four stages.  The
+    // matrix cores' power depends on what they multiply, and this kernel runs at the board's power limit: a tile
+    // half of whose rows repeat row M - 1 costs as much as a full one, half of zeros close to half.
+    uint64_t ma[MB];
+#pragma unroll
+    for (int q = 0; q < MB; ++q) {
+        const int row = wave * 16 * MB + 16 * q + (lane >> 2);
+        ma[q] = __builtin_amdgcn_ballot_w64(row < mrows);
+        if (row >= mrows) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) *reinterpret_cast<v4i*>(lds + u * STAGE + OPER + row * 64 + (lane & 3) * 16) = v4i{0, 0, 0, 0};
+        }
+    }
+    const uint8_t* sbase[SPW];
+    uint32_t sdst[SPW];
+    int sstep[SPW], slast[SPW];                                // superstage to superstage, and where the last one starts
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+        const int idx = min(wave + 4 * i, S - 1);              // uniform
+        const bool isw = idx < NA, tl = isw ? w_tiled != 0 : a_tiled != 0;
+        vsc[i] = isw ? scale_off(64 * idx + lane, nrows, tl) : scale_off(64 * (idx - NA) + lane, mrows, tl);
+        const uint8_t* b = isw ? ws + (tl ? wslab * (Kp / 512) * 1024 : n0 * (K / 32))
+                               : as + (tl ? aslab * (Kp / 512) * 1024 : m0 * (K / 32));
+        sbase[i] = uniform_ptr(b);
+        sdst[i] = lds0 + SCALE_BASE + idx * 1024;
+        sstep[i] = tl ? 1024 : 16;
+        slast[i] = tl ? (KQ - 1) * 1024 : K / 32 - 16;
+    }
+    const int w_stage = w_tiled ? 4096 : 64, w_last = w_tiled ? (KQ - 1) * 16384 : K / 2 - 256;
+    const int a_stage = a_tiled ? 4096 : 64, a_last = a_tiled ? (KQ - 1) * 16384 : K / 2 - 256;
+    const uint32_t dst_w = lds0 + wave * (1024 * NA), dst_a = lds0 + OPER + wave * (1024 * MB);
+    const uint8_t *pw = wbase, *pa = abase;                    // superstage that is being loaded
+    auto dma_scales = [&](int q) {                             // superstage q into scale buffer q & 1
+        const uint32_t b = (q & 1) ? (uint32_t)SCALE_BUF : 0u;
+#pragma unroll
+        for (int i = 0; i < SPW; ++i) dma16<0>(sdst[i] + b, sbase[i] + (q == KQ - 1 ? slast[i] : q * sstep[i]), vsc[i]);
+    };
+    auto load_super = [&](int q) {
+        pw = wbase + (q == KQ - 1 ? w_last : q * 4 * w_stage);
+        pa = abase + (q == KQ - 1 ? a_last : q * 4 * a_stage);
+    };
+    // load I of stage U of that superstage, W and A alternating while there are both
+    auto dma_code = [&](auto Uc, auto Ic) {
+        constexpr int U = decltype(Uc)::value, I = decltype(Ic)::value, MN = NA < MB ? NA : MB;
+        constexpr bool W = I < 2 * MN ? (I & 1) == 0 : NA > MB;
+        constexpr int q = I < 2 * MN ? I / 2 : I - MN;
+        if constexpr (W) dma16<U * STAGE + q * 1024>(dst_w, pw + U * w_stage, vw[q]);
+        else dma16_masked<U * STAGE + q * 1024>(dst_a, pa + U * a_stage, va[q], ma[q]);
+    };
+
+    // ---- fragments and scales
+    const int sw = (r >> 2) & 3;
+    const uint8_t *wp[2][2], *ap[2][2];                        // [stage pair][step]: a ds_read's immediate reaches 64 KB
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint32_t c16 = (uint32_t)(((2 * h + j) ^ sw) << 4);
+        wp[0][j] = lds + (wn * 32 * NA + r) * 64 + c16;
+        ap[0][j] = lds + OPER + (wm * 32 * MB + r) * 64 + c16;
+        wp[1][j] = wp[0][j] + 2 * STAGE;
+        ap[1][j] = ap[0][j] + 2 * STAGE;
+    }
+    const uint8_t* const wsp = lds + SCALE_BASE + (wn * 32 * NA + r) * 16;
+    const uint8_t* const asp = lds + SCALE_BASE + 1024 * NA + (wm * 32 * MB + r) * 16;
+    const int hshift = h * 16;
+    v4i wf[2][2][NA], af[2][2][MB];                            // [stage parity][step][tile]
+    int scw[2][NA], sca[2][MB];
+    v4i srw[NA], sra[MB];                                      // a superstage's 16 scale bytes of this lane's rows
+    v16f acc[NA][MB];
+    // read I of the 2 S fragments of stage U into parity P, in the order the MFMAs take them
+    auto read_frag = [&](auto Uc, auto Pc, auto Ic) {
+        constexpr int U = decltype(Uc)::value, P = decltype(Pc)::value, J = decltype(Ic)::value / S, k = decltype(Ic)::value % S;
+        if constexpr (k >= 1 && k <= MB) af[P][J][k - 1] = *reinterpret_cast<const v4i*>(ap[U >> 1][J] + (U & 1) * STAGE + (k - 1) * 2048);
+        else {
+            constexpr int t = k == 0 ? 0 : k - MB;
+            wf[P][J][t] = *reinterpret_cast<const v4i*>(wp[U >> 1][J] + (U & 1) * STAGE + t * 2048);
+        }
+    };
+    auto read_scales = [&](auto Ic, uint32_t buf) {            // scale rows of W tile I and A tile I
+        constexpr int I = decltype(Ic)::value;
+        if constexpr (I < NA) srw[I] = *reinterpret_cast<const v4i*>(wsp + buf + I * 512);
+        if constexpr (I < MB) sra[I] = *reinterpret_cast<const v4i*>(asp + buf + I * 512);
+    };
+    // scale registers of stage U from the rows: dword U, this lane half's two bytes; `keep` is 0 for a masked stage
+    auto set_scale = [&](auto Uc, auto Pc, auto Ic, int keep) {
+        constexpr int U = decltype(Uc)::value, P = decltype(Pc)::value, I = decltype(Ic)::value;
+        if constexpr (I < NA) scw[P][I] = (int)((uint32_t)(srw[I][U] & keep) >> hshift);
+        else sca[P][I - NA] = (int)((uint32_t)(sra[I - NA][U] & keep) >> hshift);
+    };
+
+    // ---- stage U of superstage kq.  LAST: the last superstage, nothing is loaded for a successor.
+    auto stage = [&](auto Uc, auto Lastc, int kq) __attribute__((always_inline)) {
+        constexpr int U = decltype(Uc)::value, P = U & 1, NU = (U + 1) & 3;
+        constexpr bool LAST = decltype(Lastc)::value != 0, NEXT = !(LAST && U == 3);
+        // The next stage's loads have landed once only the 2 S of the two stages after it are outstanding (any
+        // scale loads among those make the wait stricter; a superstage's own scale loads are older than the 2 S
+        // youngest by the start of its predecessor's last stage, where its rows are read).
+        if constexpr (!LAST || U == 0) wait_vm_and_barrier<2 * S>();
+        else if constexpr (U == 1) wait_vm_and_barrier<S>();
+        else if constexpr (U == 2) wait_vm_and_barrier<0>();
+        else lds_wait_and_barrier();
+        const int nq = U == 3 ? kq + 1 : kq;                   // superstage of the next stage
+        const int keep = (nq == KQ - 1 && NU < ovd) ? 0 : -1;  // uniform
+        constexpr int RPS = NS >= 2 * S + 2 ? 1 : 2;           // fragment reads per slot
+        if constexpr (U == 0 && !LAST) load_super(kq + 1);
+        static_for([&](auto Sc) __attribute__((always_inline)) {
+            constexpr int s = decltype(Sc)::value, J = s / NM, X = s % NM, A = X / MB, B = X % MB;
+            mfma_fp4(acc[A][B], wf[P][J][A], af[P][J][B], IC<J>{}, scw[P][A], sca[P][B]);
+            if constexpr (NEXT) {
+                static_for([&](auto Ic) __attribute__((always_inline)) {
+                    constexpr int i = s * RPS + decltype(Ic)::value;
+                    if constexpr (i < 2 * S) read_frag(IC<NU>{}, IC<P ^ 1>{}, IC<i>{});
+                }, IC<RPS>{});
+                if constexpr (U == 3 && s < (NA > MB ? NA : MB)) read_scales(IC<s>{}, (nq & 1) ? SCALE_BUF : 0);
+                constexpr int first = NS - 1 - (S + 1) / 2;    // two scale registers per slot, done one slot before the end
+                static_assert(first >= (NA > MB ? NA : MB) - 1, "the rows are read before the registers are made from them");
+                static_for([&](auto Ic) __attribute__((always_inline)) {
+                    constexpr int i = (s - first) * 2 + decltype(Ic)::value;
+                    if constexpr (s >= first && i < S) set_scale(IC<NU>{}, IC<P ^ 1>{}, IC<i>{}, keep);
+                }, IC<2>{});
+            }
+            if constexpr (!LAST) {
+                if constexpr (U == 0 && s == 0) dma_scales(kq + 1);
+                static_for([&](auto Ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(Ic)::value;
+                    if constexpr ((2 * i + 1) * NM / S == s) dma_code(Uc, IC<i>{});
+                }, IC<S>{});
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }, IC<NS>{});
+    };
+    auto superstage = [&](auto Lastc, int kq) __attribute__((always_inline)) {
+        stage(IC<0>{}, Lastc, kq);
+        stage(IC<1>{}, Lastc, kq);
+        stage(IC<2>{}, Lastc, kq);
+        stage(IC<3>{}, Lastc, kq);
+    };
+
+    // ---- prologue: superstage 0 in flight, accumulators cleared meanwhile, stage 0 in registers
+    load_super(0);
+    dma_scales(0);
+    static_for([&](auto Uc) { static_for([&](auto Ic) { dma_code(Uc, Ic); }, IC<S>{}); }, IC<4>{});
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < MB; ++b) acc[a][b] = v16f{};
+    wait_vm_and_barrier<3 * S>();
+    static_for([&](auto Ic) { read_frag(IC<0>{}, IC<0>{}, Ic); }, IC<2 * S>{});
+    static_for([&](auto Ic) { read_scales(Ic, 0); }, IC<(NA > MB ? NA : MB)>{});
+    static_for([&](auto Ic) { set_scale(IC<0>{}, IC<0>{}, Ic, -1); }, IC<S>{});   // (a single superstage shares nothing)
+    for (int kq = 0; kq < KQ - 1; ++kq) superstage(IC<0>{}, kq);
+    superstage(IC<1>{}, KQ - 1);
+
+    // ---- output.  The accumulators were last written by MFMAs hidden in inline assembly: the compiler does not
+    // know to keep the wait states between a 16-pass MFMA and a read of its result.  Each wavefront turns its
+    // 32-row x 128-byte blocks round in 4 KB of the ring (whose last reads are behind the last barrier):
+    // chunk c of row i at i * 128 + ((c ^ (i & 7)) << 4), stored as 8 rows x 128 contiguous bytes.
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    constexpr int ES = OUT_BF16 ? 2 : 4, EPC = 16 / ES, XPB = OUT_BF16 ? 2 : 1;
+    const int64_t pitch = ldy * ES;
+    uint8_t* const ebuf = lds + wave * 4096;
+    uint8_t* const ytile = reinterpret_cast<uint8_t*>(y) + (m0 + wm * 32 * MB) * pitch + (n0 + wn * 32 * NA) * ES;
+    uint8_t* const ewr = ebuf + r * 128;
+    const uint32_t wsw = (uint32_t)((r & 7) ^ h) << 4;
+    const uint8_t* const erd = ebuf + (lane >> 3) * 128 + (((lane & 7) ^ ((lane >> 3) & 7)) << 4);
+    const int64_t mrem = mrows - wm * 32 * MB - (lane >> 3), nrem = nrows - wn * 32 * NA - (lane & 7) * EPC;
+    static_for([&](auto Xc) __attribute__((always_inline)) {
+        constexpr int X = decltype(Xc)::value, A = PairA<X, MB>::value, B = PairB<X, MB>::value;
+        float c[16];
+        read_acc8(acc[A][B], IC<0>{}, c);
+        read_acc8(acc[A][B], IC<8>{}, c);
+        if constexpr (OUT_BF16) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint32_t x0 = pack_bf16x2(c[8 * p + 0], c[8 * p + 1]), x1 = pack_bf16x2(c[8 * p + 2], c[8 * p + 3]);
+                const uint32_t y0 = pack_bf16x2(c[8 * p + 4], c[8 * p + 5]), y1 = pack_bf16x2(c[8 * p + 6], c[8 * p + 7]);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+                *reinterpret_cast<uint4*>(ewr + (wsw ^ (uint32_t)(((A & 1) * 4 + 2 * p) << 4))) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(ewr + (wsw ^ (uint32_t)(q << 5))) = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+        }
+        if constexpr (X % XPB == XPB - 1) {
+            constexpr int row = B * 32, colbytes = (OUT_BF16 ? A / 2 : A) * 128;
+            uint8_t* const dst = ytile + (row + (lane >> 3)) * pitch + colbytes + (lane & 7) * 16;
+            const int64_t cols = nrem - colbytes / ES;          // columns left from this lane's chunk on
+            typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+            u4 ob[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ob[j] = *reinterpret_cast<const u4*>(erd + j * 1024);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (row + 8 * j < mrem && cols > 0) {
+                    if (vec) {                                  // uniform
+                        __builtin_nontemporal_store(ob[j], reinterpret_cast<u4*>(dst + 8 * j * pitch));
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < EPC; ++e)
+                            if (e < cols) {
+                                if constexpr (OUT_BF16) reinterpret_cast<uint16_t*>(dst + 8 * j * pitch)[e] = (uint16_t)(ob[j][e >> 1] >> (16 * (e & 1)));
+                                else reinterpret_cast<uint32_t*>(dst + 8 * j * pitch)[e] = ob[j][e];
+                            }
+                    }
+                }
+        }
+    }, IC<NM>{});
+}
+
+using Kern = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int64_t, int, int, int);
+struct Variant { int na, mb; Kern bf16, f32; };
+#define BRQ_MID(NA, MB) {NA, MB, k_gemm_mid<true, NA, MB>, k_gemm_mid<false, NA, MB>}
+static const Variant variants[MID_TILES] = {BRQ_MID(2, 1), BRQ_MID(2, 2), BRQ_MID(2, 3), BRQ_MID(4, 3)};
+#undef BRQ_MID
+
+}  // namespace mid
+
+hipError_t setup_gemm_mid() {
+    for (const auto& v : mid::variants)
+        for (mid::Kern k : {v.bf16, v.f32})
+            if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                   mid::lds_bytes(v.na, v.mb)); e != hipSuccess) return e;
+    return hipSuccess;
+}
+
+// Whole superstages: K % 512 == 0 or both operands tiled (zero-padded), or both row-major with K a multiple of
+// 128 and at least one superstage.  Offsets inside a tile (at most 256 rows) fit 32 bits.
+bool mid_gemm_supported(int64_t M, int64_t N, int64_t K, bool a_tiled, bool w_tiled) {
+    const int64_t Kp = (K + 511) / 512 * 512;
+    const bool k_ok = K == Kp || (a_tiled && w_tiled) || (!a_tiled && !w_tiled && K % 128 == 0 && K >= 512);
+    return M > 0 && N > 0 && k_ok && Kp <= (int64_t(1) << 24);
+}
+
+hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
+                           bool out_bf16, int64_t ldy, hipStream_t s) {
+    const mid::Variant& v = mid::variants[tile];
+    const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
+    const int epc = out_bf16 ? 8 : 4, vec = N % epc == 0 && ldy % epc == 0;
+    hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb), s,
+                       a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy, (int)a.tiled, (int)w.tiled, vec);
+    return hipGetLastError();
+}
+
+}  // namespace brq

@@ -39,50 +39,17 @@
 //
 // LDS map (bytes): [0, 128K) 4 stages x (W rows 16K | A rows 16K); [128K, 144K) 2 scale
 // buffers x (W 4K | A 4K); [144K, 160K) 4 epilogue blocks.
-#include "brq_device.h"
+#include "mfma_fp4.h"
 #include "brq_launch.h"
 
 namespace brq {
 namespace tiled {
 
-constexpr int TM = 256, TN = 256, KS = 128;
+constexpr int TN = 256, KS = 128;
 constexpr int STAGE_BYTES = 32768, OPER_BYTES = 16384;
 constexpr int SCALE_BASE = 4 * STAGE_BYTES, SCALE_BUF = 8192, SCALE_OPER = 4096;
 constexpr int EPI_BASE = SCALE_BASE + 2 * SCALE_BUF;    // 147456: one 4 KB output block per wavefront
 constexpr int LDS_BYTES = EPI_BASE + 4 * 4096;          // 163840, all of the CU's 160 KB
-
-template <int V>
-struct IC { static constexpr int value = V; };
-
-// Wait until at most N of this wavefront's vector-memory operations are outstanding and all
-// its LDS reads have returned, then meet the other wavefronts.
-template <int N>
-__device__ __forceinline__ void wait_vm_and_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier\n\t" ::"n"(N) : "memory");
-}
-// Elements O .. O + 7 of an accumulator, copied to vector registers by instructions that stay where they
-// are written (volatile, ordered with the MFMAs).
-template <int O>
-__device__ __forceinline__ void read_acc8(const v16f& a, IC<O>, float (&c)[16]) {
-    asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\t"
-                 "v_accvgpr_read_b32 %3, %11\n\tv_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\t"
-                 "v_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
-                 : "=v"(c[O]), "=v"(c[O + 1]), "=v"(c[O + 2]), "=v"(c[O + 3]), "=v"(c[O + 4]), "=v"(c[O + 5]), "=v"(c[O + 6]), "=v"(c[O + 7])
-                 : "a"(a[O]), "a"(a[O + 1]), "a"(a[O + 2]), "a"(a[O + 3]), "a"(a[O + 4]), "a"(a[O + 5]), "a"(a[O + 6]), "a"(a[O + 7]));
-}
-
-// The same without a wait for global memory: the caller has already seen its loads land.
-__device__ __forceinline__ void lds_wait_and_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier\n\t" ::: "memory");
-}
-
-// Pair order of the NACC = 4 * MB accumulators of a wavefront (the order in which a tile's first stage
-// starts them and the output path takes them): index X -> W tile 2 * ((X / 2) / MB) + X % 2, A tile
-// (X / 2) % MB: the two W tiles of one 128-byte bf16 output block are neighbours.
-template <int X, int MB>
-struct PairA { static constexpr int value = 2 * ((X >> 1) / MB) + (X & 1); };
-template <int X, int MB>
-struct PairB { static constexpr int value = (X >> 1) % MB; };
 
 // f(IC<-1>), f(IC<0>), ..., f(IC<N>)
 template <class F, int N, int S = -1>
@@ -91,40 +58,6 @@ __device__ __forceinline__ void static_for_drain(F& f, IC<N> n, IC<S> = {}) {
     if constexpr (S < N) static_for_drain(f, n, IC<S + 1>{});
 }
 
-// Tiles of one workgroup.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its
-// own L2: XCD x takes the contiguous id range [x*per_xcd, (x+1)*per_xcd), and ids run down 8
-// tile rows before moving to the next tile column, so the 32 tiles an XCD works on at one
-// time form an 8 x 4 patch and share operand panels in its L2.
-struct TileWalk {
-    int first, end, stride, tiles_m, tiles_n;
-    __device__ __forceinline__ void tile(int i, int& tm, int& tn) const {
-        int id = first + i * stride;
-        int group = id / (8 * tiles_n), rem = id - group * 8 * tiles_n;
-        int rows = min(8, tiles_m - group * 8);
-        tm = group * 8 + rem % rows;
-        tn = rem / rows;
-    }
-};
-
-// The MFMAs are issued through volatile inline assembly: the compiler treats pure intrinsic
-// calls as freely movable and sinks all of a stage's MFMAs behind its memory operations,
-// which is the opposite of the interleaving this kernel lives on.  Volatile asm statements
-// keep their source order relative to each other and to the LDS reads.  The accumulator is
-// an AGPR tuple ("a"), the fragments are 4-register VGPR tuples; SEL picks scale byte 0 / 1.
-__device__ __forceinline__ void mfma_fp4(v16f& acc, const v4i& wf, const v4i& af, IC<0>, int sw, int sa) {
-    asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
-                 : "+a"(acc) : "v"(wf), "v"(af), "v"(sw), "v"(sa));
-}
-__device__ __forceinline__ void mfma_fp4(v16f& acc, const v4i& wf, const v4i& af, IC<1>, int sw, int sa) {
-    asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel:[1,1,0] op_sel_hi:[0,0,0] cbsz:4 blgp:4"
-                 : "+a"(acc) : "v"(wf), "v"(af), "v"(sw), "v"(sa));
-}
-// The same with C = 0: the first MFMA of a tile on its accumulator (step 0 of the tile's first stage)
-// starts the sum, so the 256 accumulator registers are never cleared by separate instructions.
-__device__ __forceinline__ void mfma_fp4_init(v16f& acc, const v4i& wf, const v4i& af, int sw, int sa) {
-    asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
-                 : "+a"(acc) : "v"(wf), "v"(af), "v"(sw), "v"(sa));     // (tied like the others; the old value is not read)
-}
 #define BRQ_MFMA(ACC, WF, AF, SEL, SW, SA) mfma_fp4(ACC, WF, AF, IC<SEL>{}, SW, SA)
 #define BRQ_SLOT_END() __builtin_amdgcn_sched_barrier(0)
 // Refill loads are spread over the whole stage, one every fourth slot, for all four wavefronts alike: the
@@ -144,8 +77,8 @@ struct ClockOut {};
 template <>
 struct ClockOut<true> { unsigned long long* p; };
 
-// MB = A tiles (32 rows) per wavefront: 4 -> 256 x 256 output tile, 2 -> 128 x 256 (for shapes
-// with too few 256 x 256 tiles to fill the chip; the stage is then 16 MFMA slots long).
+// MB = A tiles (32 rows) per wavefront: 4 -> 256 x 256 output tile, 2 -> 128 x 256 (the stage is then
+// 16 MFMA slots long).
 // DIAG != 0 = the measurement aids of brq_diag.h: workgroup 0 also reports the shader-clock cycles and the
 // 100 MHz ticks it ran for, and how the cycles split into prologue, K loops and epilogues.  DIAG == 2 in
 // addition issues no refill loads in the K loops: the ring keeps the first superstage the prologue brought, every
@@ -703,16 +636,12 @@ hipError_t setup_gemm_tiled() {
 }
 
 hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
-                             bool out_bf16, int64_t ldy, hipStream_t s, unsigned long long* clk, bool no_loads) {
+                             bool out_bf16, int64_t ldy, hipStream_t s, bool half, unsigned long long* clk, bool no_loads) {
     int cus = 0;
     if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
     cus = cus >= 8 ? (cus & ~7) : 8;     // whole rounds of the 8 XCDs
     K = (K + 511) / 512 * 512;   // padded K of tiled operands (a no-op otherwise)
-    // 256 x 256 tiles unless there are too few of them to give every CU one: then 128 x 256
-    const int64_t tn = (N + tiled::TN - 1) / tiled::TN;
-    const int64_t T4 = ((M + 255) / 256) * tn, T2 = ((M + 127) / 128) * tn;
-    const bool half = T4 < cus && T2 > T4;
-    const int T = (int)(half ? T2 : T4);
+    const int T = (int)((half ? (M + 127) / 128 : (M + 255) / 256) * ((N + tiled::TN - 1) / tiled::TN));
     const int grid = T < cus ? ((T + 7) & ~7) : cus;
     const dim3 g(grid);
     const int Mi = (int)M, Ni = (int)N, Ki = (int)K;
