@@ -20,15 +20,51 @@ struct SummaryArgs {
     double* sums;                   // [4] or null, added to
 };
 
-// One block per lane and pass, four passes' loads in flight (a lane's loads are 4 bytes; every load is
-// unconditional - an absent array is replaced by the scales themselves - because a load behind a branch makes
-// the compiler wait for all earlier ones).  Histogram: the edges ascend, so a scale that exceeds edge e exceeds
-// every edge below it; per edge the wavefront counts its lanes above it with one comparison and the scalar
-// unit's bit count, and bin j follows as (count above edge j - 1) - (count above edge j).  Class counts the same
-// way.  The fp64 sums are added across a wavefront's lanes in a fixed butterfly, across the workgroup's
+// Eight blocks per lane and pass, 16 bytes of each array per load (VEC; arrays that are not 16-byte aligned are read
+// 4 bytes at a time), the next pass's loads issued before this pass's blocks are looked at.  Histogram: the edges
+// ascend, so a scale that exceeds edge e exceeds every edge below it; per edge the wavefront counts its lanes above it
+// with one comparison and the scalar unit's bit count, and bin j follows as (count above edge j - 1) - (count above
+// edge j).  Class counts the same way.  The outlier sums are touched only where the wavefront has an outlier block.
+// The fp64 sums are added across a wavefront's lanes in a fixed butterfly, across the workgroup's
 // wavefronts in index order, and across workgroups by the hardware's fp64 atomic add (the generic atomicAdd on a
 // double is a compare-and-swap loop): the result depends on the order in which workgroups finish, to a few units
 // of 2^-53 times their number.
+// 4.19 M blocks with seven edges (50 MB): 19.4 -> 15.9 us; with 4-byte loads, and every one of 32 possible edges looked
+// at by the compiler's own choice, the scalar registers' contents went through vector registers (56 spilled).
+// NE: edges that are looked at, 0 (no histogram), 8, 16 or 32; those beyond nedges are +inf.  With the number known to
+// the compiler the edges and their counters stay in scalar registers.
+template <int NE>
+struct SummaryAcc {
+    unsigned int cnt[4], nlive, gt[NE ? NE : 1];     // wavefront-uniform, held by the scalar unit
+    double sum[4];
+};
+// One block per lane; `live` = this lane has one.
+template <int NE>
+__device__ __forceinline__ void summary_block(SummaryAcc<NE>& s, const SummaryArgs& a, float am, float rf, float sq, bool live, bool has_sq, bool has_ref) {
+    const unsigned long long lm = __builtin_amdgcn_ballot_w64(live);
+    const unsigned long long mo = __builtin_amdgcn_ballot_w64(rf > a.outlier) & lm;
+    const unsigned long long mr = lm & ~mo;
+    const unsigned long long mg = has_ref ? __builtin_amdgcn_ballot_w64(am > rf) : 0ull;
+    s.cnt[0] += (unsigned int)__builtin_popcountll(mr);
+    s.cnt[2] += (unsigned int)__builtin_popcountll(mr & mg);
+    const bool isr = (mr >> (threadIdx.x & 63u)) & 1ull;
+    s.sum[0] += (double)((isr && has_sq) ? sq : 0.0f);
+    s.sum[2] += (double)(isr ? am : 0.0f);
+    if (mo) {   // uniform
+        s.cnt[1] += (unsigned int)__builtin_popcountll(mo);
+        s.cnt[3] += (unsigned int)__builtin_popcountll(mo & mg);
+        const bool iso = (mo >> (threadIdx.x & 63u)) & 1ull;
+        s.sum[1] += (double)((iso && has_sq) ? sq : 0.0f);
+        s.sum[3] += (double)(iso ? am : 0.0f);
+    }
+    if constexpr (NE > 0) {
+        s.nlive += (unsigned int)__builtin_popcountll(lm);
+        const float v = live ? am : -__builtin_inff();     // above no edge
+#pragma unroll
+        for (int e = 0; e < NE; ++e) count_above<false>(s.gt[e], v, a.edges[e]);
+    }
+}
+template <bool VEC, int NE>
 __global__ void __launch_bounds__(1024) k_block_summary(SummaryArgs a) {
     __shared__ unsigned int s_gt[33];        // [e]: blocks above edge e; [32]: all blocks of the workgroup
     __shared__ unsigned int s_cnt[4];
@@ -39,51 +75,59 @@ __global__ void __launch_bounds__(1024) k_block_summary(SummaryArgs a) {
     const float* const refp = a.ref ? a.ref : a.amax;
     const float* const sqp = a.sqerr ? a.sqerr : a.amax;
     const bool has_sq = a.sqerr != nullptr, has_ref = a.ref != nullptr, lane0 = (threadIdx.x & 63u) == 0;
-    unsigned int cnt[4] = {0, 0, 0, 0}, nlive = 0, gt[32];     // wavefront-uniform, held by the scalar unit
+    SummaryAcc<NE> s;
+    s.nlive = 0;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) gt[e] = 0;
-    double sum[4] = {0.0, 0.0, 0.0, 0.0};
-    constexpr int U = 4;
-    const unsigned long long step = (unsigned long long)gridDim.x * 1024 * U;
-    for (unsigned long long i0 = (unsigned long long)blockIdx.x * 1024 * U; i0 < a.n; i0 += step) {
-        float am[U], rf[U], sq[U];
-        bool live[U];
+    for (int e = 0; e < NE; ++e) s.gt[e] = 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned long long i = i0 + (unsigned long long)u * 1024 + threadIdx.x;
-            live[u] = i < a.n;
-            const unsigned long long ic = live[u] ? i : a.n - 1;       // past the end: the last block again, masked below
-            am[u] = a.amax[ic];
-            rf[u] = refp[ic];
-            sq[u] = sqp[ic];
-        }
+    for (int k = 0; k < 4; ++k) { s.cnt[k] = 0; s.sum[k] = 0.0; }
+    constexpr unsigned int U = 8, SPAN = 1024 * U;
+    const unsigned long long step = (unsigned long long)gridDim.x * SPAN;
+    unsigned long long i0 = (unsigned long long)blockIdx.x * SPAN;
+    // (every load is unconditional - an absent array is replaced by the scales themselves - because a load behind a
+    // branch makes the compiler wait for all earlier ones)
+    struct Batch { v4f am[2], rf[2], sq[2]; };
+    auto load = [&](unsigned long long at, Batch& b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned long long lm = __builtin_amdgcn_ballot_w64(live[u]);
-            const unsigned long long mo = __builtin_amdgcn_ballot_w64(rf[u] > a.outlier) & lm;
-            const unsigned long long mr = lm & ~mo;
-            const unsigned long long mg = has_ref ? __builtin_amdgcn_ballot_w64(am[u] > rf[u]) : 0ull;
-            cnt[0] += (unsigned int)__builtin_popcountll(mr);
-            cnt[1] += (unsigned int)__builtin_popcountll(mo);
-            cnt[2] += (unsigned int)__builtin_popcountll(mr & mg);
-            cnt[3] += (unsigned int)__builtin_popcountll(mo & mg);
-            const bool isr = (mr >> (threadIdx.x & 63u)) & 1ull, iso = (mo >> (threadIdx.x & 63u)) & 1ull;
-            sum[0] += (double)((isr && has_sq) ? sq[u] : 0.0f);
-            sum[1] += (double)((iso && has_sq) ? sq[u] : 0.0f);
-            sum[2] += (double)(isr ? am[u] : 0.0f);
-            sum[3] += (double)(iso ? am[u] : 0.0f);
-            if (a.hist) {   // uniform; the edges beyond nedges are +inf, eight at a time behind a uniform test
-                nlive += (unsigned int)__builtin_popcountll(lm);
+        for (int q = 0; q < 2; ++q) {
+            if constexpr (VEC) {
+                const unsigned long long i = at + q * 4096u + threadIdx.x * 4u;
+                b.am[q] = *reinterpret_cast<const v4f*>(a.amax + i);
+                b.rf[q] = *reinterpret_cast<const v4f*>(refp + i);
+                b.sq[q] = *reinterpret_cast<const v4f*>(sqp + i);
+            } else {
 #pragma unroll
-                for (int e0 = 0; e0 < 32; e0 += 8)
-                    if (e0 < a.nedges) {
-#pragma unroll
-                        for (int e = e0; e < e0 + 8; ++e)
-                            gt[e] += (unsigned int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(am[u] > a.edges[e]) & lm);
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    const unsigned long long i = at + q * 4096u + u * 1024u + threadIdx.x;
+                    b.am[q][u] = a.amax[i];
+                    b.rf[q][u] = refp[i];
+                    b.sq[q][u] = sqp[i];
+                }
             }
         }
+    };
+    Batch cur;
+    if (i0 + SPAN <= a.n) load(i0, cur);
+    for (; i0 + SPAN <= a.n; i0 += step) {
+        Batch nxt;
+        load(i0 + step + SPAN <= a.n ? i0 + step : i0, nxt);       // (nothing follows: this one again)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) summary_block(s, a, cur.am[q][u], cur.rf[q][u], cur.sq[q][u], true, has_sq, has_ref);
+        cur = nxt;
     }
+    if (i0 < a.n) {   // the ragged end: one workgroup
+        for (unsigned int u = 0; u < U; ++u) {
+            const unsigned long long i = i0 + u * 1024u + threadIdx.x;
+            const bool live = i < a.n;
+            const unsigned long long ic = live ? i : a.n - 1;
+            summary_block(s, a, a.amax[ic], refp[ic], sqp[ic], live, has_sq, has_ref);
+        }
+    }
+    unsigned int (&cnt)[4] = s.cnt;
+    double (&sum)[4] = s.sum;
+    const unsigned int nlive = s.nlive;
     const unsigned int wave = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -95,14 +139,14 @@ __global__ void __launch_bounds__(1024) k_block_summary(SummaryArgs a) {
             if (cnt[k]) atomicAdd(&s_cnt[k], cnt[k]);
         }
     }
-    if (lane0 && a.hist) {
+    if (lane0 && NE > 0) {
         atomicAdd(&s_gt[32], nlive);
 #pragma unroll
-        for (int e = 0; e < 32; ++e)
-            if (gt[e]) atomicAdd(&s_gt[e], gt[e]);
+        for (int e = 0; e < NE; ++e)
+            if (s.gt[e]) atomicAdd(&s_gt[e], s.gt[e]);
     }
     __syncthreads();
-    if (a.hist && threadIdx.x <= (unsigned)a.nedges) {
+    if (NE > 0 && threadIdx.x <= (unsigned)a.nedges) {
         const unsigned int above_prev = threadIdx.x == 0 ? s_gt[32] : s_gt[threadIdx.x - 1];
         const unsigned int above_this = threadIdx.x == (unsigned)a.nedges ? 0u : s_gt[threadIdx.x];
         if (above_prev != above_this) atomicAdd(&a.hist[threadIdx.x], (unsigned long long)(above_prev - above_this));
@@ -127,9 +171,15 @@ hipError_t launch_block_summary(const float* amax, const float* sqerr, const flo
     // One workgroup of 16 wavefronts per compute unit at most: every workgroup ends with an atomic per output
     // word, and atomics on the same few words from thousands of workgroups would take longer than the pass
     // over the data.
-    const int64_t want = (n + 4095) / 4096;
+    const int64_t want = (n + 8191) / 8192;
     const int64_t cap = (int64_t)cus;
-    hipLaunchKernelGGL(k_block_summary, dim3((uint32_t)(want < cap ? (want < 1 ? 1 : want) : cap)), dim3(1024), 0, s, a);
+    const dim3 grid((uint32_t)(want < cap ? (want < 1 ? 1 : want) : cap));
+    const bool vec = ((reinterpret_cast<uintptr_t>(amax) | reinterpret_cast<uintptr_t>(sqerr) | reinterpret_cast<uintptr_t>(ref)) & 15u) == 0;
+    using Kern = void (*)(SummaryArgs);
+    static const Kern kern[2][4] = {{k_block_summary<false, 0>, k_block_summary<false, 8>, k_block_summary<false, 16>, k_block_summary<false, 32>},
+                                    {k_block_summary<true, 0>, k_block_summary<true, 8>, k_block_summary<true, 16>, k_block_summary<true, 32>}};
+    const Kern k = kern[vec][!hist ? 0 : nedges <= 8 ? 1 : nedges <= 16 ? 2 : 3];
+    hipLaunchKernelGGL(k, grid, dim3(1024), 0, s, a);
     return hipGetLastError();
 }
 

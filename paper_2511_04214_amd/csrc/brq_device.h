@@ -107,18 +107,36 @@ __device__ __forceinline__ void wht_cross_quad(float (&v)[8], float s1, float s2
 }
 #undef BRQ_FMAC_DPP
 
-// A lane's chunk of 8 consecutive elements, read once with the streaming hint (16 bytes of bf16, 32 of fp32).
+// A lane's chunk of 8 consecutive elements, read once with the streaming hint (16 bytes of bf16, 32 of fp32), as it
+// comes from memory and as fp32 values.
 template <bool BF16>
-__device__ __forceinline__ void load_chunk(const void* p, float (&v)[8]) {
+struct RawChunk { v4f a, b; };
+template <>
+struct RawChunk<true> { v4i w; };
+template <bool BF16>
+__device__ __forceinline__ RawChunk<BF16> load_raw(const void* p) {
+    RawChunk<BF16> c;
     if constexpr (BF16) {
-        v4i w = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
+        c.w = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
+    } else {
+        c.a = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
+        c.b = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p) + 1);
+    }
+    return c;
+}
+template <bool BF16>
+__device__ __forceinline__ void widen(const RawChunk<BF16>& c, float (&v)[8]) {
+    if constexpr (BF16) {
+        const v4i w = c.w;
         v[0] = bf16_lo((uint32_t)w.x); v[1] = bf16_hi((uint32_t)w.x); v[2] = bf16_lo((uint32_t)w.y); v[3] = bf16_hi((uint32_t)w.y);
         v[4] = bf16_lo((uint32_t)w.z); v[5] = bf16_hi((uint32_t)w.z); v[6] = bf16_lo((uint32_t)w.w); v[7] = bf16_hi((uint32_t)w.w);
     } else {
-        v4f a = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
-        v4f b = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p) + 1);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        v[0] = c.a.x; v[1] = c.a.y; v[2] = c.a.z; v[3] = c.a.w; v[4] = c.b.x; v[5] = c.b.y; v[6] = c.b.z; v[7] = c.b.w;
     }
+}
+template <bool BF16>
+__device__ __forceinline__ void load_chunk(const void* p, float (&v)[8]) {
+    widen<BF16>(load_raw<BF16>(p), v);
 }
 
 // The random sign diagonal of a randomized Hadamard rotation, applied on load: `signs` points at the 8 sign
@@ -216,6 +234,36 @@ __device__ __forceinline__ float quad_sum(float v) {
         "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         : "+v"(v));
     return v;
+}
+
+// cnt += how many of the wavefront's values v are above lim, by magnitude (MAG) or as they are: the comparison writes
+// a lane mask to scalar registers and the scalar unit counts its bits.  Written out, and volatile, because the
+// compiler takes a comparison for something to be done early wherever its result is only used under a condition:
+// with eight limits of which a caller uses two it made all the masks for every value, and moved them through vector
+// registers one lane at a time for want of scalar ones.
+template <bool MAG>
+__device__ __forceinline__ void count_above(uint32_t& cnt, float v, float lim) {
+    uint64_t m;
+    uint32_t n;
+    if constexpr (MAG)
+        asm volatile("v_cmp_gt_f32_e64 %1, |%3|, %4\n\ts_bcnt1_i32_b64 %2, %1\n\ts_add_u32 %0, %0, %2"
+                     : "+s"(cnt), "=&s"(m), "=&s"(n) : "v"(v), "v"(lim) : "scc");
+    else
+        asm volatile("v_cmp_gt_f32_e64 %1, %3, %4\n\ts_bcnt1_i32_b64 %2, %1\n\ts_add_u32 %0, %0, %2"
+                     : "+s"(cnt), "=&s"(m), "=&s"(n) : "v"(v), "v"(lim) : "scc");
+}
+// The same for 8 values of a lane, two chains of comparison and count interleaved.
+__device__ __forceinline__ void count_above8(uint32_t& cnt, const float (&y)[8], float lim) {
+    uint64_t m0, m1, m2, m3;
+    uint32_t n;
+#pragma unroll
+    for (int i = 0; i < 8; i += 4)
+        asm volatile("v_cmp_gt_f32_e64 %1, |%6|, %10\n\tv_cmp_gt_f32_e64 %2, |%7|, %10\n\t"
+                     "v_cmp_gt_f32_e64 %3, |%8|, %10\n\tv_cmp_gt_f32_e64 %4, |%9|, %10\n\t"
+                     "s_bcnt1_i32_b64 %5, %1\n\ts_add_u32 %0, %0, %5\n\ts_bcnt1_i32_b64 %5, %2\n\ts_add_u32 %0, %0, %5\n\t"
+                     "s_bcnt1_i32_b64 %5, %3\n\ts_add_u32 %0, %0, %5\n\ts_bcnt1_i32_b64 %5, %4\n\ts_add_u32 %0, %0, %5"
+                     : "+s"(cnt), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3), "=&s"(n)
+                     : "v"(y[i]), "v"(y[i + 1]), "v"(y[i + 2]), "v"(y[i + 3]), "v"(lim) : "scc");
 }
 
 // E8M0 byte of a group from its maximum magnitude: max(exponent field - 2, 0).

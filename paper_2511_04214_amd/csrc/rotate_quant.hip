@@ -178,8 +178,8 @@ __device__ __forceinline__ void quant_store(const float (&y)[8], uint32_t row, u
 // block's MXFP4 quantization loss sum (y - deq(q(y)))^2 (fp32; each difference is exact, the
 // squares and the 32-term sum round), and per threshold the number of values with |y| above it.
 //
-// Counting costs one vector instruction per value and threshold: the comparison writes a lane mask to
-// scalar registers, and the scalar unit, which has nothing else to do in this kernel, counts its bits
+// Counting costs one vector instruction per value and threshold (count_above8): the comparison writes a lane mask
+// to scalar registers, and the scalar unit, which has nothing else to do in this kernel, counts its bits
 // and keeps the wavefront's running sums (`cnt`, wavefront-uniform; a wavefront meets fewer than 2^32
 // values per launch).  Per-lane counters cost a second vector instruction per value and threshold on a
 // kernel whose vector units are the busiest part.
@@ -211,8 +211,7 @@ __device__ __forceinline__ void stats_chunk(const float (&y)[8], uint32_t gidx0,
     }
     e2 = quad_sum(e2);
     // lane j < 16 takes over block j of the wavefront (held by lanes 4 j .. 4 j + 3) and stores it
-    const bool blive = __builtin_amdgcn_ds_bpermute((int)((lane & 15u) << 4), (int)live) != 0;
-    const bool st = lane < 16u && blive;
+    const bool st = lane < 16u && gidx0 + lane < (a.nchunks >> 2);
     if (a.amax) {   // uniform
         const float g = gather_quads(am, lane);
         if (st) a.amax[gidx0 + lane] = g;
@@ -251,9 +250,7 @@ __device__ __forceinline__ void stats_chunk(const float (&y)[8], uint32_t gidx0,
             const float th = a.th[t];
             // a lane without a chunk carries a copy of the last one: its comparisons are masked out
             const float lim = live ? th : __builtin_inff();
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                cnt[t] += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(fabsf(y[i]) > lim));
+            count_above8(cnt[t], y, lim);
         }
     }
 }
@@ -270,10 +267,16 @@ __device__ __forceinline__ void stats_flush(const uint32_t (&cnt)[8], uint32_t* 
     if (threadIdx.x < a.nt && red[threadIdx.x]) atomicAdd(&a.counts[threadIdx.x], (unsigned long long)red[threadIdx.x]);
 }
 
+// Threads of a workgroup of k_rowwise.  Statistics: every workgroup ends with an atomic per counter, on one cache line
+// for all of them (3.5 ns each: 4096 atomics of 2048 workgroups were 14 us of an 80 us launch), so the wavefronts a CU
+// needs come in few large workgroups, see STATS_WGS_PER_CU.
+constexpr int row_threads(int mode) { return mode == MODE_STATS ? 512 : 256; }
+
 // One chunk per lane per step, U steps in flight (the launcher uses U = 1).  LOG2B = 0 means "no rotation":
 // the quantizer alone, or (MODE_ROTATE with a producer) the gated activation alone, stored to y.
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool CONTIG, int U, bool PROD>
-__global__ void __launch_bounds__(256) k_rowwise(RowArgs a) {
+__global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
+    constexpr uint32_t NT = row_threads(MODE);
     const uint32_t lane = threadIdx.x & 63;
     constexpr bool ROT = MODE != MODE_QUANT && LOG2B > 0;   // LOG2B = 0 with MODE_ROTATE: the producer alone
     __shared__ uint32_t red[8];
@@ -285,25 +288,40 @@ __global__ void __launch_bounds__(256) k_rowwise(RowArgs a) {
     constexpr uint32_t inwave_bits = (LOG2B >= 3) ? ((1u << (LOG2B - 3)) - 1u) : 0u;
     const float sigma = (__builtin_popcount(lane & inwave_bits) & 1) ? -1.0f : 1.0f;
     const float cs = as_f32(norm_bits(LOG2B)) * sigma;
-    const uint32_t step = gridDim.x * 256u * U;
+    const uint32_t step = gridDim.x * NT * U;
     uint32_t sm[U][8];
     const bool presigned = ROT && a.signs && a.sign_fixed;   // uniform
     if (presigned) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            sign_masks(sm[u], a.signs + (size_t)((blockIdx.x * 256u * U + u * 256u + threadIdx.x) % a.cpr) * 8);
+            sign_masks(sm[u], a.signs + (size_t)((blockIdx.x * NT * U + u * NT + threadIdx.x) % a.cpr) * 8);
     }
     // `bb` is uniform over the workgroup and nothing below branches on the lane: chunks past
     // the end re-read the last chunk (clamped index) and only their stores are masked, so
     // every lane exchange sees a full wavefront.
-    for (uint32_t bb = blockIdx.x * 256u * U; bb < a.nchunks; bb += step) {
+    // The statistics run a fixed number of workgroups through many passes: the next pass's chunk is requested before
+    // this one's is worked on (the short-lived workgroups of the other modes overlap each other instead).
+    auto chunk_at = [&](uint32_t c) { return (const char*)a.x + chunk_offset<CONTIG>(min(c, a.nchunks - 1u), a.cpr, a.ldx) * (IN_BF16 ? 2 : 4); };
+    RawChunk<IN_BF16> ahead[MODE == MODE_STATS ? U : 1];
+    if constexpr (MODE == MODE_STATS) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) ahead[u] = load_raw<IN_BF16>(chunk_at(blockIdx.x * NT * U + u * NT + threadIdx.x));
+    }
+    for (uint32_t bb = blockIdx.x * NT * U; bb < a.nchunks; bb += step) {
         float v[U][8];
+        if constexpr (MODE == MODE_STATS) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                widen<IN_BF16>(ahead[u], v[u]);
+                ahead[u] = load_raw<IN_BF16>(chunk_at(bb + step + u * NT + threadIdx.x));
+            }
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            uint32_t c = min(bb + u * 256u + threadIdx.x, a.nchunks - 1u);
+            uint32_t c = min(bb + u * NT + threadIdx.x, a.nchunks - 1u);
             const char* p = (const char*)a.x + chunk_offset<CONTIG>(c, a.cpr, a.ldx) * (IN_BF16 ? 2 : 4);
             const char* p2 = PROD ? (const char*)a.x2 + chunk_offset<CONTIG>(c, a.cpr, a.ldx2) * (IN_BF16 ? 2 : 4) : nullptr;
-            load_input<IN_BF16, PROD>(p, p2, a.hround != 0, v[u]);
+            if constexpr (MODE != MODE_STATS) load_input<IN_BF16, PROD>(p, p2, a.hround != 0, v[u]);
             if constexpr (ROT) {
                 if (presigned) {
                     flip(v[u], sm[u]);
@@ -321,7 +339,7 @@ __global__ void __launch_bounds__(256) k_rowwise(RowArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t c = bb + u * 256u + threadIdx.x;
+            const uint32_t c = bb + u * NT + threadIdx.x;
             const bool live = c < a.nchunks;
             if constexpr (ROT) {
                 wht_inwave<LOG2B>(v[u], lane);
@@ -523,10 +541,10 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
 
 // ---- host side ---------------------------------------------------------------------
 
-// Workgroups per compute unit of a statistics launch: each ends with up to 8 atomics on the caller's counters.
-#ifndef BRQ_STATS_WGS_PER_CU
-#define BRQ_STATS_WGS_PER_CU 8
-#endif
+// Workgroups per compute unit of a statistics launch (each ends with up to 8 atomics on the caller's counters): of 512
+// threads for k_rowwise, of up to 256 for k_rowwise_lds.  X 16384 x 8192, two thresholds, B = 1 / 32, us: 3 x 512 threads
+// 57.8 / 63.9; 2 x 512 with two chunks a pass 60.9 / 72.6; 2 x 768 57.8 / 64.6; 2 x 1024 56.2 / 73.6; 8 x 256 68.7 / 74.5.
+constexpr int STATS_WGS_PER_CU = 3, STATS_LDS_WGS_PER_CU = 8;
 
 // Workgroups of a streaming launch.  Measured on X 16384 x 8192 (bf16, B = 32): one chunk in
 // flight per lane and many short-lived workgroups beat a persistent grid (8 per CU, two
@@ -574,17 +592,18 @@ static hipError_t launch_inwave(const RowArgs& a, bool contig, hipStream_t s) {
         }
     }
     constexpr int U = 1;
+    constexpr int NT = row_threads(MODE);
     int grid = rowwise_grid(a.nchunks, U, cus);
     if constexpr (MODE == MODE_STATS) {   // fewer, longer-lived workgroups: each ends with atomics on the counters
-        const int cap = cus * BRQ_STATS_WGS_PER_CU;
-        if (grid > cap) grid = cap;
+        const int need = (int)((a.nchunks + NT * U - 1) / (NT * U)), cap = cus * STATS_WGS_PER_CU;
+        grid = need < cap ? need : cap;
     }
     RowArgs b = a;
-    b.sign_fixed = (a.signs && MODE != MODE_QUANT && LOG2B > 0) ? fix_columns(grid, a.cpr, 256 * U) : 0;
+    b.sign_fixed = (a.signs && MODE != MODE_QUANT && LOG2B > 0) ? fix_columns(grid, a.cpr, NT * U) : 0;
     if (contig)
-        hipLaunchKernelGGL((k_rowwise<LOG2B, IN_BF16, MODE, OUT_BF16, true, U, PROD>), dim3(grid), dim3(256), 0, s, b);
+        hipLaunchKernelGGL((k_rowwise<LOG2B, IN_BF16, MODE, OUT_BF16, true, U, PROD>), dim3(grid), dim3(NT), 0, s, b);
     else
-        hipLaunchKernelGGL((k_rowwise<LOG2B, IN_BF16, MODE, OUT_BF16, false, U, PROD>), dim3(grid), dim3(256), 0, s, b);
+        hipLaunchKernelGGL((k_rowwise<LOG2B, IN_BF16, MODE, OUT_BF16, false, U, PROD>), dim3(grid), dim3(NT), 0, s, b);
     return hipGetLastError();
 }
 
@@ -598,7 +617,7 @@ static hipError_t launch_lds(const RowArgs& a, int64_t M, int64_t K, hipStream_t
     if (MODE == MODE_STATS) {
         int cus = 0;
         if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
-        const uint32_t cap = (uint32_t)cus * (uint32_t)BRQ_STATS_WGS_PER_CU;
+        const uint32_t cap = (uint32_t)cus * (uint32_t)STATS_LDS_WGS_PER_CU;
         if (grid > cap) grid = cap;
     }
     hipLaunchKernelGGL((k_rowwise_lds<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>), dim3(grid), dim3(NT),

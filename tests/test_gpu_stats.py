@@ -170,6 +170,28 @@ def test_summary_matches_oracle(brq, orc, n):
     check_summary(brq, orc, amax, sq, ref, 1.0e30, [float(i) for i in range(32)])   # the most edges
 
 
+@pytest.mark.parametrize("n", [8191, 8192, 16385, 8192 * 300 + 5])   # spans of a workgroup: short, whole, more than the grid's
+def test_summary_spans_edges_and_unaligned_arrays(brq, orc, n):
+    rng = np.random.default_rng(720 + n)
+    amax, ref = ((np.abs(rng.standard_t(3, size=n + 1)) * 2).astype(np.float32) for _ in range(2))
+    sq = rng.random(n + 1).astype(np.float32)
+    d = [to_dev(t)[1:] for t in (amax, sq, ref)]           # 4 bytes past a 16-byte boundary
+    for ne in (0, 8, 9, 17):
+        edges = [0.25 * (i + 1) for i in range(ne)]
+        rh, rc, rs = check_summary(brq, orc, amax[1:].copy(), sq[1:].copy(), ref[1:].copy(), 5.0, edges)
+        hist, counts, sums = brq.block_stats_summary(*d, outlier_threshold=5.0, edges=edges)
+        assert np.array_equal(to_host(hist).astype(np.uint64), rh) and np.array_equal(to_host(counts).astype(np.uint64), rc)
+        assert np.allclose(to_host(sums), rs, rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("nt", [1, 4, 8])
+def test_stats_number_of_thresholds(brq, orc, nt):
+    x = make_x(130, 1056, 650 + nt, "bf16")
+    th = [0.5 * (i + 1) for i in range(nt)]
+    for B in (1, 32):
+        assert np.array_equal(to_host(brq.block_stats(to_dev(x), B, th)[1]).astype(np.uint64), orc.block_stats(x, B, th)[1])
+
+
 def test_summary_adds_to_its_outputs_and_takes_nothing(brq):
     amax = torch.full((1000,), 3.0, dtype=torch.float32, device="cuda")
     hist = torch.tensor([5, 0, 0], dtype=torch.int64, device="cuda")
