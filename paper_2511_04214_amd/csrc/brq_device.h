@@ -34,23 +34,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// Value of `v` held by lane (lane ^ MASK).  MASK 1 and 2 stay inside a quad and fold
-// into the consuming VALU instruction as a DPP modifier; 4, 8, 16 use the swizzle
-// crossbar; 32 crosses the two halves of the wavefront.
-template <int MASK>
-__device__ __forceinline__ float lane_xor(float v) {
+// Value of `v` held by the neighbouring lane (lane ^ 1); folds into the consuming VALU instruction as a DPP modifier.
+__device__ __forceinline__ float lane_xor1(float v) {
     int iv = __builtin_bit_cast(int, v);
-    if constexpr (MASK == 1) {
-        iv = __builtin_amdgcn_update_dpp(iv, iv, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
-    } else if constexpr (MASK == 2) {
-        iv = __builtin_amdgcn_update_dpp(iv, iv, 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, true);
-    } else if constexpr (MASK == 4 || MASK == 8 || MASK == 16) {
-        iv = __builtin_amdgcn_ds_swizzle(iv, 0x1F | (MASK << 10)); /* and 0x1f, or 0, xor MASK */
-    } else {
-        static_assert(MASK == 32, "lane_xor: mask must be a power of two below 64");
-        int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        iv = __builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, iv);
-    }
+    iv = __builtin_amdgcn_update_dpp(iv, iv, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
     return __builtin_bit_cast(float, iv);
 }
 
@@ -70,17 +57,16 @@ __device__ __forceinline__ void wht8(float (&v)[8]) {
     }
 }
 
-// One cross-lane stage (partner lane = lane ^ MASK).  The lane whose MASK bit is clear
-// owns a and needs a+b; the other owns b and needs a-b.  Both evaluate
+// Cross-lane stages.  The lane whose bit is clear owns a and needs a+b; the other owns b and needs a-b.  Both evaluate
 // fma(partner, s, own) with s = +1 / -1: the lower lane gets a+b, the upper lane gets
 // b-a, i.e. the NEGATED result (one rounding, so exactly -fl(a-b)).  The caller tracks
 // the sign (it flips once per stage in which the lane is the upper one) and folds it into
 // the final normalisation multiply; only the sign of exact zeros can differ, and the
 // encoder stores every zero magnitude as code 0.
-template <int MASK>
-__device__ __forceinline__ void wht_cross(float (&v)[8], float s) {
+// This one: partner lane ^ 1 alone (B = 16).
+__device__ __forceinline__ void wht_cross1(float (&v)[8], float s) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = __builtin_fmaf(lane_xor<MASK>(v[i]), s, v[i]);
+    for (int i = 0; i < 8; ++i) v[i] = __builtin_fmaf(lane_xor1(v[i]), s, v[i]);
 }
 
 // The two stages that stay inside a quad (partner lane ^ 1, then lane ^ 2), i.e. h = 8 and
@@ -106,6 +92,54 @@ __device__ __forceinline__ void wht_cross_quad(float (&v)[8], float s1, float s2
         : "v"(s1), "v"(s2));
 }
 #undef BRQ_FMAC_DPP
+
+// Blocks wider than a quad.  No DPP modifier reaches lane ^ 4 or lane ^ 8, but two reach the mirror image: lane ^ 7
+// inside 8 lanes and lane ^ 15 inside 16.  So the chunks are dealt to the lanes in an order in which the mirror image
+// IS the partner: lane L of a 16-lane row holds chunk M(L), M linear over the bits with M(1) = 1, M(2) = 2,
+// M(7) = 4, M(15) = 8.  Quads still hold whole 32-element groups (in reverse order where bit 2 of the lane is
+// set), 16 lanes still read 256 contiguous bytes, and the stages h = 32 and 64 cost one instruction per value
+// like those inside a quad (through the LDS swizzle they cost that, an LDS operation and its latency).
+__device__ __forceinline__ uint32_t chunk_of_lane(uint32_t lane) {
+    return lane ^ ((lane & 4u) ? 3u : 0u) ^ ((lane & 8u) ? 4u : 0u);
+}
+#define BRQ_FMAC_MIRROR(r, how) "v_fmac_f32_dpp " r ", " r ", %8 " how " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define BRQ_CROSS_MIRROR(v, s, how)                                                                                \
+    asm volatile("s_nop 1\n\t" BRQ_FMAC_MIRROR("%0", how) BRQ_FMAC_MIRROR("%1", how) BRQ_FMAC_MIRROR("%2", how)     \
+                 BRQ_FMAC_MIRROR("%3", how) BRQ_FMAC_MIRROR("%4", how) BRQ_FMAC_MIRROR("%5", how)                  \
+                 BRQ_FMAC_MIRROR("%6", how) BRQ_FMAC_MIRROR("%7", how)                                             \
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])    \
+                 : "v"(s))
+__device__ __forceinline__ void wht_cross_mirror8(float (&v)[8], float s) { BRQ_CROSS_MIRROR(v, s, "row_half_mirror"); }
+__device__ __forceinline__ void wht_cross_mirror16(float (&v)[8], float s) { BRQ_CROSS_MIRROR(v, s, "row_mirror"); }
+#undef BRQ_CROSS_MIRROR
+#undef BRQ_FMAC_MIRROR
+
+// The stages between 16-lane rows (h = 128) and between the halves of the wavefront (h = 256): two registers trade
+// the part the stage pairs, the butterfly is then between the two registers of one lane, and trading again puts the
+// values back: three instructions per two values and stage, no LDS, true signs.
+template <bool HALVES>
+__device__ __forceinline__ void trade(float& x, float& y) {
+    if constexpr (HALVES) {
+        const auto s = __builtin_amdgcn_permlane32_swap(as_u32(x), as_u32(y), false, false);
+        x = as_f32(s[0]);
+        y = as_f32(s[1]);
+    } else {
+        const auto s = __builtin_amdgcn_permlane16_swap(as_u32(x), as_u32(y), false, false);
+        x = as_f32(s[0]);
+        y = as_f32(s[1]);
+    }
+}
+template <bool HALVES>
+__device__ __forceinline__ void wht_cross_rows(float (&v)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        trade<HALVES>(v[i], v[i + 1]);
+        const float a = v[i], b = v[i + 1];
+        v[i] = a + b;
+        v[i + 1] = a - b;
+        trade<HALVES>(v[i], v[i + 1]);
+    }
+}
 
 // A lane's chunk of 8 consecutive elements, read once with the streaming hint (16 bytes of bf16, 32 of fp32), as it
 // comes from memory and as fp32 values.
@@ -150,19 +184,25 @@ __device__ __forceinline__ void apply_signs(float (&v)[8], const int8_t* signs) 
     }
 }
 
-// Stages of the order-2^LOG2B transform for the chunk in `v`; returns the value through
-// sign-tracked cross-lane stages: afterwards v holds sigma * (x H), with sigma = -1 for
-// lanes with an odd number of set bits among the lane bits that took part.
+// Stages of the order-2^LOG2B transform (at most a wavefront's 512 elements) for the chunk in `v`.  `chunk`: which
+// chunk of the wavefront the lane holds: the lane's own number up to B = 32, chunk_of_lane beyond.  The DPP stages
+// track signs: afterwards v holds wht_sign<LOG2B>(chunk) * (x H).
+constexpr bool wht_mirrored(int log2b) { return log2b >= 6; }
 template <int LOG2B>
-__device__ __forceinline__ void wht_inwave(float (&v)[8], uint32_t lane) {
-    static_assert(LOG2B >= 3, "a lane holds 8 elements");
+__device__ __forceinline__ float wht_sign(uint32_t chunk) {
+    constexpr uint32_t bits = LOG2B < 3 ? 0u : LOG2B >= 7 ? 15u : (1u << (LOG2B - 3)) - 1u;
+    return (__builtin_popcount(chunk & bits) & 1) ? -1.0f : 1.0f;
+}
+template <int LOG2B>
+__device__ __forceinline__ void wht_inwave(float (&v)[8], uint32_t chunk) {
+    static_assert(LOG2B >= 3 && LOG2B <= 9, "a lane holds 8 elements, a wavefront 512");
     wht8(v);
-    if constexpr (LOG2B == 4) wht_cross<1>(v, (lane & 1) ? -1.0f : 1.0f);
-    if constexpr (LOG2B >= 5) wht_cross_quad(v, (lane & 1) ? -1.0f : 1.0f, (lane & 2) ? -1.0f : 1.0f);
-    if constexpr (LOG2B >= 6) wht_cross<4>(v, (lane & 4) ? -1.0f : 1.0f);
-    if constexpr (LOG2B >= 7) wht_cross<8>(v, (lane & 8) ? -1.0f : 1.0f);
-    if constexpr (LOG2B >= 8) wht_cross<16>(v, (lane & 16) ? -1.0f : 1.0f);
-    if constexpr (LOG2B >= 9) wht_cross<32>(v, (lane & 32) ? -1.0f : 1.0f);
+    if constexpr (LOG2B == 4) wht_cross1(v, (chunk & 1) ? -1.0f : 1.0f);
+    if constexpr (LOG2B >= 5) wht_cross_quad(v, (chunk & 1) ? -1.0f : 1.0f, (chunk & 2) ? -1.0f : 1.0f);
+    if constexpr (LOG2B >= 6) wht_cross_mirror8(v, (chunk & 4) ? -1.0f : 1.0f);
+    if constexpr (LOG2B >= 7) wht_cross_mirror16(v, (chunk & 8) ? -1.0f : 1.0f);
+    if constexpr (LOG2B >= 8) wht_cross_rows<false>(v);
+    if constexpr (LOG2B >= 9) wht_cross_rows<true>(v);
 }
 
 // silu(g) * u = g / (1 + exp(-g)) * u, the gated activation that produces the input of the rotated

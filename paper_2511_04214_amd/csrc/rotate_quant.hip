@@ -6,7 +6,8 @@
 // 32 bytes of fp32), held by one lane; 4 consecutive lanes (a DPP quad) hold one
 // 32-element MXFP4 group, so the group maximum is two quad-permute steps and the group's
 // 8 packed codes per lane form one dword store.  Rotation stages h = 1, 2, 4 run inside
-// the lane, h = 8 ... 256 between lanes of the wavefront, larger h through LDS.
+// the lane, h = 8 ... 256 between lanes of the wavefront, larger h between the chunks a lane holds (B <= 8192: a
+// wavefront holds the whole block) or through LDS (B = 16384).
 #include "brq_device.h"
 #include "brq_launch.h"
 
@@ -90,11 +91,13 @@ __device__ __forceinline__ void store_chunk(void* p, const float (&v)[8]) {
 // one lane at a time (178 us on X 16384 x 8192, where a plain conversion copy of the same traffic takes
 // 137).  The four lanes of a quad hold 128 contiguous bytes (consecutive lanes = consecutive chunks of
 // one row): the 16-byte pieces are traded inside the quad so that store A writes pieces 0..3 and store
-// B pieces 4..7, lane t piece t - 64 contiguous bytes per quad and instruction.  Piece k sits in lane
-// k >> 1, half k & 1.  Every lane of the quad must be active.
-__device__ __forceinline__ void store_chunk_f32_quad(char* p, const float (&v)[8], uint32_t lane) {
-    const uint32_t t = lane & 3u;
+// B pieces 4..7, chunk t's lane piece t - 64 contiguous bytes per quad and instruction.  Piece k sits in chunk
+// k >> 1, half k & 1.  A quad that holds its chunks in reverse order (chunk_of_lane) finds the pieces of store B where
+// the others find those of store A.  Every lane of the quad must be active.
+__device__ __forceinline__ void store_chunk_f32_quad(char* p, const float (&v)[8], uint32_t lane, uint32_t chunk) {
+    const uint32_t t = chunk & 3u;
     const bool odd = (t & 1u) != 0;
+    const int first = ((lane ^ chunk) & 3u) != 0 ? 64 : 0;     // 0 or 3: in order or reversed
     v4f a, b;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -106,8 +109,8 @@ __device__ __forceinline__ void store_chunk_f32_quad(char* p, const float (&v)[8
         a[k] = __builtin_bit_cast(float, odd ? a_hi : a_lo);
         b[k] = __builtin_bit_cast(float, odd ? b_hi : b_lo);
     }
-    __builtin_nontemporal_store(a, reinterpret_cast<v4f*>(p - 16 * (int)t));
-    __builtin_nontemporal_store(b, reinterpret_cast<v4f*>(p + 64 - 16 * (int)t));
+    __builtin_nontemporal_store(a, reinterpret_cast<v4f*>(p + first - 16 * (int)t));
+    __builtin_nontemporal_store(b, reinterpret_cast<v4f*>(p + (64 - first) - 16 * (int)t));
 }
 
 // The lane's 8 input values: the chunk at p, or (PROD) the gated activation of the chunks at p
@@ -187,9 +190,13 @@ __device__ __forceinline__ void quant_store(const float (&y)[8], uint32_t row, u
 // The per-block outputs of a wavefront's 16 blocks sit in lanes 0, 4, 8, ...; stored from there they are
 // 16 separate 4-byte accesses.  One lane permute brings them to lanes 0..15, which store 64 contiguous
 // bytes.  gidx0 = block index of the wavefront's first chunk; `live` = this lane's chunk exists.
+// (MIRRORED: block b sits in quad b ^ (bit 1 of b), chunk_of_lane's order.)
+template <bool MIRRORED>
 __device__ __forceinline__ float gather_quads(float v, uint32_t lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((int)((lane & 15u) << 4), __builtin_bit_cast(int, v)));
+    const uint32_t quad = MIRRORED ? lane ^ ((lane >> 1) & 1u) : lane;
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((int)((quad & 15u) << 4), __builtin_bit_cast(int, v)));
 }
+template <bool MIRRORED>
 __device__ __forceinline__ void stats_chunk(const float (&y)[8], uint32_t gidx0, bool live, uint32_t lane,
                                             const RowArgs& a, uint32_t (&cnt)[8]) {
     typedef float f2 __attribute__((ext_vector_type(2)));
@@ -210,14 +217,14 @@ __device__ __forceinline__ void stats_chunk(const float (&y)[8], uint32_t gidx0,
         e2 = __builtin_fmaf(e1, e1, e2);
     }
     e2 = quad_sum(e2);
-    // lane j < 16 takes over block j of the wavefront (held by lanes 4 j .. 4 j + 3) and stores it
+    // lane j < 16 takes over block j of the wavefront and stores it
     const bool st = lane < 16u && gidx0 + lane < (a.nchunks >> 2);
     if (a.amax) {   // uniform
-        const float g = gather_quads(am, lane);
+        const float g = gather_quads<MIRRORED>(am, lane);
         if (st) a.amax[gidx0 + lane] = g;
     }
     if (a.sqerr) {
-        const float g = gather_quads(e2, lane);
+        const float g = gather_quads<MIRRORED>(e2, lane);
         if (st) a.sqerr[gidx0 + lane] = g;
     }
     if (a.sqerr_bfp4) {   // uniform
@@ -241,7 +248,7 @@ __device__ __forceinline__ void stats_chunk(const float (&y)[8], uint32_t gidx0,
             eb = __builtin_fmaf(e1, e1, eb);
         }
         eb = quad_sum(eb);
-        const float g = gather_quads(eb, lane);
+        const float g = gather_quads<MIRRORED>(eb, lane);
         if (st) a.sqerr_bfp4[gidx0 + lane] = g;
     }
 #pragma unroll
@@ -285,16 +292,16 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
         if (threadIdx.x < 8) red[threadIdx.x] = 0;
         __syncthreads();
     }
-    constexpr uint32_t inwave_bits = (LOG2B >= 3) ? ((1u << (LOG2B - 3)) - 1u) : 0u;
-    const float sigma = (__builtin_popcount(lane & inwave_bits) & 1) ? -1.0f : 1.0f;
-    const float cs = as_f32(norm_bits(LOG2B)) * sigma;
+    const uint32_t lc = wht_mirrored(LOG2B) ? chunk_of_lane(lane) : lane;      // this lane's chunk of the wavefront's 64
+    const uint32_t tc = (threadIdx.x & ~63u) + lc;                              // ... of the workgroup's
+    const float cs = as_f32(norm_bits(LOG2B)) * wht_sign<LOG2B>(lc);
     const uint32_t step = gridDim.x * NT * U;
     uint32_t sm[U][8];
     const bool presigned = ROT && a.signs && a.sign_fixed;   // uniform
     if (presigned) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            sign_masks(sm[u], a.signs + (size_t)((blockIdx.x * NT * U + u * NT + threadIdx.x) % a.cpr) * 8);
+            sign_masks(sm[u], a.signs + (size_t)((blockIdx.x * NT * U + u * NT + tc) % a.cpr) * 8);
     }
     // `bb` is uniform over the workgroup and nothing below branches on the lane: chunks past
     // the end re-read the last chunk (clamped index) and only their stores are masked, so
@@ -305,7 +312,7 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
     RawChunk<IN_BF16> ahead[MODE == MODE_STATS ? U : 1];
     if constexpr (MODE == MODE_STATS) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) ahead[u] = load_raw<IN_BF16>(chunk_at(blockIdx.x * NT * U + u * NT + threadIdx.x));
+        for (int u = 0; u < U; ++u) ahead[u] = load_raw<IN_BF16>(chunk_at(blockIdx.x * NT * U + u * NT + tc));
     }
     for (uint32_t bb = blockIdx.x * NT * U; bb < a.nchunks; bb += step) {
         float v[U][8];
@@ -313,12 +320,12 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 widen<IN_BF16>(ahead[u], v[u]);
-                ahead[u] = load_raw<IN_BF16>(chunk_at(bb + step + u * NT + threadIdx.x));
+                ahead[u] = load_raw<IN_BF16>(chunk_at(bb + step + u * NT + tc));
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            uint32_t c = min(bb + u * NT + threadIdx.x, a.nchunks - 1u);
+            uint32_t c = min(bb + u * NT + tc, a.nchunks - 1u);
             const char* p = (const char*)a.x + chunk_offset<CONTIG>(c, a.cpr, a.ldx) * (IN_BF16 ? 2 : 4);
             const char* p2 = PROD ? (const char*)a.x2 + chunk_offset<CONTIG>(c, a.cpr, a.ldx2) * (IN_BF16 ? 2 : 4) : nullptr;
             if constexpr (MODE != MODE_STATS) load_input<IN_BF16, PROD>(p, p2, a.hround != 0, v[u]);
@@ -339,10 +346,10 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t c = bb + u * NT + threadIdx.x;
+            const uint32_t c = bb + u * NT + tc;
             const bool live = c < a.nchunks;
             if constexpr (ROT) {
-                wht_inwave<LOG2B>(v[u], lane);
+                wht_inwave<LOG2B>(v[u], lc);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) v[u][i] *= cs;
             }
@@ -351,10 +358,10 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
                     char* p = (char*)a.y + chunk_offset<CONTIG>(c, a.cpr, a.ldy) * (OUT_BF16 ? 2 : 4);
                     // (a quad's four chunks are live together: the chunk count is a multiple of 4)
                     if constexpr (OUT_BF16) store_chunk<true>(p, v[u]);
-                    else store_chunk_f32_quad(p, v[u], lane);
+                    else store_chunk_f32_quad(p, v[u], lane, lc);
                 }
             } else if constexpr (MODE == MODE_STATS) {
-                stats_chunk(v[u], (c - lane) >> 2, live, lane, a, cnt);
+                stats_chunk<wht_mirrored(LOG2B)>(v[u], (c - lc) >> 2, live, lane, a, cnt);
             } else {
                 uint32_t sb = e8m0_from_amax(quad_max(absmax8(v[u])));
                 uint32_t w = encode8_e2m1(v[u], sb);
@@ -371,8 +378,8 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
                     uint8_t* cbase = reinterpret_cast<uint8_t*>(a.codes) + tiled_code_offset(row, kc0, a.stages);
                     uint8_t* sbase = a.scales + tiled_scale_offset(row, kc0, a.sstages);
                     if (live) {
-                        __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + (lane >> 4) * 4096u + (lane & 15u) * 4u));
-                        if ((lane & 3) == 0) *(sbase + (lane >> 2)) = (uint8_t)sb;
+                        __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + (lc >> 4) * 4096u + (lc & 15u) * 4u));
+                        if ((lane & 3) == 0) *(sbase + (lc >> 2)) = (uint8_t)sb;
                     }
                 } else if (live) {
                     const uint32_t row = c / a.cpr, kc = c - row * a.cpr;
@@ -399,18 +406,17 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a, uint32_t rows, ui
     static_assert(LOG2B == 0 || (LOG2B >= 3 && LOG2B <= 7), "a rotation block must fit 16 lanes");
     constexpr int ES = IN_BF16 ? 2 : 4;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    constexpr uint32_t inwave_bits = (LOG2B >= 3) ? ((1u << (LOG2B - 3)) - 1u) : 0u;
-    const float sigma = (__builtin_popcount(lane & inwave_bits) & 1) ? -1.0f : 1.0f;
-    const float cs = as_f32(norm_bits(LOG2B)) * sigma;
+    const uint32_t lc = (wht_mirrored(LOG2B) ? chunk_of_lane(lane) : lane) & 15u;   // this lane's chunk of the stage
+    const float cs = as_f32(norm_bits(LOG2B)) * wht_sign<LOG2B>(lc);
     const uint32_t spr = a.cpr >> 4;                                   // stages per row
     const uint32_t lrow = lane >> 4;
     uint32_t sm[8];
     const bool presigned = MODE != MODE_QUANT && a.signs && a.sign_fixed;   // uniform
-    if (presigned) sign_masks(sm, a.signs + ((size_t)((blockIdx.x * 4u + wave) % spr) * 16u + (lane & 15u)) * 8);
+    if (presigned) sign_masks(sm, a.signs + ((size_t)((blockIdx.x * 4u + wave) % spr) * 16u + lc) * 8);
     // Every address is a wavefront-uniform base plus a per-lane constant (the host checked that
     // 4 rows of pitch fit 32 bits): the loop body spends no vector instruction on addresses.
-    const uint32_t in_lane = lrow * (uint32_t)a.ldx * ES + (lane & 15u) * (8u * ES);
-    const uint32_t in_lane2 = PROD ? lrow * (uint32_t)a.ldx2 * ES + (lane & 15u) * (8u * ES) : 0u;
+    const uint32_t in_lane = lrow * (uint32_t)a.ldx * ES + lc * (8u * ES);
+    const uint32_t in_lane2 = PROD ? lrow * (uint32_t)a.ldx2 * ES + lc * (8u * ES) : 0u;
     const uint32_t step = gridDim.x * 4u;
     for (uint32_t it = blockIdx.x * 4u + wave; it < nitems; it += step) {
         const uint32_t rq = it / spr, st = it - rq * spr;              // scalar
@@ -423,16 +429,16 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a, uint32_t rows, ui
         if (row0 + 4u > rows) {   // uniform: M % 4 != 0, last item of a column; rows past the end
                                   // re-read the last row, their stores are masked below
             const uint32_t rrow = min(row0 + lrow, rows - 1u);
-            p = (const char*)a.x + ((uint64_t)rrow * (uint64_t)a.ldx + (uint64_t)st * 128u + (lane & 15u) * 8u) * ES;
+            p = (const char*)a.x + ((uint64_t)rrow * (uint64_t)a.ldx + (uint64_t)st * 128u + lc * 8u) * ES;
             if constexpr (PROD)
-                p2 = (const char*)a.x2 + ((uint64_t)rrow * (uint64_t)a.ldx2 + (uint64_t)st * 128u + (lane & 15u) * 8u) * ES;
+                p2 = (const char*)a.x2 + ((uint64_t)rrow * (uint64_t)a.ldx2 + (uint64_t)st * 128u + lc * 8u) * ES;
         }
         float v[8];
         load_input<IN_BF16, PROD>(p, p2, a.hround != 0, v);
         if constexpr (MODE != MODE_QUANT) {
             if (presigned) flip(v, sm);
-            else if (a.signs) apply_signs(v, a.signs + ((size_t)st * 16u + (lane & 15u)) * 8);
-            wht_inwave<LOG2B>(v, lane);
+            else if (a.signs) apply_signs(v, a.signs + ((size_t)st * 16u + lc) * 8);
+            wht_inwave<LOG2B>(v, lc);
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] *= cs;
         }
@@ -441,13 +447,164 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a, uint32_t rows, ui
         uint8_t* cbase = reinterpret_cast<uint8_t*>(a.codes) + ((uint64_t)(row0 >> 6) * a.stages + st) * 4096u + (row0 & 63u) * 64u;
         uint8_t* sbase = a.scales + ((uint64_t)(row0 >> 6) * a.sstages + (st >> 2)) * 1024u + (row0 & 63u) * 16u + (st & 3u) * 4u;
         if (row0 + lrow < rows) {
-            __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + lane * 4u));
-            if ((lane & 3) == 0) *(sbase + lrow * 16u + ((lane >> 2) & 3u)) = (uint8_t)sb;
+            __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + lrow * 64u + lc * 4u));
+            if ((lane & 3) == 0) *(sbase + lrow * 16u + (lc >> 2)) = (uint8_t)sb;
         }
     }
 }
 
-// ---- LDS-staged rotation, 1024 <= B <= 16384 (includes the global, full-K rotation) ----
+// ---- 1024 <= B <= 8192 in registers (includes the global, full-K rotation) ----
+//
+// A lane holds up to 8 chunks, one of each 512-element piece of the block: the stages h < 512 run between lanes, the
+// others (still ascending) between a lane's own registers, and all of a block's loads are in flight at once.  Up to
+// B = 4096 a wavefront has the whole block and there is no LDS and no barrier.  At B = 8192 two wavefronts (one
+// workgroup) share it: for the last stage each gives half of its pieces to the other through LDS, 16 KB there and back.
+// (One wavefront with 16 chunks a lane leaves room for 3 per SIMD and spills.)
+// Through LDS altogether (two trips for the stages h >= 512, the stages h = 32 .. 256 through its swizzle) the block
+// cost 34 LDS operations per 8 values of a lane and was bound by them; now the vector units (about 2 instructions per
+// value) are just under HBM.  A row's 128-byte lines of tiled codes (two rows each) are left to two wavefronts: the L2
+// merges their halves (plain stores).
+// Quantizing X bf16, tiled codes, before -> after, us: 4096 x 8192 B = 1024 / 2048 / 4096 / 8192 30 / 31 / 28 / 31 ->
+// 25 / 23 / 24 / 26; 16384 x 8192 101 / 102 / 102 / 108 -> 78 / 77 / 76 / 83.
+constexpr int reg_waves(int log2b) { return log2b == 13 ? 2 : 1; }              // wavefronts per block
+constexpr int reg_threads(int log2b) { return log2b == 13 ? 128 : 256; }        // threads per workgroup
+// wavefronts per SIMD that the registers are to leave room for (storing rotated values takes an address per piece)
+constexpr int reg_occ(int log2b, int mode) { return log2b >= 12 ? (mode == MODE_ROTATE ? 3 : 4) : log2b == 11 ? (mode == MODE_ROTATE ? 5 : 6) : 8; }
+template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD>
+__global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_rowwise_reg(RowArgs a, uint32_t blocks_per_row, uint32_t nblocks) {
+    static_assert(IN_BF16, "fp32 blocks go through LDS");
+    constexpr int W = reg_waves(LOG2B), BPW = reg_threads(LOG2B) / 64 / W;     // blocks per workgroup
+    constexpr int NP = 1 << (LOG2B - 9), NJ = NP / W;                          // pieces per block and per wavefront
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t half = W == 2 ? wave : 0u;
+    const uint32_t lc = chunk_of_lane(lane);
+    const float cs = as_f32(norm_bits(LOG2B)) * wht_sign<9>(lc);
+    __shared__ v4f xch[W == 2 ? 2 * NJ * 64 : 1];                               // [wavefront][piece][4 values][lane]
+    __shared__ uint32_t red[8];
+    uint32_t cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if constexpr (MODE == MODE_STATS) {
+        if (threadIdx.x < 8) red[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    for (uint32_t bid = blockIdx.x * BPW + (W == 1 ? wave : 0u); bid < nblocks; bid += gridDim.x * BPW) {   // uniform per block
+        const uint32_t row = bid / blocks_per_row, blk = bid - row * blocks_per_row;
+        const uint32_t kc0 = blk * (64u * NP);                                  // the block's first chunk
+        const uint32_t first = kc0 + half * (64u * NJ) + lc;                    // this lane's, in the wavefront's first piece
+        const char* const p = (const char*)a.x + ((int64_t)row * a.ldx + (int64_t)first * 8) * 2;
+        float v[NJ][8];
+        {
+            RawChunk<true> raw[NJ], raw2[PROD ? NJ : 1];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) raw[j] = load_raw<true>(p + j * 1024);
+            if constexpr (PROD) {
+                const char* const p2 = (const char*)a.x2 + ((int64_t)row * a.ldx2 + (int64_t)first * 8) * 2;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) raw2[j] = load_raw<true>(p2 + j * 1024);
+            }
+            __builtin_amdgcn_sched_barrier(0);      // all loads first
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                widen<true>(raw[j], v[j]);
+                if constexpr (PROD) {
+                    float u[8];
+                    widen<true>(raw2[j], u);
+                    swiglu8(v[j], u, a.hround != 0);
+                }
+            }
+        }
+        if (a.signs) {   // uniform
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) apply_signs(v[j], a.signs + (size_t)(first + 64u * j) * 8);
+        }
+        // (one chunk after the other, here and below: the scheduler interleaves them all and runs out of registers)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            wht_inwave<9>(v[j], lc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int g = 1; g < NJ; g *= 2)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if ((j & g) == 0) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float s0 = v[j][i], s1 = v[j + g][i];
+                        v[j][i] = s0 + s1;
+                        v[j + g][i] = s0 - s1;
+                    }
+                }
+        if constexpr (W == 2) {
+            // the last stage: piece j of the first wavefront with piece j of the second.  The first keeps its lower
+            // pieces and takes the second's, the second keeps its upper ones and takes the first's.
+            constexpr int H = NJ / 2;
+            auto give = [&](const float (&y)[8], int j) {
+                xch[((half * H + j) * 2 + 0) * 64 + lane] = v4f{y[0], y[1], y[2], y[3]};
+                xch[((half * H + j) * 2 + 1) * 64 + lane] = v4f{y[4], y[5], y[6], y[7]};
+            };
+            if (half == 0) {
+#pragma unroll
+                for (int j = 0; j < H; ++j) give(v[H + j], j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < H; ++j) give(v[j], j);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < H; ++j) {
+                const v4f r0 = xch[(((1u - half) * H + j) * 2 + 0) * 64 + lane], r1 = xch[(((1u - half) * H + j) * 2 + 1) * 64 + lane];
+                const float r[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+                if (half == 0) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) { const float s0 = v[j][i]; v[j][i] = s0 + r[i]; v[H + j][i] = s0 - r[i]; }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) { const float s1 = v[H + j][i]; v[j][i] = r[i] + s1; v[H + j][i] = r[i] - s1; }
+                }
+            }
+        }
+        // (every value is made here: the compiler sinks sums and differences to where they are used and keeps both of
+        // their operands instead)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                v[j][i] *= cs;
+                asm volatile("" : "+v"(v[j][i]));
+            }
+        // v[j] is now piece `piece(j)` of the block, counted from the wavefront's first
+        constexpr auto piece = [](int j) { return W == 1 || j < NJ / 2 ? j : NJ / 2 + j; };
+        const uint32_t out0 = kc0 + half * (64u * (NJ / 2)) + lc;
+        // where this lane's codes and scales of the first piece go, and from piece to piece
+        const bool rm = a.stages == 0;
+        uint8_t* const cd = reinterpret_cast<uint8_t*>(a.codes) + (rm ? (uint64_t)(row * a.cpr + out0) * 4u : tiled_code_offset(row, out0, a.stages));
+        uint8_t* const sd = a.scales + (rm ? (uint64_t)((row * a.cpr + out0) >> 2) : tiled_scale_offset(row, out0, a.sstages));
+        const uint32_t cstep = rm ? 256u : 16384u, sstep = rm ? 16u : 1024u;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint32_t kc = out0 + 64u * piece(j);
+            if constexpr (MODE == MODE_ROTATE) {
+                static_assert(OUT_BF16, "fp32 blocks go through LDS");
+                store_chunk<true>((char*)a.y + ((int64_t)row * a.ldy + (int64_t)kc * 8) * 2, v[j]);
+            } else if constexpr (MODE == MODE_STATS) {
+                stats_chunk<true>(v[j], (row * a.cpr + kc - lc) >> 2, true, lane, a, cnt);
+            } else {
+                const uint32_t sb = e8m0_from_amax(quad_max(absmax8(v[j])));
+                const uint32_t w = encode8_e2m1(v[j], sb);
+                *reinterpret_cast<uint32_t*>(cd + piece(j) * cstep) = w;
+                if ((lane & 3u) == 0) sd[piece(j) * sstep] = (uint8_t)sb;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (W == 2 && MODE == MODE_STATS) __syncthreads();            // the next block's pieces go where this one's were read
+    }
+    if constexpr (MODE == MODE_STATS) {
+        if (a.counts) stats_flush(cnt, red, a);   // uniform
+    }
+}
+
+// ---- LDS-staged rotation, B = 16384 (a wavefront cannot hold the block) ----
 //
 // One workgroup of NT = min(256, B/8) lanes transforms one B-block of one row.  Each
 // lane holds CH = B/(8*NT) chunks.  Stages h < 512 run as above; the remaining
@@ -465,7 +622,8 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
     extern __shared__ float lds[];   // B floats
 
     const uint32_t tid = threadIdx.x, lane = tid & 63;
-    const float sigma = (__builtin_popcount(lane) & 1) ? -1.0f : 1.0f;
+    const uint32_t lc = chunk_of_lane(lane);
+    const float sigma = wht_sign<9>(lc);
     __shared__ uint32_t red[8];
     uint32_t cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if constexpr (MODE == MODE_STATS) {
@@ -481,12 +639,12 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             float v[8];
-            uint32_t q = c * NT + tid;   // chunk index inside the block
+            uint32_t q = c * NT + (tid & ~63u) + lc;   // chunk index inside the block
             load_input<IN_BF16, PROD>((const char*)a.x + (xoff + (int64_t)q * 8) * (IN_BF16 ? 2 : 4),
                                       PROD ? (const char*)a.x2 + (xoff2 + (int64_t)q * 8) * (IN_BF16 ? 2 : 4) : nullptr,
                                       a.hround != 0, v);
             if (a.signs) apply_signs(v, a.signs + ((size_t)blk * B + (size_t)q * 8));
-            wht_inwave<9>(v, lane);
+            wht_inwave<9>(v, lc);
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] *= sigma;   // exact: back to the true sign
             float4* dst = reinterpret_cast<float4*>(lds + q * 8);
@@ -525,9 +683,9 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
             if constexpr (MODE == MODE_ROTATE) {
                 int64_t yoff = (int64_t)row * a.ldy + (int64_t)blk * B + (int64_t)q * 8;
                 if constexpr (OUT_BF16) store_chunk<true>((char*)a.y + yoff * 2, y);
-                else store_chunk_f32_quad((char*)a.y + yoff * 4, y, lane);
+                else store_chunk_f32_quad((char*)a.y + yoff * 4, y, lane, lane);
             } else if constexpr (MODE == MODE_STATS) {
-                stats_chunk(y, (row * a.cpr + blk * (B / 8) + q - lane) >> 2, true, lane, a, cnt);
+                stats_chunk<false>(y, (row * a.cpr + blk * (B / 8) + q - lane) >> 2, true, lane, a, cnt);
             } else {
                 quant_store(y, row, blk * (B / 8) + q, lane, a);
             }
@@ -625,6 +783,31 @@ static hipError_t launch_lds(const RowArgs& a, int64_t M, int64_t K, hipStream_t
     return hipGetLastError();
 }
 
+template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD = false>
+static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t s) {
+    const uint32_t bpr = (uint32_t)(K >> LOG2B), nblocks = (uint32_t)M * bpr;
+    constexpr int NT = reg_threads(LOG2B);
+    constexpr uint32_t per_wg = NT / 64 / reg_waves(LOG2B);
+    uint32_t grid = (nblocks + per_wg - 1u) / per_wg;
+    if (MODE == MODE_STATS) {
+        int cus = 0;
+        if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
+        const uint32_t cap = (uint32_t)cus * (uint32_t)STATS_LDS_WGS_PER_CU;
+        if (grid > cap) grid = cap;
+    }
+    hipLaunchKernelGGL((k_rowwise_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>), dim3(grid), dim3(NT), 0, s, a, bpr, nblocks);
+    return hipGetLastError();
+}
+
+// 1024 <= B <= 8192: in registers where the values come and go as bf16 (or go as codes or statistics);
+// blocks of fp32 values through LDS (X 16384 x 8192 fp32, B = 1024 / 4096, us: 107 / 117, in registers 119 / 130;
+// fp32 out of bf16: 139 / 137 against 154 / 163).
+template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD>
+static hipError_t launch_wide(const RowArgs& a, int64_t M, int64_t K, hipStream_t s) {
+    if constexpr (IN_BF16 && (MODE != MODE_ROTATE || OUT_BF16)) return launch_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
+    else return launch_lds<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
+}
+
 template <bool IN_BF16, int MODE, bool OUT_BF16, bool PROD = false>
 static hipError_t dispatch_b(int log2b, const RowArgs& a, bool contig, int64_t M, int64_t K, hipStream_t s) {
     switch (log2b) {
@@ -635,10 +818,10 @@ static hipError_t dispatch_b(int log2b, const RowArgs& a, bool contig, int64_t M
         case 7: return launch_inwave<7, IN_BF16, MODE, OUT_BF16, PROD>(a, contig, s);
         case 8: return launch_inwave<8, IN_BF16, MODE, OUT_BF16, PROD>(a, contig, s);
         case 9: return launch_inwave<9, IN_BF16, MODE, OUT_BF16, PROD>(a, contig, s);
-        case 10: return launch_lds<10, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
-        case 11: return launch_lds<11, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
-        case 12: return launch_lds<12, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
-        case 13: return launch_lds<13, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
+        case 10: return launch_wide<10, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
+        case 11: return launch_wide<11, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
+        case 12: return launch_wide<12, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
+        case 13: return launch_wide<13, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
         case 14: return launch_lds<14, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
         default: return hipErrorInvalidValue;
     }

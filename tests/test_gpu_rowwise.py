@@ -302,3 +302,28 @@ def test_many_rows_sampled(brq, orc):
     ct, st_ = brq.rotate_quantize_fused(x, 32, layout="tiled")
     c2, s2 = brq.to_rowmajor(ct, st_, M, K)
     assert torch.equal(c2, c) and torch.equal(s2, s)
+
+
+@pytest.mark.parametrize("B", [64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_wide_blocks_every_path(brq, orc, B):
+    # lane order inside the wavefront (B >= 64), blocks in registers and through LDS: odd numbers of blocks, two
+    # blocks a row where that fits, both types, signs, both layouts, the statistics' gather
+    rng = np.random.default_rng(900 + B)
+    for M, K in ((1, B), (5, B), (67, 2 * B)) if B <= 8192 else ((3, B),):
+        x = windowed_bf16(rng, M, K, lo=100, hi=150)
+        xf = (x.astype(np.uint32) << 16).view(np.float32)
+        for signs in (None, rng.choice([-1, 1], size=K).astype(np.int8)):
+            sd = None if signs is None else to_dev(signs)
+            rc, rs = orc.rotate_quantize_fused(x, B, signs=signs)
+            ra, rn, _ = orc.block_stats(x, B, [1.0, 1.0e6], signs=signs)
+            for xd in (to_dev(x), to_dev(xf)):
+                c, s = brq.rotate_quantize_fused(xd, B, signs=sd)
+                assert np.array_equal(to_host(s), rs) and np.array_equal(to_host(c), rc)
+                c, s = brq.to_rowmajor(*brq.rotate_quantize_fused(xd, B, layout="tiled", signs=sd), M, K)
+                assert np.array_equal(to_host(s), rs) and np.array_equal(to_host(c), rc)
+                amax, counts, _ = brq.block_stats(xd, B, [1.0, 1.0e6], signs=sd)
+                assert np.array_equal(to_host(amax), ra) and np.array_equal(to_host(counts).astype(np.uint64), rn)
+                y32 = brq.block_rotate(xd, B, signs=sd)
+                assert np.array_equal(to_host(y32), orc.block_rotate(x, B, signs=signs))
+                y16 = brq.block_rotate(xd, B, out_dtype=torch.bfloat16, signs=sd)
+                assert torch.equal(y16.float(), y32.to(torch.bfloat16).float())
