@@ -336,6 +336,38 @@ __device__ __forceinline__ uint32_t encode8_e2m1(const float (&y)[8], uint32_t s
     return w & (nz | 0x77777777u);
 }
 
+// ---- the tiled operand layout
+
+// Byte offsets of chunk kc (8 elements = 4 code bytes) of row `row` in the tiled layout.
+__device__ __forceinline__ uint64_t tiled_code_offset(uint32_t row, uint32_t kc, uint32_t stages) {
+    return ((uint64_t)(row >> 6) * stages + (kc >> 4)) * 4096u + (row & 63u) * 64u + (kc & 15u) * 4u;
+}
+__device__ __forceinline__ uint64_t tiled_scale_offset(uint32_t row, uint32_t kc, uint32_t sstages) {
+    return ((uint64_t)(row >> 6) * sstages + (kc >> 6)) * 1024u + (row & 63u) * 16u + ((kc >> 2) & 15u);
+}
+
+// Tiled layout, K not a multiple of 512: the groups between K and the next multiple of 512 are written as zeros (16
+// zero code bytes, scale byte 0) for every row, so that the LDS-staged product kernels can run whole 512-element
+// superstages over tiled operands of any K.  Every quantizing kernel does it itself, spread over all of its
+// threads: as a launch of its own it cost 2 to 4 us in front of a kernel of 10.
+struct KPad {
+    uint8_t *codes, *scales;
+    uint32_t rows, g0, n, stages, sstages;     // n groups per row from group g0 on; 0: nothing to do
+    static KPad of(bool tiled, uint8_t* codes, uint8_t* scales, int64_t M, int64_t K) {
+        const int64_t Kp = (K + 511) / 512 * 512;
+        return KPad{codes, scales, (uint32_t)M, (uint32_t)(K / 32), tiled ? (uint32_t)((Kp - K) / 32) : 0u,
+                    (uint32_t)(Kp / 128), (uint32_t)(Kp / 512)};
+    }
+    __device__ __forceinline__ void zero(uint32_t thread, uint32_t threads) const {
+        if (n == 0) return;     // uniform
+        for (uint64_t i = thread; i < (uint64_t)rows * n; i += threads) {
+            const uint32_t row = (uint32_t)(i / n), g = g0 + (uint32_t)(i - (uint64_t)row * n);
+            *reinterpret_cast<v4i*>(codes + tiled_code_offset(row, g * 4, stages)) = v4i{0, 0, 0, 0};
+            scales[tiled_scale_offset(row, g * 4, sstages)] = 0;
+        }
+    }
+};
+
 // ---- LDS-DMA loads (global memory -> LDS without passing through VGPRs)
 
 // One LDS-DMA load: 64 lanes x 16 bytes from base + voff(lane) to LDS lds_base + LDS_OFF +

@@ -48,9 +48,6 @@ hipError_t launch_block_summary(const float* amax, const float* sqerr, const flo
                                 const float* edges, int nedges, unsigned long long* hist, unsigned long long* counts,
                                 double* sums, hipStream_t s);
 
-// Tiled operand whose K is not a multiple of 512: writes the K padding of rows 0..M-1 as zeros.
-hipError_t launch_zero_kpad(uint8_t* codes, uint8_t* scales, int64_t M, int64_t K, hipStream_t s);
-
 // Rotation by caller-supplied 32 x 32 blocks R[nR][32][32] (nR = 1 or K/32) on the matrix cores.
 // mode 0: y = x R_block (y fp32 or bf16); mode 2: fused with the quantizer.  K % 128 == 0.
 hipError_t launch_matrix_rotate(int mode, bool in_bf16, bool out_bf16, const void* x, int64_t M, int64_t K, int64_t ldx,

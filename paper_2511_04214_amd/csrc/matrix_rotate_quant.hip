@@ -40,6 +40,7 @@ struct Args {
     uint8_t* codes;
     uint8_t* scales;
     uint32_t stages, sstages;   // tiled output: blocks per slab; 0 = row-major
+    KPad pad;               // tiled output: the groups between K and the next multiple of 512
     uint32_t ntiles, nsplits, ncols;   // row tiles of 32, row walkers per column group, column groups (32 NB columns each)
 };
 
@@ -99,6 +100,7 @@ __global__ void __launch_bounds__(256) k_matrot(Args a) {
                                                       // rows of one chunk then cover all 64 banks
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t m = lane & 31, h = lane >> 5;
+    if constexpr (MODE == 2) a.pad.zero(blockIdx.x * 256u + threadIdx.x, gridDim.x * 256u);
     const uint32_t wid = blockIdx.x * 4u + wave;
     if (wid >= a.ncols * a.nsplits) return;          // uniform per wavefront; no barrier below
     const uint32_t colgrp = wid % a.ncols, split = wid / a.ncols;
@@ -339,10 +341,7 @@ hipError_t launch_matrix_rotate(int mode, bool in_bf16, bool out_bf16, const voi
     if (want < 1) want = 1;
     const uint32_t most = (a.ntiles + 3u) / 4u;
     a.nsplits = want < most ? want : most;
-    if (mode == 2 && tiled && Kp != K) {
-        hipError_t e = launch_zero_kpad(codes, scales, M, K, s);
-        if (e != hipSuccess) return e;
-    }
+    a.pad = KPad::of(mode == 2 && tiled, codes, scales, M, K);
     constexpr int LDS = 4 * matrot::wave_lds(NB);          // 72 KB: above the default limit (setup_matrix_rotate)
     const dim3 grid((a.ncols * a.nsplits + 3u) / 4u), block(256);
     if (mode == 0) {

@@ -31,6 +31,8 @@ struct RowArgs {
     const void* x2;        // producer kernels: the `up` matrix [M][ldx2] (x is then `gate`)
     int64_t ldx2;
     uint32_t hround;       // producer kernels: the activation passes through bf16
+    uint32_t sign_fixed;   // the grid was sized so that a lane's column is the same in every pass
+    uint32_t rows, nitems; // k_rowwise_t4 (next to the words it needs first: one scalar load)
     // MODE_STATS outputs (any may be null) and thresholds
     float* amax;                   // [M][K/32]
     float* sqerr;                  // [M][K/32]
@@ -38,7 +40,7 @@ struct RowArgs {
     unsigned long long* counts;    // [nt], added to
     uint32_t nt;
     float th[8];
-    uint32_t sign_fixed;   // the grid was sized so that a lane's column is the same in every pass
+    KPad pad;              // tiled output: the groups between K and the next multiple of 512
 };
 
 // The random sign diagonal of a randomized Hadamard rotation (Sec. 5.1 and the Appendix use
@@ -56,14 +58,6 @@ __device__ __forceinline__ void flip(float (&v)[8], const uint32_t (&m)[8]) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = as_f32(as_u32(v[i]) ^ m[i]);
 }
-// Byte offsets of chunk kc (8 elements = 4 code bytes) of row `row` in the tiled layout.
-__device__ __forceinline__ uint64_t tiled_code_offset(uint32_t row, uint32_t kc, uint32_t stages) {
-    return ((uint64_t)(row >> 6) * stages + (kc >> 4)) * 4096u + (row & 63u) * 64u + (kc & 15u) * 4u;
-}
-__device__ __forceinline__ uint64_t tiled_scale_offset(uint32_t row, uint32_t kc, uint32_t sstages) {
-    return ((uint64_t)(row >> 6) * sstages + (kc >> 6)) * 1024u + (row & 63u) * 16u + ((kc >> 2) & 15u);
-}
-
 // ---- chunk load / store ---------------------------------------------------------
 
 // X is read exactly once and the outputs are next touched by another kernel: loads and the
@@ -390,6 +384,7 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
             }
         }
     }
+    if constexpr (MODE == MODE_QUANT || MODE == MODE_FUSED) a.pad.zero(blockIdx.x * NT + threadIdx.x, gridDim.x * NT);
     if constexpr (MODE == MODE_STATS) {
         if (a.counts) stats_flush(cnt, red, a);   // uniform
     }
@@ -401,15 +396,17 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
 // stage: lane l holds chunk (l & 15) of row 4 rq + (l >> 4), reads 4 x 256 contiguous bytes and
 // writes 256 contiguous bytes of codes (two whole lines).  Every address is a wavefront-uniform
 // base plus a per-lane constant.  Rotation blocks of up to 16 chunks stay inside one row's lanes.
-template <int LOG2B, bool IN_BF16, int MODE, bool PROD>
-__global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a, uint32_t rows, uint32_t nitems) {
+// PAD: K % 512 != 0.  (Where there is nothing to pad, testing for it costs 1 % of 56 us: the workgroups are short.)
+template <int LOG2B, bool IN_BF16, int MODE, bool PROD, bool PAD>
+__global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
+    const uint32_t rows = a.rows, nitems = a.nitems;
     static_assert(LOG2B == 0 || (LOG2B >= 3 && LOG2B <= 7), "a rotation block must fit 16 lanes");
     constexpr int ES = IN_BF16 ? 2 : 4;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lc = (wht_mirrored(LOG2B) ? chunk_of_lane(lane) : lane) & 15u;   // this lane's chunk of the stage
     const float cs = as_f32(norm_bits(LOG2B)) * wht_sign<LOG2B>(lc);
     const uint32_t spr = a.cpr >> 4;                                   // stages per row
-    const uint32_t lrow = lane >> 4;
+    const uint32_t lrow = lane >> 4, out_lane = wht_mirrored(LOG2B) ? (lane & 48u) + lc : lane;
     uint32_t sm[8];
     const bool presigned = MODE != MODE_QUANT && a.signs && a.sign_fixed;   // uniform
     if (presigned) sign_masks(sm, a.signs + ((size_t)((blockIdx.x * 4u + wave) % spr) * 16u + lc) * 8);
@@ -447,10 +444,11 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a, uint32_t rows, ui
         uint8_t* cbase = reinterpret_cast<uint8_t*>(a.codes) + ((uint64_t)(row0 >> 6) * a.stages + st) * 4096u + (row0 & 63u) * 64u;
         uint8_t* sbase = a.scales + ((uint64_t)(row0 >> 6) * a.sstages + (st >> 2)) * 1024u + (row0 & 63u) * 16u + (st & 3u) * 4u;
         if (row0 + lrow < rows) {
-            __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + lrow * 64u + lc * 4u));
+            __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + out_lane * 4u));
             if ((lane & 3) == 0) *(sbase + lrow * 16u + (lc >> 2)) = (uint8_t)sb;
         }
     }
+    if constexpr (PAD) a.pad.zero(blockIdx.x * 256u + threadIdx.x, gridDim.x * 256u);
 }
 
 // ---- 1024 <= B <= 8192 in registers (includes the global, full-K rotation) ----
@@ -479,6 +477,7 @@ __global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_ro
     const uint32_t half = W == 2 ? wave : 0u;
     const uint32_t lc = chunk_of_lane(lane);
     const float cs = as_f32(norm_bits(LOG2B)) * wht_sign<9>(lc);
+    if constexpr (MODE == MODE_FUSED) a.pad.zero(blockIdx.x * (uint32_t)reg_threads(LOG2B) + threadIdx.x, gridDim.x * (uint32_t)reg_threads(LOG2B));
     __shared__ v4f xch[W == 2 ? 2 * NJ * 64 : 1];                               // [wavefront][piece][4 values][lane]
     __shared__ uint32_t red[8];
     uint32_t cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -622,6 +621,7 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
     extern __shared__ float lds[];   // B floats
 
     const uint32_t tid = threadIdx.x, lane = tid & 63;
+    if constexpr (MODE == MODE_FUSED) a.pad.zero(blockIdx.x * (uint32_t)NT + tid, gridDim.x * (uint32_t)NT);
     const uint32_t lc = chunk_of_lane(lane);
     const float sigma = wht_sign<9>(lc);
     __shared__ uint32_t red[8];
@@ -745,7 +745,10 @@ static hipError_t launch_inwave(const RowArgs& a, bool contig, hipStream_t s) {
             int grid = rowwise_grid(nitems * 64u, 1, cus);
             RowArgs b = a;
             b.sign_fixed = a.signs ? fix_columns(grid, a.cpr >> 4, 4) : 0;
-            hipLaunchKernelGGL((k_rowwise_t4<LOG2B, IN_BF16, MODE, PROD>), dim3(grid), dim3(256), 0, s, b, rows, nitems);
+            b.rows = rows;
+            b.nitems = nitems;
+            if (b.pad.n) hipLaunchKernelGGL((k_rowwise_t4<LOG2B, IN_BF16, MODE, PROD, true>), dim3(grid), dim3(256), 0, s, b);
+            else hipLaunchKernelGGL((k_rowwise_t4<LOG2B, IN_BF16, MODE, PROD, false>), dim3(grid), dim3(256), 0, s, b);
             return hipGetLastError();
         }
     }
@@ -827,31 +830,6 @@ static hipError_t dispatch_b(int log2b, const RowArgs& a, bool contig, int64_t M
     }
 }
 
-// Tiled layout, K not a multiple of 512: the groups between K and the next multiple of 512 are
-// written as zeros (16 zero code bytes, scale byte 0) for every row, so that the persistent
-// product kernel can run whole 512-element superstages over tiled operands.  One lane per
-// padding group.
-__global__ void __launch_bounds__(256) k_zero_kpad(uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                                                   uint32_t rows, uint32_t g0, uint32_t gpad, uint32_t stages,
-                                                   uint32_t sstages) {
-    const uint64_t n = (uint64_t)rows * gpad;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) {
-        const uint32_t row = (uint32_t)(i / gpad), g = g0 + (uint32_t)(i - (uint64_t)row * gpad);
-        *reinterpret_cast<v4i*>(codes + tiled_code_offset(row, g * 4, stages)) = v4i{0, 0, 0, 0};
-        scales[tiled_scale_offset(row, g * 4, sstages)] = 0;
-    }
-}
-
-hipError_t launch_zero_kpad(uint8_t* codes, uint8_t* scales, int64_t M, int64_t K, hipStream_t s) {
-    const int64_t Kp = (K + 511) / 512 * 512;
-    if (Kp == K || M == 0) return hipSuccess;
-    const uint32_t gpad = (uint32_t)((Kp - K) / 32);
-    const int64_t want = (M * gpad + 255) / 256;
-    hipLaunchKernelGGL(k_zero_kpad, dim3((uint32_t)(want < 4096 ? want : 4096)), dim3(256), 0, s, codes, scales,
-                       (uint32_t)M, (uint32_t)(K / 32), gpad, (uint32_t)(Kp / 128), (uint32_t)(Kp / 512));
-    return hipGetLastError();
-}
-
 // mode: RowMode; log2b: 0 for MODE_QUANT, else 3..14.  Arguments are already validated.
 hipError_t launch_rowwise(int mode, int log2b, bool in_bf16, bool out_bf16, const void* x, int64_t M,
                           int64_t K, int64_t ldx, void* y, int64_t ldy, uint8_t* codes, uint8_t* scales,
@@ -868,16 +846,14 @@ hipError_t launch_rowwise(int mode, int log2b, bool in_bf16, bool out_bf16, cons
     a.hround = (prod && prod->through_bf16) ? 1u : 0u;
     a.signs = signs;
     a.sign_fixed = 0;
+    a.rows = a.nitems = 0;
     a.x = x; a.y = y; a.codes = reinterpret_cast<uint32_t*>(codes); a.scales = scales;
     a.ldx = ldx; a.ldy = ldy; a.cpr = (uint32_t)(K / 8); a.nchunks = (uint32_t)(M * (K / 8));
     const int64_t Kp = (K + 511) / 512 * 512;
     a.stages = tiled ? (uint32_t)(Kp / 128) : 0u;
     a.sstages = tiled ? (uint32_t)(Kp / 512) : 0u;
+    a.pad = KPad::of(tiled && mode != MODE_ROTATE && mode != MODE_STATS, codes, scales, M, K);
     bool contig = (ldx == K) && (mode != MODE_ROTATE || ldy == K) && (!prod || prod->ldu == K);
-    if (tiled && Kp != K && mode != MODE_ROTATE) {
-        hipError_t e = launch_zero_kpad(codes, scales, M, K, s);
-        if (e != hipSuccess) return e;
-    }
     if (mode == MODE_STATS) {   // log2b = 0: no rotation
         if (log2b == 0)
             return in_bf16 ? launch_inwave<0, true, MODE_STATS, false>(a, contig, s)
