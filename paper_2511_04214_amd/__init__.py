@@ -84,7 +84,7 @@ def init():
 
 
 def _check(status):
-    if status != 0:
+    if status:
         raise BrqError(status, lib().brq_strerror(status).decode())
 
 
@@ -99,14 +99,17 @@ def _dtype_code(t):
 def _rows(t, name):
     if not t.is_cuda:
         raise ValueError("%s must be a GPU tensor (libbrq has no CPU path)" % name)
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or (shape[1] > 1 and stride[1] != 1):
         raise ValueError("%s must be 2-D with contiguous rows" % name)
-    return t.shape[0], t.shape[1], (t.stride(0) if t.shape[0] > 1 else t.shape[1])
+    return shape[0], shape[1], (stride[0] if shape[0] > 1 else shape[1])
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # the handle alone: a Stream object for every call costs as much as the launch behind it
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _signs_ptr(signs, K):
@@ -129,9 +132,19 @@ def block_rotate(x, B, out_dtype=torch.float32, out=None, stream=None, signs=Non
 
 
 def _layout_code(layout):
-    if layout not in LAYOUTS:
+    code = LAYOUTS.get(layout) if isinstance(layout, str) else None
+    if code is None:
         raise ValueError("layout must be one of %s" % sorted(LAYOUTS))
-    return LAYOUTS[layout]
+    return code
+
+
+def _operand_size(rows, K, layout):
+    """operand_bytes without the call into the library, which costs more than the sum; sizes it refuses go there."""
+    if rows < 0 or K <= 0 or K % 32 != 0 or rows >= 1 << 31 or K >= 1 << 31:
+        return operand_bytes(rows, K, layout)
+    if layout == "tiled":
+        rows, K = (rows + 63) // 64 * 64, (K + 511) // 512 * 512
+    return rows * (K // 2), rows * (K // 32)
 
 
 def operand_bytes(rows, K, layout="rowmajor"):
@@ -144,20 +157,18 @@ def operand_bytes(rows, K, layout="rowmajor"):
 def _alloc_q(x, M, K, codes, scales, layout):
     """Row-major operands are [M, K/2] and [M, K/32] tensors, tiled operands flat byte buffers."""
     if layout == "rowmajor":
-        cshape, sshape = (M, K // 2), (M, K // 32)
+        nc, ns = M * (K // 2), M * (K // 32)
     else:
-        cb, sb = operand_bytes(M, K, layout)
-        cshape, sshape = (cb,), (sb,)
+        nc, ns = _operand_size(M, K, layout)
     if codes is None:
-        codes = torch.empty(cshape, dtype=torch.uint8, device=x.device)
+        codes = torch.empty((M, K // 2) if layout == "rowmajor" else (nc,), dtype=torch.uint8, device=x.device)
     if scales is None:
-        scales = torch.empty(sshape, dtype=torch.uint8, device=x.device)
+        scales = torch.empty((M, K // 32) if layout == "rowmajor" else (ns,), dtype=torch.uint8, device=x.device)
     if not (codes.is_contiguous() and scales.is_contiguous()):
         raise ValueError("codes and scales must be contiguous")
     if codes.dtype != torch.uint8 or scales.dtype != torch.uint8 or not (codes.is_cuda and scales.is_cuda):
         raise ValueError("codes and scales must be uint8 GPU tensors")
-    if codes.numel() < cshape[0] * (cshape[1] if len(cshape) > 1 else 1) or \
-            scales.numel() < sshape[0] * (sshape[1] if len(sshape) > 1 else 1):
+    if codes.numel() < nc or scales.numel() < ns:
         raise ValueError("codes or scales buffer too small for this operand and layout")
     return codes, scales
 
@@ -318,6 +329,16 @@ def to_rowmajor(codes_tiled, scales_tiled, rows, K, stream=None):
     return codes, scales
 
 
+def _result(out, M, N, dtype, device):
+    """(the product's result tensor, its row pitch): `out`, checked, or a new one."""
+    if out is None:
+        return torch.empty((M, N), dtype=dtype, device=device), (N if M <= 1 or N > 0 else 1)
+    _, _, ldy = _rows(out, "out")
+    if out.shape[0] != M or out.shape[1] != N:
+        raise ValueError("out must be [M, N]")
+    return out, ldy
+
+
 def mxfp4_gemm(aq, as_, wq, ws, out_dtype=torch.float32, out=None, stream=None, a_layout="rowmajor",
                w_layout="rowmajor", M=None, N=None, K=None, clock=None, no_loads=False):
     """Y[M, N] = deq(aq, as) @ deq(wq, ws)^T on the block-scaled MFMA (brq_mxfp4_gemm).
@@ -344,13 +365,10 @@ def mxfp4_gemm(aq, as_, wq, ws, out_dtype=torch.float32, out=None, stream=None, 
     if M is None or N is None or K is None:
         raise ValueError("M, N and K must be given for tiled operands")
     for (c, s_, rows, lay, n) in ((aq, as_, M, a_layout, "a"), (wq, ws, N, w_layout, "w")):
-        cb, sb = operand_bytes(rows, K, lay)
+        cb, sb = _operand_size(rows, K, lay)
         if c.numel() < cb or s_.numel() < sb or (lay == "rowmajor" and tuple(s_.shape) != (rows, K // 32)):
             raise ValueError("operand %s: buffers do not match its shape and layout" % n)
-    y = torch.empty((M, N), dtype=out_dtype, device=aq.device) if out is None else out
-    _, _, ldy = _rows(y, "out")
-    if y.shape[0] != M or y.shape[1] != N:
-        raise ValueError("out must be [M, N]")
+    y, ldy = _result(out, M, N, out_dtype, aq.device)
     if clock is not None:
         if not (clock.is_cuda and clock.is_contiguous() and clock.dtype == torch.int64 and clock.numel() == 6):
             raise ValueError("clock must be a contiguous int64 GPU tensor of 6 elements")
@@ -372,15 +390,13 @@ def rotate_quantize_gemm_fused(x, B, wq, ws, N, out_dtype=torch.float32, out=Non
     for t, n in ((wq, "wq"), (ws, "ws")):
         if not (t.is_cuda and t.is_contiguous() and t.dtype == torch.uint8):
             raise ValueError("%s must be a contiguous uint8 GPU tensor" % n)
-    cb, sb = operand_bytes(N, K, w_layout)
+    lw = _layout_code(w_layout)
+    cb, sb = _operand_size(N, K, w_layout)
     if wq.numel() < cb or ws.numel() < sb:
         raise ValueError("weight buffers do not match N, K and the layout")
-    y = torch.empty((M, N), dtype=out_dtype, device=x.device) if out is None else out
-    _, _, ldy = _rows(y, "out")
-    if y.shape[0] != M or y.shape[1] != N:
-        raise ValueError("out must be [M, N]")
+    y, ldy = _result(out, M, N, out_dtype, x.device)
     _check(lib().brq_rotate_quantize_gemm_fused(x.data_ptr(), _dtype_code(x), M, K, ldx, B, _signs_ptr(signs, K),
-                                                wq.data_ptr(), ws.data_ptr(), _layout_code(w_layout), N, y.data_ptr(),
+                                                wq.data_ptr(), ws.data_ptr(), lw, N, y.data_ptr(),
                                                 _dtype_code(y), ldy, _stream(stream)))
     return y
 
