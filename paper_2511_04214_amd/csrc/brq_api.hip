@@ -26,7 +26,6 @@ hipError_t device_cus(int* cus) {
         if (v <= 0) return hipErrorInvalidDevice;
         if (hipError_t e = setup_gemm_tiled(); e != hipSuccess) return e;
         if (hipError_t e = setup_gemm_mid(); e != hipSuccess) return e;
-        if (hipError_t e = setup_gemm_smallm(); e != hipSuccess) return e;
         if (hipError_t e = setup_matrix_rotate(); e != hipSuccess) return e;
         if (hipError_t e = setup_gemm_decode_fused(); e != hipSuccess) return e;
         slot.cus = v;

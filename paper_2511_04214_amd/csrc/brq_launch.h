@@ -6,14 +6,13 @@
 namespace brq {
 
 // Per-device facts and one-time set-up.  The launchers size their grids by the number of compute units
-// and three kernel families ask for more than the default 64 KB of LDS, which HIP wants declared per
+// and four kernel families ask for more than the default 64 KB of LDS, which HIP wants declared per
 // function and device before the first launch.  device_cus() returns the CU count of the CURRENT device and
 // on its first call for that device (under a lock, keyed by the device id) runs the three set-up routines;
 // brq_init() is that call made ahead of time.  Nothing else in the library outlives a call.
 hipError_t device_cus(int* cus);
 hipError_t setup_gemm_tiled();     // mxfp4_gemm_tiled.hip
 hipError_t setup_gemm_mid();       // mxfp4_gemm_mid.hip
-hipError_t setup_gemm_smallm();    // mxfp4_gemm.hip
 hipError_t setup_matrix_rotate();  // matrix_rotate_quant.hip
 hipError_t setup_gemm_decode_fused();   // mxfp4_gemm.hip
 
@@ -82,7 +81,7 @@ hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int6
                              bool no_loads = false);
 
 // One output tile per workgroup, the tile one of a family (mxfp4_gemm_mid.hip): any M, N and pitch.
-constexpr int MID_TILES = 4;
+constexpr int MID_TILES = 5;
 bool mid_gemm_supported(int64_t M, int64_t N, int64_t K, bool a_tiled, bool w_tiled);
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s);

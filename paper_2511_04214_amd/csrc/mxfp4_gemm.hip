@@ -126,19 +126,15 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
     }
 }
 
-// ---- M <= 128 (decode batches): weight streaming with the activations in LDS ----------------
+// ---- M <= 16 (decode batches): weight streaming with the activations in LDS ----------------
 // HBM-bound: every weight byte is read exactly once.  A wavefront owns its weight rows for the whole
 // of K (no cross-wavefront reduction, fixed summation order) and streams them through registers,
-// three 512-element superstages in rotation.  With several tiles of activation rows every wavefront
-// would re-read all of A (M x K/2 bytes against its own weight bytes), so the 4 wavefronts of a
+// three 512-element superstages in rotation.  Every wavefront would re-read all of A, so the 4 wavefronts of a
 // workgroup share the activations: one superstage of A at a time goes into LDS by LDS-DMA (three
 // buffers, one barrier per superstage), wavefront w bringing stage w.  The MFMA is the 32x32x64
-// one, a wavefront per 32 weight rows and MT tiles of 32 activation rows: with the 16x16x128 form
-// every wavefront reads all of A out of LDS for only 16 weight rows and the fragment reads bound the
-// kernel (28 us at M = 64, 40 at M = 128 on the 28672 x 8192 decode shape, against 23 and 31 here);
-// the persistent tiled kernel at these sizes has one 128 x 256 tile on fewer than half of the CUs,
-// each with only its 4-stage ring of weights in flight (44 us), where 4 x N/128 wavefronts here
-// each keep two superstages of their own rows in flight.
+// one, a wavefront per 32 weight rows; rows past M repeat row M - 1.  (More rows than one tile of 32 go to the
+// one-tile kernel: with two to four row tiles a turn waits for the latency of two superstages and multiplies longer
+// than it waits, 28672 x 8192 with 64 / 128 rows 28.9 / 34.7 us against 24.8 / 28.9.)
 // Operand fragments (32x32x64: lane (r, h) = (lane & 31, lane >> 5) supplies 32 consecutive K
 // elements of row r): within a 128-element stage (64 code bytes per row) lane half h owns bytes
 // [32 h, 32 h + 32), MFMA step j of the stage takes bytes 32 h + 16 j, i.e. group 2 h + j of the
@@ -149,20 +145,20 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 
 // Weight register sets = LDS buffers of A; SETS - 1 superstages are in flight (4 sets measured no faster).
 constexpr int SMALLM_SETS = 3;
-constexpr int smallm_lds_bytes(int MT) { return SMALLM_SETS * (MT * 8192 + 4096); }
+constexpr int SMALLM_LDS_BYTES = SMALLM_SETS * (8192 + 4096);
 
 // TAIL = (K / 512) % SETS: the superstages left after the main loop, which takes them SETS at a time in
 // one basic block (no load behind a branch: the compiler's count of the outstanding weight loads is
 // then exact; with early exits inside the loop it falls back to waiting for all of them).
-template <int MT, int TAIL>
+template <int TAIL>
 __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as,
                                                      int a_tiled, const uint8_t* __restrict__ wq,
                                                      const uint8_t* __restrict__ ws, int w_tiled, int M, int N, int K,
                                                      void* __restrict__ y, int out_bf16, int64_t ldy) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    constexpr int STG = MT * 2048;                      // one stage of A codes: MT * 32 rows x 64 bytes
-    constexpr int BUF = 4 * STG + 4096;                 // codes [4 stages][MT * 32 rows][64], then scales [4 tiles][64 rows][16]
-    constexpr int NA = 2 * MT + 1;                      // LDS-DMA instructions per wavefront and superstage
+    constexpr int STG = 2048;                           // one stage of A codes: 32 rows x 64 bytes
+    constexpr int BUF = 4 * STG + 4096;                 // codes [4 stages][32 rows][64], then scales, 1 KB per wavefront
+    constexpr int NA = 3;                               // LDS-DMA instructions per wavefront and superstage
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
     const int n0 = blockIdx.x * 128 + wave * 32;
@@ -181,9 +177,9 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
         return a_tiled ? (uint32_t)((row >> 6) * (Kp / 512) * 1024 + (row & 63) * 16) : (uint32_t)((int64_t)row * (K / 32));
     };
     // one DMA instruction = 16 rows x 64 bytes; lane i brings chunk (i & 3) ^ ((i >> 4) & 3) of row i >> 2
-    uint32_t voc[2 * MT];
+    uint32_t voc[2];
 #pragma unroll
-    for (int j = 0; j < 2 * MT; ++j)
+    for (int j = 0; j < 2; ++j)
         voc[j] = row_off_c(16 * j + (lane >> 2)) + (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
     // ... and one more the scale rows of 32-row tile `wave` (lanes 32..63 repeat them into the second half of
     // the tile's 1 KB slot; a wavefront without a tile of its own repeats row M - 1): every wavefront
@@ -193,17 +189,8 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     auto dma_a = [&](int ss, uint32_t buf) {
         const uint8_t* cb = uniform_ptr(aq + (int64_t)(4 * ss + wave) * a_cstep);
         const uint32_t lb = lds0 + buf * BUF + (uint32_t)wave * STG;
-#pragma unroll
-        for (int j = 0; j < 2 * MT; ++j) {
-            if (j == 0) dma16<0>(lb, cb, voc[0]);
-            if (j == 1) dma16<1024>(lb, cb, voc[1]);
-            if (j == 2) dma16<2048>(lb, cb, voc[j]);
-            if (j == 3) dma16<3072>(lb, cb, voc[j]);
-            if (j == 4) dma16<4096>(lb, cb, voc[j]);
-            if (j == 5) dma16<5120>(lb, cb, voc[j]);
-            if (j == 6) dma16<6144>(lb, cb, voc[j]);
-            if (j == 7) dma16<7168>(lb, cb, voc[j]);
-        }
+        dma16<0>(lb, cb, voc[0]);
+        dma16<1024>(lb, cb, voc[1]);
         dma16<0>(lds0 + buf * BUF + 4 * STG + (uint32_t)wave * 1024, uniform_ptr(as + (int64_t)ss * a_sstep), vos);
     };
     // a superstage of this lane's weight row: per stage t its two steps (32 bytes at 32 h), and the 16 scale bytes.
@@ -217,41 +204,29 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
                 c[2 * t + j] = *reinterpret_cast<const v4i*>(vw.codes + (int64_t)(4 * ss + t) * vw.cstep + h * 32 + j * 16);
         sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(vw.scales + (int64_t)ss * vw.sstep));
     };
-    v16f acc[MT];
-#pragma unroll
-    for (int j = 0; j < MT; ++j) acc[j] = v16f{};
+    v16f acc = {};
     const uint32_t sw = (uint32_t)(r >> 2) & 3u;
-    // The 8 steps (stage t, half-step j) of a superstage, each over the MT row tiles: consecutive MFMAs go
-    // to different accumulators, and the A fragments of step s + 1 are read while those of step s multiply.
+    // The 8 steps (stage t, half-step j) of a superstage; the A fragment of step s + 1 is read while step s multiplies.
     auto superstage = [&](uint32_t buf, const v4i (&c)[8], const v4i& sc) {
         const uint8_t* cb = lds + buf * BUF + r * 64;
-        const uint8_t* sb = lds + buf * BUF + 4 * STG + r * 16;
-        v4i asc[MT], af[2][MT];
-#pragma unroll
-        for (int jt = 0; jt < MT; ++jt) asc[jt] = *reinterpret_cast<const v4i*>(sb + jt * 1024);
-        auto read_step = [&](int st, v4i (&f)[MT]) {
-            const int t = st >> 1, j = st & 1;
-#pragma unroll
-            for (int jt = 0; jt < MT; ++jt)
-                f[jt] = *reinterpret_cast<const v4i*>(cb + t * STG + jt * 2048 + (((uint32_t)(2 * h + j) ^ sw) << 4));
+        const v4i asc = *reinterpret_cast<const v4i*>(lds + buf * BUF + 4 * STG + r * 16);
+        v4i af[2];
+        auto read_step = [&](int st) -> v4i {
+            return *reinterpret_cast<const v4i*>(cb + (st >> 1) * STG + (((uint32_t)(2 * h + (st & 1)) ^ sw) << 4));
         };
-        read_step(0, af[0]);
+        af[0] = read_step(0);
 #pragma unroll
         for (int st = 0; st < 8; ++st) {
             const int t = st >> 1, j = st & 1;
-            if (st + 1 < 8) read_step(st + 1, af[(st + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);   // keeps the reads ahead of this step's MFMAs
+            if (st + 1 < 8) af[(st + 1) & 1] = read_step(st + 1);
+            __builtin_amdgcn_sched_barrier(0);   // keeps the read ahead of this step's MFMA
             // group 4 t + 2 h + j of the superstage: byte 2 h + j of scale dword t
             const int scb = (int)(((uint32_t)sc[t] >> (16 * h + 8 * j)) & 0xffu);
-            v8i b = {};
+            const int sca = (int)(((uint32_t)asc[t] >> (16 * h + 8 * j)) & 0xffu);
+            v8i a = {}, b = {};
             b[0] = c[st][0]; b[1] = c[st][1]; b[2] = c[st][2]; b[3] = c[st][3];
-#pragma unroll
-            for (int jt = 0; jt < MT; ++jt) {
-                v8i a = {};
-                a[0] = af[st & 1][jt][0]; a[1] = af[st & 1][jt][1]; a[2] = af[st & 1][jt][2]; a[3] = af[st & 1][jt][3];
-                const int sca = (int)(((uint32_t)asc[jt][t] >> (16 * h + 8 * j)) & 0xffu);
-                acc[jt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[jt], 4, 4, 0, sca, 0, scb);
-            }
+            a[0] = af[st & 1][0]; a[1] = af[st & 1][1]; a[2] = af[st & 1][2]; a[3] = af[st & 1][3];
+            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 4, 4, 0, sca, 0, scb);
         }
     };
     // D = SETS - 1 superstages ahead.  Issue order per wavefront: A(0), W(0), .., A(D - 1), W(D - 1); then turn
@@ -309,14 +284,12 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the repeated loads land before the LDS is released
     const int col = n0 + r;
 #pragma unroll
-    for (int jt = 0; jt < MT; ++jt)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = 32 * jt + 8 * q + 4 * h + i;
-                if (row < M && col < N) store_out(y, out_bf16, (int64_t)row * ldy + col, acc[jt][4 * q + i]);
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int row = 8 * q + 4 * h + i;
+            if (row < M && col < N) store_out(y, out_bf16, (int64_t)row * ldy + col, acc[4 * q + i]);
+        }
 }
 
 // ---- M <= 16 with the online step inside (Sec. 4.3: the rotation R_4 and the quantizer in front of the
@@ -325,7 +298,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
 // the same arithmetic as the row-wise kernels, a quad of lanes per 32-element group - in the layout the
 // weight-streaming loop reads: codes [stage][16 rows][64 bytes] with the 16-byte chunks of row i XOR-swizzled
 // by (i >> 2) & 3, scales [superstage][16 rows][16 bytes].  Then it streams its 128 weight rows exactly like
-// k_gemm_smallm with one tile, without any barrier (the activations never change), so the result is bit
+// k_gemm_smallm, without any barrier (the activations never change), so the result is bit
 // for bit that of brq_mxfp4_gemm on the output of brq_rotate_quantize_fused.  The first superstages of
 // weights are requested before the prologue and arrive under it.  What this saves is one small launch; what
 // it costs is that every one of the N / 128 workgroups repeats the quantization of the same activations.
@@ -494,20 +467,7 @@ hipError_t launch_mfma_ceiling(const uint8_t* operands, int iters, int workgroup
 
 using SmallmKern = void (*)(const uint8_t*, const uint8_t*, int, const uint8_t*, const uint8_t*, int, int, int, int, void*,
                             int, int64_t);
-static const SmallmKern smallm_kern[4][4] = {
-    {k_gemm_smallm<1, 0>, k_gemm_smallm<1, 1>, k_gemm_smallm<1, 2>, k_gemm_smallm<1, 3 % SMALLM_SETS>},
-    {k_gemm_smallm<2, 0>, k_gemm_smallm<2, 1>, k_gemm_smallm<2, 2>, k_gemm_smallm<2, 3 % SMALLM_SETS>},
-    {k_gemm_smallm<3, 0>, k_gemm_smallm<3, 1>, k_gemm_smallm<3, 2>, k_gemm_smallm<3, 3 % SMALLM_SETS>},
-    {k_gemm_smallm<4, 0>, k_gemm_smallm<4, 1>, k_gemm_smallm<4, 2>, k_gemm_smallm<4, 3 % SMALLM_SETS>}};
-
-// The weight-streaming kernels use up to 108 KB of LDS per workgroup: declared once per device.
-hipError_t setup_gemm_smallm() {
-    for (int m = 0; m < 4; ++m)
-        for (int t = 0; t < 4; ++t)
-            if (hipError_t e = hipFuncSetAttribute((const void*)smallm_kern[m][t], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   smallm_lds_bytes(1 + m)); e != hipSuccess) return e;
-    return hipSuccess;
-}
+static const SmallmKern smallm_kern[SMALLM_SETS] = {k_gemm_smallm<0>, k_gemm_smallm<1>, k_gemm_smallm<2>};
 
 static_assert(SMALLM_SETS == 3, "k_gemm_decode_fused writes its turns out for three register sets");
 
@@ -539,24 +499,26 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // ---- which LDS-staged kernel and output tile -------------------------------------------------
 // The candidates: the persistent kernel with its 256 x 256 and 128 x 256 tiles, and the one-tile-per-workgroup
 // kernel's family.  They are told apart by an estimate of the time, in microseconds:
-//     fixed + max(stages * alone * ceil(tiles / places), stages * full * tiles / CUs * filled + output)
+//     fixed + |stages * alone * ceil(tiles / places), stages * full * tiles / CUs * filled, bytes / 5 TB/s|_4 + store * output
 // `alone`: a stage of a tile while the chip is not full (the issue, load and LDS bound of one workgroup, at the
 // full clock); `full`: a stage's share of a chip full of them, which is what its energy costs (the chip holds 1.6
 // to 1.8 GHz of 2.4 with every CU multiplying); places = CUs x workgroups that fit one; filled: rows past M
-// are zeros in the one-tile kernel and cost half; output: 0.3 us per MB of bf16.  The constants are fitted to the six candidates'
-// times on 64 shapes (M 129 .. 8192, N 256 .. 28672, K 512 .. 11264) in each layout; there the choice is within
-// 1.3 % (tiled) and 0.8 % (row-major) of the best of the six on average, 17 % and 13 % at worst.  What it gives over
-// the rule it replaces (256 x 256, or 128 x 256 where the former do not fill the chip), tiled, us:
-// 300 x 28672 x 8192 54.3 -> 42.7; 1000 x 4096 x 11008 30.3 -> 26.6; 192 x 256 x 4096 12.6 -> 6.7.
-struct TileCost { float fixed, alone, full; };
+// are zeros in the one-tile kernel and cost half; bytes: both operands, from HBM; output: 0.6 us per MB of bf16.  The
+// three bounds blend into each other (4-norm).  The constants are fitted to the candidates' times, weights not in any
+// cache, on 50 tiled and 46 row-major shapes (M 17 .. 8192, N 256 .. 28672, K 512 .. 13312): the choice costs 1.0 % over
+// the best of the seven on average in either layout (22 % and 19 % at worst); the fit to repeated weights that it
+// replaces cost 3.9 % and 5.2 % (34 %, 42 %).  What the estimate gives over 256 x 256, or 128 x 256 where the former do not
+// fill the chip, tiled, us: 300 x 28672 x 8192 61 -> 45; 1000 x 4096 x 11008 41 -> 30; 200 x 512 x 4096 12.7 -> 8.2.
+struct TileCost { float fixed, alone, full, store; };
 struct Tile { int na, mb, per_cu, mid; TileCost tiled, rowmajor; };      // 64 mb x 64 na; mid: its number there, -1 = persistent
 static const Tile TILES[2 + MID_TILES] = {
-    {4, 4, 1, -1, {6.29f, 0.487f, 0.630f}, {6.33f, 0.521f, 0.838f}},
-    {4, 2, 1, -1, {4.19f, 0.266f, 0.393f}, {4.09f, 0.342f, 0.512f}},
-    {2, 1, 2, 0, {2.90f, 0.152f, 0.152f}, {2.36f, 0.193f, 0.221f}},
-    {2, 2, 2, 1, {3.31f, 0.188f, 0.237f}, {3.04f, 0.253f, 0.330f}},
-    {2, 3, 1, 2, {4.78f, 0.216f, 0.390f}, {4.09f, 0.300f, 0.501f}},
-    {4, 3, 1, 3, {6.55f, 0.382f, 0.610f}, {6.22f, 0.441f, 0.810f}},
+    {4, 4, 1, -1, {6.293f, 0.532f, 0.707f, 0.638f}, {6.786f, 0.666f, 0.844f, 0.744f}},
+    {4, 2, 1, -1, {5.092f, 0.299f, 0.380f, 0.762f}, {4.800f, 0.401f, 0.719f, 0.706f}},
+    {2, 1, 2, 0, {3.558f, 0.147f, 0.240f, 0.515f}, {2.661f, 0.269f, 0.301f, 0.723f}},
+    {2, 2, 2, 1, {3.816f, 0.226f, 0.254f, 0.464f}, {2.665f, 0.325f, 0.468f, 0.638f}},
+    {2, 3, 1, 2, {5.479f, 0.238f, 0.373f, 0.906f}, {4.662f, 0.335f, 0.426f, 1.157f}},
+    {4, 3, 1, 3, {5.916f, 0.376f, 0.741f, 0.601f}, {4.888f, 0.511f, 0.636f, 1.111f}},
+    {2, 5, 1, 4, {7.720f, 0.308f, 0.461f, 0.872f}, {7.159f, 0.402f, 0.548f, 0.792f}},
 };
 
 // Index into TILES, or -1 where no LDS-staged kernel takes the shape.
@@ -564,6 +526,8 @@ static int pick_tile(const Operand& a, const Operand& w, int64_t M, int64_t N, i
     const bool persistent = tiled_gemm_supported(M, N, K, out_bf16, ldy, a.tiled && w.tiled);
     const bool one_tile = mid_gemm_supported(M, N, K, a.tiled, w.tiled);
     const float stages = (float)((K + 511) / 512 * 4), output = 0.6e-6f * (float)M * (float)N * (out_bf16 ? 1.0f : 2.0f);
+    const float bytes = 0.53125f * ((float)M + (float)N) * (float)K / 5.0e6f;
+    auto pow4 = [](float x) { return x * x * x * x; };
     int best = -1;
     float least = 0.0f;
     for (int i = 0; i < 2 + MID_TILES; ++i) {
@@ -573,8 +537,8 @@ static int pick_tile(const Operand& a, const Operand& w, int64_t M, int64_t N, i
         const int64_t tm = (M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * t.per_cu;
         const float filled = t.mid < 0 ? 1.0f : 0.5f + 0.5f * (float)M / (float)(64 * t.mb * tm);
         const float alone = stages * c.alone * (float)((T + places - 1) / places);
-        const float full = stages * c.full * (float)T / (float)cus * filled + output;
-        const float cost = c.fixed + (alone > full ? alone : full);
+        const float full = stages * c.full * (float)T / (float)cus * filled;
+        const float cost = c.fixed + sqrtf(sqrtf(pow4(alone) + pow4(full) + pow4(bytes))) + c.store * output;
         if (best < 0 || cost < least) { best = i; least = cost; }
     }
     return best;
@@ -585,16 +549,17 @@ hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, int64_t M, int6
     const int64_t Kp = (K + 511) / 512 * 512;
     int cus = 0;
     if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;      // (also the per-device kernel set-up)
-    if (M <= 128 && (K == Kp || (a.tiled && w.tiled)) && Kp < (int64_t(1) << 26)) {
-        // decode batches: weight streaming with the activations shared through LDS
-        const auto& kern = smallm_kern;
-        const int mi = (int)((M - 1) / 32), tail = (int)((Kp / 512) % SMALLM_SETS);
+    // A few rows: weight streaming.  16 rows tiled, us, against the one-tile kernel's 64 x 128: N x K = 512 x 1024 4.0 / 4.5,
+    // 28672 x 8192 23.7 / 24.1, 8192 x 4096 9.8 / 9.5; row-major 2048 x 2048 7.9 / 6.2, 4096 x 8192 28.0 / 23.0; 32 rows
+    // 8192 x 4096 10.8 / 10.3 and, where it needed more row tiles, 64 rows 13.0 / 11.0, 128 rows 17.5 / 10.9.
+    if (M <= 16 && (K == Kp || (a.tiled && w.tiled)) && ((a.tiled && w.tiled) || !mid_gemm_supported(M, N, K, a.tiled, w.tiled)) &&
+        Kp < (int64_t(1) << 26)) {
         const dim3 grid((uint32_t)((N + 127) / 128)), block(256);
-        hipLaunchKernelGGL(kern[mi][tail], grid, block, smallm_lds_bytes(1 + mi), s, a.codes, a.scales, (int)a.tiled,
+        hipLaunchKernelGGL(smallm_kern[(Kp / 512) % SMALLM_SETS], grid, block, SMALLM_LDS_BYTES, s, a.codes, a.scales, (int)a.tiled,
                            w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy);
         return hipGetLastError();
     }
-    const int t = M > 16 ? pick_tile(a, w, M, N, K, out_bf16, ldy, cus) : -1;
+    const int t = M > 16 || K == Kp ? pick_tile(a, w, M, N, K, out_bf16, ldy, cus) : -1;
     if (t >= 0) {
         const int mid = TILES[t].mid;
         return mid < 0 ? launch_gemm_tiled(a, w, M, N, K, y, out_bf16, ldy, s, TILES[t].mb == 2)

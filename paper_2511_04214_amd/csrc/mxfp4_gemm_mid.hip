@@ -5,14 +5,14 @@
 //
 // Workgroup = 4 wavefronts (2 x 2), each with NA x MB MFMA tiles of 32 x 32.  As in the persistent kernel the
 // weights are the MFMA's row operand, K is consumed in stages of 128 elements, within a stage lane half h owns
-// groups 2h and 2h + 1, and operands travel HBM -> LDS by LDS-DMA into a ring of 4 stages whose 64-byte rows
+// groups 2h and 2h + 1, and operands travel HBM -> LDS by LDS-DMA into a ring of D stages whose 64-byte rows
 // have their 16-byte chunks XOR-swizzled by (row >> 2) & 3.
 //
 // What differs is the fragment schedule.  A stage of these tiles is 8 to 24 MFMAs (264 to 800 cycles) long,
 // too short to hide an LDS read between its barrier and its use.  The register file has room (64 to 192
 // accumulators of 512 registers), so ALL fragments of stage t + 1 are read while stage t multiplies:
 //   start of stage t   stage t + 1 has landed, everyone's reads of stage t's buffer are done: one barrier
-//   during stage t     2 (NA + MB) fragment reads of stage t + 1, the loads of stage t + 4 into stage t's
+//   during stage t     2 (NA + MB) fragment reads of stage t + 1, the loads of stage t + D into stage t's
 //                      buffer, and the MFMAs of stage t from registers filled a stage ago.
 // Nothing between the barrier and the MFMAs waits for LDS.
 //
@@ -21,8 +21,13 @@
 // bounds, and the stages that the window shares with the superstage before get scale bytes 0 in BOTH operands
 // (2^-127 * 2^-127 times at most 36 * 32 vanishes in an fp32 sum).
 //
-// LDS map (bytes), S = NA + MB: [0, 16K S) 4 stages x (W rows 4K NA | A rows 4K MB); then 2 scale buffers x
+// LDS map (bytes), S = NA + MB: D stages x (W rows 4K NA | A rows 4K MB); then ceil(D / 4) scale buffers x
 // (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the ring.
+//
+// D: as many stages as the LDS takes where that measured faster.  Two workgroups of 64 x 128 on a CU with 6 stages each
+// instead of 4: 200 x 4096 x 4096 11.2 -> 9.7 us, 300 x 28672 x 8192 75 -> 68.  The other tiles gain nothing from
+// depth (128 x 128 with 8 stages and one workgroup a CU instead of 4 and two: 58 -> 65 us on the latter); 320 x 128, for a few hundred rows, has
+// 5 and reads its weights once: 47.6 -> 44.8 us on the latter, row-major 2000 x 4096 x 11008 74 -> 66.
 #include "mfma_fp4.h"
 #include "brq_launch.h"
 
@@ -30,18 +35,20 @@ namespace brq {
 namespace mid {
 
 constexpr int stage_bytes(int NA, int MB) { return 4096 * (NA + MB); }
-constexpr int lds_bytes(int NA, int MB) { return 4 * stage_bytes(NA, MB) + 2 * 1024 * (NA + MB); }
+// D code stages and the scales of every superstage that has a stage among them
+constexpr int scale_bufs(int D) { return (D + 3) / 4; }
+constexpr int lds_bytes(int NA, int MB, int D) { return D * stage_bytes(NA, MB) + scale_bufs(D) * 1024 * (NA + MB); }
 
 // VEC: every 16-byte chunk of an output row is aligned and either wholly inside or outside N (N and ldy multiples
 // of 16 / sizeof(out)); otherwise elements are stored one by one.
-template <bool OUT_BF16, int NA, int MB>
-__global__ void __launch_bounds__(256, (lds_bytes(NA, MB) <= 81920 ? 2 : 1))
+template <bool OUT_BF16, int NA, int MB, int D>
+__global__ void __launch_bounds__(256, (lds_bytes(NA, MB, D) <= 81920 ? 2 : 1))
 k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const uint8_t* __restrict__ wq,
            const uint8_t* __restrict__ ws, int M, int N, int K, void* __restrict__ y, int64_t ldy, int a_tiled,
            int w_tiled, int vec) {
     constexpr int S = NA + MB, NM = NA * MB, NS = 2 * NM;      // MFMAs per step and per stage
     constexpr int TM = 64 * MB, TN = 64 * NA, STAGE = stage_bytes(NA, MB), OPER = 4096 * NA;
-    constexpr int SCALE_BASE = 4 * STAGE, SCALE_BUF = 1024 * S;
+    constexpr int NSB = scale_bufs(D), SCALE_BASE = D * STAGE, SCALE_BUF = 1024 * S;
     constexpr int SPW = (S + 3) / 4;                           // scale loads per wavefront and superstage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -100,7 +107,7 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
         ma[q] = __builtin_amdgcn_ballot_w64(row < mrows);
         if (row >= mrows) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<v4i*>(lds + u * STAGE + OPER + row * 64 + (lane & 3) * 16) = v4i{0, 0, 0, 0};
+            for (int u = 0; u < D; ++u) *reinterpret_cast<v4i*>(lds + u * STAGE + OPER + row * 64 + (lane & 3) * 16) = v4i{0, 0, 0, 0};
         }
     }
     const uint8_t* sbase[SPW];
@@ -122,34 +129,46 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     const int a_stage = a_tiled ? 4096 : 64, a_last = a_tiled ? (KQ - 1) * 16384 : K / 2 - 256;
     const uint32_t dst_w = lds0 + wave * (1024 * NA), dst_a = lds0 + OPER + wave * (1024 * MB);
     const uint8_t *pw = wbase, *pa = abase;                    // superstage that is being loaded
-    auto dma_scales = [&](int q) {                             // superstage q into scale buffer q & 1
-        const uint32_t b = (q & 1) ? (uint32_t)SCALE_BUF : 0u;
+    uint32_t ld_buf = 0, rd_buf = 0;                           // scale buffers of the superstages being loaded and read
+    auto mask_if_less = [](int a, int b) -> uint64_t {         // all lanes if a < b (uniform), in scalar registers
+        uint32_t m;                                            // (written out: the compiler makes vector registers of it)
+        asm("s_sub_i32 %0, %1, %2\n\ts_ashr_i32 %0, %0, 31" : "=s"(m) : "s"(a), "s"(b) : "scc");
+        return ((uint64_t)m << 32) | m;
+    };
+    auto load_super = [&](int q) {                             // (past the last superstage nothing is loaded: see dma_code)
+        const int qc = min(q, KQ - 1);
+        pw = wbase + (qc == KQ - 1 ? w_last : qc * 4 * w_stage);
+        pa = abase + (qc == KQ - 1 ? a_last : qc * 4 * a_stage);
+    };
+    auto dma_scales = [&](int q) {
+        const int qc = min(q, KQ - 1);
+        const uint64_t live = mask_if_less(q, KQ);
 #pragma unroll
-        for (int i = 0; i < SPW; ++i) dma16<0>(sdst[i] + b, sbase[i] + (q == KQ - 1 ? slast[i] : q * sstep[i]), vsc[i]);
+        for (int i = 0; i < SPW; ++i)
+            dma16_masked<0>(sdst[i] + ld_buf, sbase[i] + (qc == KQ - 1 ? slast[i] : qc * sstep[i]), vsc[i], live);
+        ld_buf = ld_buf + SCALE_BUF == NSB * SCALE_BUF ? 0u : ld_buf + SCALE_BUF;
     };
-    auto load_super = [&](int q) {
-        pw = wbase + (q == KQ - 1 ? w_last : q * 4 * w_stage);
-        pa = abase + (q == KQ - 1 ? a_last : q * 4 * a_stage);
-    };
-    // load I of stage U of that superstage, W and A alternating while there are both
-    auto dma_code = [&](auto Uc, auto Ic) {
+    // load I of stage U of that superstage into the ring's slot at byte `slot`, W and A alternating while there are
+    // both.  Past the last superstage (`live` = 0) no lane takes part: nothing is read or written, and the counted
+    // waits below see the same number of instructions in every stage.
+    auto dma_code = [&](auto Uc, auto Ic, uint32_t slot, auto Sure, uint64_t live) {
         constexpr int U = decltype(Uc)::value, I = decltype(Ic)::value, MN = NA < MB ? NA : MB;
         constexpr bool W = I < 2 * MN ? (I & 1) == 0 : NA > MB;
         constexpr int q = I < 2 * MN ? I / 2 : I - MN;
-        if constexpr (W) dma16<U * STAGE + q * 1024>(dst_w, pw + U * w_stage, vw[q]);
-        else dma16_masked<U * STAGE + q * 1024>(dst_a, pa + U * a_stage, va[q], ma[q]);
+        if constexpr (W && decltype(Sure)::value != 0) dma16<q * 1024>(dst_w + slot, pw + U * w_stage, vw[q]);
+        else if constexpr (W) dma16_masked<q * 1024>(dst_w + slot, pw + U * w_stage, vw[q], live);
+        else if constexpr (decltype(Sure)::value != 0) dma16_masked<q * 1024>(dst_a + slot, pa + U * a_stage, va[q], ma[q]);
+        else dma16_masked<q * 1024>(dst_a + slot, pa + U * a_stage, va[q], ma[q] & live);
     };
 
     // ---- fragments and scales
     const int sw = (r >> 2) & 3;
-    const uint8_t *wp[2][2], *ap[2][2];                        // [stage pair][step]: a ds_read's immediate reaches 64 KB
+    uint32_t wo[2], ao[2];                                     // [step]: this lane's bytes in slot 0
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const uint32_t c16 = (uint32_t)(((2 * h + j) ^ sw) << 4);
-        wp[0][j] = lds + (wn * 32 * NA + r) * 64 + c16;
-        ap[0][j] = lds + OPER + (wm * 32 * MB + r) * 64 + c16;
-        wp[1][j] = wp[0][j] + 2 * STAGE;
-        ap[1][j] = ap[0][j] + 2 * STAGE;
+        wo[j] = (uint32_t)((wn * 32 * NA + r) * 64) + c16;
+        ao[j] = (uint32_t)(OPER + (wm * 32 * MB + r) * 64) + c16;
     }
     const uint8_t* const wsp = lds + SCALE_BASE + (wn * 32 * NA + r) * 16;
     const uint8_t* const asp = lds + SCALE_BASE + 1024 * NA + (wm * 32 * MB + r) * 16;
@@ -158,13 +177,13 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     int scw[2][NA], sca[2][MB];
     v4i srw[NA], sra[MB];                                      // a superstage's 16 scale bytes of this lane's rows
     v16f acc[NA][MB];
-    // read I of the 2 S fragments of stage U into parity P, in the order the MFMAs take them
-    auto read_frag = [&](auto Uc, auto Pc, auto Ic) {
-        constexpr int U = decltype(Uc)::value, P = decltype(Pc)::value, J = decltype(Ic)::value / S, k = decltype(Ic)::value % S;
-        if constexpr (k >= 1 && k <= MB) af[P][J][k - 1] = *reinterpret_cast<const v4i*>(ap[U >> 1][J] + (U & 1) * STAGE + (k - 1) * 2048);
+    // read I of the 2 S fragments of the stage in `slot` into parity P, in the order the MFMAs take them
+    auto read_frag = [&](auto Pc, auto Ic, uint32_t slot) {
+        constexpr int P = decltype(Pc)::value, J = decltype(Ic)::value / S, k = decltype(Ic)::value % S;
+        if constexpr (k >= 1 && k <= MB) af[P][J][k - 1] = *reinterpret_cast<const v4i*>(lds + (ao[J] + slot) + (k - 1) * 2048);
         else {
             constexpr int t = k == 0 ? 0 : k - MB;
-            wf[P][J][t] = *reinterpret_cast<const v4i*>(wp[U >> 1][J] + (U & 1) * STAGE + t * 2048);
+            wf[P][J][t] = *reinterpret_cast<const v4i*>(lds + (wo[J] + slot) + t * 2048);
         }
     };
     auto read_scales = [&](auto Ic, uint32_t buf) {            // scale rows of W tile I and A tile I
@@ -179,30 +198,34 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
         else sca[P][I - NA] = (int)((uint32_t)(sra[I - NA][U] & keep) >> hshift);
     };
 
-    // ---- stage U of superstage kq.  LAST: the last superstage, nothing is loaded for a successor.
+    // ---- stage U of superstage kq.  LAST: the last superstage, nothing is loaded any more.
+    uint32_t slot = 0;                                         // this stage's slot of the ring (bytes)
     auto stage = [&](auto Uc, auto Lastc, int kq) __attribute__((always_inline)) {
         constexpr int U = decltype(Uc)::value, P = U & 1, NU = (U + 1) & 3;
         constexpr bool LAST = decltype(Lastc)::value != 0, NEXT = !(LAST && U == 3);
-        // The next stage's loads have landed once only the 2 S of the two stages after it are outstanding (any
-        // scale loads among those make the wait stricter; a superstage's own scale loads are older than the 2 S
-        // youngest by the start of its predecessor's last stage, where its rows are read).
-        if constexpr (!LAST || U == 0) wait_vm_and_barrier<2 * S>();
-        else if constexpr (U == 1) wait_vm_and_barrier<S>();
-        else if constexpr (U == 2) wait_vm_and_barrier<0>();
+        constexpr int LU = (U + D) & 3, LQ = (U + D) / 4;      // the stage that is loaded: stage LU of superstage kq + LQ
+        // The next stage's loads have landed once only those of the D - 2 stages after it are outstanding: S each, and
+        // the scale loads of the superstages that begin among them (a superstage's scale loads are issued right before
+        // its first stage's).  In the last superstage there are fewer, and leaving the scale loads out is only stricter.
+        constexpr int BEGIN = (U + D - 1) / 4 - (U + 1) / 4;   // multiples of 4 in [U + 2, U + D - 1]
+        if constexpr (!LAST) wait_vm_and_barrier<(D - 2) * S + BEGIN * SPW>();
+        else if constexpr (U < 3) wait_vm_and_barrier<(D - 2 - U) * S>();
         else lds_wait_and_barrier();
         const int nq = U == 3 ? kq + 1 : kq;                   // superstage of the next stage
         const int keep = (nq == KQ - 1 && NU < ovd) ? 0 : -1;  // uniform
+        const uint32_t nslot = slot + STAGE == D * STAGE ? 0u : slot + STAGE;
         constexpr int RPS = NS >= 2 * S + 2 ? 1 : 2;           // fragment reads per slot
-        if constexpr (U == 0 && !LAST) load_super(kq + 1);
+        const uint64_t live = mask_if_less(kq + LQ, KQ);
+        if constexpr (LU == 0 && !LAST) load_super(kq + LQ);
         static_for([&](auto Sc) __attribute__((always_inline)) {
             constexpr int s = decltype(Sc)::value, J = s / NM, X = s % NM, A = X / MB, B = X % MB;
             mfma_fp4(acc[A][B], wf[P][J][A], af[P][J][B], IC<J>{}, scw[P][A], sca[P][B]);
             if constexpr (NEXT) {
                 static_for([&](auto Ic) __attribute__((always_inline)) {
                     constexpr int i = s * RPS + decltype(Ic)::value;
-                    if constexpr (i < 2 * S) read_frag(IC<NU>{}, IC<P ^ 1>{}, IC<i>{});
+                    if constexpr (i < 2 * S) read_frag(IC<P ^ 1>{}, IC<i>{}, nslot);
                 }, IC<RPS>{});
-                if constexpr (U == 3 && s < (NA > MB ? NA : MB)) read_scales(IC<s>{}, (nq & 1) ? SCALE_BUF : 0);
+                if constexpr (U == 3 && s < (NA > MB ? NA : MB)) read_scales(IC<s>{}, rd_buf);
                 constexpr int first = NS - 1 - (S + 1) / 2;    // two scale registers per slot, done one slot before the end
                 static_assert(first >= (NA > MB ? NA : MB) - 1, "the rows are read before the registers are made from them");
                 static_for([&](auto Ic) __attribute__((always_inline)) {
@@ -211,14 +234,16 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
                 }, IC<2>{});
             }
             if constexpr (!LAST) {
-                if constexpr (U == 0 && s == 0) dma_scales(kq + 1);
+                if constexpr (LU == 0 && s == 0) dma_scales(kq + LQ);
                 static_for([&](auto Ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(Ic)::value;
-                    if constexpr ((2 * i + 1) * NM / S == s) dma_code(Uc, IC<i>{});
+                    if constexpr ((2 * i + 1) * NM / S == s) dma_code(IC<LU>{}, IC<i>{}, slot, IC<(LQ < 2)>{}, live);
                 }, IC<S>{});
             }
             __builtin_amdgcn_sched_barrier(0);
         }, IC<NS>{});
+        slot = nslot;
+        if constexpr (U == 3) rd_buf = rd_buf + SCALE_BUF == NSB * SCALE_BUF ? 0u : rd_buf + SCALE_BUF;
     };
     auto superstage = [&](auto Lastc, int kq) __attribute__((always_inline)) {
         stage(IC<0>{}, Lastc, kq);
@@ -227,18 +252,21 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
         stage(IC<3>{}, Lastc, kq);
     };
 
-    // ---- prologue: superstage 0 in flight, accumulators cleared meanwhile, stage 0 in registers
-    load_super(0);
-    dma_scales(0);
-    static_for([&](auto Uc) { static_for([&](auto Ic) { dma_code(Uc, Ic); }, IC<S>{}); }, IC<4>{});
+    // ---- prologue: the first D stages in flight, accumulators cleared meanwhile, stage 0 in registers
+    static_for([&](auto Tc) __attribute__((always_inline)) {
+        constexpr int T = decltype(Tc)::value;
+        if constexpr (T % 4 == 0) { load_super(T / 4); dma_scales(T / 4); }
+        static_for([&](auto Ic) { dma_code(IC<(T & 3)>{}, Ic, (uint32_t)(T * STAGE), IC<(T < 4)>{}, mask_if_less(T / 4, KQ)); }, IC<S>{});
+    }, IC<D>{});
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
         for (int b = 0; b < MB; ++b) acc[a][b] = v16f{};
-    wait_vm_and_barrier<3 * S>();
-    static_for([&](auto Ic) { read_frag(IC<0>{}, IC<0>{}, Ic); }, IC<2 * S>{});
+    wait_vm_and_barrier<(D - 1) * S + (NSB - 1) * SPW>();
+    static_for([&](auto Ic) { read_frag(IC<0>{}, Ic, 0u); }, IC<2 * S>{});
     static_for([&](auto Ic) { read_scales(Ic, 0); }, IC<(NA > MB ? NA : MB)>{});
     static_for([&](auto Ic) { set_scale(IC<0>{}, IC<0>{}, Ic, -1); }, IC<S>{});   // (a single superstage shares nothing)
+    rd_buf = NSB == 1 ? 0u : (uint32_t)SCALE_BUF;
     for (int kq = 0; kq < KQ - 1; ++kq) superstage(IC<0>{}, kq);
     superstage(IC<1>{}, KQ - 1);
 
@@ -301,9 +329,9 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
 }
 
 using Kern = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int64_t, int, int, int);
-struct Variant { int na, mb; Kern bf16, f32; };
-#define BRQ_MID(NA, MB) {NA, MB, k_gemm_mid<true, NA, MB>, k_gemm_mid<false, NA, MB>}
-static const Variant variants[MID_TILES] = {BRQ_MID(2, 1), BRQ_MID(2, 2), BRQ_MID(2, 3), BRQ_MID(4, 3)};
+struct Variant { int na, mb, d; Kern bf16, f32; };
+#define BRQ_MID(NA, MB, D) {NA, MB, D, k_gemm_mid<true, NA, MB, D>, k_gemm_mid<false, NA, MB, D>}
+static const Variant variants[MID_TILES] = {BRQ_MID(2, 1, 6), BRQ_MID(2, 2, 4), BRQ_MID(2, 3, 4), BRQ_MID(4, 3, 4), BRQ_MID(2, 5, 5)};
 #undef BRQ_MID
 
 }  // namespace mid
@@ -312,7 +340,7 @@ hipError_t setup_gemm_mid() {
     for (const auto& v : mid::variants)
         for (mid::Kern k : {v.bf16, v.f32})
             if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   mid::lds_bytes(v.na, v.mb)); e != hipSuccess) return e;
+                                                   mid::lds_bytes(v.na, v.mb, v.d)); e != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -329,7 +357,7 @@ hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t
     const mid::Variant& v = mid::variants[tile];
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
     const int epc = out_bf16 ? 8 : 4, vec = N % epc == 0 && ldy % epc == 0;
-    hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb), s,
+    hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.d), s,
                        a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy, (int)a.tiled, (int)w.tiled, vec);
     return hipGetLastError();
 }

@@ -1,4 +1,4 @@
-"""Parity of the one-tile-per-workgroup product kernel (64 x 128, 128 x 128, 192 x 128 and 192 x 256 tiles) where it
+"""Parity of the one-tile-per-workgroup product kernel (64 x 128, 128 x 128, 192 x 128, 192 x 256 and 320 x 128 tiles) where it
 can go wrong: one row or column past a tile, one short of it, one element per store (N or the pitch not a multiple
 of a 16-byte chunk), K of a single superstage, and row-major K that is not a multiple of 512 (the last superstage is
 then a window that overlaps the one before, its shared stages masked).  Bars as in test_gpu_gemm.py; every shape in
@@ -22,17 +22,20 @@ def brq():
     return b
 
 
-# the tile that the dispatcher takes (rows x columns), then the shape
+# the tile that the shape is meant for (rows x columns), then the shape
 @pytest.mark.parametrize("tile,M,N,K", [
     ("64x128", 129, 77, 512), ("64x128", 129, 130, 640), ("64x128", 191, 136, 896), ("64x128", 193, 257, 1152),
     ("64x128", 129, 128, 2048), ("128x128", 193, 16390, 640), ("128x128", 577, 6150, 640), ("128x128", 383, 8200, 640),
     ("128x128", 500, 8200, 512), ("192x128", 129, 28672, 2048), ("192x128", 191, 16390, 4096),
-    ("192x256", 1153, 28672, 640), ("192x256", 1153, 16390, 4096)])
+    ("192x256", 1153, 28672, 640), ("192x256", 1153, 16390, 4096),
+    # few rows (from 16 row-major, 17 tiled on); rings deeper than K's stages and K of a few more stages than the ring
+    ("64x128", 16, 300, 512), ("64x128", 17, 77, 512), ("64x128", 33, 130, 1024), ("64x128", 64, 520, 1536),
+    ("64x128", 65, 264, 896), ("128x128", 128, 28672, 1024), ("320x128", 300, 28672, 2048), ("320x128", 600, 28674, 640)])
 def test_tiles_of_the_mid_kernel(brq, orc, tile, M, N, K):
     from paper_2511_04214_amd import inputs
     aq, as_ = inputs.random_mxfp4(M, K, seed=M * 3 + K)
     wq, ws = inputs.random_mxfp4(N, K, seed=N * 7 + K)
-    rows = sorted({0, 31, 32, 63, 64, 127, 128, M - 1, M - 2, M // 2} | {r for r in (191, 192, 255, 256) if r < M})
+    rows = sorted({M - 1, M - 2, M // 2} | {r for r in (0, 31, 32, 63, 64, 127, 128, 191, 192, 255, 256) if r < M})
     ref, bound = orc.mxfp4_gemm(aq, as_, wq, ws, rows=rows)
     ops = {"rowmajor": [to_dev(t) for t in (aq, as_, wq, ws)],
            "tiled": [to_dev(t) for t in to_tiled(aq, as_) + to_tiled(wq, ws)]}
