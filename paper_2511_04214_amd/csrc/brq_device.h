@@ -372,17 +372,20 @@ struct KPad {
 
 // One LDS-DMA load: 64 lanes x 16 bytes from base + voff(lane) to LDS lds_base + LDS_OFF +
 // 16 * lane (M0 carries the LDS address).  lds_base and base must be wavefront-uniform.
+// Between a write of M0 and the load that takes its LDS address from it the hardware wants one wait state and does not
+// check (the compiler puts an s_nop 0 there, and sees none of this).
 template <int LDS_OFF>
 __device__ __forceinline__ void dma16(uint32_t lds_base, const uint8_t* base, uint32_t voff) {
-    asm volatile("s_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
                  :: "s"(lds_base), "v"(voff), "s"(base), "n"(LDS_OFF)
                  : "memory", "scc", "m0");
 }
 
-// The same for the lanes of `mask` only (uniform); every lane of the wavefront is active around it.
+// The same for the lanes of `mask` only (uniform); every lane of the wavefront is active around it.  (The write of the
+// lane mask is the wait state.)
 template <int LDS_OFF>
 __device__ __forceinline__ void dma16_masked(uint32_t lds_base, const uint8_t* base, uint32_t voff, uint64_t mask) {
-    asm volatile("s_mov_b64 exec, %4\n\ts_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1\n\t"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1\n\t"
                  :: "s"(lds_base), "v"(voff), "s"(base), "n"(LDS_OFF), "s"(mask)
                  : "memory", "scc", "m0");
 }
@@ -390,7 +393,7 @@ __device__ __forceinline__ void dma16_masked(uint32_t lds_base, const uint8_t* b
 // dma16 with the non-temporal hint, for data that is read once.
 template <int LDS_OFF>
 __device__ __forceinline__ void dma16_stream(uint32_t lds_base, const uint8_t* base, uint32_t voff) {
-    asm volatile("s_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\t"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\t"
                  :: "s"(lds_base), "v"(voff), "s"(base), "n"(LDS_OFF)
                  : "memory", "scc", "m0");
 }
