@@ -261,7 +261,14 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int b = 0; b < MB; ++b) acc[a][b] = v16f{};
+        for (int b = 0; b < MB; ++b) {
+            // One definition the compiler cannot see into: from a constant it made one set of zeros for a K of a single
+            // superstage and another for the loop, and moved all accumulators from register to register between the
+            // loop and the last superstage, reading some 10 wait states after the MFMA that writes them (12 are needed,
+            // and it does not know that these are MFMAs).
+            acc[a][b] = v16f{};
+            asm volatile("" : "+a"(acc[a][b]));
+        }
     wait_vm_and_barrier<(D - 1) * S + (NSB - 1) * SPW>();
     static_for([&](auto Ic) { read_frag(IC<0>{}, Ic, 0u); }, IC<2 * S>{});
     static_for([&](auto Ic) { read_scales(Ic, 0); }, IC<(NA > MB ? NA : MB)>{});

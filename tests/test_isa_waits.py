@@ -126,9 +126,15 @@ def is_lds_dma(i):
     return i.is_vmem() and "load_lds" in i.op
 
 
+def is_fp4_mfma(i):
+    return i.op == "v_mfma_scale_f32_32x32x64_f8f6f4" and "cbsz:4 blgp:4" in i.text
+
+
 PAIRS = {
     "M0 written, then an LDS-DMA load": (lambda i: i.op.startswith("s_"), is_lds_dma, 1, lambda i: {("m0", 0)}),
     "scalar register from the vector unit, then an address of a memory access": (Instruction.is_valu, Instruction.is_vmem, 5, lambda i: {r for r in i.read() if r[0] == "s"}),
+    # (8 passes: fp4 operands)
+    "result of a block-scaled MFMA, then the vector unit": (is_fp4_mfma, Instruction.is_valu, 12, lambda i: i.read() | i.written()),
 }
 
 
