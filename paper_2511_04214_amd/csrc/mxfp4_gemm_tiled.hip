@@ -540,6 +540,13 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tiled(const uint8_t* __restrict
     for (int t = 0; t < 4; ++t) { srw[t] = *reinterpret_cast<const v4i*>(wsp + t * 512); scw[0][t] = (int)((uint32_t)srw[t][0] >> hshift); }
 #pragma unroll
     for (int t = 0; t < MB; ++t) { sra[t] = *reinterpret_cast<const v4i*>(asp + t * ASC_TILE); sca[0][t] = (int)((uint32_t)sra[t][0] >> hshift); }
+    // An MFMA may read a register only two wait states after the vector unit wrote it, and the compiler does not know
+    // that the first statement of the first stage is one: the scale registers are made here, the wait follows.
+#pragma unroll
+    for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(scw[0][t]));
+#pragma unroll
+    for (int t = 0; t < MB; ++t) asm volatile("" : "+v"(sca[0][t]));
+    asm volatile("s_nop 1" ::: "memory");
 
     // One superstage = 4 stages of MFMAs on the consumer side, and the loads of the producer's
     // superstage (the next one of the stream) on the other.

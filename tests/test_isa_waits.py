@@ -133,6 +133,7 @@ def is_fp4_mfma(i):
 PAIRS = {
     "M0 written, then an LDS-DMA load": (lambda i: i.op.startswith("s_"), is_lds_dma, 1, lambda i: {("m0", 0)}),
     "scalar register from the vector unit, then an address of a memory access": (Instruction.is_valu, Instruction.is_vmem, 5, lambda i: {r for r in i.read() if r[0] == "s"}),
+    "vector register from the vector unit, then an MFMA": (Instruction.is_valu, Instruction.is_mfma, 2, Instruction.read),
     # (8 passes: fp4 operands)
     "result of a block-scaled MFMA, then the vector unit": (is_fp4_mfma, Instruction.is_valu, 12, lambda i: i.read() | i.written()),
 }
