@@ -61,6 +61,39 @@ brq_status brq_diag_mxfp4_gemm_no_loads(const uint8_t* aq, const uint8_t* as, br
                                         int64_t M, int64_t N, int64_t K, void* y, brq_dtype ydt,
                                         int64_t ldy, uint64_t* clock, void* stream);
 
+/*
+ * The kernels of brq_mxfp4_gemm.  Which of them takes a call is decided by its shape, layouts and output type; the two
+ * calls below name the choice and make it, so that a kernel can be tested and timed where another one is the
+ * faster.
+ */
+enum {
+    BRQ_GEMM_GENERAL = 0,        /* any shape */
+    BRQ_GEMM_SKINNY = 1,         /* M <= 16, any K */
+    BRQ_GEMM_STREAM = 2,         /* M <= 16, K of whole 512-element superstages */
+    BRQ_GEMM_256x256 = 3,        /* the persistent kernel and its two output tiles (rows x columns) */
+    BRQ_GEMM_128x256 = 4,
+    BRQ_GEMM_64x128 = 5,         /* the one-tile-per-workgroup kernel and its five */
+    BRQ_GEMM_128x128 = 6,
+    BRQ_GEMM_192x128 = 7,
+    BRQ_GEMM_192x256 = 8,
+    BRQ_GEMM_320x128 = 9
+};
+
+/*
+ * *route = the kernel that brq_mxfp4_gemm takes for this shape on a device of `cus` compute units.  Host arithmetic
+ * only: no device is needed.  An empty product has none (BRQ_ERR_SHAPE).
+ */
+brq_status brq_diag_mxfp4_gemm_route(brq_layout a_layout, brq_layout w_layout, int64_t M, int64_t N,
+                                     int64_t K, brq_dtype ydt, int64_t ldy, int64_t cus, int32_t* route);
+
+/*
+ * brq_mxfp4_gemm on the kernel `route`; BRQ_ERR_SHAPE where that kernel does not take the shape.
+ */
+brq_status brq_diag_mxfp4_gemm_on(int32_t route, const uint8_t* aq, const uint8_t* as,
+                                  brq_layout a_layout, const uint8_t* wq, const uint8_t* ws,
+                                  brq_layout w_layout, int64_t M, int64_t N, int64_t K, void* y,
+                                  brq_dtype ydt, int64_t ldy, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -18,7 +18,8 @@ BRQ_F32, BRQ_BF16 = 0, 1
 LAYOUTS = {"rowmajor": 0, "tiled": 1}
 EXPORTS = ["brq_init", "brq_block_rotate", "brq_operand_bytes", "brq_mxfp4_quantize", "brq_rotate_quantize_fused",
            "brq_swiglu", "brq_swiglu_rotate_quantize_fused", "brq_matrix_rotate",
-           "brq_matrix_rotate_quantize_fused", "brq_block_stats", "brq_block_stats_summary", "brq_mxfp4_gemm", "brq_rotate_quantize_gemm_fused", "brq_to_rowmajor", "brq_diag_mfma_ceiling", "brq_diag_mxfp4_gemm_clock", "brq_diag_mxfp4_gemm_no_loads", "brq_strerror", "brq_version"]
+           "brq_matrix_rotate_quantize_fused", "brq_block_stats", "brq_block_stats_summary", "brq_mxfp4_gemm", "brq_rotate_quantize_gemm_fused", "brq_to_rowmajor", "brq_diag_mfma_ceiling", "brq_diag_mxfp4_gemm_clock", "brq_diag_mxfp4_gemm_no_loads", "brq_diag_mxfp4_gemm_route",
+           "brq_diag_mxfp4_gemm_on", "brq_strerror", "brq_version"]
 
 _lib = None
 
@@ -68,6 +69,10 @@ def lib():
         L.brq_diag_mxfp4_gemm_clock.restype = i32
         L.brq_diag_mxfp4_gemm_no_loads.argtypes = L.brq_diag_mxfp4_gemm_clock.argtypes
         L.brq_diag_mxfp4_gemm_no_loads.restype = i32
+        L.brq_diag_mxfp4_gemm_route.argtypes = [i32, i32, i64, i64, i64, i32, i64, i64, ctypes.POINTER(ctypes.c_int32)]
+        L.brq_diag_mxfp4_gemm_route.restype = i32
+        L.brq_diag_mxfp4_gemm_on.argtypes = [i32] + L.brq_mxfp4_gemm.argtypes
+        L.brq_diag_mxfp4_gemm_on.restype = i32
         L.brq_diag_mfma_ceiling.argtypes = [vp, i64, i64, vp, vp]
         L.brq_diag_mfma_ceiling.restype = i32
         L.brq_init.restype = i32
@@ -411,6 +416,32 @@ def diag_mxfp4_gemm_no_loads(aq, as_, wq, ws, clock, **kw):
     """The large-shape product kernel without its refill loads (brq_diag_mxfp4_gemm_no_loads): a timing aid, the
     output is NOT the product."""
     return mxfp4_gemm(aq, as_, wq, ws, clock=clock, no_loads=True, **kw)
+
+
+# the kernels of mxfp4_gemm (include/brq_diag.h), by their numbers there
+GEMM_ROUTES = ("general", "skinny", "stream", "256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128")
+
+
+def diag_mxfp4_gemm_route(M, N, K, a_layout="rowmajor", w_layout="rowmajor", out_dtype=torch.float32, ldy=None, cus=256):
+    """The kernel that mxfp4_gemm takes for a shape on a device of `cus` compute units, one of GEMM_ROUTES
+    (brq_diag_mxfp4_gemm_route; needs no GPU)."""
+    r = ctypes.c_int32()
+    _check(lib().brq_diag_mxfp4_gemm_route(_layout_code(a_layout), _layout_code(w_layout), M, N, K, BRQ_BF16 if out_dtype == torch.bfloat16 else BRQ_F32,
+                                           N if ldy is None else ldy, cus, ctypes.byref(r)))
+    return GEMM_ROUTES[r.value]
+
+
+def diag_mxfp4_gemm_on(route, aq, as_, wq, ws, out, K, a_layout="rowmajor", w_layout="rowmajor", stream=None):
+    """out[M, N] = the product on the kernel `route`, one of GEMM_ROUTES (brq_diag_mxfp4_gemm_on)."""
+    M, N, ldy = _rows(out, "out")
+    for t, st, rows, lay, n in ((aq, as_, M, a_layout, "a"), (wq, ws, N, w_layout, "w")):
+        cb, sb = operand_bytes(rows, K, lay)
+        if not all(u.is_cuda and u.is_contiguous() and u.dtype == torch.uint8 for u in (t, st)) or t.numel() < cb or st.numel() < sb:
+            raise ValueError("operand %s: not contiguous uint8 GPU buffers of its shape and layout" % n)
+    _check(lib().brq_diag_mxfp4_gemm_on(GEMM_ROUTES.index(route), aq.data_ptr(), as_.data_ptr(), _layout_code(a_layout), wq.data_ptr(),
+                                        ws.data_ptr(), _layout_code(w_layout), M, N, K, out.data_ptr(), _dtype_code(out), ldy,
+                                        _stream(stream)))
+    return out
 
 
 def diag_mfma_ceiling(operands, iters, workgroups, sink=None, stream=None):

@@ -60,8 +60,24 @@ struct Operand {
     bool tiled;
 };
 
-hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
-                             bool out_bf16, int64_t ldy, hipStream_t s);
+// A product's shape, and the kernels that take it (the numbers of brq_diag.h).
+struct GemmShape {
+    int64_t M, N, K;
+    bool a_tiled, w_tiled, out_bf16;
+    int64_t ldy;
+    int64_t padded_k() const { return (K + 511) / 512 * 512; }
+    // K of whole 512-element superstages: tiled operands are zero-padded to that
+    bool whole_k() const { return K % 512 == 0 || (a_tiled && w_tiled); }
+};
+enum GemmRoute { ROUTE_GENERAL, ROUTE_SKINNY, ROUTE_STREAM, ROUTE_256x256, ROUTE_128x256, ROUTE_ONE_TILE };   // + a tile's number
+constexpr int MID_TILES = 5;
+constexpr int GEMM_ROUTES = ROUTE_ONE_TILE + MID_TILES;
+bool gemm_route_supported(int route, const GemmShape& g);
+// The route of a product on a device of `cus` compute units: host arithmetic.
+int gemm_route(const GemmShape& g, int cus);
+hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s);
+// The same on a route that takes the shape (gemm_route_supported), device_cus() having been called.
+hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s);
 
 // The decode-size product with the online step (B = 32 rotation + quantizer) of its activations in its own
 // prologue: x [M <= 16][ldx] bf16 or fp32, K % 512 == 0, K <= DECODE_FUSED_MAX_K (the quantized activations of
@@ -81,8 +97,7 @@ hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int6
                              bool no_loads = false);
 
 // One output tile per workgroup, the tile one of a family (mxfp4_gemm_mid.hip): any M, N and pitch.
-constexpr int MID_TILES = 5;
-bool mid_gemm_supported(int64_t M, int64_t N, int64_t K, bool a_tiled, bool w_tiled);
+bool mid_gemm_supported(int tile, const GemmShape& g);
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s);
 

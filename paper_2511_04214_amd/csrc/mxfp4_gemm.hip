@@ -510,70 +510,88 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // replaces cost 3.9 % and 5.2 % (34 %, 42 %).  What the estimate gives over 256 x 256, or 128 x 256 where the former do not
 // fill the chip, tiled, us: 300 x 28672 x 8192 61 -> 45; 1000 x 4096 x 11008 41 -> 30; 200 x 512 x 4096 12.7 -> 8.2.
 struct TileCost { float fixed, alone, full, store; };
-struct Tile { int na, mb, per_cu, mid; TileCost tiled, rowmajor; };      // 64 mb x 64 na; mid: its number there, -1 = persistent
+struct Tile { int na, mb, per_cu, route; TileCost tiled, rowmajor; };    // 64 mb x 64 na
 static const Tile TILES[2 + MID_TILES] = {
-    {4, 4, 1, -1, {6.293f, 0.532f, 0.707f, 0.638f}, {6.786f, 0.666f, 0.844f, 0.744f}},
-    {4, 2, 1, -1, {5.092f, 0.299f, 0.380f, 0.762f}, {4.800f, 0.401f, 0.719f, 0.706f}},
-    {2, 1, 2, 0, {3.558f, 0.147f, 0.240f, 0.515f}, {2.661f, 0.269f, 0.301f, 0.723f}},
-    {2, 2, 2, 1, {3.816f, 0.226f, 0.254f, 0.464f}, {2.665f, 0.325f, 0.468f, 0.638f}},
-    {2, 3, 1, 2, {5.479f, 0.238f, 0.373f, 0.906f}, {4.662f, 0.335f, 0.426f, 1.157f}},
-    {4, 3, 1, 3, {5.916f, 0.376f, 0.741f, 0.601f}, {4.888f, 0.511f, 0.636f, 1.111f}},
-    {2, 5, 1, 4, {7.720f, 0.308f, 0.461f, 0.872f}, {7.159f, 0.402f, 0.548f, 0.792f}},
+    {4, 4, 1, ROUTE_256x256, {6.293f, 0.532f, 0.707f, 0.638f}, {6.786f, 0.666f, 0.844f, 0.744f}},
+    {4, 2, 1, ROUTE_128x256, {5.092f, 0.299f, 0.380f, 0.762f}, {4.800f, 0.401f, 0.719f, 0.706f}},
+    {2, 1, 2, ROUTE_ONE_TILE, {3.558f, 0.147f, 0.240f, 0.515f}, {2.661f, 0.269f, 0.301f, 0.723f}},
+    {2, 2, 2, ROUTE_ONE_TILE + 1, {3.816f, 0.226f, 0.254f, 0.464f}, {2.665f, 0.325f, 0.468f, 0.638f}},
+    {2, 3, 1, ROUTE_ONE_TILE + 2, {5.479f, 0.238f, 0.373f, 0.906f}, {4.662f, 0.335f, 0.426f, 1.157f}},
+    {4, 3, 1, ROUTE_ONE_TILE + 3, {5.916f, 0.376f, 0.741f, 0.601f}, {4.888f, 0.511f, 0.636f, 1.111f}},
+    {2, 5, 1, ROUTE_ONE_TILE + 4, {7.720f, 0.308f, 0.461f, 0.872f}, {7.159f, 0.402f, 0.548f, 0.792f}},
 };
 
-// Index into TILES, or -1 where no LDS-staged kernel takes the shape.
-static int pick_tile(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, bool out_bf16, int64_t ldy, int cus) {
-    const bool persistent = tiled_gemm_supported(M, N, K, out_bf16, ldy, a.tiled && w.tiled);
-    const bool one_tile = mid_gemm_supported(M, N, K, a.tiled, w.tiled);
-    const float stages = (float)((K + 511) / 512 * 4), output = 0.6e-6f * (float)M * (float)N * (out_bf16 ? 1.0f : 2.0f);
-    const float bytes = 0.53125f * ((float)M + (float)N) * (float)K / 5.0e6f;
+// The cheapest of the LDS-staged kernels that take the shape, or -1.
+static int pick_tile(const GemmShape& g, int cus) {
+    const bool tiled = g.a_tiled && g.w_tiled;
+    const float stages = (float)((g.K + 511) / 512 * 4), output = 0.6e-6f * (float)g.M * (float)g.N * (g.out_bf16 ? 1.0f : 2.0f);
+    const float bytes = 0.53125f * ((float)g.M + (float)g.N) * (float)g.K / 5.0e6f;
     auto pow4 = [](float x) { return x * x * x * x; };
     int best = -1;
     float least = 0.0f;
     for (int i = 0; i < 2 + MID_TILES; ++i) {
         const Tile& t = TILES[i];
-        if (!(t.mid < 0 ? persistent : one_tile)) continue;
-        const TileCost& c = a.tiled && w.tiled ? t.tiled : t.rowmajor;
-        const int64_t tm = (M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * t.per_cu;
-        const float filled = t.mid < 0 ? 1.0f : 0.5f + 0.5f * (float)M / (float)(64 * t.mb * tm);
+        if (!gemm_route_supported(t.route, g)) continue;
+        const bool one_tile = t.route >= ROUTE_ONE_TILE;
+        const TileCost& c = tiled ? t.tiled : t.rowmajor;
+        const int64_t tm = (g.M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((g.N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * t.per_cu;
+        const float filled = one_tile ? 0.5f + 0.5f * (float)g.M / (float)(64 * t.mb * tm) : 1.0f;
         const float alone = stages * c.alone * (float)((T + places - 1) / places);
         const float full = stages * c.full * (float)T / (float)cus * filled;
         const float cost = c.fixed + sqrtf(sqrtf(pow4(alone) + pow4(full) + pow4(bytes))) + c.store * output;
-        if (best < 0 || cost < least) { best = i; least = cost; }
+        if (best < 0 || cost < least) { best = t.route; least = cost; }
     }
     return best;
 }
 
-hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
-                             bool out_bf16, int64_t ldy, hipStream_t s) {
-    const int64_t Kp = (K + 511) / 512 * 512;
-    int cus = 0;
-    if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;      // (also the per-device kernel set-up)
+bool gemm_route_supported(int route, const GemmShape& g) {
+    switch (route) {
+        case ROUTE_GENERAL: return true;
+        case ROUTE_SKINNY: return g.M <= 16;
+        case ROUTE_STREAM: return g.M <= 16 && g.whole_k() && g.padded_k() < (int64_t(1) << 26);
+        case ROUTE_256x256:
+        case ROUTE_128x256: return tiled_gemm_supported(g.M, g.N, g.K, g.out_bf16, g.ldy, g.a_tiled && g.w_tiled);
+        default: return route >= ROUTE_ONE_TILE && route < GEMM_ROUTES && mid_gemm_supported(route - ROUTE_ONE_TILE, g);
+    }
+}
+
+int gemm_route(const GemmShape& g, int cus) {
     // A few rows: weight streaming.  16 rows tiled, us, against the one-tile kernel's 64 x 128: N x K = 512 x 1024 4.0 / 4.5,
     // 28672 x 8192 23.7 / 24.1, 8192 x 4096 9.8 / 9.5; row-major 2048 x 2048 7.9 / 6.2, 4096 x 8192 28.0 / 23.0; 32 rows
     // 8192 x 4096 10.8 / 10.3 and, where it needed more row tiles, 64 rows 13.0 / 11.0, 128 rows 17.5 / 10.9.
-    if (M <= 16 && (K == Kp || (a.tiled && w.tiled)) && ((a.tiled && w.tiled) || !mid_gemm_supported(M, N, K, a.tiled, w.tiled)) &&
-        Kp < (int64_t(1) << 26)) {
-        const dim3 grid((uint32_t)((N + 127) / 128)), block(256);
-        hipLaunchKernelGGL(smallm_kern[(Kp / 512) % SMALLM_SETS], grid, block, SMALLM_LDS_BYTES, s, a.codes, a.scales, (int)a.tiled,
-                           w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy);
-        return hipGetLastError();
+    if (gemm_route_supported(ROUTE_STREAM, g) && ((g.a_tiled && g.w_tiled) || !gemm_route_supported(ROUTE_ONE_TILE, g))) return ROUTE_STREAM;
+    const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
+    return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
+}
+
+hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {
+    const int64_t M = g.M, N = g.N, K = g.K;
+    switch (route) {
+        case ROUTE_GENERAL: {
+            const dim3 grid((uint32_t)((N + 63) / 64), (uint32_t)((M + 63) / 64));
+            hipLaunchKernelGGL(k_gemm_direct, grid, dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales,
+                               (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);
+            return hipGetLastError();
+        }
+        case ROUTE_SKINNY:
+            hipLaunchKernelGGL(k_gemm_skinny, dim3((uint32_t)((N + 15) / 16)), dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes,
+                               w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);
+            return hipGetLastError();
+        case ROUTE_STREAM:
+            hipLaunchKernelGGL(smallm_kern[(g.padded_k() / 512) % SMALLM_SETS], dim3((uint32_t)((N + 127) / 128)), dim3(256), SMALLM_LDS_BYTES,
+                               s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y,
+                               (int)g.out_bf16, g.ldy);
+            return hipGetLastError();
+        case ROUTE_256x256:
+        case ROUTE_128x256: return launch_gemm_tiled(a, w, M, N, K, y, g.out_bf16, g.ldy, s, route == ROUTE_128x256);
+        default: return launch_gemm_mid(route - ROUTE_ONE_TILE, a, w, M, N, K, y, g.out_bf16, g.ldy, s);
     }
-    const int t = M > 16 || K == Kp ? pick_tile(a, w, M, N, K, out_bf16, ldy, cus) : -1;
-    if (t >= 0) {
-        const int mid = TILES[t].mid;
-        return mid < 0 ? launch_gemm_tiled(a, w, M, N, K, y, out_bf16, ldy, s, TILES[t].mb == 2)
-                       : launch_gemm_mid(mid, a, w, M, N, K, y, out_bf16, ldy, s);
-    } else if (M <= 16) {
-        dim3 grid((uint32_t)((N + 15) / 16));
-        hipLaunchKernelGGL(k_gemm_skinny, grid, dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales,
-                           (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy);
-    } else {
-        dim3 grid((uint32_t)((N + 63) / 64), (uint32_t)((M + 63) / 64));
-        hipLaunchKernelGGL(k_gemm_direct, grid, dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales,
-                           (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy);
-    }
-    return hipGetLastError();
+}
+
+hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {
+    int cus = 0;
+    if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;      // (also the per-device kernel set-up)
+    return launch_gemm_route(gemm_route(g, cus), a, w, g, y, s);
 }
 
 }  // namespace brq

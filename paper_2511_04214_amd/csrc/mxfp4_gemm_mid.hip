@@ -353,10 +353,9 @@ hipError_t setup_gemm_mid() {
 
 // Whole superstages: K % 512 == 0 or both operands tiled (zero-padded), or both row-major with K a multiple of
 // 128 and at least one superstage.  Offsets inside a tile (at most 256 rows) fit 32 bits.
-bool mid_gemm_supported(int64_t M, int64_t N, int64_t K, bool a_tiled, bool w_tiled) {
-    const int64_t Kp = (K + 511) / 512 * 512;
-    const bool k_ok = K == Kp || (a_tiled && w_tiled) || (!a_tiled && !w_tiled && K % 128 == 0 && K >= 512);
-    return M > 0 && N > 0 && k_ok && Kp <= (int64_t(1) << 24);
+bool mid_gemm_supported(int, const GemmShape& g) {
+    return g.M > 0 && g.N > 0 && (g.whole_k() || (!g.a_tiled && !g.w_tiled && g.K % 128 == 0 && g.K >= 512)) &&
+           g.padded_k() <= (int64_t(1) << 24);
 }
 
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,

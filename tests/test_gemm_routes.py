@@ -1,0 +1,51 @@
+"""Which kernel the product takes for a shape, on the CPU (host arithmetic for a device of 256 compute units).  The
+parity tests of test_gpu_gemm_routes.py run every kernel by its name; these say that the dispatcher uses them."""
+import pytest
+import torch
+
+import paper_2511_04214_amd as brq
+
+BF16, F32 = torch.bfloat16, torch.float32
+
+
+def route(M, N, K, layout="tiled", dtype=BF16, **kw):
+    return brq.diag_mxfp4_gemm_route(M, N, K, layout, layout, dtype, **kw)
+
+
+@pytest.mark.parametrize("shape,layout,want", [
+    ((16, 256, 256), "rowmajor", "skinny"), ((16, 256, 256), "tiled", "stream"), ((1, 28672, 8192), "tiled", "stream"),
+    ((16, 28672, 8192), "tiled", "stream"), ((100, 28672, 8192), "tiled", "128x128"), ((300, 28672, 8192), "tiled", "320x128"),
+    ((300, 28672, 8192), "rowmajor", "320x128"), ((2048, 8192, 2048), "tiled", "256x256"), ((4096, 2048, 8192), "tiled", "128x256"),
+    ((8192, 14336, 4096), "tiled", "256x256"), ((1000, 4096, 11008), "tiled", "128x128"), ((1000, 4096, 11008), "rowmajor", "192x128"),
+    ((2000, 4096, 11008), "rowmajor", "320x128"), ((192, 256, 4096), "tiled", "64x128"),
+    # ragged rows and columns, and K of one superstage, on the persistent kernel
+    ((4100, 14344, 4096), "tiled", "256x256"), ((5000, 8200, 4096), "tiled", "256x256"), ((5000, 8200, 4096), "rowmajor", "256x256"),
+    ((8192, 14336, 512), "rowmajor", "256x256"),
+    # N or K that no staged kernel takes
+    ((300, 520, 96), "rowmajor", "general"), ((40, 70, 256), "rowmajor", "general"), ((4, 70, 1056), "rowmajor", "skinny")])
+def test_route(shape, layout, want):
+    assert route(*shape, layout=layout) == want
+
+
+def test_every_kernel_is_taken_somewhere():
+    seen = {}
+    for layout in ("rowmajor", "tiled"):
+        for M in (1, 16, 40, 130, 200, 300, 500, 600, 1000, 1100, 2048, 4096, 8192):
+            for N in (128, 1024, 2048, 4096, 8192, 28672):
+                for K in (96, 512, 2048, 4096, 8192, 11008):
+                    seen.setdefault(route(M, N, K, layout=layout), set()).add(layout)
+    assert set(seen) == set(brq.GEMM_ROUTES)
+
+
+def test_arguments():
+    for bad in (dict(ldy=127), dict(cus=0)):
+        with pytest.raises(brq.BrqError) as e:
+            route(4, 128, 512, **bad)
+        assert e.value.status == 2
+    for shape in ((0, 128, 512), (4, 0, 512), (4, 128, 40)):
+        with pytest.raises(brq.BrqError) as e:
+            route(*shape)
+        assert e.value.status == 2
+    # N or a pitch that is not whole 16-byte chunks keeps a call off the persistent kernel
+    assert route(8192, 14338, 4096) not in ("256x256", "128x256")
+    assert route(8192, 14336, 4096, ldy=14339) not in ("256x256", "128x256")
