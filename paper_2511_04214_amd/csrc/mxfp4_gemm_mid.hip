@@ -351,11 +351,13 @@ hipError_t setup_gemm_mid() {
     return hipSuccess;
 }
 
-// Whole superstages: K % 512 == 0 or both operands tiled (zero-padded), or both row-major with K a multiple of
-// 128 and at least one superstage.  Offsets inside a tile (at most 256 rows) fit 32 bits.
-bool mid_gemm_supported(int, const GemmShape& g) {
+// Whole superstages, or both operands row-major with K a multiple of 128 and at least one superstage.  A lane's offset
+// inside the tile, below 64 max(NA, MB) rows of Kp / 2 bytes, has 32 bits, and the offset along K 31 (32 Kp bytes).
+bool mid_gemm_supported(int tile, const GemmShape& g) {
+    const mid::Variant& v = mid::variants[tile];
+    const int64_t Kp = g.padded_k(), slabs = v.na > v.mb ? v.na : v.mb;
     return g.M > 0 && g.N > 0 && (g.whole_k() || (!g.a_tiled && !g.w_tiled && g.K % 128 == 0 && g.K >= 512)) &&
-           g.padded_k() <= (int64_t(1) << 24);
+           Kp < (int64_t(1) << 26) && slabs * 32 * Kp <= (int64_t(1) << 32);
 }
 
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,

@@ -49,3 +49,13 @@ def test_arguments():
     # N or a pitch that is not whole 16-byte chunks keeps a call off the persistent kernel
     assert route(8192, 14338, 4096) not in ("256x256", "128x256")
     assert route(8192, 14336, 4096, ldy=14339) not in ("256x256", "128x256")
+
+
+@pytest.mark.parametrize("layout", ["rowmajor", "tiled"])
+def test_long_k_stays_on_a_staged_kernel(layout):
+    # a lane's 32-bit offset inside a tile: 2 slabs of 64 rows up to K < 2^26, 4 up to 2^25
+    for K in (2 ** 24 + 512, 2 ** 25, 2 ** 26 - 512):
+        for M in (17, 100, 128):
+            assert route(M, 130, K, layout=layout) in ("64x128", "128x128")
+    assert route(17, 130, 2 ** 26, layout=layout) == "general"
+    assert route(300, 130, 2 ** 25 + 512, layout=layout) in ("64x128", "128x128", "192x128")

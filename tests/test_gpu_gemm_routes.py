@@ -123,3 +123,30 @@ def test_a_kernel_refuses_what_it_does_not_take(brq):
         with pytest.raises(brq.BrqError) as e:
             brq.diag_mxfp4_gemm_on(route, *q(M, K), *q(N, K), out, K)
         assert e.value.status == 2 and (out == -7.0).all()
+
+
+@pytest.mark.parametrize("layout", ["rowmajor", "tiled"])
+def test_longest_k(brq, layout):
+    """K = 2^26 - 512: a lane's offset into the second 64-row slab of the weights passes 2^31, the last one's 2^32 - 2^15.
+    All codes 1; every row's last group has a scale of its own, and so has its first.  All sums are exact."""
+    M, N, K = 17, 130, 2 ** 26 - 512
+    assert brq.diag_mxfp4_gemm_route(M, N, K, layout, layout) == "64x128"
+    def operand(rows):
+        slabs = -(-rows // 64)
+        c = torch.full((slabs * 64 * (K // 2),), 0x22, dtype=torch.uint8, device="cuda")
+        s = torch.full((slabs * 64 * (K // 32),), 127, dtype=torch.uint8, device="cuda")
+        e = torch.arange(slabs * 64, device="cuda", dtype=torch.int64)
+        if layout == "tiled":
+            v = s.view(slabs, K // 512, 64, 16)
+            v[:, -1, :, 15] = (127 + e % 5).to(torch.uint8).view(slabs, 64)
+            v[:, 0, :, 0] = (127 + e % 3).to(torch.uint8).view(slabs, 64)
+        else:
+            c, s = c.view(-1, K // 2)[:rows], s.view(-1, K // 32)[:rows]
+            s[:, -1] = (127 + e % 5).to(torch.uint8)[:rows]
+            s[:, 0] = (127 + e % 3).to(torch.uint8)[:rows]
+        return c, s, 2.0 ** (e % 5)[:rows].double(), 2.0 ** (e % 3)[:rows].double()
+    ac, as_, al, af = operand(M)
+    wc, ws, wl, wf = operand(N)
+    y = brq.mxfp4_gemm(ac, as_, wc, ws, a_layout=layout, w_layout=layout, M=M, N=N, K=K)
+    want = K - 64 + 32 * (al[:, None] * wl[None, :] + af[:, None] * wf[None, :])
+    assert torch.equal(y.double(), want)
