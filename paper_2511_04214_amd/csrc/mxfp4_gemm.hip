@@ -556,10 +556,15 @@ bool gemm_route_supported(int route, const GemmShape& g) {
 }
 
 int gemm_route(const GemmShape& g, int cus) {
-    // A few rows: weight streaming.  16 rows tiled, us, against the one-tile kernel's 64 x 128: N x K = 512 x 1024 4.0 / 4.5,
-    // 28672 x 8192 23.7 / 24.1, 8192 x 4096 9.8 / 9.5; row-major 2048 x 2048 7.9 / 6.2, 4096 x 8192 28.0 / 23.0; 32 rows
-    // 8192 x 4096 10.8 / 10.3 and, where it needed more row tiles, 64 rows 13.0 / 11.0, 128 rows 17.5 / 10.9.
-    if (gemm_route_supported(ROUTE_STREAM, g) && ((g.a_tiled && g.w_tiled) || !gemm_route_supported(ROUTE_ONE_TILE, g))) return ROUTE_STREAM;
+    // Up to 16 rows: weight streaming where the weights are tiled, or row-major with K of a single superstage; other
+    // row-major weights go to the one-tile kernel, which takes their half lines through the LDS ring.  Weight streaming
+    // against the 64 x 128 tile, us, weights in no cache, 1 / 16 rows:
+    //   weights tiled      N x K = 256 x 512 2.9 / 3.2 : 3.6 / 3.7,  2048 x 2048 5.4 / 5.8 : 5.8 / 5.9,  8192 x 4096 9.6 / 10.3 : 9.2 / 9.9,
+    //                      28672 x 4096 14.0 / 13.7 : 14.2 / 13.7,  28672 x 8192 24.9 / 24.4 : 24.2 / 24.5  (activations of either layout)
+    //   weights row-major  256 x 512 3.3 / 3.6 : 3.6 / 3.7,  28672 x 512 4.7 / 5.0 : 5.1 / 5.1,  1024 x 1024 4.3 / 4.6 : 4.2 / 4.3,
+    //                      28672 x 1024 6.2 / 6.7 : 6.6 / 6.6,  8192 x 4096 15.0 / 15.7 : 12.7 / 13.5,  28672 x 8192 35.3 / 34.6 : 28.5 / 29.0
+    // 32 rows, tiled, 8192 x 4096 10.8 : 10.3, and where it needed more row tiles 64 rows 13.0 : 11.0, 128 rows 17.5 : 10.9.
+    if (gemm_route_supported(ROUTE_STREAM, g) && (g.w_tiled || g.K <= 512 || !gemm_route_supported(ROUTE_ONE_TILE, g))) return ROUTE_STREAM;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
     return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
 }
