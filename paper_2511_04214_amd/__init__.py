@@ -110,11 +110,17 @@ def _rows(t, name):
     return shape[0], shape[1], (stride[0] if shape[0] > 1 else shape[1])
 
 
+# (two functions of torch that are not part of its interface: the public way stands in where a torch has them not)
+_raw_stream, _raw_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     # the handle alone: a Stream object for every call costs as much as the launch behind it
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _signs_ptr(signs, K):

@@ -172,6 +172,18 @@ def test_binding_refuses_cpu_tensors():
         brq.rotate_quantize_fused(x, 32)
 
 
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device"])
+def test_current_stream_without_torchs_private_functions(missing, monkeypatch):
+    import torch
+    import paper_2511_04214_amd as brq
+
+    class Stream:
+        cuda_stream = 0x51
+    monkeypatch.setattr(brq, missing, None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    assert brq._stream(None) == 0x51
+
+
 def test_product_never_imports_the_oracle():
     pkg = os.path.join(ROOT, "paper_2511_04214_amd")
     for dirpath, _, files in os.walk(pkg):
