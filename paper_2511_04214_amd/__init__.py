@@ -313,11 +313,18 @@ def block_stats_summary(amax, sqerr=None, amax_ref=None, outlier_threshold=0.0, 
         if t is not None and not (t.is_cuda and t.is_contiguous() and t.dtype == torch.float32 and t.numel() == n):
             raise ValueError("%s must be a contiguous float32 GPU tensor with one element per block" % nm)
     ed = (ctypes.c_float * max(1, len(edges)))(*[float(e) for e in edges])
-    if hist is None or counts is None or sums is None:      # one fill for whichever are missing
-        z = torch.zeros((len(edges) + 9,), dtype=torch.int64, device=amax.device)
-        hist = z[8:] if hist is None else hist
-        counts = z[:4] if counts is None else counts
-        sums = z[4:8].view(torch.float64) if sums is None else sums
+    new = []                        # outputs that are made here, each a tensor of its own, cleared by one launch
+    if hist is None:
+        hist = torch.empty((len(edges) + 1,), dtype=torch.int64, device=amax.device)
+        new.append(hist)
+    if counts is None:
+        counts = torch.empty((4,), dtype=torch.int64, device=amax.device)
+        new.append(counts)
+    if sums is None:
+        sums = torch.empty((4,), dtype=torch.float64, device=amax.device)
+        new.append(sums.view(torch.int64))
+    if new:
+        torch._foreach_zero_(new)
     for t, nm, dt, ne in ((hist, "hist", torch.int64, len(edges) + 1), (counts, "counts", torch.int64, 4), (sums, "sums", torch.float64, 4)):
         if not (t.is_cuda and t.is_contiguous() and t.dtype == dt and t.numel() == ne):
             raise ValueError("%s must be a contiguous GPU tensor of %d elements of %s" % (nm, ne, dt))

@@ -192,6 +192,20 @@ def test_stats_number_of_thresholds(brq, orc, nt):
         assert np.array_equal(to_host(brq.block_stats(to_dev(x), B, th)[1]).astype(np.uint64), orc.block_stats(x, B, th)[1])
 
 
+def test_summary_outputs_are_tensors_of_their_own(brq):
+    # no storage and no version counter in common: keeping, resizing, saving or changing one leaves the others alone
+    amax = torch.full((1000,), 3.0, dtype=torch.float32, device="cuda")
+    for given in (dict(), dict(counts=torch.zeros(4, dtype=torch.int64, device="cuda"))):
+        out = brq.block_stats_summary(amax, edges=(1.0, 2.0), **given)
+        assert len({t.untyped_storage().data_ptr() for t in out}) == 3
+        for t in out:
+            assert t.storage_offset() == 0 and t.untyped_storage().nbytes() == t.numel() * 8
+        versions = [t._version for t in out[1:]]
+        out[0].add_(1)
+        assert [t._version for t in out[1:]] == versions
+        assert out[0].tolist() == [1, 1, 1001] and out[1].tolist() == [0, 1000, 0, 0] and out[2].tolist() == [0.0, 0.0, 0.0, 3000.0]
+
+
 def test_summary_adds_to_its_outputs_and_takes_nothing(brq):
     amax = torch.full((1000,), 3.0, dtype=torch.float32, device="cuda")
     hist = torch.tensor([5, 0, 0], dtype=torch.int64, device="cuda")
