@@ -32,7 +32,7 @@ struct SummaryArgs {
 // 4.19 M blocks with seven edges (50 MB): 19.4 -> 15.9 us; with 4-byte loads, and every one of 32 possible edges looked
 // at by the compiler's own choice, the scalar registers' contents went through vector registers (56 spilled).
 // NE: edges that are looked at, 0 (no histogram), 8, 16 or 32; those beyond nedges are +inf.  With the number known to
-// the compiler the edges and their counters stay in scalar registers.
+// the compiler the edges and their counters stay in scalar registers, up to 8 of them (16 edges spill 6 registers, 32 edges 48).
 template <int NE>
 struct SummaryAcc {
     unsigned int cnt[4], nlive, gt[NE ? NE : 1];     // wavefront-uniform, held by the scalar unit

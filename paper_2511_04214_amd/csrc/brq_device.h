@@ -116,7 +116,7 @@ __device__ __forceinline__ void wht_cross_mirror16(float (&v)[8], float s) { BRQ
 
 // The stages between 16-lane rows (h = 128) and between the halves of the wavefront (h = 256): two registers trade
 // the part the stage pairs, the butterfly is then between the two registers of one lane, and trading again puts the
-// values back: three instructions per two values and stage, no LDS, true signs.
+// values back: four instructions per two values and stage, no LDS, true signs.
 template <bool HALVES>
 __device__ __forceinline__ void trade(float& x, float& y) {
     if constexpr (HALVES) {
@@ -349,7 +349,8 @@ __device__ __forceinline__ uint64_t tiled_scale_offset(uint32_t row, uint32_t kc
 // Tiled layout, K not a multiple of 512: the groups between K and the next multiple of 512 are written as zeros (16
 // zero code bytes, scale byte 0) for every row, so that the LDS-staged product kernels can run whole 512-element
 // superstages over tiled operands of any K.  Every quantizing kernel does it itself, spread over all of its
-// threads: as a launch of its own it cost 2 to 4 us in front of a kernel of 10.
+// threads (rotations of B >= 512 have nothing to pad, B dividing K): as a launch of its own it cost 2 to 4 us in front
+// of a kernel of 10.
 struct KPad {
     uint8_t *codes, *scales;
     uint32_t rows, g0, n, stages, sstages;     // n groups per row from group g0 on; 0: nothing to do

@@ -8,7 +8,7 @@ namespace brq {
 // Per-device facts and one-time set-up.  The launchers size their grids by the number of compute units
 // and four kernel families ask for more than the default 64 KB of LDS, which HIP wants declared per
 // function and device before the first launch.  device_cus() returns the CU count of the CURRENT device and
-// on its first call for that device (under a lock, keyed by the device id) runs the three set-up routines;
+// on its first call for that device (under a lock, keyed by the device id) runs the four set-up routines;
 // brq_init() is that call made ahead of time.  Nothing else in the library outlives a call.
 hipError_t device_cus(int* cus);
 hipError_t setup_gemm_tiled();     // mxfp4_gemm_tiled.hip

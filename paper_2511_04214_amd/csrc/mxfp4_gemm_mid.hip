@@ -1,6 +1,6 @@
 // Medium-shape W4A4 MXFP4 product for gfx950: one output tile per workgroup, the tile chosen from a family
 // (64 MB rows x 64 NA columns) so that the shape fills the chip (the product of Sec. 2 on the MXFP4 operands
-// of Sec. 4.1).  The persistent 256 x 256 kernel is the better one where there are many tiles; here are the
+// of Sec. 4.1; which tile takes a shape: gemm_route).  The persistent 256 x 256 kernel is the better one where there are many tiles; here are the
 // shapes in between: a chunk of a prompt, a few hundred rows against wide weights, a projection with few columns.
 //
 // Workgroup = 4 wavefronts (2 x 2), each with NA x MB MFMA tiles of 32 x 32.  As in the persistent kernel the
@@ -8,8 +8,8 @@
 // groups 2h and 2h + 1, and operands travel HBM -> LDS by LDS-DMA into a ring of D stages whose 64-byte rows
 // have their 16-byte chunks XOR-swizzled by (row >> 2) & 3.
 //
-// What differs is the fragment schedule.  A stage of these tiles is 8 to 24 MFMAs (264 to 800 cycles) long,
-// too short to hide an LDS read between its barrier and its use.  The register file has room (64 to 192
+// What differs is the fragment schedule.  A stage of these tiles is 4 to 24 MFMAs (130 to 800 cycles) long,
+// too short to hide an LDS read between its barrier and its use.  The register file has room (32 to 192
 // accumulators of 512 registers), so ALL fragments of stage t + 1 are read while stage t multiplies:
 //   start of stage t   stage t + 1 has landed, everyone's reads of stage t's buffer are done: one barrier
 //   during stage t     2 (NA + MB) fragment reads of stage t + 1, the loads of stage t + D into stage t's
@@ -39,7 +39,7 @@ constexpr int stage_bytes(int NA, int MB) { return 4096 * (NA + MB); }
 constexpr int scale_bufs(int D) { return (D + 3) / 4; }
 constexpr int lds_bytes(int NA, int MB, int D) { return D * stage_bytes(NA, MB) + scale_bufs(D) * 1024 * (NA + MB); }
 
-// VEC: every 16-byte chunk of an output row is aligned and either wholly inside or outside N (N and ldy multiples
+// vec: every 16-byte chunk of an output row is aligned and either wholly inside or outside N (N and ldy multiples
 // of 16 / sizeof(out)); otherwise elements are stored one by one.
 template <bool OUT_BF16, int NA, int MB, int D>
 __global__ void __launch_bounds__(256, (lds_bytes(NA, MB, D) <= 81920 ? 2 : 1))
@@ -97,7 +97,8 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     for (int q = 0; q < NA; ++q) vw[q] = code_off(wave * 16 * NA + 16 * q + (lane >> 2), nrows, w_tiled != 0);
 #pragma unroll
     for (int q = 0; q < MB; ++q) va[q] = code_off(wave * 16 * MB + 16 * q + (lane >> 2), mrows, a_tiled != 0);
-    // Rows of A past M: their lanes' loads are masked off and their LDS rows are zero in all four stages.  The
+    // Rows of A past M: their lanes' loads are masked off and their LDS rows are zero in all D stages.  (A load
+    // without any lane is issued and counted like another: the waits below are the same for every wavefront.)  The
     // matrix cores' power depends on what they multiply, and this kernel runs at the board's power limit: a tile
     // half of whose rows repeat row M - 1 costs as much as a full one, half of zeros close to half.
     uint64_t ma[MB];

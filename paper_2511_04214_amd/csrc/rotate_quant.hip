@@ -6,8 +6,8 @@
 // 32 bytes of fp32), held by one lane; 4 consecutive lanes (a DPP quad) hold one
 // 32-element MXFP4 group, so the group maximum is two quad-permute steps and the group's
 // 8 packed codes per lane form one dword store.  Rotation stages h = 1, 2, 4 run inside
-// the lane, h = 8 ... 256 between lanes of the wavefront, larger h between the chunks a lane holds (B <= 8192: a
-// wavefront holds the whole block) or through LDS (B = 16384).
+// the lane, h = 8 ... 256 between lanes of the wavefront, larger h between the chunks a lane holds (bf16 values, B <= 8192:
+// one or two wavefronts hold the whole block) or through LDS (fp32 values, and B = 16384).
 #include "brq_device.h"
 #include "brq_launch.h"
 
@@ -384,7 +384,8 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
             }
         }
     }
-    if constexpr (MODE == MODE_QUANT || MODE == MODE_FUSED) a.pad.zero(blockIdx.x * NT + threadIdx.x, gridDim.x * NT);
+    // (a block of 512 and more divides K: nothing to pad)
+    if constexpr ((MODE == MODE_QUANT || MODE == MODE_FUSED) && LOG2B < 9) a.pad.zero(blockIdx.x * NT + threadIdx.x, gridDim.x * NT);
     if constexpr (MODE == MODE_STATS) {
         if (a.counts) stats_flush(cnt, red, a);   // uniform
     }
@@ -459,8 +460,8 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
 // workgroup) share it: for the last stage each gives half of its pieces to the other through LDS, 16 KB there and back.
 // (One wavefront with 16 chunks a lane leaves room for 3 per SIMD and spills.)
 // Through LDS altogether (two trips for the stages h >= 512, the stages h = 32 .. 256 through its swizzle) the block
-// cost 34 LDS operations per 8 values of a lane and was bound by them; now the vector units (about 2 instructions per
-// value) are just under HBM.  A row's 128-byte lines of tiled codes (two rows each) are left to two wavefronts: the L2
+// cost 34 LDS operations per 8 values of a lane and was bound by them; now it is bound by the vector units (about 20
+// instructions per value of a lane at B = 8192, 18 of the 26 us on 4096 x 8192).  A row's 128-byte lines of tiled codes (two rows each) are left to two wavefronts: the L2
 // merges their halves (plain stores).
 // Quantizing X bf16, tiled codes, before -> after, us: 4096 x 8192 B = 1024 / 2048 / 4096 / 8192 30 / 31 / 28 / 31 ->
 // 25 / 23 / 24 / 26; 16384 x 8192 101 / 102 / 102 / 108 -> 78 / 77 / 76 / 83.
@@ -477,7 +478,6 @@ __global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_ro
     const uint32_t half = W == 2 ? wave : 0u;
     const uint32_t lc = chunk_of_lane(lane);
     const float cs = as_f32(norm_bits(LOG2B)) * wht_sign<9>(lc);
-    if constexpr (MODE == MODE_FUSED) a.pad.zero(blockIdx.x * (uint32_t)reg_threads(LOG2B) + threadIdx.x, gridDim.x * (uint32_t)reg_threads(LOG2B));
     __shared__ v4f xch[W == 2 ? 2 * NJ * 64 : 1];                               // [wavefront][piece][4 values][lane]
     __shared__ uint32_t red[8];
     uint32_t cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -603,7 +603,8 @@ __global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_ro
     }
 }
 
-// ---- LDS-staged rotation, B = 16384 (a wavefront cannot hold the block) ----
+// ---- LDS-staged rotation: B = 16384, and fp32 values from B = 1024 on (more registers than a wavefront has, or slower, see
+// launch_wide) ----
 //
 // One workgroup of NT = min(256, B/8) lanes transforms one B-block of one row.  Each
 // lane holds CH = B/(8*NT) chunks.  Stages h < 512 run as above; the remaining
@@ -621,7 +622,6 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
     extern __shared__ float lds[];   // B floats
 
     const uint32_t tid = threadIdx.x, lane = tid & 63;
-    if constexpr (MODE == MODE_FUSED) a.pad.zero(blockIdx.x * (uint32_t)NT + tid, gridDim.x * (uint32_t)NT);
     const uint32_t lc = chunk_of_lane(lane);
     const float sigma = wht_sign<9>(lc);
     __shared__ uint32_t red[8];
@@ -700,7 +700,7 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
 // ---- host side ---------------------------------------------------------------------
 
 // Workgroups per compute unit of a statistics launch (each ends with up to 8 atomics on the caller's counters): of 512
-// threads for k_rowwise, of up to 256 for k_rowwise_lds.  X 16384 x 8192, two thresholds, B = 1 / 32, us: 3 x 512 threads
+// threads for k_rowwise, of up to 256 for k_rowwise_lds and k_rowwise_reg.  X 16384 x 8192, two thresholds, B = 1 / 32, us: 3 x 512 threads
 // 57.8 / 63.9; 2 x 512 with two chunks a pass 60.9 / 72.6; 2 x 768 57.8 / 64.6; 2 x 1024 56.2 / 73.6; 8 x 256 68.7 / 74.5.
 constexpr int STATS_WGS_PER_CU = 3, STATS_LDS_WGS_PER_CU = 8;
 
