@@ -41,6 +41,10 @@ def check(brq, orc, x, w, layout, signs=None, xd=None):
     z32 = brq.mxfp4_gemm(aq, as_, wq, ws, w_layout=layout, N=N, K=K)
     z16 = brq.mxfp4_gemm(aq, as_, wq, ws, w_layout=layout, N=N, K=K, out_dtype=torch.bfloat16)
     assert torch.equal(y32, z32) and torch.equal(y16, z16), "differs from the two-call sequence"
+    # ... and with the activations in the tiled layout
+    at, ast = brq.rotate_quantize_fused(xd, 32, layout="tiled", signs=sg)
+    z32 = brq.mxfp4_gemm(at, ast, wq, ws, a_layout="tiled", w_layout=layout, M=M, N=N, K=K)
+    assert torch.equal(y32, z32), "differs from the two-call sequence on tiled activations"
     # the oracle
     oa, oas = orc.rotate_quantize_fused(x, 32, signs=signs)
     ow, ows = orc.rotate_quantize_fused(w, 32, signs=signs)

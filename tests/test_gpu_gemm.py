@@ -34,7 +34,8 @@ def bf16_rne(a):
     return ((u + (np.uint32(0x7FFF) + ((u >> np.uint32(16)) & np.uint32(1)))) >> np.uint32(16)).astype(np.uint16)
 
 
-def check_gemm(brq, orc, aq, as_, wq, ws, rows=None, ldy=None):
+def check_gemm(brq, orc, aq, as_, wq, ws, rows=None, ldy=None, on=()):
+    """`on`: kernels (diag_mxfp4_gemm_on) that must give the same bits as the one the dispatcher takes."""
     daq, das, dwq, dws = to_dev(aq), to_dev(as_), to_dev(wq), to_dev(ws)
     M, N = aq.shape[0], wq.shape[0]
     if ldy is None:
@@ -52,13 +53,17 @@ def check_gemm(brq, orc, aq, as_, wq, ws, rows=None, ldy=None):
     yb = to_host(brq.mxfp4_gemm(daq, das, dwq, dws, out_dtype=torch.bfloat16))
     y32 = to_host(brq.mxfp4_gemm(daq, das, dwq, dws))
     assert np.array_equal(yb, bf16_rne(y32)), "bf16 output is not RNE of the fp32 output"
+    for route in on:
+        for dt, want in ((torch.float32, y32), (torch.bfloat16, yb)):
+            out = torch.empty((M, N), dtype=dt, device="cuda")
+            assert np.array_equal(to_host(brq.diag_mxfp4_gemm_on(route, daq, das, dwq, dws, out, 2 * aq.shape[1])), want), route
     return y32
 
 
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (33, 70, 96), (128, 256, 512), (1, 16, 32), (100, 36, 2080),
                                    (256, 256, 1024), (300, 520, 768), (17, 1000, 256),
                                    (256, 256, 512), (512, 768, 2048), (768, 256, 1536), (2304, 512, 512),
-                                   # ragged M in the persistent tiled kernel (N % 256 == 0, K % 512 == 0)
+                                   # ragged M, whole N, K of whole superstages
                                    (300, 256, 512), (257, 512, 1024), (17, 256, 512), (1000, 768, 2048),
                                    (255, 256, 512), (64, 256, 512), (513, 256, 512)])
 def test_gemm_random_codes(brq, orc, M, N, K):
@@ -153,9 +158,8 @@ def test_gemm_full_size_sampled_rows(brq, orc, name):
 
 
 def test_gemm_half_tiles_several_per_workgroup(brq, orc):
-    """4096 x 2560: 160 tiles of 256 x 256 would leave CUs idle, so the kernel runs 320 tiles of
-    128 x 256 and some workgroups take two of them (ring running across a tile boundary); ragged
-    variant: M = 4000."""
+    """4096 x 2560 on 320 tiles of 128 x 256: some workgroups take two of them (ring running across a tile
+    boundary); ragged variant: M = 4000.  (The dispatcher takes 128 x 128 tiles here.)"""
     from paper_2511_04214_amd import inputs
     for M in (4096, 4000):
         N, K = 2560, 1024
@@ -163,12 +167,12 @@ def test_gemm_half_tiles_several_per_workgroup(brq, orc):
         wq, ws = inputs.random_mxfp4(N, K, seed=42)
         rng = np.random.default_rng(43)
         rows = sorted(set([0, 63, 64, 127, 128, 255, 256, M - 129, M - 128, M - 1] + rng.integers(0, M, 12).tolist()))
-        check_gemm(brq, orc, aq, as_, wq, ws, rows=rows)
+        check_gemm(brq, orc, aq, as_, wq, ws, rows=rows, on=("128x256",))
 
 
 @pytest.mark.parametrize("K", [512, 1024, 1536])
 def test_gemm_full_tiles_ragged_last_row(brq, orc, K):
-    """4100 x 4096: 17 x 16 = 272 tiles of 256 x 256, enough for the full-height tile kernel, whose last
+    """4100 x 4096 on 17 x 16 = 272 tiles of 256 x 256 (and on what the dispatcher takes): the last
     tile row has 4 live rows: clamped A loads (row-major and tiled operands take different paths there)
     and masked stores.  Rows next to the ragged edge, of every tile row, and random ones.  Sixteen workgroups
     take two tiles: with K of one, two and three superstages the second tile's first stage (which carries
@@ -181,18 +185,21 @@ def test_gemm_full_tiles_ragged_last_row(brq, orc, K):
     rng = np.random.default_rng(47)
     rows = sorted(set([r for t in range(0, 4096, 256) for r in (t, t + 255)] + [4096, 4097, 4098, 4099, 3840, 4095]
                       + rng.integers(0, M, 8).tolist()))
-    y32 = check_gemm(brq, orc, aq, as_, wq, ws, rows=rows)
-    # the same product on tiled operands (slab-clamped A loads): same kernel, same summation order
+    y32 = check_gemm(brq, orc, aq, as_, wq, ws, rows=rows, on=("256x256",))
+    # the same product on tiled operands (slab-clamped A loads): same summation order
     at, wt = [to_dev(t) for t in to_tiled(aq, as_)], [to_dev(t) for t in to_tiled(wq, ws)]
     buf = torch.full((M + 3, N), -7.0, dtype=torch.float32, device="cuda")
     brq.mxfp4_gemm(at[0], at[1], wt[0], wt[1], out=buf[:M], a_layout="tiled", w_layout="tiled", M=M, N=N, K=K)
     assert np.array_equal(to_host(buf[:M]), y32)
     assert (buf[M:] == -7.0).all(), "wrote below the last row"
+    brq.diag_mxfp4_gemm_on("256x256", *at, *wt, buf[:M], K, a_layout="tiled", w_layout="tiled")
+    assert np.array_equal(to_host(buf[:M]), y32)
+    assert (buf[M:] == -7.0).all(), "wrote below the last row"
 
 
-# N not a multiple of 256 in the persistent tiled kernel: the last tile column clamps its W loads into the
-# operand (row-major: per-lane rows; tiled: the slab index) and masks its stores by 16-byte chunk.  bf16
-# output needs N % 8 == 0 and fp32 N % 4 == 0 (else the general kernel takes the call: N = 130 below).
+# N not a multiple of the tile's columns.  The persistent kernel's last tile column clamps its W loads into the
+# operand (row-major: per-lane rows; tiled: the slab index) and masks its stores by 16-byte chunk: bf16
+# output needs N % 8 == 0 and fp32 N % 4 == 0.  The one-tile kernel, which the dispatcher takes here, needs neither.
 @pytest.mark.parametrize("M,N,K", [(300, 264, 512), (257, 8, 1024), (200, 64, 512), (1000, 1160, 1024), (513, 520, 1536),
                                    (300, 260, 512), (129, 130, 512), (384, 248, 2048)])
 def test_gemm_ragged_last_tile_column(brq, orc, M, N, K):
@@ -208,24 +215,29 @@ def test_gemm_ragged_last_tile_column(brq, orc, M, N, K):
         got = to_host(buf[:M, :N])
         assert np.array_equal(got, y32 if dt == torch.float32 else bf16_rne(y32))
         assert (buf[M:] == -7.0).all() and (buf[:, N:] == -7.0).all(), "wrote outside the M x N block"
+        if N % 8 == 0:
+            for route in ("256x256", "128x256"):
+                for lay, a, w in (("tiled", at, wt), ("rowmajor", (to_dev(aq), to_dev(as_)), (to_dev(wq), to_dev(ws)))):
+                    buf.fill_(-7.0)
+                    brq.diag_mxfp4_gemm_on(route, *a, *w, buf[:M, :N], K, a_layout=lay, w_layout=lay)
+                    assert np.array_equal(to_host(buf[:M, :N]), got)
+                    assert (buf[M:] == -7.0).all() and (buf[:, N:] == -7.0).all(), "wrote outside the M x N block"
 
 
 def test_gemm_full_tiles_ragged_row_and_column(brq, orc):
-    """4100 x 4104: 17 x 17 = 289 tiles of 256 x 256 (the full-height kernel), 4 live rows in the last tile row
-    and 8 live columns in the last tile column; rows of every tile row, all columns."""
+    """4100 x 4104 on 17 x 17 = 289 tiles of 256 x 256 (and on what the dispatcher takes): 4 live rows in the last
+    tile row and 8 live columns in the last tile column; rows of every tile row, all columns."""
     from paper_2511_04214_amd import inputs
     M, N, K = 4100, 4104, 512
     aq, as_ = inputs.random_mxfp4(M, K, seed=48)
     wq, ws = inputs.random_mxfp4(N, K, seed=49)
     rng = np.random.default_rng(50)
     rows = sorted(set([r for t in range(0, 4096, 256) for r in (t, t + 255)] + [4096, 4099] + rng.integers(0, M, 6).tolist()))
-    check_gemm(brq, orc, aq, as_, wq, ws, rows=rows, ldy=N + 8)
+    check_gemm(brq, orc, aq, as_, wq, ws, rows=rows, ldy=N + 8, on=("256x256",))
 
 
-# 16 < M <= 128: the weight-streaming kernel that shares the activations through LDS (1 to 4 tiles of 32
-# rows, ragged M inside the last tile, ragged N inside the last workgroup and wavefront; K of 1 to 7
-# superstages, so that the main loop runs 0, 1 and 2 times with 0, 1 and 2 superstages left over);
-# 129 rows take the neighbouring code path
+# 16 < M <= 128: few rows, most of the tile past M; ragged N inside the last workgroup and wavefront; K of 1 to 7
+# superstages.  (The streaming kernel, for up to 16 rows, is tested in test_gpu_gemm_routes.py.)
 @pytest.mark.parametrize("M,N,K", [(17, 1000, 512), (32, 256, 1024), (33, 320, 1536), (64, 4096, 2048), (50, 130, 512),
                                    (48, 64, 512), (20, 16, 3584), (63, 75, 1024), (65, 1000, 512), (128, 384, 2048),
                                    (100, 130, 1536), (96, 40, 1024), (17, 200, 1536), (33, 128, 2560), (97, 256, 3072),

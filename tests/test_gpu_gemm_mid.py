@@ -2,7 +2,8 @@
 can go wrong: one row or column past a tile, one short of it, one element per store (N or the pitch not a multiple
 of a 16-byte chunk), K of a single superstage, and row-major K that is not a multiple of 512 (the last superstage is
 then a window that overlaps the one before, its shared stages masked).  Bars as in test_gpu_gemm.py; every shape in
-both layouts, both output types, with a guard right of column N - 1 and below row M - 1."""
+both layouts, both output types, with a guard right of column N - 1 and below row M - 1.  Each shape runs on the tile it is
+listed for, and through the dispatcher, which may take another and must give the same bits."""
 import numpy as np
 import pytest
 import torch
@@ -22,13 +23,13 @@ def brq():
     return b
 
 
-# the tile that the shape is meant for (rows x columns), then the shape
+# the tile (rows x columns), then the shape
 @pytest.mark.parametrize("tile,M,N,K", [
     ("64x128", 129, 77, 512), ("64x128", 129, 130, 640), ("64x128", 191, 136, 896), ("64x128", 193, 257, 1152),
     ("64x128", 129, 128, 2048), ("128x128", 193, 16390, 640), ("128x128", 577, 6150, 640), ("128x128", 383, 8200, 640),
     ("128x128", 500, 8200, 512), ("192x128", 129, 28672, 2048), ("192x128", 191, 16390, 4096),
     ("192x256", 1153, 28672, 640), ("192x256", 1153, 16390, 4096),
-    # few rows (from 16 row-major, 17 tiled on); rings deeper than K's stages and K of a few more stages than the ring
+    # few rows (16 and more); rings deeper than K's stages and K of a few more stages than the ring
     ("64x128", 16, 300, 512), ("64x128", 17, 77, 512), ("64x128", 33, 130, 1024), ("64x128", 64, 520, 1536),
     ("64x128", 65, 264, 896), ("128x128", 128, 28672, 1024), ("320x128", 300, 28672, 2048), ("320x128", 600, 28674, 640)])
 def test_tiles_of_the_mid_kernel(brq, orc, tile, M, N, K):
@@ -45,7 +46,9 @@ def test_tiles_of_the_mid_kernel(brq, orc, tile, M, N, K):
             out = {}
             for dt in (torch.float32, torch.bfloat16):
                 buf = torch.full((M + 2, N + pad), -7.0, dtype=dt, device="cuda")
-                brq.mxfp4_gemm(a, sa, w, sw, out=buf[:M, :N], a_layout=layout, w_layout=layout, M=M, N=N, K=K)
+                brq.diag_mxfp4_gemm_on(tile, a, sa, w, sw, buf[:M, :N], K, a_layout=layout, w_layout=layout)
+                y = brq.mxfp4_gemm(a, sa, w, sw, out_dtype=dt, a_layout=layout, w_layout=layout, M=M, N=N, K=K)
+                assert torch.equal(y, buf[:M, :N]), "differs from the dispatcher's kernel"
                 assert (buf[M:] == -7.0).all() and (buf[:, N:] == -7.0).all(), "wrote outside the M x N block"
                 out[dt] = to_host(buf[:M, :N])
             got = out[torch.float32][np.asarray(rows)].astype(np.float64)

@@ -97,7 +97,7 @@ def test_fused_tiled_against_the_oracle(brq, orc):
     assert np.array_equal(to_host(st)[si], os_)
 
 
-# tiled persistent kernel, general 32x32-tile kernel, M <= 128 and M <= 16 kernels
+# the one-tile, general, streaming and skinny kernels (every kernel by its name: test_gpu_gemm_routes.py)
 @pytest.mark.parametrize("M,N,K", [(512, 768, 2048), (256, 256, 512), (100, 200, 544), (300, 64, 1024),
                                    (8, 300, 1024), (16, 48, 96), (300, 256, 1024), (65, 512, 512), (700, 256, 512),
                                    (300, 256, 544), (512, 512, 1152), (64, 256, 96)])
@@ -118,7 +118,7 @@ def test_product_does_not_depend_on_the_layout(brq, M, N, K):
         if K % 512 == 0 or (M > 128 and N % 256 != 0):
             assert torch.equal(y0, y1)
         elif dt == torch.float32:
-            # two tiled operands with K % 512 != 0 run on the persistent or the small-batch kernel
+            # two tiled operands with K % 512 != 0 run on the one-tile or the streaming kernel
             # (over the zero K padding), the mixed cases on the general one: same sum, another order
             d = (y1.double() - y0.double()).norm() / y0.double().norm()
             assert d < 1e-5, float(d)
@@ -139,8 +139,8 @@ def test_end_to_end_tiled_against_the_oracle(brq, orc):
 
 def test_tiled_product_with_k_not_a_multiple_of_512(brq, orc):
     """K = 1408 (11 stages of 128, e.g. the shape class of an 11008-wide down projection): tiled
-    operands are zero-padded to 1536 by the quantizer and the persistent kernel runs over the
-    padding; against the oracle on the oracle's own quantization."""
+    operands are zero-padded to 1536 by the quantizer and the staged kernels (the dispatcher's and the persistent
+    one) run over the padding; against the oracle on the oracle's own quantization."""
     M, N, K = 300, 512, 1408
     xh, wh = make_x(M, K, 51, "bf16"), make_x(N, K, 52, "bf16")
     act, ast = brq.rotate_quantize_fused(to_dev(xh), 32, layout="tiled")
@@ -150,6 +150,10 @@ def test_tiled_product_with_k_not_a_multiple_of_512(brq, orc):
     ow, ows = orc.rotate_quantize_fused(wh, 32)
     ref, bound = orc.mxfp4_gemm(oa, oas, ow, ows)
     assert (np.abs(y - ref) <= 1e-5 * bound + 2.0 ** -126).all()
+    for route in ("256x256", "128x256"):
+        out = torch.empty((M, N), dtype=torch.float32, device="cuda")
+        brq.diag_mxfp4_gemm_on(route, act, ast, wct, wst, out, K, a_layout="tiled", w_layout="tiled")
+        assert np.array_equal(to_host(out).astype(np.float64), y)
     # the same buffers through the general kernel (row-major A forces it) agree to the tolerance
     ar, asr = brq.to_rowmajor(act, ast, M, K)
     y2 = to_host(brq.mxfp4_gemm(ar, asr, wct, wst, w_layout="tiled", N=N, K=K)).astype(np.float64)

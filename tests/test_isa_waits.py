@@ -1,7 +1,7 @@
 """Wait states of the built code, on the CPU.  Some instructions may follow others only after a number of wait states
 that the hardware does not enforce (the published tables of required no-ops; an instruction is one wait state,
 s_nop N is N + 1).  The compiler keeps them between instructions that it knows, not around those that sit in inline
-assembly: the LDS-DMA loads and the block-scaled MFMAs.  So the library as built is disassembled and every pair is
+assembly: the LDS-DMA loads, the block-scaled MFMAs, the additions of another lane's value.  So the library as built is disassembled and every pair is
 looked at, along every path that leads to the second instruction."""
 import functools
 import os
@@ -130,10 +130,15 @@ def is_fp4_mfma(i):
     return i.op == "v_mfma_scale_f32_32x32x64_f8f6f4" and "cbsz:4 blgp:4" in i.text
 
 
+def is_dpp(i):
+    return i.is_valu() and re.search(r" (quad_perm:|row_)", i.text) is not None
+
+
 PAIRS = {
     "M0 written, then an LDS-DMA load": (lambda i: i.op.startswith("s_"), is_lds_dma, 1, lambda i: {("m0", 0)}),
     "scalar register from the vector unit, then an address of a memory access": (Instruction.is_valu, Instruction.is_vmem, 5, lambda i: {r for r in i.read() if r[0] == "s"}),
     "vector register from the vector unit, then an MFMA": (Instruction.is_valu, Instruction.is_mfma, 2, Instruction.read),
+    "vector register from the vector unit, then another lane's copy of it": (Instruction.is_valu, is_dpp, 2, lambda i: registers(i.operands[1])),
     # (8 passes: fp4 operands)
     "result of a block-scaled MFMA, then the vector unit": (is_fp4_mfma, Instruction.is_valu, 12, lambda i: i.read() | i.written()),
 }
