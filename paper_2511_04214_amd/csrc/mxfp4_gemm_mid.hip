@@ -21,34 +21,51 @@
 // bounds, and the stages that the window shares with the superstage before get scale bytes 0 in BOTH operands
 // (2^-127 * 2^-127 times at most 36 * 32 vanishes in an fp32 sum).
 //
-// LDS map (bytes), S = NA + MB: D stages x (W rows 4K NA | A rows 4K MB); then ceil(D / 4) scale buffers x
-// (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the ring.
+// Pairs (PAIR: an operand is row-major).  A stage of a row-major operand is half of a 128-byte line of every row.  Taken
+// stage by stage each line crosses from the L2 to the CU twice, and from HBM its halves come at two times: with
+// 128 x 128 tiles 1000 x 4096 x 11008 ran at 936 cycles a stage (681 with W in the memory-side cache), tiled operands at 490.
+// So two stages are loaded as one: 8 rows x 128 bytes per load, 128-byte rows in LDS, chunk c of row i at c ^ ((i >> 1) & 7)
+// (16 rows of one chunk then cover all banks).  A slot of the ring is free once the second of its stages has been read,
+// in the first half of that stage, so loads are issued in the odd stages: A's first, then W's.  W comes from HBM and
+// A from the L2 or the memory-side cache, where the quantizer has just left it, and loads complete in order: behind
+// A's they have two stages more to arrive (DW > DA), where the LDS has no room for as many of both.
+// Cycles a stage and us, row-major, weights in no cache, before -> now: 1000 x 4096 x 11008 936 -> 705, 41.2 -> 35.7; 300 x
+// 28672 x 8192 (320 x 128) 1340 -> 1046, 57.6 -> 50.9; 2000 x 4096 x 11008 1200 -> 1010, 67 -> 58; 1000 x 4096 x 11008 on 64 x 128
+// 56 -> 45.  What is left over tiled operands is the order in which HBM is read (hot: 495 cycles).
+// Both kinds take either layout; tiled operands keep single stages (4 of them in LDS twice a CU: 29.5 against 30.4 us).
 //
-// D: as many stages as the LDS takes where that measured faster.  Two workgroups of 64 x 128 on a CU with 6 stages each
-// instead of 4: 200 x 4096 x 4096 11.2 -> 9.7 us, 300 x 28672 x 8192 75 -> 68.  The other tiles gain nothing from
-// depth (128 x 128 with 8 stages and one workgroup a CU instead of 4 and two: 58 -> 65 us on the latter); 320 x 128, for a few hundred rows, has
-// 5 and reads its weights once: 47.6 -> 44.8 us on the latter, row-major 2000 x 4096 x 11008 74 -> 66.
+// LDS map (bytes), S = NA + MB: W's DW stages x 4K NA | A's DA stages x 4K MB; then ceil(DW / 4) scale buffers x
+// (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the rings.
+//
+// DW, DA: as many stages as the LDS takes where that measured faster.  Single stages: two workgroups of 64 x 128 on a CU
+// with 6 stages each instead of 4: 200 x 4096 x 4096 11.2 -> 9.7 us, 300 x 28672 x 8192 75 -> 68.  The other tiles gain nothing
+// from depth (128 x 128 with 8 stages and one workgroup a CU instead of 4 and two: 58 -> 65 us on the latter); 320 x 128, for a
+// few hundred rows, has 5 and reads its weights once: 47.6 -> 44.8 us on the latter.  Pairs: 4 stages of both wait for
+// every load (128 x 128: 1082 cycles a stage, 6 of both 705, 8 the same); 64 x 128 with 6 and 4, 45.1, 6 and 6, 47.0 us.
 #include "mfma_fp4.h"
 #include "brq_launch.h"
 
 namespace brq {
 namespace mid {
 
-constexpr int stage_bytes(int NA, int MB) { return 4096 * (NA + MB); }
-// D code stages and the scales of every superstage that has a stage among them
-constexpr int scale_bufs(int D) { return (D + 3) / 4; }
-constexpr int lds_bytes(int NA, int MB, int D) { return D * stage_bytes(NA, MB) + scale_bufs(D) * 1024 * (NA + MB); }
+// DW and DA code stages of W and A, and the scales of every superstage that has a stage among W's
+constexpr int scale_bufs(int DW) { return (DW + 3) / 4; }
+constexpr int lds_bytes(int NA, int MB, int DW, int DA) { return 4096 * (NA * DW + MB * DA) + scale_bufs(DW) * 1024 * (NA + MB); }
 
+// DW == DA unless PAIR.
 // vec: every 16-byte chunk of an output row is aligned and either wholly inside or outside N (N and ldy multiples
 // of 16 / sizeof(out)); otherwise elements are stored one by one.
-template <bool OUT_BF16, int NA, int MB, int D>
-__global__ void __launch_bounds__(256, (lds_bytes(NA, MB, D) <= 81920 ? 2 : 1))
+template <bool OUT_BF16, int NA, int MB, int DW, int DA, bool PAIR>
+__global__ void __launch_bounds__(256, (lds_bytes(NA, MB, DW, DA) <= 81920 ? 2 : 1))
 k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const uint8_t* __restrict__ wq,
            const uint8_t* __restrict__ ws, int M, int N, int K, void* __restrict__ y, int64_t ldy, int a_tiled,
            int w_tiled, int vec) {
     constexpr int S = NA + MB, NM = NA * MB, NS = 2 * NM;      // MFMAs per step and per stage
-    constexpr int TM = 64 * MB, TN = 64 * NA, STAGE = stage_bytes(NA, MB), OPER = 4096 * NA;
-    constexpr int NSB = scale_bufs(D), SCALE_BASE = D * STAGE, SCALE_BUF = 1024 * S;
+    constexpr int TM = 64 * MB, TN = 64 * NA, G = PAIR ? 2 : 1;       // G: stages per slot of the rings
+    constexpr int WSLOT = 4096 * NA * G, ASLOT = 4096 * MB * G, ABASE = 4096 * NA * DW;
+    constexpr int NSB = scale_bufs(DW), SCALE_BASE = ABASE + 4096 * MB * DA, SCALE_BUF = 1024 * S;
+    constexpr int PW = DW / 2, PA = DA / 2;                    // pairs: how far ahead of the one that is read they are loaded
+    static_assert(PAIR ? DW % 2 == 0 && DA % 2 == 0 && PW >= PA && PA >= 2 : DW == DA, "");
     constexpr int SPW = (S + 3) / 4;                           // scale loads per wavefront and superstage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -74,14 +91,16 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     const int ovd = (K == Kp || w_tiled) ? 0 : (int)((Kp - K) / 128);   // stages the last window shares with the one before
 
     // ---- loads.  A wavefront brings 16 NA rows of W and 16 MB rows of A per stage, 16 rows x 64 bytes per
-    // instruction (lane i: chunk (i & 3) ^ ((i >> 4) & 3) of row i >> 2), and its share of the scale rows, 64
+    // instruction (lane i: chunk (i & 3) ^ ((i >> 4) & 3) of row i >> 2), or 8 rows x 128 bytes of a pair, and its share of the scale rows, 64
     // rows x 16 bytes per instruction, once per superstage (wavefronts without a share repeat the last one, so that
     // all count the same).  Every per-lane offset is relative to one uniform base per operand that moves along
     // K; rows past the last one are clamped to it and never stored.
-    const uint32_t swz16 = (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
-    auto code_off = [&](int64_t row, int64_t rows, bool tiled) -> uint32_t {
-        row = min(row, rows - 1);
-        return (tiled ? (uint32_t)((row >> 6) * (Kp / 128) * 4096 + (row & 63) * 64) : (uint32_t)(row * (K / 2))) + swz16;
+    const int lrow = PAIR ? lane >> 3 : lane >> 2;             // this lane's row of the 16 / G that a load brings
+    auto code_off = [&](int64_t row, int q, int64_t rows, bool tiled) -> uint32_t {
+        row = min(row + lrow, rows - 1);
+        const uint32_t c = PAIR ? (uint32_t)((lane & 7) ^ ((q & 1) * 4 + (lane >> 4))) : (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
+        return tiled ? (uint32_t)((row >> 6) * (Kp / 128) * 4096 + (row & 63) * 64) + (c & 3) * 16 + (c >> 2) * 4096
+                     : (uint32_t)(row * (K / 2)) + c * 16;
     };
     auto scale_off = [&](int64_t row, int64_t rows, bool tiled) -> uint32_t {
         row = min(row, rows - 1);
@@ -92,23 +111,24 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     const uint8_t* const wbase = uniform_ptr(wq + (w_tiled ? wslab * (Kp / 128) * 4096 : n0 * (K / 2)));
     const uint8_t* const abase = uniform_ptr(aq + (a_tiled ? aslab * (Kp / 128) * 4096 : m0 * (K / 2)));
     const int64_t nrows = N - n0, mrows = M - m0;
-    uint32_t vw[NA], va[MB], vsc[SPW];
+    uint32_t vw[G * NA], va[G * MB], vsc[SPW];
 #pragma unroll
-    for (int q = 0; q < NA; ++q) vw[q] = code_off(wave * 16 * NA + 16 * q + (lane >> 2), nrows, w_tiled != 0);
+    for (int q = 0; q < G * NA; ++q) vw[q] = code_off(wave * 16 * NA + 16 / G * q, q, nrows, w_tiled != 0);
 #pragma unroll
-    for (int q = 0; q < MB; ++q) va[q] = code_off(wave * 16 * MB + 16 * q + (lane >> 2), mrows, a_tiled != 0);
-    // Rows of A past M: their lanes' loads are masked off and their LDS rows are zero in all D stages.  (A load
+    for (int q = 0; q < G * MB; ++q) va[q] = code_off(wave * 16 * MB + 16 / G * q, q, mrows, a_tiled != 0);
+    // Rows of A past M: their lanes' loads are masked off and their LDS rows are zero in all stages.  (A load
     // without any lane is issued and counted like another: the waits below are the same for every wavefront.)  The
     // matrix cores' power depends on what they multiply, and this kernel runs at the board's power limit: a tile
     // half of whose rows repeat row M - 1 costs as much as a full one, half of zeros close to half.
-    uint64_t ma[MB];
+    uint64_t ma[G * MB];
 #pragma unroll
-    for (int q = 0; q < MB; ++q) {
-        const int row = wave * 16 * MB + 16 * q + (lane >> 2);
+    for (int q = 0; q < G * MB; ++q) {
+        const int row = wave * 16 * MB + 16 / G * q + lrow;
         ma[q] = __builtin_amdgcn_ballot_w64(row < mrows);
         if (row >= mrows) {
 #pragma unroll
-            for (int u = 0; u < D; ++u) *reinterpret_cast<v4i*>(lds + u * STAGE + OPER + row * 64 + (lane & 3) * 16) = v4i{0, 0, 0, 0};
+            for (int u = 0; u < DA / G; ++u)
+                *reinterpret_cast<v4i*>(lds + ABASE + u * ASLOT + row * (64 * G) + (lane & (4 * G - 1)) * 16) = v4i{0, 0, 0, 0};
         }
     }
     const uint8_t* sbase[SPW];
@@ -128,17 +148,20 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     }
     const int w_stage = w_tiled ? 4096 : 64, w_last = w_tiled ? (KQ - 1) * 16384 : K / 2 - 256;
     const int a_stage = a_tiled ? 4096 : 64, a_last = a_tiled ? (KQ - 1) * 16384 : K / 2 - 256;
-    const uint32_t dst_w = lds0 + wave * (1024 * NA), dst_a = lds0 + OPER + wave * (1024 * MB);
-    const uint8_t *pw = wbase, *pa = abase;                    // superstage that is being loaded
+    const uint32_t dst_w = lds0 + wave * (WSLOT / 4), dst_a = lds0 + ABASE + wave * (ASLOT / 4);
+    const uint8_t *pw = wbase, *pa = abase;                    // superstages that are being loaded
     uint32_t ld_buf = 0, rd_buf = 0;                           // scale buffers of the superstages being loaded and read
     auto mask_if_less = [](int a, int b) -> uint64_t {         // all lanes if a < b (uniform), in scalar registers
         uint32_t m;                                            // (written out: the compiler makes vector registers of it)
         asm("s_sub_i32 %0, %1, %2\n\ts_ashr_i32 %0, %0, 31" : "=s"(m) : "s"(a), "s"(b) : "scc");
         return ((uint64_t)m << 32) | m;
     };
-    auto load_super = [&](int q) {                             // (past the last superstage nothing is loaded: see dma_code)
+    auto load_super_w = [&](int q) {                           // (past the last superstage nothing is loaded: see dma_w)
         const int qc = min(q, KQ - 1);
         pw = wbase + (qc == KQ - 1 ? w_last : qc * 4 * w_stage);
+    };
+    auto load_super_a = [&](int q) {
+        const int qc = min(q, KQ - 1);
         pa = abase + (qc == KQ - 1 ? a_last : qc * 4 * a_stage);
     };
     auto dma_scales = [&](int q) {
@@ -149,27 +172,35 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
             dma16_masked<0>(sdst[i] + ld_buf, sbase[i] + (qc == KQ - 1 ? slast[i] : qc * sstep[i]), vsc[i], live);
         ld_buf = ld_buf + SCALE_BUF == NSB * SCALE_BUF ? 0u : ld_buf + SCALE_BUF;
     };
-    // load I of stage U of that superstage into the ring's slot at byte `slot`, W and A alternating while there are
-    // both.  Past the last superstage (`live` = 0) no lane takes part: nothing is read or written, and the counted
-    // waits below see the same number of instructions in every stage.
-    auto dma_code = [&](auto Uc, auto Ic, uint32_t slot, auto Sure, uint64_t live) {
-        constexpr int U = decltype(Uc)::value, I = decltype(Ic)::value, MN = NA < MB ? NA : MB;
+    // load q of stage U (and U + 1) of that superstage into the ring's slot at byte `slot`.  Past the last superstage
+    // (`live` = 0) no lane takes part: nothing is read or written, and the counted waits below see the same number of
+    // instructions in every stage.
+    auto dma_w = [&](auto Uc, auto Qc, uint32_t slot, auto Sure, uint64_t live) {
+        constexpr int U = decltype(Uc)::value, q = decltype(Qc)::value;
+        if constexpr (decltype(Sure)::value != 0) dma16<q * 1024>(dst_w + slot, pw + U * w_stage, vw[q]);
+        else dma16_masked<q * 1024>(dst_w + slot, pw + U * w_stage, vw[q], live);
+    };
+    auto dma_a = [&](auto Uc, auto Qc, uint32_t slot, auto Sure, uint64_t live) {
+        constexpr int U = decltype(Uc)::value, q = decltype(Qc)::value;
+        if constexpr (decltype(Sure)::value != 0) dma16_masked<q * 1024>(dst_a + slot, pa + U * a_stage, va[q], ma[q]);
+        else dma16_masked<q * 1024>(dst_a + slot, pa + U * a_stage, va[q], ma[q] & live);
+    };
+    // load I of a stage, W and A alternating while there are both
+    auto dma_code = [&](auto Uc, auto Ic, uint32_t wslot, uint32_t aslot, auto Sure, uint64_t live) {
+        constexpr int I = decltype(Ic)::value, MN = NA < MB ? NA : MB;
         constexpr bool W = I < 2 * MN ? (I & 1) == 0 : NA > MB;
         constexpr int q = I < 2 * MN ? I / 2 : I - MN;
-        if constexpr (W && decltype(Sure)::value != 0) dma16<q * 1024>(dst_w + slot, pw + U * w_stage, vw[q]);
-        else if constexpr (W) dma16_masked<q * 1024>(dst_w + slot, pw + U * w_stage, vw[q], live);
-        else if constexpr (decltype(Sure)::value != 0) dma16_masked<q * 1024>(dst_a + slot, pa + U * a_stage, va[q], ma[q]);
-        else dma16_masked<q * 1024>(dst_a + slot, pa + U * a_stage, va[q], ma[q] & live);
+        if constexpr (W) dma_w(Uc, IC<q>{}, wslot, Sure, live);
+        else dma_a(Uc, IC<q>{}, aslot, Sure, live);
     };
 
     // ---- fragments and scales
-    const int sw = (r >> 2) & 3;
-    uint32_t wo[2], ao[2];                                     // [step]: this lane's bytes in slot 0
+    uint32_t wo[2 * G], ao[2 * G];                             // [step, in a pair both stages']: this lane's bytes in slot 0
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const uint32_t c16 = (uint32_t)(((2 * h + j) ^ sw) << 4);
-        wo[j] = (uint32_t)((wn * 32 * NA + r) * 64) + c16;
-        ao[j] = (uint32_t)(OPER + (wm * 32 * MB + r) * 64) + c16;
+    for (int j = 0; j < 2 * G; ++j) {
+        const int c = PAIR ? ((j >> 1) * 4 + 2 * h + (j & 1)) ^ ((r >> 1) & 7) : (2 * h + j) ^ ((r >> 2) & 3);
+        wo[j] = (uint32_t)((wn * 32 * NA + r) * (64 * G) + c * 16);
+        ao[j] = (uint32_t)(ABASE + (wm * 32 * MB + r) * (64 * G) + c * 16);
     }
     const uint8_t* const wsp = lds + SCALE_BASE + (wn * 32 * NA + r) * 16;
     const uint8_t* const asp = lds + SCALE_BASE + 1024 * NA + (wm * 32 * MB + r) * 16;
@@ -178,13 +209,13 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     int scw[2][NA], sca[2][MB];
     v4i srw[NA], sra[MB];                                      // a superstage's 16 scale bytes of this lane's rows
     v16f acc[NA][MB];
-    // read I of the 2 S fragments of the stage in `slot` into parity P, in the order the MFMAs take them
-    auto read_frag = [&](auto Pc, auto Ic, uint32_t slot) {
-        constexpr int P = decltype(Pc)::value, J = decltype(Ic)::value / S, k = decltype(Ic)::value % S;
-        if constexpr (k >= 1 && k <= MB) af[P][J][k - 1] = *reinterpret_cast<const v4i*>(lds + (ao[J] + slot) + (k - 1) * 2048);
+    // read I of the 2 S fragments of a stage of parity P in these slots, in the order the MFMAs take them
+    auto read_frag = [&](auto Pc, auto Ic, uint32_t wslot, uint32_t aslot) {
+        constexpr int P = decltype(Pc)::value, J = decltype(Ic)::value / S, k = decltype(Ic)::value % S, O = PAIR ? 2 * P + J : J;
+        if constexpr (k >= 1 && k <= MB) af[P][J][k - 1] = *reinterpret_cast<const v4i*>(lds + (ao[O] + aslot) + (k - 1) * (2048 * G));
         else {
             constexpr int t = k == 0 ? 0 : k - MB;
-            wf[P][J][t] = *reinterpret_cast<const v4i*>(lds + (wo[J] + slot) + t * 2048);
+            wf[P][J][t] = *reinterpret_cast<const v4i*>(lds + (wo[O] + wslot) + t * (2048 * G));
         }
     };
     auto read_scales = [&](auto Ic, uint32_t buf) {            // scale rows of W tile I and A tile I
@@ -199,32 +230,51 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
         else sca[P][I - NA] = (int)((uint32_t)(sra[I - NA][U] & keep) >> hshift);
     };
 
+    // Pairs.  In stage 2 p + 1 pair p has been read and the loads of A's pair p + PA are issued, then the scale loads if W's
+    // pair p + PW is a superstage's first, then the loads of that pair.  How many loads are younger than the last one
+    // of pair u (odd or not): A's if W's are older, in the stage that issued it and the PA - 2 after it.
+    constexpr auto pair_wait = [](int odd) constexpr {
+        int n = (PA - 2) * 2 * S + (PW > PA ? 2 * NA : 0);
+        for (int b = PW > PA ? PA : PA - 1; b >= 2; --b) n += (odd - b + PW) % 2 == 0 ? SPW : 0;     // issued for p = u - b
+        return n;
+    };
+
     // ---- stage U of superstage kq.  LAST: the last superstage, nothing is loaded any more.
-    uint32_t slot = 0;                                         // this stage's slot of the ring (bytes)
+    uint32_t wslot = 0, aslot = 0;                             // this stage's slots of the rings (bytes)
     auto stage = [&](auto Uc, auto Lastc, int kq) __attribute__((always_inline)) {
         constexpr int U = decltype(Uc)::value, P = U & 1, NU = (U + 1) & 3;
         constexpr bool LAST = decltype(Lastc)::value != 0, NEXT = !(LAST && U == 3);
-        constexpr int LU = (U + D) & 3, LQ = (U + D) / 4;      // the stage that is loaded: stage LU of superstage kq + LQ
+        // the stages of W and A that are loaded (pairs: the first ones): stage LU of superstage kq + LQ
+        constexpr int WD = PAIR ? U - 1 + DW : U + DW, AD = PAIR ? U - 1 + DA : U + DA;
+        constexpr int WU = WD & 3, WQ = WD / 4, AU = AD & 3, AQ = AD / 4;
+        constexpr bool LOADS = !LAST && (!PAIR || U % 2 == 1);
         // The next stage's loads have landed once only those of the D - 2 stages after it are outstanding: S each, and
         // the scale loads of the superstages that begin among them (a superstage's scale loads are issued right before
         // its first stage's).  In the last superstage there are fewer, and leaving the scale loads out is only stricter.
-        constexpr int BEGIN = (U + D - 1) / 4 - (U + 1) / 4;   // multiples of 4 in [U + 2, U + D - 1]
-        if constexpr (!LAST) wait_vm_and_barrier<(D - 2) * S + BEGIN * SPW>();
-        else if constexpr (U < 3) wait_vm_and_barrier<(D - 2 - U) * S>();
+        constexpr int BEGIN = (U + DW - 1) / 4 - (U + 1) / 4;   // multiples of 4 in [U + 2, U + D - 1]
+        if constexpr (PAIR) {
+            if constexpr (U % 2 == 0 || !NEXT) lds_wait_and_barrier();     // the same pair as this stage
+            else wait_vm_and_barrier<pair_wait(U == 1 ? 1 : 0)>();
+        }
+        else if constexpr (!LAST) wait_vm_and_barrier<(DW - 2) * S + BEGIN * SPW>();
+        else if constexpr (U < 3) wait_vm_and_barrier<(DW - 2 - U) * S>();
         else lds_wait_and_barrier();
         const int nq = U == 3 ? kq + 1 : kq;                   // superstage of the next stage
         const int keep = (nq == KQ - 1 && NU < ovd) ? 0 : -1;  // uniform
-        const uint32_t nslot = slot + STAGE == D * STAGE ? 0u : slot + STAGE;
+        const bool stay = PAIR && U % 2 == 0;
+        const uint32_t nwslot = stay ? wslot : wslot + WSLOT == DW / G * WSLOT ? 0u : wslot + WSLOT;
+        const uint32_t naslot = stay ? aslot : aslot + ASLOT == DA / G * ASLOT ? 0u : aslot + ASLOT;
         constexpr int RPS = NS >= 2 * S + 2 ? 1 : 2;           // fragment reads per slot
-        const uint64_t live = mask_if_less(kq + LQ, KQ);
-        if constexpr (LU == 0 && !LAST) load_super(kq + LQ);
+        const uint64_t live = mask_if_less(kq + WQ, KQ), alive = mask_if_less(kq + AQ, KQ);
+        if constexpr (WU == 0 && LOADS) load_super_w(kq + WQ);
+        if constexpr (AU == 0 && LOADS) load_super_a(kq + AQ);
         static_for([&](auto Sc) __attribute__((always_inline)) {
             constexpr int s = decltype(Sc)::value, J = s / NM, X = s % NM, A = X / MB, B = X % MB;
             mfma_fp4(acc[A][B], wf[P][J][A], af[P][J][B], IC<J>{}, scw[P][A], sca[P][B]);
             if constexpr (NEXT) {
                 static_for([&](auto Ic) __attribute__((always_inline)) {
                     constexpr int i = s * RPS + decltype(Ic)::value;
-                    if constexpr (i < 2 * S) read_frag(IC<P ^ 1>{}, IC<i>{}, nslot);
+                    if constexpr (i < 2 * S) read_frag(IC<P ^ 1>{}, IC<i>{}, nwslot, naslot);
                 }, IC<RPS>{});
                 if constexpr (U == 3 && s < (NA > MB ? NA : MB)) read_scales(IC<s>{}, rd_buf);
                 constexpr int first = NS - 1 - (S + 1) / 2;    // two scale registers per slot, done one slot before the end
@@ -234,16 +284,24 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
                     if constexpr (s >= first && i < S) set_scale(IC<NU>{}, IC<P ^ 1>{}, IC<i>{}, keep);
                 }, IC<2>{});
             }
-            if constexpr (!LAST) {
-                if constexpr (LU == 0 && s == 0) dma_scales(kq + LQ);
+            if constexpr (LOADS) {
+                if constexpr (!PAIR && WU == 0 && s == 0) dma_scales(kq + WQ);
                 static_for([&](auto Ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(Ic)::value;
-                    if constexpr ((2 * i + 1) * NM / S == s) dma_code(IC<LU>{}, IC<i>{}, slot, IC<(LQ < 2)>{}, live);
-                }, IC<S>{});
+                    if constexpr ((2 * i + 1) * NM / (G * S) == s) {
+                        if constexpr (!PAIR) dma_code(IC<WU>{}, Ic, wslot, aslot, IC<(WQ < 2)>{}, live);
+                        else if constexpr (i < 2 * MB) dma_a(IC<AU>{}, Ic, aslot, IC<(AQ < 2)>{}, alive);
+                        else {
+                            if constexpr (i == 2 * MB && WU == 0) dma_scales(kq + WQ);
+                            dma_w(IC<WU>{}, IC<i - 2 * MB>{}, wslot, IC<(WQ < 2)>{}, live);
+                        }
+                    }
+                }, IC<G * S>{});
             }
             __builtin_amdgcn_sched_barrier(0);
         }, IC<NS>{});
-        slot = nslot;
+        wslot = nwslot;
+        aslot = naslot;
         if constexpr (U == 3) rd_buf = rd_buf + SCALE_BUF == NSB * SCALE_BUF ? 0u : rd_buf + SCALE_BUF;
     };
     auto superstage = [&](auto Lastc, int kq) __attribute__((always_inline)) {
@@ -254,11 +312,23 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     };
 
     // ---- prologue: the first D stages in flight, accumulators cleared meanwhile, stage 0 in registers
-    static_for([&](auto Tc) __attribute__((always_inline)) {
-        constexpr int T = decltype(Tc)::value;
-        if constexpr (T % 4 == 0) { load_super(T / 4); dma_scales(T / 4); }
-        static_for([&](auto Ic) { dma_code(IC<(T & 3)>{}, Ic, (uint32_t)(T * STAGE), IC<(T < 4)>{}, mask_if_less(T / 4, KQ)); }, IC<S>{});
-    }, IC<D>{});
+    if constexpr (PAIR) {
+        static_for([&](auto Tc) __attribute__((always_inline)) {        // as in stage 2 p + 1, p = -PW, .., -1
+            constexpr int w = decltype(Tc)::value, a = w - PW + PA;     // the pairs of W and A
+            if constexpr (a >= 0) {
+                if constexpr (a % 2 == 0) load_super_a(a / 2);
+                static_for([&](auto Qc) { dma_a(IC<(2 * a & 3)>{}, Qc, (uint32_t)(a * ASLOT), IC<(a < 2)>{}, mask_if_less(a / 2, KQ)); }, IC<2 * MB>{});
+            }
+            if constexpr (w % 2 == 0) { load_super_w(w / 2); dma_scales(w / 2); }
+            static_for([&](auto Qc) { dma_w(IC<(2 * w & 3)>{}, Qc, (uint32_t)(w * WSLOT), IC<(w < 2)>{}, mask_if_less(w / 2, KQ)); }, IC<2 * NA>{});
+        }, IC<PW>{});
+    } else {
+        static_for([&](auto Tc) __attribute__((always_inline)) {
+            constexpr int T = decltype(Tc)::value;
+            if constexpr (T % 4 == 0) { load_super_w(T / 4); load_super_a(T / 4); dma_scales(T / 4); }
+            static_for([&](auto Ic) { dma_code(IC<(T & 3)>{}, Ic, (uint32_t)(T * WSLOT), (uint32_t)(T * ASLOT), IC<(T < 4)>{}, mask_if_less(T / 4, KQ)); }, IC<S>{});
+        }, IC<DW>{});
+    }
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
@@ -270,8 +340,8 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
             acc[a][b] = v16f{};
             asm volatile("" : "+a"(acc[a][b]));
         }
-    wait_vm_and_barrier<(D - 1) * S + (NSB - 1) * SPW>();
-    static_for([&](auto Ic) { read_frag(IC<0>{}, Ic, 0u); }, IC<2 * S>{});
+    wait_vm_and_barrier<(PAIR ? pair_wait(0) : (DW - 1) * S + (NSB - 1) * SPW)>();
+    static_for([&](auto Ic) { read_frag(IC<0>{}, Ic, 0u, 0u); }, IC<2 * S>{});
     static_for([&](auto Ic) { read_scales(Ic, 0); }, IC<(NA > MB ? NA : MB)>{});
     static_for([&](auto Ic) { set_scale(IC<0>{}, IC<0>{}, Ic, -1); }, IC<S>{});   // (a single superstage shares nothing)
     rd_buf = NSB == 1 ? 0u : (uint32_t)SCALE_BUF;
@@ -337,25 +407,31 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
 }
 
 using Kern = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int64_t, int, int, int);
-struct Variant { int na, mb, d; Kern bf16, f32; };
-#define BRQ_MID(NA, MB, D) {NA, MB, D, k_gemm_mid<true, NA, MB, D>, k_gemm_mid<false, NA, MB, D>}
-static const Variant variants[MID_TILES] = {BRQ_MID(2, 1, 6), BRQ_MID(2, 2, 4), BRQ_MID(2, 3, 4), BRQ_MID(4, 3, 4), BRQ_MID(2, 5, 5)};
+struct Variant { int na, mb, dw, da; Kern bf16, f32; };
+#define BRQ_MID(NA, MB, DW, DA, PAIR) {NA, MB, DW, DA, k_gemm_mid<true, NA, MB, DW, DA, PAIR>, k_gemm_mid<false, NA, MB, DW, DA, PAIR>}
+static const Variant singles[MID_TILES] = {BRQ_MID(2, 1, 6, 6, false), BRQ_MID(2, 2, 4, 4, false), BRQ_MID(2, 3, 4, 4, false),
+                                           BRQ_MID(4, 3, 4, 4, false), BRQ_MID(2, 5, 5, 5, false)};
+static const Variant pairs[MID_TILES] = {BRQ_MID(2, 1, 6, 4, true), BRQ_MID(2, 2, 6, 6, true), BRQ_MID(2, 3, 6, 6, true),
+                                         BRQ_MID(4, 3, 4, 4, true), BRQ_MID(2, 5, 6, 4, true)};
 #undef BRQ_MID
+static const Variant& variant(int tile, bool both_tiled) { return both_tiled ? singles[tile] : pairs[tile]; }
 
 }  // namespace mid
 
 hipError_t setup_gemm_mid() {
-    for (const auto& v : mid::variants)
+    for (int i = 0; i < 2 * MID_TILES; ++i) {
+        const mid::Variant& v = mid::variant(i / 2, i % 2 != 0);
         for (mid::Kern k : {v.bf16, v.f32})
             if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   mid::lds_bytes(v.na, v.mb, v.d)); e != hipSuccess) return e;
+                                                   mid::lds_bytes(v.na, v.mb, v.dw, v.da)); e != hipSuccess) return e;
+    }
     return hipSuccess;
 }
 
 // Whole superstages, or both operands row-major with K a multiple of 128 and at least one superstage.  A lane's offset
 // inside the tile, below 64 max(NA, MB) rows of Kp / 2 bytes, has 32 bits, and the offset along K 31 (32 Kp bytes).
 bool mid_gemm_supported(int tile, const GemmShape& g) {
-    const mid::Variant& v = mid::variants[tile];
+    const mid::Variant& v = mid::variant(tile, g.a_tiled && g.w_tiled);
     const int64_t Kp = g.padded_k(), slabs = v.na > v.mb ? v.na : v.mb;
     return g.M > 0 && g.N > 0 && (g.whole_k() || (!g.a_tiled && !g.w_tiled && g.K % 128 == 0 && g.K >= 512)) &&
            Kp < (int64_t(1) << 26) && slabs * 32 * Kp <= (int64_t(1) << 32);
@@ -363,10 +439,10 @@ bool mid_gemm_supported(int tile, const GemmShape& g) {
 
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s) {
-    const mid::Variant& v = mid::variants[tile];
+    const mid::Variant& v = mid::variant(tile, a.tiled && w.tiled);
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
     const int epc = out_bf16 ? 8 : 4, vec = N % epc == 0 && ldy % epc == 0;
-    hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.d), s,
+    hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.dw, v.da), s,
                        a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy, (int)a.tiled, (int)w.tiled, vec);
     return hipGetLastError();
 }
