@@ -84,7 +84,8 @@ struct ClockOut<true> { unsigned long long* p; };
 // addition issues no refill loads in the K loops: the ring keeps the first superstage the prologue brought, every
 // MFMA, LDS read, barrier and output store runs as in the product, and the result is NOT the product - what
 // the kernel would cost if its operands moved themselves.  The product (DIAG == 0) has no such code.
-template <bool OUT_BF16, int MB, int DIAG>
+// LINES: the output's rows begin on 128-byte lines (asked in the kernel it cost 8192 x 14336 x 4096 3 %).
+template <bool OUT_BF16, int MB, int DIAG, bool LINES>
 __global__ void __launch_bounds__(256, 1) k_gemm_tiled(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as,
                                                        const uint8_t* __restrict__ wq, const uint8_t* __restrict__ ws,
                                                        int M, int N, int K, void* __restrict__ y, int64_t ldy, int a_tiled, int w_tiled,
@@ -349,13 +350,18 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tiled(const uint8_t* __restrict
         constexpr int colbytes = (OUT_BF16 ? PairA<X, MB>::value / 2 : PairA<X, MB>::value) * 128;
         uint8_t* dst = ytile + row * pitch + colbytes + st_off;
         // whole 128-byte lines that this kernel never reads back: with the streaming hint the output does not
-        // displace the operand panels that the other XCDs are about to fetch from the memory-side cache
+        // displace the operand panels that the other XCDs are about to fetch from the memory-side cache.  Where rows do not
+        // begin on a line the hint would send its halves to memory one by one (5000 x 8200 x 4096 107 us instead of 90, 1163 x
+        // 24048 x 512 36.9 instead of 21.3): there the L2 puts the lines together (the tiles beside it are the same XCD's).
         typedef unsigned int u4 __attribute__((ext_vector_type(4)));
         const int mr = (colbytes / ES < nrem) ? mrem : 0;     // a chunk past column N - 1 is not stored
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (row + 8 * j < mr)
-                __builtin_nontemporal_store(u4{ob[Kb][j].x, ob[Kb][j].y, ob[Kb][j].z, ob[Kb][j].w}, reinterpret_cast<u4*>(dst + 8 * j * pitch));
+            if (row + 8 * j < mr) {
+                const u4 v = {ob[Kb][j].x, ob[Kb][j].y, ob[Kb][j].z, ob[Kb][j].w};
+                if constexpr (LINES) __builtin_nontemporal_store(v, reinterpret_cast<u4*>(dst + 8 * j * pitch));
+                else *reinterpret_cast<u4*>(dst + 8 * j * pitch) = v;
+            }
     };
     // What the output path does after MFMA slot S of the next tile's first stage (S = -1: before slot 0;
     // S = NACC: the first slot of that stage's second step): accumulator S + 1 is packed and written (the
@@ -621,22 +627,22 @@ bool tiled_gemm_supported(int64_t M, int64_t N, int64_t K, bool out_bf16, int64_
            (Kp / 2) * 64 < (int64_t(1) << 31);
 }
 
-template <bool OUT_BF16, int MB, int DIAG>
+template <bool OUT_BF16, int MB, int DIAG, bool LINES = true>
 static void launch_one(dim3 g, hipStream_t s, const Operand& a, const Operand& w, int M, int N, int K, void* y, int64_t ldy,
                        unsigned long long* clk) {
     tiled::ClockOut<DIAG != 0> c;
     if constexpr (DIAG != 0) c.p = clk;
-    hipLaunchKernelGGL((tiled::k_gemm_tiled<OUT_BF16, MB, DIAG>), g, dim3(256), tiled::LDS_BYTES, s, a.codes, a.scales, w.codes,
+    hipLaunchKernelGGL((tiled::k_gemm_tiled<OUT_BF16, MB, DIAG, LINES>), g, dim3(256), tiled::LDS_BYTES, s, a.codes, a.scales, w.codes,
                        w.scales, M, N, K, y, ldy, (int)a.tiled, (int)w.tiled, c);
 }
 
 // The kernels use all 160 KB of the CU's LDS: declared once per device.
 hipError_t setup_gemm_tiled() {
-    const void* kernels[9] = {(const void*)tiled::k_gemm_tiled<true, 4, 0>, (const void*)tiled::k_gemm_tiled<false, 4, 0>,
-                              (const void*)tiled::k_gemm_tiled<true, 2, 0>, (const void*)tiled::k_gemm_tiled<false, 2, 0>,
-                              (const void*)tiled::k_gemm_tiled<true, 4, 1>, (const void*)tiled::k_gemm_tiled<false, 4, 1>,
-                              (const void*)tiled::k_gemm_tiled<true, 2, 1>, (const void*)tiled::k_gemm_tiled<false, 2, 1>,
-                              (const void*)tiled::k_gemm_tiled<true, 4, 2>};
+#define BRQ_TILED(BF, MB) (const void*)tiled::k_gemm_tiled<BF, MB, 0, true>, (const void*)tiled::k_gemm_tiled<BF, MB, 0, false>, \
+                          (const void*)tiled::k_gemm_tiled<BF, MB, 1, true>
+    const void* kernels[13] = {BRQ_TILED(true, 4), BRQ_TILED(false, 4), BRQ_TILED(true, 2), BRQ_TILED(false, 2),
+                               (const void*)tiled::k_gemm_tiled<true, 4, 2, true>};
+#undef BRQ_TILED
     for (const void* k : kernels)
         if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, tiled::LDS_BYTES); e != hipSuccess) return e;
     return hipSuccess;
@@ -659,8 +665,11 @@ hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int6
         if (half) out_bf16 ? launch_one<true, 2, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<false, 2, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk);
         else out_bf16 ? launch_one<true, 4, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<false, 4, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk);
     } else {
-        if (half) out_bf16 ? launch_one<true, 2, 0>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<false, 2, 0>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk);
-        else out_bf16 ? launch_one<true, 4, 0>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<false, 4, 0>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk);
+        const bool lines = reinterpret_cast<uintptr_t>(y) % 128 == 0 && ldy * (out_bf16 ? 2 : 4) % 128 == 0;
+#define BRQ_LAUNCH(BF, MB) (lines ? launch_one<BF, MB, 0, true>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<BF, MB, 0, false>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk))
+        if (half) out_bf16 ? BRQ_LAUNCH(true, 2) : BRQ_LAUNCH(false, 2);
+        else out_bf16 ? BRQ_LAUNCH(true, 4) : BRQ_LAUNCH(false, 4);
+#undef BRQ_LAUNCH
     }
     return hipGetLastError();
 }
