@@ -22,6 +22,7 @@ struct RowArgs {
     uint8_t* scales;    // quant/fused: [M][K/32]
     int64_t ldx, ldy;   // in elements
     uint32_t cpr;       // chunks per row = K/8
+    uint32_t through;   // how codes are stored: store_codes
     uint32_t nchunks;   // M * K/8
     // Tiled output (codes: 64 rows x 64 bytes per (slab, stage) block; scales: 64 rows x 16
     // bytes per (slab, superstage) block): blocks per slab, 0 = row-major output.
@@ -145,6 +146,14 @@ __device__ __forceinline__ int64_t chunk_offset(uint32_t c, uint32_t cpr, int64_
     }
 }
 
+// A lane's 8 codes.  They are read next by another kernel, on all XCDs.  With the streaming hint they go to memory and the
+// product fetches them from there; stored through the L2 (a store at device scope, `through`, uniform) they are also in the
+// memory-side cache.  What the two give is in code_stores_through.
+__device__ __forceinline__ void store_codes(uint32_t* p, uint32_t w, uint32_t through) {
+    if (through) __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else __builtin_nontemporal_store(w, p);
+}
+
 // ---- in-wavefront rotation, 32 <= B <= 512 ------------------------------------------
 
 // fl(1/sqrt(2^LOG2B)) as fp32 bits: sqrt(2)/2 = 0x3F3504F3 scaled by a power of two.
@@ -161,11 +170,10 @@ __device__ __forceinline__ void quant_store(const float (&y)[8], uint32_t row, u
     uint32_t w = encode8_e2m1(y, sb);
     if (a.stages == 0) {
         uint32_t c = row * a.cpr + kc;
-        __builtin_nontemporal_store(w, &a.codes[c]);
+        store_codes(&a.codes[c], w, a.through);
         if ((lane & 3) == 0) *(&a.scales[c >> 2]) = (uint8_t)sb;
     } else {
-        __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(a.codes) +
-                                                                   tiled_code_offset(row, kc, a.stages)));
+        store_codes(reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(a.codes) + tiled_code_offset(row, kc, a.stages)), w, a.through);
         if ((lane & 3) == 0) *(a.scales + tiled_scale_offset(row, kc, a.sstages)) = (uint8_t)sb;
     }
 }
@@ -361,7 +369,7 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
                 uint32_t w = encode8_e2m1(v[u], sb);
                 if (a.stages == 0) {
                     if (live) {
-                        __builtin_nontemporal_store(w, &a.codes[c]);
+                        store_codes(&a.codes[c], w, a.through);
                         if ((lane & 3) == 0) *(&a.scales[c >> 2]) = (uint8_t)sb;
                     }
                 } else if ((a.cpr & 63u) == 0) {
@@ -372,13 +380,12 @@ __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
                     uint8_t* cbase = reinterpret_cast<uint8_t*>(a.codes) + tiled_code_offset(row, kc0, a.stages);
                     uint8_t* sbase = a.scales + tiled_scale_offset(row, kc0, a.sstages);
                     if (live) {
-                        __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + (lc >> 4) * 4096u + (lc & 15u) * 4u));
+                        store_codes(reinterpret_cast<uint32_t*>(cbase + (lc >> 4) * 4096u + (lc & 15u) * 4u), w, a.through);
                         if ((lane & 3) == 0) *(sbase + (lc >> 2)) = (uint8_t)sb;
                     }
                 } else if (live) {
                     const uint32_t row = c / a.cpr, kc = c - row * a.cpr;
-                    __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(a.codes) +
-                                                                               tiled_code_offset(row, kc, a.stages)));
+                    store_codes(reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(a.codes) + tiled_code_offset(row, kc, a.stages)), w, a.through);
                     if ((lane & 3) == 0) *(a.scales + tiled_scale_offset(row, kc, a.sstages)) = (uint8_t)sb;
                 }
             }
@@ -445,7 +452,7 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
         uint8_t* cbase = reinterpret_cast<uint8_t*>(a.codes) + ((uint64_t)(row0 >> 6) * a.stages + st) * 4096u + (row0 & 63u) * 64u;
         uint8_t* sbase = a.scales + ((uint64_t)(row0 >> 6) * a.sstages + (st >> 2)) * 1024u + (row0 & 63u) * 16u + (st & 3u) * 4u;
         if (row0 + lrow < rows) {
-            __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(cbase + out_lane * 4u));
+            store_codes(reinterpret_cast<uint32_t*>(cbase + out_lane * 4u), w, a.through);
             if ((lane & 3) == 0) *(sbase + lrow * 16u + (lc >> 2)) = (uint8_t)sb;
         }
     }
@@ -591,7 +598,7 @@ __global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_ro
             } else {
                 const uint32_t sb = e8m0_from_amax(quad_max(absmax8(v[j])));
                 const uint32_t w = encode8_e2m1(v[j], sb);
-                *reinterpret_cast<uint32_t*>(cd + piece(j) * cstep) = w;
+                store_codes(reinterpret_cast<uint32_t*>(cd + piece(j) * cstep), w, 1u);
                 if ((lane & 3u) == 0) sd[piece(j) * sstep] = (uint8_t)sb;
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -830,6 +837,15 @@ static hipError_t dispatch_b(int log2b, const RowArgs& a, bool contig, int64_t M
     }
 }
 
+// Whether codes are stored through the L2 (store_codes).  Online step and product together, us, streaming hint -> through:
+// row-major 256 x 4096 x 4096 16.2 -> 13.9, 1000 x 4096 x 11008 49.1 -> 43.6, 2000 x 4096 x 11008 79.2 -> 69.4, 4096 x 4096 x 4096
+// 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands, whose product reads
+// whole pages of them, gain less, and with a few MB of codes lose as often: 512 x 4096 x 4096 15.6 -> 13.4, but 971 x 4096 x 2048
+// 12.9 -> 14.4; from 16 MB on the quantizer itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x 8192 as before).
+static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
+    return M * (K / 2) >= (int64_t(1) << (tiled ? 24 : 18));
+}
+
 // mode: RowMode; log2b: 0 for MODE_QUANT, else 3..14.  Arguments are already validated.
 hipError_t launch_rowwise(int mode, int log2b, bool in_bf16, bool out_bf16, const void* x, int64_t M,
                           int64_t K, int64_t ldx, void* y, int64_t ldy, uint8_t* codes, uint8_t* scales,
@@ -850,6 +866,7 @@ hipError_t launch_rowwise(int mode, int log2b, bool in_bf16, bool out_bf16, cons
     a.x = x; a.y = y; a.codes = reinterpret_cast<uint32_t*>(codes); a.scales = scales;
     a.ldx = ldx; a.ldy = ldy; a.cpr = (uint32_t)(K / 8); a.nchunks = (uint32_t)(M * (K / 8));
     const int64_t Kp = (K + 511) / 512 * 512;
+    a.through = code_stores_through(tiled, M, K) ? 1u : 0u;
     a.stages = tiled ? (uint32_t)(Kp / 128) : 0u;
     a.sstages = tiled ? (uint32_t)(Kp / 512) : 0u;
     a.pad = KPad::of(tiled && mode != MODE_ROTATE && mode != MODE_STATS, codes, scales, M, K);
