@@ -5,6 +5,9 @@ passes their device pointers and the current HIP stream through the C ABI declar
 include/brq.h, and returns the output tensors.  No arithmetic of the method happens
 here.  There is no CPU fallback: without the built library, or without a GPU tensor, the
 calls raise.
+
+The five calls that layers are made of are marshalled in csrc/binding.cpp where their arguments are plain; what it leaves
+(it returns None) goes the way written here, which takes and refuses everything.
 """
 import ctypes
 import os
@@ -22,6 +25,7 @@ EXPORTS = ["brq_init", "brq_block_rotate", "brq_operand_bytes", "brq_mxfp4_quant
            "brq_diag_mxfp4_gemm_on", "brq_strerror", "brq_version"]
 
 _lib = None
+_native = None          # the compiled marshalling, its entry points bound to those of _lib
 
 
 class BrqError(RuntimeError):
@@ -32,11 +36,12 @@ class BrqError(RuntimeError):
 
 def lib():
     """Load libbrq.so (built in-tree by `python -m paper_2511_04214_amd.build`)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
+        if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_binding.so")):
             raise ImportError("libbrq.so is not built: run __graft_entry__.build() "
                               "(python paper_2511_04214_amd/build.py) first")
+        from . import _binding
         L = ctypes.CDLL(LIB_PATH)
         vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
         L.brq_block_rotate.argtypes = [vp, i32, i64, i64, i64, i64, vp, vp, i32, i64, vp]
@@ -79,6 +84,10 @@ def lib():
         L.brq_strerror.argtypes = [i32]
         L.brq_strerror.restype = ctypes.c_char_p
         L.brq_version.restype = i32
+        _binding.bind(*(ctypes.cast(f, vp).value for f in (
+            L.brq_rotate_quantize_fused, L.brq_swiglu_rotate_quantize_fused, L.brq_matrix_rotate_quantize_fused, L.brq_mxfp4_gemm,
+            L.brq_rotate_quantize_gemm_fused)))
+        _native = _binding
         _lib = L
     return _lib
 
@@ -196,6 +205,13 @@ def mxfp4_quantize(x, codes=None, scales=None, stream=None, layout="rowmajor"):
 
 def rotate_quantize_fused(x, B, codes=None, scales=None, stream=None, layout="rowmajor", signs=None):
     """Block rotation fused with MXFP4 quantization (brq_rotate_quantize_fused)."""
+    if codes is not None and stream is None:
+        if _lib is None:
+            lib()
+        st = _native.rotate_quantize(x, B, codes, scales, layout, signs)
+        if st is not None:
+            _check(st)
+            return codes, scales
     M, K, ldx = _rows(x, "x")
     lc = _layout_code(layout)
     codes, scales = _alloc_q(x, M, K, codes, scales, layout)
@@ -224,6 +240,13 @@ def swiglu_rotate_quantize_fused(gate, up, B, h_dtype=torch.float32, codes=None,
     h_dtype: torch.bfloat16 rounds the activation to bf16 before the rotation, torch.float32
     keeps it.  B = 1 quantizes without rotating.
     """
+    if codes is not None and stream is None:
+        if _lib is None:
+            lib()
+        st = _native.swiglu_rotate_quantize(gate, up, B, h_dtype, codes, scales, layout, signs)
+        if st is not None:
+            _check(st)
+            return codes, scales
     M, K, ldg = _rows(gate, "gate")
     M2, K2, ldu = _rows(up, "up")
     if (M, K) != (M2, K2) or gate.dtype != up.dtype:
@@ -263,6 +286,13 @@ def matrix_rotate(x, R, out_dtype=torch.float32, out=None, stream=None):
 
 def matrix_rotate_quantize_fused(x, R, codes=None, scales=None, stream=None, layout="rowmajor"):
     """Rotation by caller-supplied blocks fused with MXFP4 quantization (brq_matrix_rotate_quantize_fused)."""
+    if codes is not None and stream is None:
+        if _lib is None:
+            lib()
+        st = _native.matrix_rotate_quantize(x, R, codes, scales, layout)
+        if st is not None:
+            _check(st)
+            return codes, scales
     M, K, ldx = _rows(x, "x")
     R, nR = _blocks(R, K)
     lc = _layout_code(layout)
@@ -368,6 +398,14 @@ def mxfp4_gemm(aq, as_, wq, ws, out_dtype=torch.float32, out=None, stream=None, 
     `no_loads` (with `clock`; brq_diag_mxfp4_gemm_no_loads) runs the measurement variant without refill
     loads instead: `out` is written with values without meaning.
     """
+    if stream is None and clock is None and not no_loads:
+        if _lib is None:
+            lib()
+        y = _native.gemm(aq, as_, wq, ws, out_dtype, out, a_layout, w_layout, M, N, K)
+        if y is not None:
+            if type(y) is int:
+                _check(y)
+            return y
     for t, n in ((aq, "aq"), (as_, "as"), (wq, "wq"), (ws, "ws")):
         if not (t.is_cuda and t.is_contiguous() and t.dtype == torch.uint8):
             raise ValueError("%s must be a contiguous uint8 GPU tensor" % n)
@@ -404,6 +442,14 @@ def mxfp4_gemm(aq, as_, wq, ws, out_dtype=torch.float32, out=None, stream=None, 
 def rotate_quantize_gemm_fused(x, B, wq, ws, N, out_dtype=torch.float32, out=None, stream=None, w_layout="rowmajor",
                                signs=None):
     """Y = mxfp4_gemm(rotate_quantize_fused(x, B), (wq, ws)) in one launch, M <= 16 (brq_rotate_quantize_gemm_fused)."""
+    if stream is None:
+        if _lib is None:
+            lib()
+        y = _native.rotate_quantize_gemm(x, B, wq, ws, N, out_dtype, out, w_layout, signs)
+        if y is not None:
+            if type(y) is int:
+                _check(y)
+            return y
     M, K, ldx = _rows(x, "x")
     for t, n in ((wq, "wq"), (ws, "ws")):
         if not (t.is_cuda and t.is_contiguous() and t.dtype == torch.uint8):

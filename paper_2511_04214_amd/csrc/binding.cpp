@@ -1,0 +1,305 @@
+// The calls that a layer makes, without the interpreter's share of them: arguments are read from the tensors here, checked
+// as __init__.py checks them, and handed to the C ABI.  With Python and ctypes in between a call cost the host 6 to 9 us, of
+// which the launch is 3: a small layer (16 x 256 x 256, two calls and a result tensor) took 15.0 us, the GPU 6.7.
+//
+// Only what is plainly right is done here: tensors of torch's own type on the GPU with no other dispatch key than that,
+// plain integers, the current stream.  Anything else (a subclass, a traced or batched tensor, an argument that does not
+// fit, buffers that are to be made) returns None, and the caller goes its way through Python, which accepts or refuses it
+// as it always did.  Otherwise a call returns the library's status, 0 or not, or the result tensor.
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <ATen/ops/empty.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/brq.h"
+
+namespace {
+
+// The library's entry points, set by bind() when it is loaded.
+decltype(&brq_rotate_quantize_fused) f_rotate_quantize;
+decltype(&brq_swiglu_rotate_quantize_fused) f_swiglu;
+decltype(&brq_matrix_rotate_quantize_fused) f_matrix;
+decltype(&brq_mxfp4_gemm) f_gemm;
+decltype(&brq_rotate_quantize_gemm_fused) f_decode;
+
+// A tensor of torch's own type, on the GPU, that nothing watches or stands in for: beside the dispatch keys that every such
+// tensor has (autograd's, autocast's) it has the device's alone.
+bool on_gpu(const at::Tensor& t) {
+    return t.defined() && t.key_set() - c10::autograd_dispatch_keyset_with_ADInplaceOrView - c10::autocast_dispatch_keyset ==
+                              c10::DispatchKeySet(c10::DispatchKey::CUDA);
+}
+const at::Tensor* plain(PyObject* o) {
+    if (!THPVariable_CheckExact(o)) return nullptr;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    return on_gpu(t) ? &t : nullptr;
+}
+
+const at::Tensor* bytes(PyObject* o) {
+    const at::Tensor* t = plain(o);
+    return t && t->scalar_type() == at::kByte && t->is_contiguous() ? t : nullptr;
+}
+
+bool dtype_of(at::ScalarType s, brq_dtype* d) {
+    *d = s == at::kFloat ? BRQ_F32 : BRQ_BF16;
+    return s == at::kFloat || s == at::kBFloat16;
+}
+
+bool dtype_arg(PyObject* o, at::ScalarType* s, brq_dtype* d) {
+    if (!THPDtype_Check(o)) return false;
+    *s = reinterpret_cast<THPDtype*>(o)->scalar_type;
+    return dtype_of(*s, d);
+}
+
+// A matrix with contiguous rows.
+struct Rows {
+    const at::Tensor* t;
+    int64_t M, K, ld;
+    brq_dtype dt;
+};
+bool rows(PyObject* o, Rows* r) {
+    r->t = plain(o);
+    if (!r->t || r->t->dim() != 2 || !dtype_of(r->t->scalar_type(), &r->dt)) return false;
+    r->M = r->t->size(0);
+    r->K = r->t->size(1);
+    if (r->K > 1 && r->t->stride(1) != 1) return false;
+    r->ld = r->M > 1 ? r->t->stride(0) : r->K;
+    return true;
+}
+
+bool integer(PyObject* o, int64_t* v) {
+    if (!PyLong_CheckExact(o)) return false;
+    int overflow = 0;
+    *v = PyLong_AsLongLongAndOverflow(o, &overflow);
+    return overflow == 0;
+}
+
+PyObject *s_rowmajor, *s_tiled;
+bool layout(PyObject* o, brq_layout* l) {
+    if (!PyUnicode_CheckExact(o)) return false;
+    const bool rm = o == s_rowmajor || PyUnicode_Compare(o, s_rowmajor) == 0;
+    *l = rm ? BRQ_LAYOUT_ROWMAJOR : BRQ_LAYOUT_TILED;
+    return rm || o == s_tiled || PyUnicode_Compare(o, s_tiled) == 0;
+}
+
+// Bytes of a quantized [rows][K] operand; sizes that are no operand's are left to Python.
+bool operand_size(int64_t n, int64_t K, brq_layout l, int64_t* codes, int64_t* scales) {
+    if (n < 0 || K <= 0 || K % 32 != 0 || n >= int64_t(1) << 31 || K >= int64_t(1) << 31) return false;
+    if (l == BRQ_LAYOUT_TILED) {
+        n = (n + 63) / 64 * 64;
+        K = (K + 511) / 512 * 512;
+    }
+    *codes = n * (K / 2);
+    *scales = n * (K / 32);
+    return true;
+}
+
+bool signs_arg(PyObject* o, int64_t K, const int8_t** p) {
+    *p = nullptr;
+    if (o == Py_None) return true;
+    const at::Tensor* t = plain(o);
+    if (!t || !t->is_contiguous() || t->scalar_type() != at::kChar || t->numel() != K) return false;
+    *p = static_cast<const int8_t*>(t->const_data_ptr());
+    return true;
+}
+
+// Buffers that a quantizing call fills.
+bool buffers(PyObject* c, PyObject* s, int64_t M, int64_t K, brq_layout l, uint8_t** codes, uint8_t** scales) {
+    int64_t nc, ns;
+    const at::Tensor *tc = bytes(c), *ts = bytes(s);
+    if (!tc || !ts || !operand_size(M, K, l, &nc, &ns) || tc->numel() < nc || ts->numel() < ns) return false;
+    *codes = static_cast<uint8_t*>(tc->data_ptr());
+    *scales = static_cast<uint8_t*>(ts->data_ptr());
+    return true;
+}
+
+// An operand of a product: codes and scales, `n` rows of K (either may be -1: not given; a row-major operand says).
+bool operand(PyObject* c, PyObject* s, brq_layout l, int64_t* n, int64_t* K, const uint8_t** codes, const uint8_t** scales) {
+    const at::Tensor *tc = bytes(c), *ts = bytes(s);
+    if (!tc || !ts) return false;
+    if (l == BRQ_LAYOUT_ROWMAJOR) {
+        if (tc->dim() != 2 || (*n >= 0 && *n != tc->size(0)) || (*K >= 0 && *K != tc->size(1) * 2)) return false;
+        *n = tc->size(0);
+        *K = tc->size(1) * 2;
+        if (ts->dim() != 2 || ts->size(0) != *n || ts->size(1) != *K / 32) return false;
+    }
+    *codes = static_cast<const uint8_t*>(tc->const_data_ptr());
+    *scales = static_cast<const uint8_t*>(ts->const_data_ptr());
+    return true;
+}
+bool operand_fits(PyObject* c, PyObject* s, brq_layout l, int64_t n, int64_t K) {
+    int64_t nc, ns;
+    return operand_size(n, K, l, &nc, &ns) && THPVariable_Unpack(c).numel() >= nc && THPVariable_Unpack(s).numel() >= ns;
+}
+
+// None or a size
+bool size_arg(PyObject* o, int64_t* v) {
+    *v = -1;
+    return o == Py_None || (integer(o, v) && *v >= 0);
+}
+
+// The product's result: `out`, or a new tensor on the device of `like`.
+bool result(PyObject* out, PyObject* dtype, const at::Tensor& like, int64_t M, int64_t N, at::Tensor* y, brq_dtype* dt, int64_t* ldy) {
+    if (out != Py_None) {
+        Rows r;
+        if (!rows(out, &r) || r.M != M || r.K != N) return false;
+        *y = *r.t;
+        *dt = r.dt;
+        *ldy = r.ld;
+        return true;
+    }
+    at::ScalarType s;
+    if (!dtype_arg(dtype, &s, dt)) return false;
+    *y = at::empty({M, N}, at::TensorOptions().dtype(s).device(like.device()));
+    *ldy = N;
+    return on_gpu(*y);
+}
+
+void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+
+// Nobody looks at what is done with tensors from outside (a function mode sees every look at a shape).
+bool quiet() { return !at::impl::torch_function_mode_enabled(); }
+
+template <class F>
+brq_status released(F call) {
+    brq_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = call();
+    Py_END_ALLOW_THREADS
+    return st;
+}
+
+PyObject* status(brq_status st) { return PyLong_FromLong((long)st); }
+PyObject* result_or(brq_status st, PyObject* out, at::Tensor& y) {
+    if (st != BRQ_OK) return status(st);
+    if (out == Py_None) return THPVariable_Wrap(std::move(y));
+    Py_INCREF(out);
+    return out;
+}
+
+// rotate_quantize(x, B, codes, scales, layout, signs)
+PyObject* rotate_quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    Rows x;
+    int64_t B;
+    brq_layout l;
+    const int8_t* signs;
+    uint8_t *codes, *scales;
+    if (n != 6 || !f_rotate_quantize || !quiet() || !rows(a[0], &x) || !integer(a[1], &B) || !layout(a[4], &l) || !buffers(a[2], a[3], x.M, x.K, l, &codes, &scales) ||
+        !signs_arg(a[5], x.K, &signs)) Py_RETURN_NONE;
+    const void* p = x.t->const_data_ptr();
+    void* s = current_stream();
+    return status(released([&] { return f_rotate_quantize(p, x.dt, x.M, x.K, x.ld, B, signs, codes, scales, l, s); }));
+    END_HANDLE_TH_ERRORS
+}
+
+// swiglu_rotate_quantize(gate, up, B, h_dtype, codes, scales, layout, signs)
+PyObject* swiglu_rotate_quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    Rows g, u;
+    int64_t B;
+    brq_layout l;
+    brq_dtype hd;
+    at::ScalarType hs;
+    const int8_t* signs;
+    uint8_t *codes, *scales;
+    if (n != 8 || !f_swiglu || !quiet() || !rows(a[0], &g) || !rows(a[1], &u) || g.M != u.M || g.K != u.K || g.dt != u.dt || !integer(a[2], &B) ||
+        !dtype_arg(a[3], &hs, &hd) || !layout(a[6], &l) || !buffers(a[4], a[5], g.M, g.K, l, &codes, &scales) ||
+        !signs_arg(a[7], g.K, &signs)) Py_RETURN_NONE;
+    const void *pg = g.t->const_data_ptr(), *pu = u.t->const_data_ptr();
+    void* s = current_stream();
+    return status(released([&] { return f_swiglu(pg, pu, g.dt, g.M, g.K, g.ld, u.ld, hd, B, signs, codes, scales, l, s); }));
+    END_HANDLE_TH_ERRORS
+}
+
+// matrix_rotate_quantize(x, R, codes, scales, layout)
+PyObject* matrix_rotate_quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    Rows x;
+    brq_layout l;
+    uint8_t *codes, *scales;
+    const at::Tensor* R = n == 5 && f_matrix && quiet() ? plain(a[1]) : nullptr;
+    if (!R || !R->is_contiguous() || R->scalar_type() != at::kFloat || R->dim() < 2 || R->dim() > 3 || R->size(-1) != 32 || R->size(-2) != 32 ||
+        !rows(a[0], &x) || !layout(a[4], &l) || !buffers(a[2], a[3], x.M, x.K, l, &codes, &scales)) Py_RETURN_NONE;
+    const int64_t nR = R->dim() == 3 ? R->size(0) : 1;
+    const void* p = x.t->const_data_ptr();
+    const float* r = static_cast<const float*>(R->const_data_ptr());
+    void* s = current_stream();
+    return status(released([&] { return f_matrix(p, x.dt, x.M, x.K, x.ld, r, nR, codes, scales, l, s); }));
+    END_HANDLE_TH_ERRORS
+}
+
+// gemm(aq, as, wq, ws, out_dtype, out, a_layout, w_layout, M, N, K)
+PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    brq_layout la, lw;
+    int64_t M, N, K, ldy;
+    const uint8_t *ac, *as, *wc, *ws;
+    at::Tensor y;
+    brq_dtype dt;
+    if (n != 11 || !f_gemm || !quiet() || !layout(a[6], &la) || !layout(a[7], &lw) || !size_arg(a[8], &M) || !size_arg(a[9], &N) || !size_arg(a[10], &K) ||
+        !operand(a[0], a[1], la, &M, &K, &ac, &as) || !operand(a[2], a[3], lw, &N, &K, &wc, &ws) || M < 0 || N < 0 || K < 0 ||
+        !operand_fits(a[0], a[1], la, M, K) || !operand_fits(a[2], a[3], lw, N, K) ||
+        !result(a[5], a[4], THPVariable_Unpack(a[0]), M, N, &y, &dt, &ldy)) Py_RETURN_NONE;
+    void *p = y.data_ptr(), *s = current_stream();
+    return result_or(released([&] { return f_gemm(ac, as, la, wc, ws, lw, M, N, K, p, dt, ldy, s); }), a[5], y);
+    END_HANDLE_TH_ERRORS
+}
+
+// rotate_quantize_gemm(x, B, wq, ws, N, out_dtype, out, w_layout, signs)
+PyObject* rotate_quantize_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    Rows x;
+    brq_layout l;
+    int64_t B, N, ldy;
+    const int8_t* signs;
+    at::Tensor y;
+    brq_dtype dt;
+    if (n != 9 || !f_decode || !quiet() || !rows(a[0], &x) || !integer(a[1], &B) || !bytes(a[2]) || !bytes(a[3]) || !integer(a[4], &N) || !layout(a[7], &l) ||
+        !signs_arg(a[8], x.K, &signs) || !operand_fits(a[2], a[3], l, N, x.K) || !result(a[6], a[5], *x.t, x.M, N, &y, &dt, &ldy)) Py_RETURN_NONE;
+    const void* p = x.t->const_data_ptr();
+    const uint8_t *wc = static_cast<const uint8_t*>(THPVariable_Unpack(a[2]).const_data_ptr()), *ws = static_cast<const uint8_t*>(THPVariable_Unpack(a[3]).const_data_ptr());
+    void *q = y.data_ptr(), *s = current_stream();
+    return result_or(released([&] { return f_decode(p, x.dt, x.M, x.K, x.ld, B, signs, wc, ws, l, N, q, dt, ldy, s); }), a[6], y);
+    END_HANDLE_TH_ERRORS
+}
+
+// bind(addresses of the entry points, in the order above)
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    void* p[5];
+    if (n != 5) {
+        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of five entry points");
+        return nullptr;
+    }
+    for (int i = 0; i < 5; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[i]);
+        if (!p[i]) {
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point's address is NULL");
+            return nullptr;
+        }
+    }
+    f_rotate_quantize = reinterpret_cast<decltype(f_rotate_quantize)>(p[0]);
+    f_swiglu = reinterpret_cast<decltype(f_swiglu)>(p[1]);
+    f_matrix = reinterpret_cast<decltype(f_matrix)>(p[2]);
+    f_gemm = reinterpret_cast<decltype(f_gemm)>(p[3]);
+    f_decode = reinterpret_cast<decltype(f_decode)>(p[4]);
+    Py_RETURN_NONE;
+}
+
+#define BRQ_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {BRQ_METHOD(bind), BRQ_METHOD(rotate_quantize), BRQ_METHOD(swiglu_rotate_quantize), BRQ_METHOD(matrix_rotate_quantize),
+                         BRQ_METHOD(gemm), BRQ_METHOD(rotate_quantize_gemm), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__binding() {
+    s_rowmajor = PyUnicode_InternFromString("rowmajor");
+    s_tiled = PyUnicode_InternFromString("tiled");
+    if (!s_rowmajor || !s_tiled) return nullptr;
+    return PyModule_Create(&module);
+}

@@ -1,0 +1,113 @@
+"""The compiled marshalling of the binding takes what is plainly right and leaves everything else to Python: either way
+the results, and what is refused, are the same."""
+import pytest
+import torch
+
+import paper_2511_04214_amd as brq
+
+BF16, F32 = torch.bfloat16, torch.float32
+
+
+class Named(torch.Tensor):
+    pass
+
+
+def test_leaves_to_python_what_is_not_on_a_gpu():
+    brq.lib()
+    n, x, c = brq._native, torch.zeros((4, 512)), torch.zeros(4096, dtype=torch.uint8)
+    assert n.rotate_quantize(x, 32, c, c, "tiled", None) is None
+    assert n.swiglu_rotate_quantize(x, x, 32, F32, c, c, "tiled", None) is None
+    assert n.matrix_rotate_quantize(x, torch.eye(32), c, c, "tiled") is None
+    assert n.gemm(c, c, c, c, F32, None, "tiled", "tiled", 4, 4, 512) is None
+    assert n.rotate_quantize_gemm(x, 32, c, c, 4, F32, None, "tiled", None) is None
+    for f in (n.rotate_quantize, n.swiglu_rotate_quantize, n.matrix_rotate_quantize, n.gemm, n.rotate_quantize_gemm):
+        assert f() is None and f(None) is None
+    with pytest.raises(TypeError):
+        n.bind(1)
+    with pytest.raises(ValueError):
+        n.bind(0, 0, 0, 0, 0)
+    with pytest.raises(ValueError, match="GPU tensor"):
+        brq.rotate_quantize_fused(x, 32, codes=c, scales=c, layout="tiled")
+
+
+def bufs(M, K, layout):
+    nc, ns = brq.operand_bytes(M, K, layout)
+    shapes = ((M, K // 2), (M, K // 32)) if layout == "rowmajor" else ((nc,), (ns,))
+    return [torch.zeros(s, dtype=torch.uint8, device="cuda") for s in shapes]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", ["rowmajor", "tiled"])
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_both_ways_agree(layout, dtype):
+    """A Stream argument takes the way through Python."""
+    s = torch.cuda.current_stream()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    M, N, K = 5, 130, 512
+    x = torch.randn((M, 2 * K), generator=g, device="cuda").to(dtype)
+    signs = (torch.randint(0, 2, (K,), generator=g, device="cuda") * 2 - 1).to(torch.int8)
+    R = torch.linalg.qr(torch.randn((K // 32, 32, 32), generator=g, device="cuda"))[0].contiguous()
+    gate, up = x[:, :K], x[:, K:]
+    w = brq.rotate_quantize_fused(torch.randn((N, K), generator=g, device="cuda"), 32, layout=layout)
+    n = brq._native
+    a, b = bufs(M, K, layout), bufs(M, K, layout)
+    for native, call in (
+            (lambda c: n.rotate_quantize(gate, 32, *c, layout, signs), lambda c, **k: brq.rotate_quantize_fused(gate, 32, *c, layout=layout, signs=signs, **k)),
+            (lambda c: n.swiglu_rotate_quantize(gate, up, 64, BF16, *c, layout, None), lambda c, **k: brq.swiglu_rotate_quantize_fused(gate, up, 64, BF16, *c, layout=layout, **k)),
+            (lambda c: n.matrix_rotate_quantize(gate, R, *c, layout), lambda c, **k: brq.matrix_rotate_quantize_fused(gate, R, *c, layout=layout, **k)),
+            (lambda c: n.matrix_rotate_quantize(gate, R[0], *c, layout), lambda c, **k: brq.matrix_rotate_quantize_fused(gate, R[0], *c, layout=layout, **k))):
+        for t in a + b:
+            t.fill_(9)
+        assert native(a) == 0
+        got = call(b, stream=s)
+        assert got[0] is b[0] and got[1] is b[1] and all(torch.equal(p, q) for p, q in zip(a, b))
+        got = call(a)
+        assert got[0] is a[0] and got[1] is a[1] and all(torch.equal(p, q) for p, q in zip(a, b))
+    sizes = dict(M=M, N=N, K=K) if layout == "tiled" else {}
+    for out_dtype in (F32, BF16):
+        y = n.gemm(*a, *w, out_dtype, None, layout, layout, *(sizes.get(k) for k in "MNK"))
+        want = brq.mxfp4_gemm(*a, *w, out_dtype=out_dtype, a_layout=layout, w_layout=layout, stream=s, **sizes)
+        assert y.dtype == out_dtype and y.device == want.device and not y.requires_grad and torch.equal(y, want)
+        out = torch.zeros((M, N + 6), dtype=out_dtype, device="cuda")[:, :N]
+        assert brq.mxfp4_gemm(*a, *w, out=out, a_layout=layout, w_layout=layout, **sizes) is out and torch.equal(out, want)
+        z = n.rotate_quantize_gemm(gate, 32, *w, N, out_dtype, None, layout, None)
+        assert torch.equal(z, brq.rotate_quantize_gemm_fused(gate, 32, *w, N, out_dtype=out_dtype, w_layout=layout, stream=s))
+
+
+@pytest.mark.gpu
+def test_what_is_refused_stays_refused():
+    M, N, K = 4, 64, 512
+    x = torch.randn((M, K), device="cuda")
+    c, s = bufs(M, K, "rowmajor")
+    w = brq.rotate_quantize_fused(torch.randn((N, K), device="cuda"), 32)
+    q = brq.rotate_quantize_fused
+    for error, call in (
+            (ValueError, lambda: q(x.t(), 32, c, s)), (ValueError, lambda: q(x, 32, c[:2], s)), (ValueError, lambda: q(x, 32, c.to(torch.int8), s)),
+            (TypeError, lambda: q(x.half(), 32, c, s)), (ValueError, lambda: q(x, 32, c, s, layout="columns")),
+            (ValueError, lambda: q(x, 32, c, s, signs=torch.ones(K, device="cuda"))),
+            (ValueError, lambda: brq.mxfp4_gemm(c, s, *w, M=M + 1)), (ValueError, lambda: brq.mxfp4_gemm(c, s[:, :-1].contiguous(), *w)),
+            (ValueError, lambda: brq.mxfp4_gemm(c, s, w[0].flatten(), w[1].flatten())), (TypeError, lambda: brq.mxfp4_gemm(c, s, *w, out_dtype=torch.float16)),
+            (ValueError, lambda: brq.mxfp4_gemm(c, s, *w, out=torch.zeros((M, N + 1), device="cuda"))),
+            (ValueError, lambda: brq.rotate_quantize_gemm_fused(x, 32, w[0][:-1], w[1][:-1], N))):
+        with pytest.raises(error):
+            call()
+    for status, call in ((3, lambda: q(x, 48, c, s)), (4, lambda: q(x.flatten()[1:].as_strided((M - 1, K), (K, 1)), 32, c, s)),
+                         (3, lambda: brq.rotate_quantize_gemm_fused(x, 64, *w, N)), (2, lambda: brq.rotate_quantize_gemm_fused(x.repeat(5, 1), 32, *w, N))):
+        with pytest.raises(brq.BrqError) as e:
+            call()
+        assert e.value.status == status
+    # taken, by the way through Python
+    n = x.as_subclass(Named)
+    assert brq._native.rotate_quantize(n, 32, c, s, "rowmajor", None) is None
+    q(x, 32, c, s)
+    want = c.clone()
+    c.zero_()
+    q(n, 32, c, s)
+    assert torch.equal(c, want)
+    assert brq._native.rotate_quantize(torch.nn.Parameter(x), 32, c, s, "rowmajor", None) == 0
+    assert brq.mxfp4_gemm(c[:0], s[:0], *w).shape == (0, N)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        c.zero_()
+        q(x, 32, c, s)
+        torch.cuda.current_stream().synchronize()
+    assert torch.equal(c, want)
