@@ -503,25 +503,21 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // `alone`: a stage of a tile while the chip is not full (the issue, load and LDS bound of one workgroup, at the
 // full clock); `full`: a stage's share of a chip full of them, which is what its energy costs (the chip holds 1.6
 // to 1.8 GHz of 2.4 with every CU multiplying); places = CUs x workgroups that fit one; filled: rows past M
-// are zeros in the one-tile kernel and cost half; bytes: both operands, from HBM; output: 0.6 us per MB of bf16.  The
-// three bounds blend into each other (4-norm).  The constants are fitted to the candidates' times, weights not in any
-// cache, on 50 tiled and 46 row-major shapes (M 17 .. 8192, N 256 .. 28672, K 512 .. 13312): the choice costs 1.0 % over
-// the best of the seven on average in either layout (22 % and 19 % at worst); the fit to repeated weights that it
-// replaces cost 3.9 % and 5.2 % (34 %, 42 %).  What the estimate gives over 256 x 256, or 128 x 256 where the former do not
-// fill the chip, tiled, us: 300 x 28672 x 8192 61 -> 45; 1000 x 4096 x 11008 41 -> 30; 200 x 512 x 4096 12.7 -> 8.2.
-// Of 20000 shapes spread evenly in log M (1 .. 16384), log N (64 ..) and log K (512 ..), bf16 out, it takes 64 x 128 / 128 x 128 /
-// 192 x 128 / 192 x 256 / 320 x 128 / 128 x 256 / 256 x 256, in percent: row-major 69 / 8 / 3 / 2 / 6 / 0 / 7 (the streaming kernel 5),
-// tiled 45 / 16 / 0 / 0.1 / 2 / 1.5 / 6 (29): 192 x 128 and 192 x 256 are there for row-major operands, 128 x 256 for tiled ones.
-struct TileCost { float fixed, alone, full, store; };
-struct Tile { int na, mb, per_cu, route; TileCost tiled, rowmajor; };    // 64 mb x 64 na
+// are zeros in the one-tile kernel and cost half; bytes: both operands, from HBM; output: 0.6 us per MB of bf16, by
+// whether its rows begin on 128-byte lines.  The three bounds blend into each other (4-norm).  The constants are fitted to
+// the candidates' times, weights not in any cache, on 147 tiled and 160 row-major shapes (M 10 .. 8192, N 256 .. 28672 in
+// eights, K 512 .. 13824): the choice costs 0.9 % over the best of the seven on average, row-major 0.5 % (15 % and 27 % at
+// worst); the fit to the kernels before them (row-major stages by themselves, every row stored past the L2) cost 4 % (67 %).
+struct TileCost { float fixed, alone, full, store, store_off; int per_cu; };    // store_off: rows off lines
+struct Tile { int na, mb, route; TileCost tiled, rowmajor; };                   // 64 mb x 64 na
 static const Tile TILES[2 + MID_TILES] = {
-    {4, 4, 1, ROUTE_256x256, {6.293f, 0.532f, 0.707f, 0.638f}, {6.786f, 0.666f, 0.844f, 0.744f}},
-    {4, 2, 1, ROUTE_128x256, {5.092f, 0.299f, 0.380f, 0.762f}, {4.800f, 0.401f, 0.719f, 0.706f}},
-    {2, 1, 2, ROUTE_ONE_TILE, {3.558f, 0.147f, 0.240f, 0.515f}, {2.661f, 0.269f, 0.301f, 0.723f}},
-    {2, 2, 2, ROUTE_ONE_TILE + 1, {3.816f, 0.226f, 0.254f, 0.464f}, {2.665f, 0.325f, 0.468f, 0.638f}},
-    {2, 3, 1, ROUTE_ONE_TILE + 2, {5.479f, 0.238f, 0.373f, 0.906f}, {4.662f, 0.335f, 0.426f, 1.157f}},
-    {4, 3, 1, ROUTE_ONE_TILE + 3, {5.916f, 0.376f, 0.741f, 0.601f}, {4.888f, 0.511f, 0.636f, 1.111f}},
-    {2, 5, 1, ROUTE_ONE_TILE + 4, {7.720f, 0.308f, 0.461f, 0.872f}, {7.159f, 0.402f, 0.548f, 0.792f}},
+    {4, 4, ROUTE_256x256, {5.984f, 0.535f, 0.758f, 0.292f, 0.481f, 1}, {6.801f, 0.508f, 0.978f, 0.439f, 0.893f, 1}},
+    {4, 2, ROUTE_128x256, {3.696f, 0.280f, 0.474f, 0.377f, 0.649f, 1}, {3.535f, 0.514f, 0.682f, 0.402f, 0.724f, 1}},
+    {2, 1, ROUTE_ONE_TILE, {3.141f, 0.178f, 0.205f, 0.406f, 0.923f, 2}, {3.749f, 0.196f, 0.264f, 0.512f, 0.585f, 2}},
+    {2, 2, ROUTE_ONE_TILE + 1, {3.731f, 0.206f, 0.292f, 0.348f, 0.560f, 2}, {3.585f, 0.261f, 0.356f, 0.889f, 1.014f, 1}},
+    {2, 3, ROUTE_ONE_TILE + 2, {4.774f, 0.268f, 0.313f, 0.568f, 1.091f, 1}, {5.290f, 0.268f, 0.433f, 0.736f, 1.070f, 1}},
+    {4, 3, ROUTE_ONE_TILE + 3, {6.545f, 0.397f, 0.552f, 0.422f, 0.864f, 1}, {5.012f, 0.522f, 0.751f, 0.529f, 1.038f, 1}},
+    {2, 5, ROUTE_ONE_TILE + 4, {6.659f, 0.363f, 0.494f, 0.545f, 0.950f, 1}, {6.735f, 0.399f, 0.639f, 0.624f, 0.976f, 1}},
 };
 
 // The cheapest of the LDS-staged kernels that take the shape, or -1.
@@ -529,6 +525,7 @@ static int pick_tile(const GemmShape& g, int cus) {
     const bool tiled = g.a_tiled && g.w_tiled;
     const float stages = (float)((g.K + 511) / 512 * 4), output = 0.6e-6f * (float)g.M * (float)g.N * (g.out_bf16 ? 1.0f : 2.0f);
     const float bytes = 0.53125f * ((float)g.M + (float)g.N) * (float)g.K / 5.0e6f;
+    const bool lines = g.N * (g.out_bf16 ? 2 : 4) % 16 == 0 && g.ldy * (g.out_bf16 ? 2 : 4) % 128 == 0;
     auto pow4 = [](float x) { return x * x * x * x; };
     int best = -1;
     float least = 0.0f;
@@ -537,11 +534,11 @@ static int pick_tile(const GemmShape& g, int cus) {
         if (!gemm_route_supported(t.route, g)) continue;
         const bool one_tile = t.route >= ROUTE_ONE_TILE;
         const TileCost& c = tiled ? t.tiled : t.rowmajor;
-        const int64_t tm = (g.M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((g.N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * t.per_cu;
+        const int64_t tm = (g.M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((g.N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * c.per_cu;
         const float filled = one_tile ? 0.5f + 0.5f * (float)g.M / (float)(64 * t.mb * tm) : 1.0f;
         const float alone = stages * c.alone * (float)((T + places - 1) / places);
         const float full = stages * c.full * (float)T / (float)cus * filled;
-        const float cost = c.fixed + sqrtf(sqrtf(pow4(alone) + pow4(full) + pow4(bytes))) + c.store * output;
+        const float cost = c.fixed + sqrtf(sqrtf(pow4(alone) + pow4(full) + pow4(bytes))) + (lines ? c.store : c.store_off) * output;
         if (best < 0 || cost < least) { best = t.route; least = cost; }
     }
     return best;
