@@ -468,8 +468,9 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
 // (One wavefront with 16 chunks a lane leaves room for 3 per SIMD and spills.)
 // Through LDS altogether (two trips for the stages h >= 512, the stages h = 32 .. 256 through its swizzle) the block
 // cost 34 LDS operations per 8 values of a lane and was bound by them; now it is bound by the vector units (about 20
-// instructions per value of a lane at B = 8192, 18 of the 26 us on 4096 x 8192).  A row's 128-byte lines of tiled codes (two rows each) are left to two wavefronts: the L2
-// merges their halves (plain stores).
+// instructions per value of a lane at B = 8192, 18 of the 26 us on 4096 x 8192).  A row's 128-byte lines of tiled codes (two rows each) are left to two wavefronts: no
+// streaming hint (3000 x 8192, B = 2048, with the product behind it 39 us instead of 36); from 256 KB of codes on at device scope
+// (store_codes; 4096 x 8192 B = 8192 with its product 57.6 -> 56.8), below that plain stores (1 x 8192: 0.4 us less).
 // Quantizing X bf16, tiled codes, before -> after, us: 4096 x 8192 B = 1024 / 2048 / 4096 / 8192 30 / 31 / 28 / 31 ->
 // 25 / 23 / 24 / 26; 16384 x 8192 101 / 102 / 102 / 108 -> 78 / 77 / 76 / 83.
 constexpr int reg_waves(int log2b) { return log2b == 13 ? 2 : 1; }              // wavefronts per block
@@ -598,7 +599,9 @@ __global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_ro
             } else {
                 const uint32_t sb = e8m0_from_amax(quad_max(absmax8(v[j])));
                 const uint32_t w = encode8_e2m1(v[j], sb);
-                store_codes(reinterpret_cast<uint32_t*>(cd + piece(j) * cstep), w, 1u);
+                uint32_t* const c = reinterpret_cast<uint32_t*>(cd + piece(j) * cstep);
+                if (a.through) store_codes(c, w, 1u);                           // uniform
+                else *c = w;
                 if ((lane & 3u) == 0) sd[piece(j) * sstep] = (uint8_t)sb;
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -706,6 +709,15 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
 
 // ---- host side ---------------------------------------------------------------------
 
+// Whether codes are stored through the L2 (store_codes).  Online step and product together, us, streaming hint -> through:
+// row-major 256 x 4096 x 4096 16.2 -> 13.9, 1000 x 4096 x 11008 49.1 -> 43.6, 2000 x 4096 x 11008 79.2 -> 69.4, 4096 x 4096 x 4096
+// 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands, whose product reads
+// whole pages of them, gain less, and with a few MB of codes lose as often: 512 x 4096 x 4096 15.6 -> 13.4, but 971 x 4096 x 2048
+// 12.9 -> 14.4; from 16 MB on the quantizer itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x 8192 as before).
+static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
+    return M * (K / 2) >= (int64_t(1) << (tiled ? 24 : 18));
+}
+
 // Workgroups per compute unit of a statistics launch (each ends with up to 8 atomics on the caller's counters): of 512
 // threads for k_rowwise, of up to 256 for k_rowwise_lds and k_rowwise_reg.  X 16384 x 8192, two thresholds, B = 1 / 32, us: 3 x 512 threads
 // 57.8 / 63.9; 2 x 512 with two chunks a pass 60.9 / 72.6; 2 x 768 57.8 / 64.6; 2 x 1024 56.2 / 73.6; 8 x 256 68.7 / 74.5.
@@ -796,6 +808,8 @@ static hipError_t launch_lds(const RowArgs& a, int64_t M, int64_t K, hipStream_t
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD = false>
 static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t s) {
     const uint32_t bpr = (uint32_t)(K >> LOG2B), nblocks = (uint32_t)M * bpr;
+    RowArgs b = a;
+    b.through = code_stores_through(false, M, K) ? 1u : 0u;
     constexpr int NT = reg_threads(LOG2B);
     constexpr uint32_t per_wg = NT / 64 / reg_waves(LOG2B);
     uint32_t grid = (nblocks + per_wg - 1u) / per_wg;
@@ -805,7 +819,7 @@ static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t
         const uint32_t cap = (uint32_t)cus * (uint32_t)STATS_LDS_WGS_PER_CU;
         if (grid > cap) grid = cap;
     }
-    hipLaunchKernelGGL((k_rowwise_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>), dim3(grid), dim3(NT), 0, s, a, bpr, nblocks);
+    hipLaunchKernelGGL((k_rowwise_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>), dim3(grid), dim3(NT), 0, s, b, bpr, nblocks);
     return hipGetLastError();
 }
 
@@ -835,15 +849,6 @@ static hipError_t dispatch_b(int log2b, const RowArgs& a, bool contig, int64_t M
         case 14: return launch_lds<14, IN_BF16, MODE, OUT_BF16, PROD>(a, M, K, s);
         default: return hipErrorInvalidValue;
     }
-}
-
-// Whether codes are stored through the L2 (store_codes).  Online step and product together, us, streaming hint -> through:
-// row-major 256 x 4096 x 4096 16.2 -> 13.9, 1000 x 4096 x 11008 49.1 -> 43.6, 2000 x 4096 x 11008 79.2 -> 69.4, 4096 x 4096 x 4096
-// 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands, whose product reads
-// whole pages of them, gain less, and with a few MB of codes lose as often: 512 x 4096 x 4096 15.6 -> 13.4, but 971 x 4096 x 2048
-// 12.9 -> 14.4; from 16 MB on the quantizer itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x 8192 as before).
-static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
-    return M * (K / 2) >= (int64_t(1) << (tiled ? 24 : 18));
 }
 
 // mode: RowMode; log2b: 0 for MODE_QUANT, else 3..14.  Arguments are already validated.
