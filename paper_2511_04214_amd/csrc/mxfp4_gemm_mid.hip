@@ -41,7 +41,8 @@
 // with 6 stages each instead of 4: 200 x 4096 x 4096 11.2 -> 9.7 us, 300 x 28672 x 8192 75 -> 68.  The other tiles gain nothing
 // from depth (128 x 128 with 8 stages and one workgroup a CU instead of 4 and two: 58 -> 65 us on the latter); 320 x 128, for a
 // few hundred rows, has 5 and reads its weights once: 47.6 -> 44.8 us on the latter.  Pairs: 4 stages of both wait for
-// every load (128 x 128: 1082 cycles a stage, 6 of both 705, 8 the same); 64 x 128 with 6 and 4, 45.1, 6 and 6, 47.0 us.
+// every load (128 x 128: 1082 cycles a stage, 6 of both 705, 8 the same); 64 x 128 with 6 and 4 instead of 6 of both, 1000 x 4096 x
+// 11008 45.1 us against 47.0, but 1 x 936 x 8192 13.4 against 12.9, 200 x 4096 x 4096 12.0 against 11.8: it is for the small shapes.
 #include "mfma_fp4.h"
 #include "brq_launch.h"
 
@@ -418,7 +419,7 @@ struct Variant { int na, mb, dw, da; Kern bf16, f32; };
 #define BRQ_MID(NA, MB, DW, DA, PAIR) {NA, MB, DW, DA, k_gemm_mid<true, NA, MB, DW, DA, PAIR>, k_gemm_mid<false, NA, MB, DW, DA, PAIR>}
 static const Variant singles[MID_TILES] = {BRQ_MID(2, 1, 6, 6, false), BRQ_MID(2, 2, 4, 4, false), BRQ_MID(2, 3, 4, 4, false),
                                            BRQ_MID(4, 3, 4, 4, false), BRQ_MID(2, 5, 5, 5, false)};
-static const Variant pairs[MID_TILES] = {BRQ_MID(2, 1, 6, 4, true), BRQ_MID(2, 2, 6, 6, true), BRQ_MID(2, 3, 6, 6, true),
+static const Variant pairs[MID_TILES] = {BRQ_MID(2, 1, 6, 6, true), BRQ_MID(2, 2, 6, 6, true), BRQ_MID(2, 3, 6, 6, true),
                                          BRQ_MID(4, 3, 4, 4, true), BRQ_MID(2, 5, 6, 4, true)};
 #undef BRQ_MID
 static const Variant& variant(int tile, bool both_tiled) { return both_tiled ? singles[tile] : pairs[tile]; }
