@@ -129,39 +129,40 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 // ---- M <= 16 (decode batches): weight streaming with the activations in LDS ----------------
 // HBM-bound: every weight byte is read exactly once.  A wavefront owns its weight rows for the whole
 // of K (no cross-wavefront reduction, fixed summation order) and streams them through registers,
-// three 512-element superstages in rotation.  Every wavefront would re-read all of A, so the 4 wavefronts of a
-// workgroup share the activations: one superstage of A at a time goes into LDS by LDS-DMA (three
+// SETS 512-element superstages in rotation.  Every wavefront would re-read all of A, so the 4 wavefronts of a
+// workgroup share the activations: one superstage of A at a time goes into LDS by LDS-DMA (SETS
 // buffers, one barrier per superstage), wavefront w bringing stage w.  The MFMA is the 32x32x64
-// one, a wavefront per 32 weight rows; rows past M repeat row M - 1.  (More rows than one tile of 32 go to the
+// one, a wavefront per 32 weight rows, of which a workgroup has nw = 1, 2 or 4 (streaming_waves); the wavefronts
+// from nw on bring their share of A and no more.  Rows past M repeat row M - 1.  (More rows than one tile of 32 go to the
 // one-tile kernel: with two to four row tiles a turn waits for the latency of two superstages and multiplies longer
 // than it waits, 28672 x 8192 with 64 / 128 rows 28.9 / 34.7 us against 24.8 / 28.9.)
 // Operand fragments (32x32x64: lane (r, h) = (lane & 31, lane >> 5) supplies 32 consecutive K
 // elements of row r): within a 128-element stage (64 code bytes per row) lane half h owns bytes
 // [32 h, 32 h + 32), MFMA step j of the stage takes bytes 32 h + 16 j, i.e. group 2 h + j of the
 // stage, for both operands and both scales.  A in LDS: [stage][row][64 bytes] with the 16-byte
-// chunks of row i XOR-swizzled by (i >> 2) & 3 (lanes r = 0..31 of one read then spread over all
+// chunks of row i XOR-swizzled by (i >> 2) & 3 (the 16 rows of one read then spread over all
 // banks), scales [tile][64 rows][16 bytes].  Output: lane (r, h) holds D[8 q + 4 h + i][r] for
 // weight row n0 + r, so the 32 lanes of a half store 32 consecutive columns of one output row.
 
-// Weight register sets = LDS buffers of A; SETS - 1 superstages are in flight (4 sets measured no faster).
-constexpr int SMALLM_SETS = 3;
-constexpr int SMALLM_LDS_BYTES = SMALLM_SETS * (8192 + 4096);
+// Weight register sets = LDS buffers of A; SETS - 1 superstages are in flight.
+constexpr int smallm_buf_bytes = 4096 + 4096;
+constexpr int smallm_lds_bytes(int sets) { return sets * smallm_buf_bytes; }
 
 // TAIL = (K / 512) % SETS: the superstages left after the main loop, which takes them SETS at a time in
 // one basic block (no load behind a branch: the compiler's count of the outstanding weight loads is
 // then exact; with early exits inside the loop it falls back to waiting for all of them).
-template <int TAIL>
+template <int SETS, int TAIL>
 __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as,
                                                      int a_tiled, const uint8_t* __restrict__ wq,
                                                      const uint8_t* __restrict__ ws, int w_tiled, int M, int N, int K,
-                                                     void* __restrict__ y, int out_bf16, int64_t ldy) {
+                                                     void* __restrict__ y, int out_bf16, int64_t ldy, int nw) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    constexpr int STG = 2048;                           // one stage of A codes: 32 rows x 64 bytes
-    constexpr int BUF = 4 * STG + 4096;                 // codes [4 stages][32 rows][64], then scales, 1 KB per wavefront
-    constexpr int NA = 3;                               // LDS-DMA instructions per wavefront and superstage
+    constexpr int STG = 1024;                           // one stage of A codes: 16 rows x 64 bytes
+    constexpr int BUF = smallm_buf_bytes;               // codes [4 stages][16 rows][64], then scales, 1 KB per wavefront
+    constexpr int NA = 2;                               // LDS-DMA instructions per wavefront and superstage
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
-    const int n0 = blockIdx.x * 128 + wave * 32;
+    const int n0 = (blockIdx.x * nw + wave) * 32;       // (of the first nw wavefronts)
     const int nss = (K + 511) / 512;                    // tiled operands are zero-padded to whole superstages
     const int64_t Kp = (int64_t)nss * 512;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -177,10 +178,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
         return a_tiled ? (uint32_t)((row >> 6) * (Kp / 512) * 1024 + (row & 63) * 16) : (uint32_t)((int64_t)row * (K / 32));
     };
     // one DMA instruction = 16 rows x 64 bytes; lane i brings chunk (i & 3) ^ ((i >> 4) & 3) of row i >> 2
-    uint32_t voc[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-        voc[j] = row_off_c(16 * j + (lane >> 2)) + (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
+    const uint32_t voc = row_off_c(lane >> 2) + (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
     // ... and one more scale rows into 1 KB of its own: wavefront 0 those of A, the others row M - 1 over and over, which
     // nobody reads (lanes 32..63 repeat lanes 0..31): every wavefront issues the same number of loads, which the
     // counted waits below rely on
@@ -189,8 +187,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     auto dma_a = [&](int ss, uint32_t buf) {
         const uint8_t* cb = uniform_ptr(aq + (int64_t)(4 * ss + wave) * a_cstep);
         const uint32_t lb = lds0 + buf * BUF + (uint32_t)wave * STG;
-        dma16<0>(lb, cb, voc[0]);
-        dma16<1024>(lb, cb, voc[1]);
+        dma16<0>(lb, cb, voc);
         dma16<0>(lds0 + buf * BUF + 4 * STG + (uint32_t)wave * 1024, uniform_ptr(as + (int64_t)ss * a_sstep), vos);
     };
     // a superstage of this lane's weight row: per stage t its two steps (32 bytes at 32 h), and the 16 scale bytes.
@@ -205,11 +202,12 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
         sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(vw.scales + (int64_t)ss * vw.sstep));
     };
     v16f acc = {};
-    const uint32_t sw = (uint32_t)(r >> 2) & 3u;
+    const uint32_t ra = (uint32_t)r & 15u;              // lanes 16..31 of a half repeat rows 0..15: never stored
+    const uint32_t sw = (ra >> 2) & 3u;
     // The 8 steps (stage t, half-step j) of a superstage; the A fragment of step s + 1 is read while step s multiplies.
     auto superstage = [&](uint32_t buf, const v4i (&c)[8], const v4i& sc) {
-        const uint8_t* cb = lds + buf * BUF + r * 64;
-        const v4i asc = *reinterpret_cast<const v4i*>(lds + buf * BUF + 4 * STG + r * 16);
+        const uint8_t* cb = lds + buf * BUF + ra * 64;
+        const v4i asc = *reinterpret_cast<const v4i*>(lds + buf * BUF + 4 * STG + ra * 16);
         v4i af[2];
         auto read_step = [&](int st) -> v4i {
             return *reinterpret_cast<const v4i*>(cb + (st >> 1) * STG + (((uint32_t)(2 * h + (st & 1)) ^ sw) << 4));
@@ -237,7 +235,19 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     // flight across the barrier.  Every turn of the main loop issues its loads, past the end of K those of
     // the last superstage once more (into a free buffer and register set, and out of the L2), so the turns
     // are all alike; the TAIL turns after it issue none.
-    constexpr int SETS = SMALLM_SETS, D = SETS - 1;
+    constexpr int D = SETS - 1;
+    if (wave >= nw) {                                   // uniform: bring a share of A, turn for turn with the others
+        for (int i = 0; i < D; ++i) dma_a(min(i, nss - 1), (uint32_t)i);
+        uint32_t buf = D;                               // where superstage ss + D goes
+        for (int ss = 0; ss < nss - TAIL; ++ss) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((D - 1) * NA) : "memory");
+            dma_a(min(ss + D, nss - 1), buf);
+            buf = buf + 1 == SETS ? 0u : buf + 1;
+        }
+        for (int i = 0; i < TAIL; ++i) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return;
+    }
     v4i c[SETS][8], s4[SETS];
 #pragma unroll
     for (int i = 0; i < D; ++i) {
@@ -271,16 +281,10 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     using Yes = std::true_type;
     using No = std::false_type;
     int ss = 0;
-    for (; ss + SETS <= nss; ss += SETS) {
-        turn(IC<0>{}, IC<D - 1>{}, Yes{}, ss);
-        turn(IC<1>{}, IC<D - 1>{}, Yes{}, ss + 1);
-        turn(IC<2>{}, IC<D - 1>{}, Yes{}, ss + 2);
-        if constexpr (SETS > 3) turn(IC<3 % SETS>{}, IC<D - 1>{}, Yes{}, ss + 3);
-    }
+    for (; ss + SETS <= nss; ss += SETS)
+        static_for([&](auto Kc) __attribute__((always_inline)) { turn(Kc, IC<D - 1>{}, Yes{}, ss + decltype(Kc)::value); }, IC<SETS>{});
     // TAIL superstages are left; the loads of the D - 1 after superstage ss, real or repeated, are in flight
-    if constexpr (TAIL >= 1) turn(IC<0>{}, IC<D - 1>{}, No{}, ss);
-    if constexpr (TAIL >= 2) turn(IC<1>{}, IC<(D >= 2 ? D - 2 : 0)>{}, No{}, ss + 1);
-    if constexpr (TAIL >= 3) turn(IC<2>{}, IC<(D >= 3 ? D - 3 : 0)>{}, No{}, ss + 2);
+    static_for([&](auto Kc) __attribute__((always_inline)) { turn(Kc, IC<D - 1 - decltype(Kc)::value>{}, No{}, ss + decltype(Kc)::value); }, IC<TAIL>{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the repeated loads land before the LDS is released
     const int col = n0 + r;
 #pragma unroll
@@ -297,22 +301,22 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
 // Every workgroup first rotates (B = 32) and quantizes ALL of the activations, M <= 16 rows x K, into LDS -
 // the same arithmetic as the row-wise kernels, a quad of lanes per 32-element group - in the layout the
 // weight-streaming loop reads: codes [stage][16 rows][64 bytes] with the 16-byte chunks of row i XOR-swizzled
-// by (i >> 2) & 3, scales [superstage][16 rows][16 bytes].  Then it streams its 128 weight rows exactly like
+// by (i >> 2) & 3, scales [superstage][16 rows][16 bytes].  Then its first nw wavefronts stream their 32 weight rows each exactly like
 // k_gemm_smallm, without any barrier (the activations never change), so the result is bit
 // for bit that of brq_mxfp4_gemm on the output of brq_rotate_quantize_fused.  The first superstages of
 // weights are requested before the prologue and arrive under it.  What this saves is one small launch; what
-// it costs is that every one of the N / 128 workgroups repeats the quantization of the same activations.
+// it costs is that every one of the N / (32 nw) workgroups repeats the quantization of the same activations.
 constexpr int decode_fused_lds_bytes(int64_t K) { return (int)(K / 128 * 1024 + K / 512 * 256); }
 
-template <bool IN_BF16, int TAIL>
+template <bool IN_BF16, int SETS, int TAIL>
 __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restrict__ x, int64_t ldx, const int8_t* __restrict__ signs,
                                                            const uint8_t* __restrict__ wq, const uint8_t* __restrict__ ws,
                                                            int w_tiled, int M, int N, int K, void* __restrict__ y, int out_bf16,
-                                                           int64_t ldy) {
+                                                           int64_t ldy, int nw) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
-    const int n0 = blockIdx.x * 128 + wave * 32;
+    const int n0 = (blockIdx.x * nw + (wave & (nw - 1))) * 32;      // (from wavefront nw on: another's rows, to no use)
     const int nss = K / 512;
     uint8_t* const scl = lds + (K / 128) * 1024;          // scales behind the codes
     const RowView vw(wq, ws, w_tiled != 0, min(n0 + r, N - 1), K);
@@ -324,7 +328,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
                 c[2 * t + j] = *reinterpret_cast<const v4i*>(vw.codes + (int64_t)(4 * ss + t) * vw.cstep + h * 32 + j * 16);
         sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(vw.scales + (int64_t)ss * vw.sstep));
     };
-    constexpr int SETS = SMALLM_SETS, D = SETS - 1;
+    constexpr int D = SETS - 1;
     v4i c[SETS][8], s4[SETS];
 #pragma unroll
     for (int i = 0; i < D; ++i) load_w(min(i, nss - 1), c[i], s4[i]);
@@ -364,6 +368,12 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
         }
     }
     __syncthreads();
+    if (wave >= nw) {                                     // uniform: here for the prologue
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            asm volatile("" ::"v"(c[i][0]), "v"(c[i][1]), "v"(c[i][2]), "v"(c[i][3]), "v"(c[i][4]), "v"(c[i][5]), "v"(c[i][6]), "v"(c[i][7]), "v"(s4[i]));
+        return;
+    }
 
     v16f acc = {};
     const uint32_t ra = (uint32_t)(r & 15);               // lanes 16..31 of a half repeat rows 0..15: never stored
@@ -398,13 +408,9 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
     using Yes = std::true_type;
     using No = std::false_type;
     int ss = 0;
-    for (; ss + SETS <= nss; ss += SETS) {
-        turn(IC<0>{}, Yes{}, ss);
-        turn(IC<1>{}, Yes{}, ss + 1);
-        turn(IC<2>{}, Yes{}, ss + 2);
-    }
-    if constexpr (TAIL >= 1) turn(IC<0>{}, No{}, ss);
-    if constexpr (TAIL >= 2) turn(IC<1>{}, No{}, ss + 1);
+    for (; ss + SETS <= nss; ss += SETS)
+        static_for([&](auto Kc) __attribute__((always_inline)) { turn(Kc, Yes{}, ss + decltype(Kc)::value); }, IC<SETS>{});
+    static_for([&](auto Kc) __attribute__((always_inline)) { turn(Kc, No{}, ss + decltype(Kc)::value); }, IC<TAIL>{});
     const int col = n0 + r;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -466,18 +472,29 @@ hipError_t launch_mfma_ceiling(const uint8_t* operands, int iters, int workgroup
 }
 
 using SmallmKern = void (*)(const uint8_t*, const uint8_t*, int, const uint8_t*, const uint8_t*, int, int, int, int, void*,
-                            int, int64_t);
-static const SmallmKern smallm_kern[SMALLM_SETS] = {k_gemm_smallm<0>, k_gemm_smallm<1>, k_gemm_smallm<2>};
+                            int, int64_t, int);
+constexpr int FEW = 3, MANY = 5;      // register sets
+static const SmallmKern smallm_few[FEW] = {k_gemm_smallm<FEW, 0>, k_gemm_smallm<FEW, 1>, k_gemm_smallm<FEW, 2>};
+static const SmallmKern smallm_many[MANY] = {k_gemm_smallm<MANY, 0>, k_gemm_smallm<MANY, 1>, k_gemm_smallm<MANY, 2>, k_gemm_smallm<MANY, 3>,
+                                             k_gemm_smallm<MANY, 4>};
+using DecodeKern = void (*)(const void*, int64_t, const int8_t*, const uint8_t*, const uint8_t*, int, int, int, int, void*, int, int64_t, int);
+static const DecodeKern decode_kern[2][FEW] = {{k_gemm_decode_fused<false, FEW, 0>, k_gemm_decode_fused<false, FEW, 1>, k_gemm_decode_fused<false, FEW, 2>},
+                                               {k_gemm_decode_fused<true, FEW, 0>, k_gemm_decode_fused<true, FEW, 1>, k_gemm_decode_fused<true, FEW, 2>}};
 
-static_assert(SMALLM_SETS == 3, "k_gemm_decode_fused writes its turns out for three register sets");
+// Wavefronts of a streaming workgroup that own columns, 32 each: as many as still leave every compute unit a workgroup.
+// A CU's address path takes the four wavefronts' weight loads one after the other (half lines, 32 cycles each: 1150
+// cycles per superstage for 264 of MFMA), so columns on other CUs are faster than columns on the same.  With one
+// wavefront a CU more superstages in flight help too.  us, weights in no cache, 1 row, four wavefronts and 3 sets -> now: N x K = 2048 x
+// 8192 14.5 -> 7.3 (3 sets 8.9), 8192 x 8192 15.8 -> 10.0, 500 x 16384 20.9 -> 10.7, 4096 x 4096 9.3 -> 5.9, 300 x 2048 5.3 -> 3.4;
+// 14336 x 4096 (two wavefronts; 5 sets 8.5) 9.9 -> 8.2; 28672 x 8192 (four; two 23.3, with 16 rows 24.7 for 24.0) 23.6 -> 23.5.
+// The one-launch call, whose workgroups all quantize x, stays at 3 sets: 2048 x 8192 16.6 -> 9.8 (5 sets 10.4), 14336 x 4096 11.2 -> 9.7.
+static int streaming_waves(int64_t N, int cus) { return N <= (int64_t)32 * cus ? 1 : N <= (int64_t)64 * cus ? 2 : 4; }
 
 hipError_t setup_gemm_decode_fused() {
-    const void* kernels[6] = {(const void*)k_gemm_decode_fused<true, 0>, (const void*)k_gemm_decode_fused<true, 1>,
-                              (const void*)k_gemm_decode_fused<true, 2>, (const void*)k_gemm_decode_fused<false, 0>,
-                              (const void*)k_gemm_decode_fused<false, 1>, (const void*)k_gemm_decode_fused<false, 2>};
-    for (const void* k : kernels)
-        if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, decode_fused_lds_bytes(DECODE_FUSED_MAX_K));
-            e != hipSuccess) return e;
+    for (const auto& row : decode_kern)
+        for (DecodeKern k : row)
+            if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, decode_fused_lds_bytes(DECODE_FUSED_MAX_K));
+                e != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -485,14 +502,9 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
                                     const Operand& w, int64_t N, void* y, bool out_bf16, int64_t ldy, hipStream_t s) {
     int cus = 0;
     if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
-    const int tail = (int)((K / 512) % SMALLM_SETS);
-    const dim3 grid((uint32_t)((N + 127) / 128)), block(256);
-    const int ldsb = decode_fused_lds_bytes(K);
-#define BRQ_LAUNCH_DF(BF, T) hipLaunchKernelGGL((k_gemm_decode_fused<BF, T>), grid, block, ldsb, s, x, ldx, signs, w.codes, w.scales, \
-                                                (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy)
-    if (in_bf16) { if (tail == 0) BRQ_LAUNCH_DF(true, 0); else if (tail == 1) BRQ_LAUNCH_DF(true, 1); else BRQ_LAUNCH_DF(true, 2); }
-    else { if (tail == 0) BRQ_LAUNCH_DF(false, 0); else if (tail == 1) BRQ_LAUNCH_DF(false, 1); else BRQ_LAUNCH_DF(false, 2); }
-#undef BRQ_LAUNCH_DF
+    const int nw = streaming_waves(N, cus);
+    hipLaunchKernelGGL(decode_kern[in_bf16][K / 512 % FEW], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256), decode_fused_lds_bytes(K), s,
+                       x, ldx, signs, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy, nw);
     return hipGetLastError();
 }
 
@@ -582,11 +594,16 @@ hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, cons
             hipLaunchKernelGGL(k_gemm_skinny, dim3((uint32_t)((N + 15) / 16)), dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes,
                                w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);
             return hipGetLastError();
-        case ROUTE_STREAM:
-            hipLaunchKernelGGL(smallm_kern[(g.padded_k() / 512) % SMALLM_SETS], dim3((uint32_t)((N + 127) / 128)), dim3(256), SMALLM_LDS_BYTES,
+        case ROUTE_STREAM: {
+            int cus = 0;
+            if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
+            const int64_t nss = g.padded_k() / 512;
+            const int nw = streaming_waves(N, cus), sets = nw == 1 && nss >= MANY ? MANY : FEW;
+            hipLaunchKernelGGL((sets == MANY ? smallm_many : smallm_few)[nss % sets], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256), smallm_lds_bytes(sets),
                                s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y,
-                               (int)g.out_bf16, g.ldy);
+                               (int)g.out_bf16, g.ldy, nw);
             return hipGetLastError();
+        }
         case ROUTE_256x256:
         case ROUTE_128x256: return launch_gemm_tiled(a, w, M, N, K, y, g.out_bf16, g.ldy, s, route == ROUTE_128x256);
         default: return launch_gemm_mid(route - ROUTE_ONE_TILE, a, w, M, N, K, y, g.out_bf16, g.ldy, s);
