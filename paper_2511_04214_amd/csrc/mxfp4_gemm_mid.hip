@@ -54,9 +54,10 @@ constexpr int scale_bufs(int DW) { return (DW + 3) / 4; }
 constexpr int lds_bytes(int NA, int MB, int DW, int DA) { return 4096 * (NA * DW + MB * DA) + scale_bufs(DW) * 1024 * (NA + MB); }
 
 // DW == DA unless PAIR.
-// lines: the output's rows begin on 128-byte lines, and the streaming hint goes with every store (whole lines).  Where they
-// do not, a store of 128 bytes is the end of one line and the beginning of the next: with the hint such halves go to
-// memory as they are, without it the L2 puts the line together.  Rows that are not 16-byte aligned are stored in the same
+// lines: the output's rows begin on half lines of 64 bytes, and the streaming hint goes with every store.  Where they do
+// not, a store of 128 bytes is the end of one line and the beginning of the next, in pieces of 16 or 32 bytes more or less: with
+// the hint such pieces go to memory as they are, without it the L2 puts the line together.  (Halves of lines it had
+// better not wait for: 1668 x 1072 x 7680 fp32 14.2 us with the hint, 14.8 without, 3234 x 5040 x 1536 fp32 25.8, 27.3.)  Rows that are not 16-byte aligned are stored in the same
 // way (the memory system takes any alignment); only a row's last N % (16 / sizeof(out)) elements go one by one.  128 x 128, us,
 // before -> now: 600 x 6004 x 4096 bf16 (rows on 8 bytes, element by element before) 18.9 -> 13.5, fp32 (the hint before)
 // 17.1 -> 14.7; 600 x 6016 x 4096 12.7.
@@ -449,7 +450,7 @@ hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t
                            bool out_bf16, int64_t ldy, hipStream_t s) {
     const mid::Variant& v = mid::variant(tile, a.tiled && w.tiled);
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
-    const int es = out_bf16 ? 2 : 4, lines = N * es % 16 == 0 && ldy * es % 128 == 0 && reinterpret_cast<uintptr_t>(y) % 128 == 0;
+    const int es = out_bf16 ? 2 : 4, lines = N * es % 16 == 0 && ldy * es % 64 == 0 && reinterpret_cast<uintptr_t>(y) % 64 == 0;
     hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.dw, v.da), s,
                        a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy, (int)a.tiled, (int)w.tiled, lines);
     return hipGetLastError();

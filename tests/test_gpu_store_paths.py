@@ -26,7 +26,7 @@ def test_product_rows_on_and_off_lines(brq, route, dtype):
         w = brq.rotate_quantize_fused(torch.randn((N, K), generator=g, device="cuda"), 32, layout="tiled")
         want = torch.empty((M, N), dtype=dtype, device="cuda")
         brq.diag_mxfp4_gemm_on("general", *a, *w, want, K, a_layout="tiled", w_layout="tiled")
-        for pitch, col in ((512, 0), (512, 8), (520, 0)) + (((517, 0),) if N % 8 else ()):
+        for pitch, col in ((512, 0), (512, 8), (520, 0), (544, 32)) + (((517, 0),) if N % 8 else ()):
             print("case", route, dtype, N, pitch, col, flush=True)
             buf = torch.full((M + 1, pitch), -7.0, dtype=dtype, device="cuda")
             brq.diag_mxfp4_gemm_on(route, *a, *w, buf[:M, col:col + N], K, a_layout="tiled", w_layout="tiled")
