@@ -711,11 +711,13 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
 
 // Whether codes are stored through the L2 (store_codes).  Online step and product together, us, streaming hint -> through:
 // row-major 256 x 4096 x 4096 16.2 -> 13.9, 1000 x 4096 x 11008 49.1 -> 43.6, 2000 x 4096 x 11008 79.2 -> 69.4, 4096 x 4096 x 4096
-// 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands, whose product reads
-// whole pages of them, gain less, and with a few MB of codes lose as often: 512 x 4096 x 4096 15.6 -> 13.4, but 971 x 4096 x 2048
-// 12.9 -> 14.4; from 16 MB on the quantizer itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x 8192 as before).
+// 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands gain where K is long and
+// the product is bound by what it reads, as in front of a down-projection: 1000 x 4096 x 11008 with its activation 38.2 -> 34.9, 721 x
+// 4096 x 11008 32.8 -> 30.6, 274 x 1024 x 14336 27.7 -> 24.4 (358 x 14336 x 11008 42.8 -> 43.8, 320 x 8192 x 12288 33.6 -> 33.0); up to
+// K = 8192 they lose as often: 512 x 4096 x 4096 15.6 -> 13.4, but 971 x 4096 x 2048 12.9 -> 14.4.  From 16 MB on the quantizer
+// itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x 8192 as before).
 static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
-    return M * (K / 2) >= (int64_t(1) << (tiled ? 24 : 18));
+    return M * (K / 2) >= (int64_t(1) << (!tiled ? 18 : K > 8192 ? 20 : 24));
 }
 
 // Workgroups per compute unit of a statistics launch (each ends with up to 8 atomics on the caller's counters): of 512
