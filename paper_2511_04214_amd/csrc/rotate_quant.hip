@@ -276,16 +276,14 @@ __device__ __forceinline__ void stats_flush(const uint32_t (&cnt)[8], uint32_t* 
     if (threadIdx.x < a.nt && red[threadIdx.x]) atomicAdd(&a.counts[threadIdx.x], (unsigned long long)red[threadIdx.x]);
 }
 
-// Threads of a workgroup of k_rowwise.  Statistics: every workgroup ends with an atomic per counter, on one cache line
-// for all of them (3.5 ns each: 4096 atomics of 2048 workgroups were 14 us of an 80 us launch), so the wavefronts a CU
-// needs come in few large workgroups, see STATS_WGS_PER_CU.
-constexpr int row_threads(int mode) { return mode == MODE_STATS ? 512 : 256; }
+// Threads of a workgroup of k_rowwise (statistics: see stats_grid).
+constexpr int row_threads(int mode) { return mode == MODE_STATS ? 1024 : 256; }      // at most
 
 // One chunk per lane per step, U steps in flight (the launcher uses U = 1).  LOG2B = 0 means "no rotation":
 // the quantizer alone, or (MODE_ROTATE with a producer) the gated activation alone, stored to y.
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool CONTIG, int U, bool PROD>
 __global__ void __launch_bounds__(row_threads(MODE)) k_rowwise(RowArgs a) {
-    constexpr uint32_t NT = row_threads(MODE);
+    const uint32_t NT = MODE == MODE_STATS ? blockDim.x : (uint32_t)row_threads(MODE);
     const uint32_t lane = threadIdx.x & 63;
     constexpr bool ROT = MODE != MODE_QUANT && LOG2B > 0;   // LOG2B = 0 with MODE_ROTATE: the producer alone
     __shared__ uint32_t red[8];
@@ -474,13 +472,13 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
 // Quantizing X bf16, tiled codes, before -> after, us: 4096 x 8192 B = 1024 / 2048 / 4096 / 8192 30 / 31 / 28 / 31 ->
 // 25 / 23 / 24 / 26; 16384 x 8192 101 / 102 / 102 / 108 -> 78 / 77 / 76 / 83.
 constexpr int reg_waves(int log2b) { return log2b == 13 ? 2 : 1; }              // wavefronts per block
-constexpr int reg_threads(int log2b) { return log2b == 13 ? 128 : 256; }        // threads per workgroup
+constexpr int reg_threads(int log2b, int mode) { return log2b == 13 ? 128 : log2b == 10 && mode == MODE_STATS ? 1024 : 256; }      // per workgroup
 // wavefronts per SIMD that the registers are to leave room for (storing rotated values takes an address per piece)
 constexpr int reg_occ(int log2b, int mode) { return log2b >= 12 ? (mode == MODE_ROTATE ? 3 : 4) : log2b == 11 ? (mode == MODE_ROTATE ? 5 : 6) : 8; }
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD>
-__global__ void __launch_bounds__(reg_threads(LOG2B), reg_occ(LOG2B, MODE)) k_rowwise_reg(RowArgs a, uint32_t blocks_per_row, uint32_t nblocks) {
+__global__ void __launch_bounds__(reg_threads(LOG2B, MODE), reg_occ(LOG2B, MODE)) k_rowwise_reg(RowArgs a, uint32_t blocks_per_row, uint32_t nblocks) {
     static_assert(IN_BF16, "fp32 blocks go through LDS");
-    constexpr int W = reg_waves(LOG2B), BPW = reg_threads(LOG2B) / 64 / W;     // blocks per workgroup
+    constexpr int W = reg_waves(LOG2B), BPW = reg_threads(LOG2B, MODE) / 64 / W;     // blocks per workgroup
     constexpr int NP = 1 << (LOG2B - 9), NJ = NP / W;                          // pieces per block and per wavefront
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t half = W == 2 ? wave : 0u;
@@ -720,10 +718,19 @@ static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
     return M * (K / 2) >= (int64_t(1) << (!tiled ? 18 : K > 8192 ? 20 : 24));
 }
 
-// Workgroups per compute unit of a statistics launch (each ends with up to 8 atomics on the caller's counters): of 512
-// threads for k_rowwise, of up to 256 for k_rowwise_lds and k_rowwise_reg.  X 16384 x 8192, two thresholds, B = 1 / 32, us: 3 x 512 threads
-// 57.8 / 63.9; 2 x 512 with two chunks a pass 60.9 / 72.6; 2 x 768 57.8 / 64.6; 2 x 1024 56.2 / 73.6; 8 x 256 68.7 / 74.5.
-constexpr int STATS_WGS_PER_CU = 3, STATS_LDS_WGS_PER_CU = 8;
+// Workgroups per compute unit of a statistics launch of k_rowwise_lds and k_rowwise_reg.
+constexpr int STATS_LDS_WGS_PER_CU = 8;
+// ... and of k_rowwise.  Every workgroup ends with an atomic per counter, all of them on one cache line: two
+// counters and 768 workgroups were 10 us at the end of every launch (1000 x 8192 13.6 us, of 17 MB).  So the wavefronts a CU needs come in
+// few large workgroups, the fewer the more the atomics weigh: three of 512 threads, two of 768, one of 1024.  us, B = 1 / 32 / 128, three (before: always), one, two: 1000 x 8192 13.6 / 14.0 / 14.4, 8.6 / 9.1 / 9.7, 11.0 / 11.4 /
+// 11.5; 4000 x 4096 15.8 / 16.1 / 16.5, 11.4 / 12.9 / 13.6, 12.8 / 13.3 / 13.6; 6000 x 8192 26.5 / 28.1 / 30.1, 24.9 / 29.0 / 31.3, 24.3 / 27.5 /
+// 30.2; 16384 x 8192 59.0 / 65.4 / 70.6, 66.3 / 70.9 / 76.9, 60.0 / 64.7 / 70.5.  (Two chunks requested ahead instead of one: 2 % slower.)
+struct StatsGrid { int workgroups, threads; };
+static StatsGrid stats_grid(uint32_t chunks, int cus) {
+    const int per_cu = chunks <= (1u << 21) ? 1 : chunks <= (1u << 23) ? 2 : 3, threads = per_cu == 1 ? 1024 : per_cu == 2 ? 768 : 512;
+    const int cap = cus * per_cu, need = (int)((chunks + threads - 1) / threads);
+    return {need < cap ? need : cap, threads};
+}
 
 // Workgroups of a streaming launch.  Measured on X 16384 x 8192 (bf16, B = 32): one chunk in
 // flight per lane and many short-lived workgroups beat a persistent grid (8 per CU, two
@@ -774,11 +781,11 @@ static hipError_t launch_inwave(const RowArgs& a, bool contig, hipStream_t s) {
         }
     }
     constexpr int U = 1;
-    constexpr int NT = row_threads(MODE);
-    int grid = rowwise_grid(a.nchunks, U, cus);
-    if constexpr (MODE == MODE_STATS) {   // fewer, longer-lived workgroups: each ends with atomics on the counters
-        const int need = (int)((a.nchunks + NT * U - 1) / (NT * U)), cap = cus * STATS_WGS_PER_CU;
-        grid = need < cap ? need : cap;
+    int grid = rowwise_grid(a.nchunks, U, cus), NT = row_threads(MODE);
+    if constexpr (MODE == MODE_STATS) {
+        const StatsGrid g = stats_grid(a.nchunks, cus);
+        grid = g.workgroups;
+        NT = g.threads;
     }
     RowArgs b = a;
     b.sign_fixed = (a.signs && MODE != MODE_QUANT && LOG2B > 0) ? fix_columns(grid, a.cpr, NT * U) : 0;
@@ -812,13 +819,13 @@ static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t
     const uint32_t bpr = (uint32_t)(K >> LOG2B), nblocks = (uint32_t)M * bpr;
     RowArgs b = a;
     b.through = code_stores_through(false, M, K) ? 1u : 0u;
-    constexpr int NT = reg_threads(LOG2B);
+    constexpr int NT = reg_threads(LOG2B, MODE);
     constexpr uint32_t per_wg = NT / 64 / reg_waves(LOG2B);
     uint32_t grid = (nblocks + per_wg - 1u) / per_wg;
     if (MODE == MODE_STATS) {
         int cus = 0;
         if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
-        const uint32_t cap = (uint32_t)cus * (uint32_t)STATS_LDS_WGS_PER_CU;
+        const uint32_t cap = (uint32_t)cus * (uint32_t)(NT == 1024 ? 2 : STATS_LDS_WGS_PER_CU);
         if (grid > cap) grid = cap;
     }
     hipLaunchKernelGGL((k_rowwise_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>), dim3(grid), dim3(NT), 0, s, b, bpr, nblocks);
