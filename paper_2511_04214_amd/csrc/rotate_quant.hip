@@ -720,11 +720,12 @@ static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
 
 // Workgroups per compute unit of a statistics launch of k_rowwise_lds and k_rowwise_reg.
 constexpr int STATS_LDS_WGS_PER_CU = 8;
-// ... and of k_rowwise.  Every workgroup ends with an atomic per counter, all of them on one cache line: two
-// counters and 768 workgroups were 10 us at the end of every launch (1000 x 8192 13.6 us, of 17 MB).  So the wavefronts a CU needs come in
-// few large workgroups, the fewer the more the atomics weigh: three of 512 threads, two of 768, one of 1024.  us, B = 1 / 32 / 128, three (before: always), one, two: 1000 x 8192 13.6 / 14.0 / 14.4, 8.6 / 9.1 / 9.7, 11.0 / 11.4 /
-// 11.5; 4000 x 4096 15.8 / 16.1 / 16.5, 11.4 / 12.9 / 13.6, 12.8 / 13.3 / 13.6; 6000 x 8192 26.5 / 28.1 / 30.1, 24.9 / 29.0 / 31.3, 24.3 / 27.5 /
-// 30.2; 16384 x 8192 59.0 / 65.4 / 70.6, 66.3 / 70.9 / 76.9, 60.0 / 64.7 / 70.5.  (Two chunks requested ahead instead of one: 2 % slower.)
+// ... and of k_rowwise.  Every workgroup ends with an atomic per counter, all of them on one cache line: two counters and 768
+// workgroups were 10 us at the end of every launch (1000 x 8192 13.6 us, of 17 MB).  So the wavefronts a CU needs come in few
+// large workgroups, the fewer the more the atomics weigh: three of 512 threads, two of 768, one of 1024.  us, B = 1 / 32 / 128,
+// three (before: always), one, two: 1000 x 8192 13.6 / 14.0 / 14.4, 8.6 / 9.1 / 9.7, 11.0 / 11.4 / 11.5; 4000 x 4096 15.8 /
+// 16.1 / 16.5, 11.4 / 12.9 / 13.6, 12.8 / 13.3 / 13.6; 6000 x 8192 26.5 / 28.1 / 30.1, 24.9 / 29.0 / 31.3, 24.3 / 27.5 / 30.2;
+// 16384 x 8192 59.0 / 65.4 / 70.6, 66.3 / 70.9 / 76.9, 60.0 / 64.7 / 70.5.  (Two chunks requested ahead instead of one: 2 % slower.)
 struct StatsGrid { int workgroups, threads; };
 static StatsGrid stats_grid(uint32_t chunks, int cus) {
     const int per_cu = chunks <= (1u << 21) ? 1 : chunks <= (1u << 23) ? 2 : 3, threads = per_cu == 1 ? 1024 : per_cu == 2 ? 768 : 512;
