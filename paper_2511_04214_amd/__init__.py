@@ -7,10 +7,12 @@ here.  There is no CPU fallback: without the built library, or without a GPU ten
 calls raise.
 
 The five calls that layers are made of are marshalled in csrc/binding.cpp where their arguments are plain; what it leaves
-(it returns None) goes the way written here, which takes and refuses everything.
+(it returns None) goes the way written here, which takes and refuses everything.  So do all calls where that part cannot be
+loaded: it is linked to one torch's C++ interface, libbrq.so to none.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -25,7 +27,7 @@ EXPORTS = ["brq_init", "brq_block_rotate", "brq_operand_bytes", "brq_mxfp4_quant
            "brq_diag_mxfp4_gemm_on", "brq_strerror", "brq_version"]
 
 _lib = None
-_native = None          # the compiled marshalling, its entry points bound to those of _lib
+_native = None          # the compiled marshalling, its entry points bound to those of _lib; None: not loaded
 
 
 class BrqError(RuntimeError):
@@ -38,10 +40,9 @@ def lib():
     """Load libbrq.so (built in-tree by `python -m paper_2511_04214_amd.build`)."""
     global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_binding.so")):
+        if not os.path.exists(LIB_PATH):
             raise ImportError("libbrq.so is not built: run __graft_entry__.build() "
                               "(python paper_2511_04214_amd/build.py) first")
-        from . import _binding
         L = ctypes.CDLL(LIB_PATH)
         vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
         L.brq_block_rotate.argtypes = [vp, i32, i64, i64, i64, i64, vp, vp, i32, i64, vp]
@@ -84,12 +85,24 @@ def lib():
         L.brq_strerror.argtypes = [i32]
         L.brq_strerror.restype = ctypes.c_char_p
         L.brq_version.restype = i32
-        _binding.bind(*(ctypes.cast(f, vp).value for f in (
-            L.brq_rotate_quantize_fused, L.brq_swiglu_rotate_quantize_fused, L.brq_matrix_rotate_quantize_fused, L.brq_mxfp4_gemm,
-            L.brq_rotate_quantize_gemm_fused)))
-        _native = _binding
+        _native = _load_native(L)
         _lib = L
     return _lib
+
+
+def _load_native(L):
+    """The compiled marshalling bound to the entry points of L, or None (and a warning) where it does not fit this torch."""
+    try:
+        from . import _binding
+        if getattr(_binding, "TORCH", None) != str(torch.__version__):
+            raise ImportError("built against another torch than %s" % torch.__version__)
+    except ImportError as e:
+        warnings.warn("the compiled part of the binding is not used, calls take some us longer: %s" % e, RuntimeWarning, stacklevel=3)
+        return None
+    _binding.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.brq_rotate_quantize_fused, L.brq_swiglu_rotate_quantize_fused, L.brq_matrix_rotate_quantize_fused, L.brq_mxfp4_gemm,
+        L.brq_rotate_quantize_gemm_fused)))
+    return _binding
 
 
 def init():
@@ -205,9 +218,7 @@ def mxfp4_quantize(x, codes=None, scales=None, stream=None, layout="rowmajor"):
 
 def rotate_quantize_fused(x, B, codes=None, scales=None, stream=None, layout="rowmajor", signs=None):
     """Block rotation fused with MXFP4 quantization (brq_rotate_quantize_fused)."""
-    if codes is not None and stream is None:
-        if _lib is None:
-            lib()
+    if _native is not None and codes is not None and stream is None:
         st = _native.rotate_quantize(x, B, codes, scales, layout, signs)
         if st is not None:
             _check(st)
@@ -240,9 +251,7 @@ def swiglu_rotate_quantize_fused(gate, up, B, h_dtype=torch.float32, codes=None,
     h_dtype: torch.bfloat16 rounds the activation to bf16 before the rotation, torch.float32
     keeps it.  B = 1 quantizes without rotating.
     """
-    if codes is not None and stream is None:
-        if _lib is None:
-            lib()
+    if _native is not None and codes is not None and stream is None:
         st = _native.swiglu_rotate_quantize(gate, up, B, h_dtype, codes, scales, layout, signs)
         if st is not None:
             _check(st)
@@ -286,9 +295,7 @@ def matrix_rotate(x, R, out_dtype=torch.float32, out=None, stream=None):
 
 def matrix_rotate_quantize_fused(x, R, codes=None, scales=None, stream=None, layout="rowmajor"):
     """Rotation by caller-supplied blocks fused with MXFP4 quantization (brq_matrix_rotate_quantize_fused)."""
-    if codes is not None and stream is None:
-        if _lib is None:
-            lib()
+    if _native is not None and codes is not None and stream is None:
         st = _native.matrix_rotate_quantize(x, R, codes, scales, layout)
         if st is not None:
             _check(st)
@@ -398,9 +405,7 @@ def mxfp4_gemm(aq, as_, wq, ws, out_dtype=torch.float32, out=None, stream=None, 
     `no_loads` (with `clock`; brq_diag_mxfp4_gemm_no_loads) runs the measurement variant without refill
     loads instead: `out` is written with values without meaning.
     """
-    if stream is None and clock is None and not no_loads:
-        if _lib is None:
-            lib()
+    if _native is not None and stream is None and clock is None and not no_loads:
         y = _native.gemm(aq, as_, wq, ws, out_dtype, out, a_layout, w_layout, M, N, K)
         if y is not None:
             if type(y) is int:
@@ -442,9 +447,7 @@ def mxfp4_gemm(aq, as_, wq, ws, out_dtype=torch.float32, out=None, stream=None, 
 def rotate_quantize_gemm_fused(x, B, wq, ws, N, out_dtype=torch.float32, out=None, stream=None, w_layout="rowmajor",
                                signs=None):
     """Y = mxfp4_gemm(rotate_quantize_fused(x, B), (wq, ws)) in one launch, M <= 16 (brq_rotate_quantize_gemm_fused)."""
-    if stream is None:
-        if _lib is None:
-            lib()
+    if _native is not None and stream is None:
         y = _native.rotate_quantize_gemm(x, B, wq, ws, N, out_dtype, out, w_layout, signs)
         if y is not None:
             if type(y) is int:

@@ -6,7 +6,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbrq.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["brq_api.hip", "rotate_quant.hip", "matrix_rotate_quant.hip", "block_summary.hip", "mxfp4_gemm.hip", "mxfp4_gemm_tiled.hip", "mxfp4_gemm_mid.hip"]
 # -ffp-contract=off: the rotation's add/sub/mul sequence is part of the result's definition.
 # packed fp32 instructions are kept out of the generated code.
@@ -33,13 +33,13 @@ def build_library(verbose=False):
 
 
 def build_binding(verbose=False):
-    """_binding.so, against the installed torch (host code only)."""
+    """The compiled part of the binding, against the installed torch, whose version it is marked with (host code only)."""
     import torch
     t = os.path.dirname(os.path.abspath(torch.__file__))
     include = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
                sysconfig.get_paths()["include"], "/opt/rocm/include"]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-isystem" + i for i in include]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DBRQ_TORCH="%s"' % torch.__version__] + ["-isystem" + i for i in include]
     cmd += [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd))

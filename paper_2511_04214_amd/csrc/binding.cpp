@@ -301,5 +301,8 @@ PyMODINIT_FUNC PyInit__binding() {
     s_rowmajor = PyUnicode_InternFromString("rowmajor");
     s_tiled = PyUnicode_InternFromString("tiled");
     if (!s_rowmajor || !s_tiled) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* m = PyModule_Create(&module);
+    // The torch whose headers this was built with: tensors are read through them, so no other will do.
+    if (m && PyModule_AddStringConstant(m, "TORCH", BRQ_TORCH) != 0) Py_CLEAR(m);
+    return m;
 }

@@ -1,5 +1,7 @@
 """The compiled marshalling of the binding takes what is plainly right and leaves everything else to Python: either way
 the results, and what is refused, are the same."""
+import sys
+
 import pytest
 import torch
 
@@ -28,6 +30,27 @@ def test_leaves_to_python_what_is_not_on_a_gpu():
         n.bind(0, 0, 0, 0, 0)
     with pytest.raises(ValueError, match="GPU tensor"):
         brq.rotate_quantize_fused(x, 32, codes=c, scales=c, layout="tiled")
+
+
+@pytest.mark.parametrize("why", ["not built", "another torch"])
+def test_the_library_does_without_the_compiled_part(why, monkeypatch):
+    brq.lib()
+    monkeypatch.setattr(brq, "_lib", None)
+    monkeypatch.setattr(brq, "_native", None)
+    if why == "not built":
+        monkeypatch.delattr(brq, "_binding", raising=False)
+        monkeypatch.setitem(sys.modules, brq.__name__ + "._binding", None)
+    else:
+        monkeypatch.setattr(torch, "__version__", "0.1")
+    with pytest.warns(RuntimeWarning, match="compiled part"):
+        brq.lib()
+    assert brq._native is None and brq.operand_bytes(64, 512) == (16384, 1024)
+    x, c = torch.zeros((4, 512)), torch.zeros(4096, dtype=torch.uint8)
+    for call in (lambda: brq.rotate_quantize_fused(x, 32, c, c, layout="tiled"), lambda: brq.swiglu_rotate_quantize_fused(x, x, 32, F32, c, c),
+                 lambda: brq.matrix_rotate_quantize_fused(x, torch.eye(32), c, c), lambda: brq.mxfp4_gemm(c, c, c, c),
+                 lambda: brq.rotate_quantize_gemm_fused(x, 32, c, c, 4)):
+        with pytest.raises(ValueError, match="GPU tensor"):
+            call()
 
 
 def bufs(M, K, layout):
