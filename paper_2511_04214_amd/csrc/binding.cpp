@@ -20,6 +20,14 @@
 
 namespace {
 
+// The interpreter's lock is not held while one of these lives (an exception gives it back too).
+struct Unlocked {
+    PyThreadState* const state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // The library's entry points, set by bind() when it is loaded.
 decltype(&brq_rotate_quantize_fused) f_rotate_quantize;
 decltype(&brq_swiglu_rotate_quantize_fused) f_swiglu;
@@ -118,7 +126,7 @@ bool buffers(PyObject* c, PyObject* s, int64_t M, int64_t K, brq_layout l, uint8
 }
 
 // An operand of a product: codes and scales, `n` rows of K (either may be -1: not given; a row-major operand says).
-bool operand(PyObject* c, PyObject* s, brq_layout l, int64_t* n, int64_t* K, const uint8_t** codes, const uint8_t** scales) {
+bool operand(PyObject* c, PyObject* s, brq_layout l, int64_t* n, int64_t* K) {
     const at::Tensor *tc = bytes(c), *ts = bytes(s);
     if (!tc || !ts) return false;
     if (l == BRQ_LAYOUT_ROWMAJOR) {
@@ -127,10 +135,9 @@ bool operand(PyObject* c, PyObject* s, brq_layout l, int64_t* n, int64_t* K, con
         *K = tc->size(1) * 2;
         if (ts->dim() != 2 || ts->size(0) != *n || ts->size(1) != *K / 32) return false;
     }
-    *codes = static_cast<const uint8_t*>(tc->const_data_ptr());
-    *scales = static_cast<const uint8_t*>(ts->const_data_ptr());
     return true;
 }
+const uint8_t* data(PyObject* o) { return static_cast<const uint8_t*>(THPVariable_Unpack(o).const_data_ptr()); }
 bool operand_fits(PyObject* c, PyObject* s, brq_layout l, int64_t n, int64_t K) {
     int64_t nc, ns;
     return operand_size(n, K, l, &nc, &ns) && THPVariable_Unpack(c).numel() >= nc && THPVariable_Unpack(s).numel() >= ns;
@@ -142,7 +149,8 @@ bool size_arg(PyObject* o, int64_t* v) {
     return o == Py_None || (integer(o, v) && *v >= 0);
 }
 
-// The product's result: `out`, or a new tensor on the device of `like`.
+// The product's result: `out`, or a new tensor on the device of `like`.  The allocator may have to wait for the GPU, and the GPU
+// for work that another thread has yet to launch: the lock is not held meanwhile, and addresses are read after it.
 bool result(PyObject* out, PyObject* dtype, const at::Tensor& like, int64_t M, int64_t N, at::Tensor* y, brq_dtype* dt, int64_t* ldy) {
     if (out != Py_None) {
         Rows r;
@@ -154,7 +162,11 @@ bool result(PyObject* out, PyObject* dtype, const at::Tensor& like, int64_t M, i
     }
     at::ScalarType s;
     if (!dtype_arg(dtype, &s, dt)) return false;
-    *y = at::empty({M, N}, at::TensorOptions().dtype(s).device(like.device()));
+    const at::TensorOptions options = at::TensorOptions().dtype(s).device(like.device());
+    {
+        const Unlocked u;
+        *y = at::empty({M, N}, options);
+    }
     *ldy = N;
     return on_gpu(*y);
 }
@@ -166,11 +178,8 @@ bool quiet() { return !at::impl::torch_function_mode_enabled(); }
 
 template <class F>
 brq_status released(F call) {
-    brq_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = call();
-    Py_END_ALLOW_THREADS
-    return st;
+    const Unlocked u;
+    return call();
 }
 
 PyObject* status(brq_status st) { return PyLong_FromLong((long)st); }
@@ -238,13 +247,13 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     brq_layout la, lw;
     int64_t M, N, K, ldy;
-    const uint8_t *ac, *as, *wc, *ws;
     at::Tensor y;
     brq_dtype dt;
     if (n != 11 || !f_gemm || !quiet() || !layout(a[6], &la) || !layout(a[7], &lw) || !size_arg(a[8], &M) || !size_arg(a[9], &N) || !size_arg(a[10], &K) ||
-        !operand(a[0], a[1], la, &M, &K, &ac, &as) || !operand(a[2], a[3], lw, &N, &K, &wc, &ws) || M < 0 || N < 0 || K < 0 ||
+        !operand(a[0], a[1], la, &M, &K) || !operand(a[2], a[3], lw, &N, &K) || M < 0 || N < 0 || K < 0 ||
         !operand_fits(a[0], a[1], la, M, K) || !operand_fits(a[2], a[3], lw, N, K) ||
         !result(a[5], a[4], THPVariable_Unpack(a[0]), M, N, &y, &dt, &ldy)) Py_RETURN_NONE;
+    const uint8_t *ac = data(a[0]), *as = data(a[1]), *wc = data(a[2]), *ws = data(a[3]);
     void *p = y.data_ptr(), *s = current_stream();
     return result_or(released([&] { return f_gemm(ac, as, la, wc, ws, lw, M, N, K, p, dt, ldy, s); }), a[5], y);
     END_HANDLE_TH_ERRORS
@@ -262,7 +271,8 @@ PyObject* rotate_quantize_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 9 || !f_decode || !quiet() || !rows(a[0], &x) || !integer(a[1], &B) || !bytes(a[2]) || !bytes(a[3]) || !integer(a[4], &N) || !layout(a[7], &l) ||
         !signs_arg(a[8], x.K, &signs) || !operand_fits(a[2], a[3], l, N, x.K) || !result(a[6], a[5], *x.t, x.M, N, &y, &dt, &ldy)) Py_RETURN_NONE;
     const void* p = x.t->const_data_ptr();
-    const uint8_t *wc = static_cast<const uint8_t*>(THPVariable_Unpack(a[2]).const_data_ptr()), *ws = static_cast<const uint8_t*>(THPVariable_Unpack(a[3]).const_data_ptr());
+    if (signs) signs = reinterpret_cast<const int8_t*>(data(a[8]));
+    const uint8_t *wc = data(a[2]), *ws = data(a[3]);
     void *q = y.data_ptr(), *s = current_stream();
     return result_or(released([&] { return f_decode(p, x.dt, x.M, x.K, x.ld, B, signs, wc, ws, l, N, q, dt, ldy, s); }), a[6], y);
     END_HANDLE_TH_ERRORS

@@ -1,6 +1,8 @@
 """The compiled marshalling of the binding takes what is plainly right and leaves everything else to Python: either way
 the results, and what is refused, are the same."""
 import sys
+import threading
+import time
 
 import pytest
 import torch
@@ -134,3 +136,52 @@ def test_what_is_refused_stays_refused():
         q(x, 32, c, s)
         torch.cuda.current_stream().synchronize()
     assert torch.equal(c, want)
+
+
+@pytest.mark.gpu
+def test_other_threads_run_while_the_result_is_allocated():
+    """A result that fits only once the allocator has given memory back to the driver, which waits for the GPU's work: as on the
+    way through Python, where torch.empty lets go of the interpreter's lock, another thread must not stand still for it."""
+    M = N = 12288
+    a = brq.rotate_quantize_fused(torch.randn((M, 512), device="cuda"), 32)
+    busy, sink = torch.randn((8192, 8192), device="cuda"), torch.empty((8192, 8192), device="cuda")
+    torch.mm(busy, busy, out=sink)
+
+    def longest_pause(**kw):
+        """of another thread, and how long the call took, in seconds"""
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (800 << 20)) / torch.cuda.get_device_properties(0).total_memory)
+        try:
+            held = torch.empty((512 << 20,), dtype=torch.uint8, device="cuda")
+            del held                                                    # 512 MB in the allocator's hands; the result is 576 MB
+            pause, done = [0.0], threading.Event()
+
+            def ticks():
+                last = time.perf_counter()
+                while not done.is_set():
+                    time.sleep(0.001)
+                    now = time.perf_counter()
+                    pause[0], last = max(pause[0], now - last), now
+
+            t = threading.Thread(target=ticks)
+            t.start()
+            for _ in range(60):
+                torch.mm(busy, busy, out=sink)
+            start = time.perf_counter()
+            y = brq.mxfp4_gemm(*a, *a, **kw)
+            took = time.perf_counter() - start
+            done.set()
+            t.join()
+            return pause[0], took, y
+        finally:
+            torch.cuda.set_per_process_memory_fraction(1.0)
+
+    pause, took, want = longest_pause(stream=torch.cuda.current_stream())       # the way through Python
+    print("through Python: call %.3f s, pause %.3f s" % (took, pause))
+    assert took > 0.1 and pause < took / 2, "the allocation did not wait: this measures nothing"
+    want = want.cpu()
+    pause, took, y = longest_pause()
+    print("compiled: call %.3f s, pause %.3f s" % (took, pause))
+    assert took > 0.1 and pause < took / 2
+    assert torch.equal(y.cpu(), want)
