@@ -62,7 +62,7 @@ brq_status brq_diag_mxfp4_gemm_no_loads(const uint8_t* aq, const uint8_t* as, br
                                         int64_t ldy, uint64_t* clock, void* stream);
 
 /*
- * The kernels of brq_mxfp4_gemm.  Which of them takes a call is decided by its shape, layouts and output type; the two
+ * The kernels of brq_mxfp4_gemm.  Which of them takes a call is decided by its shape, layouts, output type and alignment; the two
  * calls below name the choice and make it, so that a kernel can be tested and timed where another one is the
  * faster.
  */
@@ -80,8 +80,8 @@ enum {
 };
 
 /*
- * *route = the kernel that brq_mxfp4_gemm takes for this shape on a device of `cus` compute units.  Host arithmetic
- * only: no device is needed.  An empty product has none (BRQ_ERR_SHAPE).
+ * *route = the kernel that brq_mxfp4_gemm takes for this shape, with an output that begins on a 128-byte line, on a device
+ * of `cus` compute units.  Host arithmetic only: no device is needed.  An empty product has none (BRQ_ERR_SHAPE).
  */
 brq_status brq_diag_mxfp4_gemm_route(brq_layout a_layout, brq_layout w_layout, int64_t M, int64_t N,
                                      int64_t K, brq_dtype ydt, int64_t ldy, int64_t cus, int32_t* route);

@@ -298,7 +298,7 @@ brq_status brq_mxfp4_gemm(const uint8_t* aq, const uint8_t* as, brq_layout a_lay
     if (st != BRQ_OK) return st;
     if (M == 0 || N == 0) return BRQ_OK;
     const brq::Operand a{aq, as, a_layout == BRQ_LAYOUT_TILED}, w{wq, ws, w_layout == BRQ_LAYOUT_TILED};
-    return launched(brq::launch_mxfp4_gemm(a, w, brq::GemmShape{M, N, K, a.tiled, w.tiled, ydt == BRQ_BF16, ldy}, y, static_cast<hipStream_t>(stream)));
+    return launched(brq::launch_mxfp4_gemm(a, w, brq::GemmShape{M, N, K, a.tiled, w.tiled, ydt == BRQ_BF16, ldy, reinterpret_cast<uintptr_t>(y)}, y, static_cast<hipStream_t>(stream)));
 }
 
 brq_status brq_diag_mxfp4_gemm_route(brq_layout a_layout, brq_layout w_layout, int64_t M, int64_t N, int64_t K, brq_dtype ydt,
@@ -308,7 +308,7 @@ brq_status brq_diag_mxfp4_gemm_route(brq_layout a_layout, brq_layout w_layout, i
     if (st != BRQ_OK) return st;
     if (!route) return BRQ_ERR_NULL;
     if (M == 0 || N == 0 || cus < 1 || cus >= (int64_t(1) << 31)) return BRQ_ERR_SHAPE;
-    *route = brq::gemm_route(brq::GemmShape{M, N, K, a_layout == BRQ_LAYOUT_TILED, w_layout == BRQ_LAYOUT_TILED, ydt == BRQ_BF16, ldy}, (int)cus);
+    *route = brq::gemm_route(brq::GemmShape{M, N, K, a_layout == BRQ_LAYOUT_TILED, w_layout == BRQ_LAYOUT_TILED, ydt == BRQ_BF16, ldy, 0}, (int)cus);
     return BRQ_OK;
 }
 
@@ -318,7 +318,7 @@ brq_status brq_diag_mxfp4_gemm_on(int32_t route, const uint8_t* aq, const uint8_
     brq_status st = check_gemm(aq, as, a_layout, wq, ws, w_layout, M, N, K, y, ydt, ldy);
     if (st != BRQ_OK) return st;
     const brq::Operand a{aq, as, a_layout == BRQ_LAYOUT_TILED}, w{wq, ws, w_layout == BRQ_LAYOUT_TILED};
-    const brq::GemmShape g{M, N, K, a.tiled, w.tiled, ydt == BRQ_BF16, ldy};
+    const brq::GemmShape g{M, N, K, a.tiled, w.tiled, ydt == BRQ_BF16, ldy, reinterpret_cast<uintptr_t>(y)};
     if (M == 0 || N == 0 || !brq::gemm_route_supported(route, g)) return BRQ_ERR_SHAPE;
     int cus = 0;
     if (brq::device_cus(&cus) != hipSuccess) return BRQ_ERR_LAUNCH;

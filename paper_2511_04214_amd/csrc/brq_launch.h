@@ -60,11 +60,15 @@ struct Operand {
     bool tiled;
 };
 
-// A product's shape, and the kernels that take it (the numbers of brq_diag.h).
+// Whether all rows of a matrix at `y` begin on multiples of `unit` bytes.
+inline bool rows_on(int unit, uintptr_t y, int64_t pitch_bytes) { return (y | (uintptr_t)pitch_bytes) % (uintptr_t)unit == 0; }
+
+// A product's shape and where its output lies, and the kernels that take it (the numbers of brq_diag.h).
 struct GemmShape {
     int64_t M, N, K;
     bool a_tiled, w_tiled, out_bf16;
     int64_t ldy;
+    uintptr_t y;
     int64_t padded_k() const { return (K + 511) / 512 * 512; }
     // K of whole 512-element superstages: tiled operands are zero-padded to that
     bool whole_k() const { return K % 512 == 0 || (a_tiled && w_tiled); }

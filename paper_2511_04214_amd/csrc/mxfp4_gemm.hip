@@ -531,7 +531,10 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // full clock); `full`: a stage's share of a chip full of them, which is what its energy costs (the chip holds 1.6
 // to 1.8 GHz of 2.4 with every CU multiplying); places = CUs x workgroups that fit one; filled: rows past M
 // are zeros in the one-tile kernel and cost half; bytes: both operands, from HBM; output: 0.6 us per MB of bf16, by
-// whether its rows begin on 128-byte lines.  The three bounds blend into each other (4-norm).  The constants are fitted to
+// whether its rows begin on 128-byte lines, by pitch and by address (outputs 32 or 64 bytes off a line, over the best of the seven
+// where only the pitch was asked -> now: row-major 1.0 -> 0.3 %, tiled 4.0 -> 3.5, 40 shapes each).  Rows on half lines count
+// as off, though the one-tile kernels store them as those on lines: as on lines for these, tiled 2.7 -> 1.9 %, but row-major 0.2 ->
+// 1.4, 36 shapes each.  The three bounds blend into each other (4-norm).  The constants are fitted to
 // the candidates' times, weights not in any cache, on 147 tiled and 160 row-major shapes (M 10 .. 8192, N 256 .. 28672 in
 // eights, K 512 .. 13824): the choice costs 0.9 % over the best of the seven on average, row-major 0.5 % (15 % and 27 % at
 // worst); the fit to the kernels before them (row-major stages by themselves, every row stored past the L2) cost 4 % (67 %).
@@ -552,7 +555,7 @@ static int pick_tile(const GemmShape& g, int cus) {
     const bool tiled = g.a_tiled && g.w_tiled;
     const float stages = (float)((g.K + 511) / 512 * 4), output = 0.6e-6f * (float)g.M * (float)g.N * (g.out_bf16 ? 1.0f : 2.0f);
     const float bytes = 0.53125f * ((float)g.M + (float)g.N) * (float)g.K / 5.0e6f;
-    const bool lines = g.N * (g.out_bf16 ? 2 : 4) % 16 == 0 && g.ldy * (g.out_bf16 ? 2 : 4) % 128 == 0;
+    const bool lines = g.N * (g.out_bf16 ? 2 : 4) % 16 == 0 && rows_on(128, g.y, g.ldy * (g.out_bf16 ? 2 : 4));
     auto pow4 = [](float x) { return x * x * x * x; };
     int best = -1;
     float least = 0.0f;

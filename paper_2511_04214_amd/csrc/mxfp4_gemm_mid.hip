@@ -450,7 +450,7 @@ hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t
                            bool out_bf16, int64_t ldy, hipStream_t s) {
     const mid::Variant& v = mid::variant(tile, a.tiled && w.tiled);
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
-    const int es = out_bf16 ? 2 : 4, lines = N * es % 16 == 0 && ldy * es % 64 == 0 && reinterpret_cast<uintptr_t>(y) % 64 == 0;
+    const int es = out_bf16 ? 2 : 4, lines = N * es % 16 == 0 && rows_on(64, reinterpret_cast<uintptr_t>(y), ldy * es);
     hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.dw, v.da), s,
                        a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy, (int)a.tiled, (int)w.tiled, lines);
     return hipGetLastError();

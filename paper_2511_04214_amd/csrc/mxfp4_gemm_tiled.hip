@@ -665,7 +665,7 @@ hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int6
         if (half) out_bf16 ? launch_one<true, 2, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<false, 2, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk);
         else out_bf16 ? launch_one<true, 4, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<false, 4, 1>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk);
     } else {
-        const bool lines = reinterpret_cast<uintptr_t>(y) % 128 == 0 && ldy * (out_bf16 ? 2 : 4) % 128 == 0;
+        const bool lines = rows_on(128, reinterpret_cast<uintptr_t>(y), ldy * (out_bf16 ? 2 : 4));
 #define BRQ_LAUNCH(BF, MB) (lines ? launch_one<BF, MB, 0, true>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk) : launch_one<BF, MB, 0, false>(g, s, a, w, Mi, Ni, Ki, y, ldy, clk))
         if (half) out_bf16 ? BRQ_LAUNCH(true, 2) : BRQ_LAUNCH(false, 2);
         else out_bf16 ? BRQ_LAUNCH(true, 4) : BRQ_LAUNCH(false, 4);

@@ -1,5 +1,8 @@
 """Which kernel the product takes for a shape, on the CPU (host arithmetic for a device of 256 compute units).  The
 parity tests of test_gpu_gemm_routes.py run every kernel by its name; these say that the dispatcher uses them."""
+import os
+import subprocess
+
 import pytest
 import torch
 
@@ -70,3 +73,22 @@ def test_long_k_stays_on_a_staged_kernel(layout):
             assert route(M, 130, K, layout=layout) in ("64x128", "128x128")
     assert route(17, 130, 2 ** 26, layout=layout) == "general"
     assert route(300, 130, 2 ** 25 + 512, layout=layout) in ("64x128", "128x128", "192x128")
+
+
+@pytest.mark.parametrize("shape,on,off", [((8108, 6976, 512), "256x256", "128x256"), ((4434, 4224, 2048), "192x256", "320x128")])
+def test_an_output_that_begins_off_a_line_is_one_off_lines(shape, on, off, tmp_path):
+    """The product's rows lie off 128-byte lines by their pitch or by where the output begins: the same choice of tile.
+    (The public call has no address: the library's own is compiled against here.)"""
+    M, N, K = shape
+    assert route(M, N, K, "rowmajor") == on and route(M, N, K, "rowmajor", ldy=N + 8) == off
+    csrc = os.path.join(os.path.dirname(brq.LIB_PATH), "csrc")
+    src, exe = tmp_path / "at.cpp", str(tmp_path / "at")
+    src.write_text('''#include <stdio.h>
+#include "brq_launch.h"
+int main() {
+    for (int at : {0, 128, 16, 32, 64, 112}) printf("%%d ", brq::gemm_route(brq::GemmShape{%d, %d, %d, false, false, true, %d, (uintptr_t)at}, 256));
+}''' % (M, N, K, N))
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-isystem/opt/rocm/include", "-I" + csrc, str(src), brq.LIB_PATH, "-o", exe,
+                           "-Wl,-rpath," + os.path.dirname(brq.LIB_PATH), "-Wl,-rpath,/opt/rocm/lib", "-Wl,--allow-shlib-undefined"])
+    got = [brq.GEMM_ROUTES[int(r)] for r in subprocess.check_output([exe], text=True).split()]
+    assert got == [on, on, off, off, off, off]
