@@ -726,9 +726,12 @@ constexpr int STATS_LDS_WGS_PER_CU = 8;
 // three (before: always), one, two: 1000 x 8192 13.6 / 14.0 / 14.4, 8.6 / 9.1 / 9.7, 11.0 / 11.4 / 11.5; 4000 x 4096 15.8 /
 // 16.1 / 16.5, 11.4 / 12.9 / 13.6, 12.8 / 13.3 / 13.6; 6000 x 8192 26.5 / 28.1 / 30.1, 24.9 / 29.0 / 31.3, 24.3 / 27.5 / 30.2;
 // 16384 x 8192 59.0 / 65.4 / 70.6, 66.3 / 70.9 / 76.9, 60.0 / 64.7 / 70.5.  (Two chunks requested ahead instead of one: 2 % slower.)
+// Up to 80 workgroups the atomics are nothing and the chunks are on more CUs in workgroups of 512, B = 32, 1024 threads -> 512: 16 x
+// 4096 3.97 -> 3.59, 64 x 736 3.92 -> 3.53, 31 x 8192 4.19 -> 4.08; 42 x 8192 (84 workgroups of 512) 4.32 either way, 54 x 8192 4.42 -> 4.59.
 struct StatsGrid { int workgroups, threads; };
 static StatsGrid stats_grid(uint32_t chunks, int cus) {
-    const int per_cu = chunks <= (1u << 21) ? 1 : chunks <= (1u << 23) ? 2 : 3, threads = per_cu == 1 ? 1024 : per_cu == 2 ? 768 : 512;
+    const int per_cu = chunks <= (1u << 21) ? 1 : chunks <= (1u << 23) ? 2 : 3;
+    const int threads = per_cu == 2 ? 768 : per_cu == 3 || chunks <= 80u * 512u ? 512 : 1024;
     const int cap = cus * per_cu, need = (int)((chunks + threads - 1) / threads);
     return {need < cap ? need : cap, threads};
 }

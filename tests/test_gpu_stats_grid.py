@@ -6,6 +6,27 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
+def whole_is_the_sum(B, K, rows, signed, part=16):
+    import paper_2511_04214_amd as brq
+    brq.lib()
+    th = (0.5, 1.5, 3.0)
+    g = torch.Generator(device="cuda").manual_seed(B + K)
+    x = torch.randn((max(rows), K), generator=g, device="cuda").to(torch.bfloat16)
+    signs = (torch.randint(0, 2, (K,), generator=g, device="cuda") * 2 - 1).to(torch.int8) if signed else None
+    flipped = x * signs.to(x.dtype) if signed else x
+    parts = [brq.block_stats(flipped[i:i + part], B, thresholds=th) for i in range(0, max(rows), part)]
+    amax, loss = (torch.cat([p[k] for p in parts]) for k in (0, 2))
+    for M in rows:
+        print("case", B, K, M, signed, flush=True)
+        got = brq.block_stats(x[:M], B, thresholds=th, signs=signs)
+        assert torch.equal(got[0], amax[:M]) and torch.equal(got[2], loss[:M])
+        full = M // part
+        want = sum((p[1] for p in parts[:full]), torch.zeros_like(got[1]))
+        if M % part:
+            want = want + brq.block_stats(flipped[full * part:M], B, thresholds=th)[1]
+        assert torch.equal(got[1], want)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("B", [1, 32, 256, 1024, 2048])
 def test_whole_is_the_sum_of_its_parts(B, dtype):
@@ -22,3 +43,10 @@ def test_whole_is_the_sum_of_its_parts(B, dtype):
         assert torch.equal(counts, sum(p[1] for p in parts))
         if B == 1:
             assert counts.tolist() == [int((x[:M].float().abs() > t).sum()) for t in th]
+
+
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("B,K,rows", [(32, 736, (1, 445, 446)), (32, 8192, (40, 41)), (512, 4096, (80, 81))])
+def test_small_launches(B, K, rows, signed):
+    """About 80 * 512 chunks of 8 values, where workgroups of 512 threads become workgroups of 1024."""
+    whole_is_the_sum(B, K, rows, signed)
