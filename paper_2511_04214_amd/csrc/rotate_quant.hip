@@ -766,6 +766,21 @@ static uint32_t fix_columns(int& grid, uint32_t period, uint32_t per_wg) {
     return 1;
 }
 
+// The same for a statistics launch, whose few workgroups feel every one that rounding takes away.  A launch of one pass would
+// become one of two: it stays as it is below 100 workgroups, from where the atomics saved pay for the second pass (us, rounded : not:
+// 300 x 736 5.08 : 4.33, 1000 x 736 5.45 : 5.29, 300 x 4128 5.69 : 6.01, 500 x 4128 6.53 : 7.37).  With several passes reading the
+// signs in each costs up to 20 % on 4 M values and more, 5 % on fewer: a grid that loses more than a quarter is not taken above
+// 2^19 chunks (1000 x 4128, 129 of 256 workgroups, 8.29 : 8.66, 2000 x 4128 12.0 : 11.1, 4000 x 4128 19.9 : 16.4; 1000 x 11008,
+// 215 of 256, 11.6 : 12.7).
+static uint32_t fix_stats_columns(int& grid, uint32_t chunks, uint32_t period, uint32_t threads) {
+    int g = grid;
+    if (!fix_columns(g, period, threads)) return 0;
+    const bool one_pass = (uint64_t)grid * threads >= chunks;
+    if (one_pass ? grid < 100 : g * 4 < grid * 3 && chunks > (1u << 19)) return 0;
+    grid = g;
+    return 1;
+}
+
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD = false>
 static hipError_t launch_inwave(const RowArgs& a, bool contig, hipStream_t s) {
     int cus = 0;
@@ -792,7 +807,8 @@ static hipError_t launch_inwave(const RowArgs& a, bool contig, hipStream_t s) {
         NT = g.threads;
     }
     RowArgs b = a;
-    b.sign_fixed = (a.signs && MODE != MODE_QUANT && LOG2B > 0) ? fix_columns(grid, a.cpr, NT * U) : 0;
+    if (a.signs && MODE != MODE_QUANT && LOG2B > 0)
+        b.sign_fixed = MODE == MODE_STATS ? fix_stats_columns(grid, a.nchunks, a.cpr, NT) : fix_columns(grid, a.cpr, NT * U);
     if (contig)
         hipLaunchKernelGGL((k_rowwise<LOG2B, IN_BF16, MODE, OUT_BF16, true, U, PROD>), dim3(grid), dim3(NT), 0, s, b);
     else

@@ -50,3 +50,9 @@ def test_whole_is_the_sum_of_its_parts(B, dtype):
 def test_small_launches(B, K, rows, signed):
     """About 80 * 512 chunks of 8 values, where workgroups of 512 threads become workgroups of 1024."""
     whole_is_the_sum(B, K, rows, signed)
+
+
+@pytest.mark.parametrize("K,rows", [(736, (300, 1090, 1130)), (4128, (300, 1000, 1050))])
+def test_signed_rows_that_do_not_divide_the_grid(K, rows):
+    """Either side of the sizes where the grid is rounded to whole rows of columns, so that signs are read once, and where not."""
+    whole_is_the_sum(32, K, rows, True, part=50)
