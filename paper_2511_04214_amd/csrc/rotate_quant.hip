@@ -472,13 +472,13 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
 // Quantizing X bf16, tiled codes, before -> after, us: 4096 x 8192 B = 1024 / 2048 / 4096 / 8192 30 / 31 / 28 / 31 ->
 // 25 / 23 / 24 / 26; 16384 x 8192 101 / 102 / 102 / 108 -> 78 / 77 / 76 / 83.
 constexpr int reg_waves(int log2b) { return log2b == 13 ? 2 : 1; }              // wavefronts per block
-constexpr int reg_threads(int log2b, int mode) { return log2b == 13 ? 128 : log2b == 10 && mode == MODE_STATS ? 1024 : 256; }      // per workgroup
+constexpr int reg_threads(int log2b) { return log2b == 13 ? 128 : 256; }        // threads per workgroup (statistics: see launch_reg)
 // wavefronts per SIMD that the registers are to leave room for (storing rotated values takes an address per piece)
 constexpr int reg_occ(int log2b, int mode) { return log2b >= 12 ? (mode == MODE_ROTATE ? 3 : 4) : log2b == 11 ? (mode == MODE_ROTATE ? 5 : 6) : 8; }
-template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD>
-__global__ void __launch_bounds__(reg_threads(LOG2B, MODE), reg_occ(LOG2B, MODE)) k_rowwise_reg(RowArgs a, uint32_t blocks_per_row, uint32_t nblocks) {
+template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD, int NT>
+__global__ void __launch_bounds__(NT, reg_occ(LOG2B, MODE)) k_rowwise_reg(RowArgs a, uint32_t blocks_per_row, uint32_t nblocks) {
     static_assert(IN_BF16, "fp32 blocks go through LDS");
-    constexpr int W = reg_waves(LOG2B), BPW = reg_threads(LOG2B, MODE) / 64 / W;     // blocks per workgroup
+    constexpr int W = reg_waves(LOG2B), BPW = NT / 64 / W;             // blocks per workgroup
     constexpr int NP = 1 << (LOG2B - 9), NJ = NP / W;                          // pieces per block and per wavefront
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t half = W == 2 ? wave : 0u;
@@ -834,12 +834,16 @@ static hipError_t launch_lds(const RowArgs& a, int64_t M, int64_t K, hipStream_t
     return hipGetLastError();
 }
 
-template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD = false>
+template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD, int NT = reg_threads(LOG2B)>
 static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t s) {
     const uint32_t bpr = (uint32_t)(K >> LOG2B), nblocks = (uint32_t)M * bpr;
+    // Statistics with B = 1024: workgroups of 1024 threads where the atomics of those of 256 weigh more than the CUs that fewer
+    // workgroups leave idle, us, 256 : 1024 threads, M x 8192: 16 4.4 : 6.0, 100 6.4 : 6.5, 112 6.7 : 6.6, 400 13.9 : 8.6, 4000 37.2 : 29.0, 6000
+    // 42.0 : 40.3, 7000 45.3 : 46.0, 12000 72.3 : 74.1.  (The number of threads as an argument of the kernel cost 1 %.)
+    if constexpr (MODE == MODE_STATS && LOG2B == 10 && NT == 256)
+        if (nblocks > 800u && nblocks <= 3u << 14) return launch_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD, 1024>(a, M, K, s);
     RowArgs b = a;
     b.through = code_stores_through(false, M, K) ? 1u : 0u;
-    constexpr int NT = reg_threads(LOG2B, MODE);
     constexpr uint32_t per_wg = NT / 64 / reg_waves(LOG2B);
     uint32_t grid = (nblocks + per_wg - 1u) / per_wg;
     if (MODE == MODE_STATS) {
@@ -848,7 +852,7 @@ static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t
         const uint32_t cap = (uint32_t)cus * (uint32_t)(NT == 1024 ? 2 : STATS_LDS_WGS_PER_CU);
         if (grid > cap) grid = cap;
     }
-    hipLaunchKernelGGL((k_rowwise_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD>), dim3(grid), dim3(NT), 0, s, b, bpr, nblocks);
+    hipLaunchKernelGGL((k_rowwise_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD, NT>), dim3(grid), dim3(NT), 0, s, b, bpr, nblocks);
     return hipGetLastError();
 }
 

@@ -52,6 +52,13 @@ def test_small_launches(B, K, rows, signed):
     whole_is_the_sum(B, K, rows, signed)
 
 
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("K,rows", [(8192, (99, 100, 101)), (1024, (800, 801, 3 << 14, (3 << 14) + 1))])
+def test_blocks_of_1024(K, rows, signed):
+    """800 and 3 * 2^14 blocks, between which workgroups have 1024 threads."""
+    whole_is_the_sum(1024, K, rows, signed, part=max(rows) // 7)
+
+
 @pytest.mark.parametrize("K,rows", [(736, (300, 1090, 1130)), (4128, (300, 1000, 1050))])
 def test_signed_rows_that_do_not_divide_the_grid(K, rows):
     """Either side of the sizes where the grid is rounded to whole rows of columns, so that signs are read once, and where not."""
