@@ -185,3 +185,150 @@ def test_other_threads_run_while_the_result_is_allocated():
     print("compiled: call %.3f s, pause %.3f s" % (took, pause))
     assert took > 0.1 and pause < took / 2
     assert torch.equal(y.cpu(), want)
+
+
+class Layer:
+    """The five calls on buffers of their own, without a stream argument: the compiled way."""
+
+    def __init__(self, seed, M=5, N=130, K=512, layout="tiled"):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        self.M, self.N, self.K, self.layout = M, N, K, layout
+        self.x = torch.randn((M, 2 * K), generator=g, device="cuda").to(BF16)
+        self.R = torch.linalg.qr(torch.randn((K // 32, 32, 32), generator=g, device="cuda"))[0].contiguous()
+        self.w = brq.rotate_quantize_fused(torch.randn((N, K), generator=g, device="cuda"), 32, layout=layout)
+        self.q = [bufs(M, K, layout) for _ in range(3)]
+        self.y = torch.zeros((M, N), device="cuda")
+
+    def clear(self):
+        for t in [t for q in self.q for t in q] + [self.y]:
+            t.zero_()
+
+    def natively(self):
+        """(what each call of the compiled part answers)"""
+        n, lay, size = brq._native, self.layout, (self.M, self.N, self.K)
+        gate, up = self.x[:, :self.K], self.x[:, self.K:]
+        return [n.rotate_quantize(gate, 32, *self.q[0], lay, None), n.swiglu_rotate_quantize(gate, up, 32, BF16, *self.q[1], lay, None),
+                n.matrix_rotate_quantize(gate, self.R, *self.q[2], lay), n.gemm(*self.q[1], *self.w, BF16, None, lay, lay, *size),
+                n.rotate_quantize_gemm(gate, 32, *self.w, self.N, F32, self.y, lay, None)]
+
+    def step(self, **kw):
+        gate, up, lay = self.x[:, :self.K], self.x[:, self.K:], self.layout
+        brq.rotate_quantize_fused(gate, 32, *self.q[0], layout=lay, **kw)
+        brq.swiglu_rotate_quantize_fused(gate, up, 32, BF16, *self.q[1], layout=lay, **kw)
+        brq.matrix_rotate_quantize_fused(gate, self.R, *self.q[2], layout=lay, **kw)
+        z = brq.mxfp4_gemm(*self.q[1], *self.w, out_dtype=BF16, a_layout=lay, w_layout=lay, M=self.M, N=self.N, K=self.K, **kw)
+        brq.rotate_quantize_gemm_fused(gate, 32, *self.w, self.N, out=self.y, w_layout=lay, **kw)
+        return [t for q in self.q for t in q] + [self.y, z]
+
+
+def same(got, want):
+    return len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def keep_busy():
+    """About 0.2 s of work on the current stream."""
+    a = torch.randn((8192, 8192), device="cuda")
+    out = torch.empty_like(a)
+    for _ in range(30):
+        torch.mm(a, a, out=out)
+    return torch.cuda.current_stream().record_event()
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream():
+    """The default stream is busy: a call that went there would be late for the copies made on the side stream."""
+    layer, side = Layer(21), torch.cuda.Stream()
+    want = [t.cpu() for t in layer.step(stream=torch.cuda.current_stream())]
+    with torch.cuda.stream(side):
+        torch.empty((1 << 20,), device="cuda")           # (the side stream's result is not the first thing allocated there)
+    layer.clear()
+    torch.cuda.synchronize()
+    late = keep_busy()
+    with torch.cuda.stream(side):
+        got = [t.cpu() for t in layer.step()]
+    assert not late.query(), "the default stream was not busy long enough: this shows nothing"
+    assert same(got, want)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", ["rowmajor", "tiled"])
+def test_calls_without_a_stream_in_a_hip_graph(layout):
+    layer = Layer(22, layout=layout)
+    xs = [layer.x.clone(), layer.x.flip(0).contiguous(), layer.x * 3]
+    eager = []
+    for x in xs:
+        layer.x.copy_(x)
+        eager.append([t.clone() for t in layer.step()])
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        out = layer.step()
+    for _ in range(2):
+        for x, want in zip(xs, eager):
+            layer.x.copy_(x)
+            layer.clear()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert same(out, want)
+            assert same(layer.step(), want)                  # eager work between the replays
+
+
+class Watching(torch.overrides.TorchFunctionMode):
+    def __init__(self):
+        super().__init__()
+        self.seen = 0
+
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        self.seen += 1
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.gpu
+def test_watched_and_batched_tensors_are_left_to_python():
+    layer = Layer(23)
+    want = [t.clone() for t in layer.step()]
+    layer.clear()
+    with Watching() as mode:
+        assert layer.natively() == [None] * 5
+        before = mode.seen
+        got = layer.step()
+        assert mode.seen > before, "the mode saw nothing of the calls"
+    assert same(got, want)
+    answers = layer.natively()
+    assert answers[:3] == [0, 0, 0] and torch.equal(answers[3], want[-1]) and answers[4] is layer.y
+
+    def batched(x):
+        layer.x = x
+        assert layer.natively()[:3] == [None] * 3 and layer.natively()[4] is None
+        for kw in ({}, dict(stream=torch.cuda.current_stream())):
+            with pytest.raises(RuntimeError):
+                layer.step(**kw)                             # no memory of its own: refused by both ways
+        return x
+
+    torch.vmap(batched)(torch.stack([layer.x, layer.x]))
+
+
+@pytest.mark.gpu
+def test_threads_with_streams_of_their_own():
+    layers = [Layer(30 + i, M=3 + i) for i in range(4)]
+    wants = [[t.cpu() for t in layer.step()] for layer in layers]
+    wrong = []
+
+    def work(layer, want):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for i in range(20):
+                    layer.clear()
+                    if not same([t.cpu() for t in layer.step()], want):
+                        wrong.append((layer.M, i))
+        except Exception as e:
+            wrong.append(e)
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=a) for a in zip(layers, wants)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong

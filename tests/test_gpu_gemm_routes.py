@@ -93,7 +93,9 @@ def test_persistent_kernel_two_tiles_a_workgroup(brq, orc, route, M, N, K):
     check_route(brq, orc, route, M, N, K, LAYOUTS[:2], rows=rows)
 
 
-@pytest.mark.parametrize("nss", [1, 2, 3, 4, 7, 16])         # 0, 1, 2 and 5 turns of the main loop, 0 to 2 superstages after it
+# three register sets up to four superstages (0 or 1 turns of the main loop), five with 7 and 16 (1 and 3 turns), and 0 to 2 superstages
+# after it
+@pytest.mark.parametrize("nss", [1, 2, 3, 4, 7, 16])
 def test_streaming_kernel(brq, orc, nss):
     for M, N in ((1, 300), (7, 77), (16, 256)):
         y = check_route(brq, orc, "stream", M, N, 512 * nss, LAYOUTS, pads=(8, 3))
