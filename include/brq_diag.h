@@ -39,7 +39,9 @@ brq_status brq_diag_mfma_ceiling(const uint8_t* operands, int64_t iters, int64_t
  *       (100 * [0] / [1] is the clock in MHz that the chip held during the product),
  *   [2] cycles inside the K loops of its output tiles, [3] cycles inside their epilogues,
  *   [4] the number of output tiles that workgroup processed, [5] cycles of the prologue.
- * y receives the product as usual.
+ * y receives the product as usual.  Its rows are stored as brq_mxfp4_gemm stores those that begin on 128-byte lines,
+ * whether these do or not: rows off lines take longer here than there, so read the clock of such a shape on a pitch
+ * of whole lines.
  */
 brq_status brq_diag_mxfp4_gemm_clock(const uint8_t* aq, const uint8_t* as, brq_layout a_layout,
                                      const uint8_t* wq, const uint8_t* ws, brq_layout w_layout,

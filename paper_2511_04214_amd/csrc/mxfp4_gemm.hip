@@ -332,10 +332,11 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
     v4i c[SETS][8], s4[SETS];
     // ---- prologue: the online step on all M rows.  A wavefront takes 64 chunks (512 elements: one
     // superstage of one row) at a time; chunk kc of a row lies in stage kc / 16, 16-byte chunk (kc % 16) / 4.
-    // Four passes' loads are issued before the first is used: a wavefront is alone on its SIMD, and nothing
-    // else would hide their latency.  The first four come before the weights' loads: loads return in order, x lies in a
-    // cache and the weights do not.  The next four are requested before these are worked on.  N x K = 28672 x 8192, 1 / 3 / 8 rows, us: the
-    // weights first and each four by themselves 25.4 / 28.7 / 36.8, x first 25.0 / 28.4 / 36.6, now 24.0 / 27.0 / 33.5; 4096 x 4096, 1 row 7.2 -> 6.2.
+    // Four passes' loads are issued before the first is used: a wavefront is alone on its SIMD, and nothing else would hide
+    // their latency.  The first four come before the weights' loads: loads return in order, x lies in a cache and the weights
+    // do not.  The next four are requested before these are worked on.  N x K = 28672 x 8192, 1 / 3 / 8 rows, us: the weights
+    // first and each four by themselves 25.4 / 28.7 / 36.8, x first 25.0 / 28.4 / 36.6, now 24.0 / 27.0 / 33.5; 4096 x 4096,
+    // 1 row 7.2 -> 6.2.
     {
         const uint32_t cpr = (uint32_t)K / 8u, nchunks = (uint32_t)M * cpr;
         const float sigma = (__builtin_popcount(lane & 3) & 1) ? -1.0f : 1.0f;
@@ -496,13 +497,14 @@ using DecodeKern = void (*)(const void*, int64_t, const int8_t*, const uint8_t*,
 static const DecodeKern decode_kern[2][FEW] = {{k_gemm_decode_fused<false, FEW, 0>, k_gemm_decode_fused<false, FEW, 1>, k_gemm_decode_fused<false, FEW, 2>},
                                                {k_gemm_decode_fused<true, FEW, 0>, k_gemm_decode_fused<true, FEW, 1>, k_gemm_decode_fused<true, FEW, 2>}};
 
-// Wavefronts of a streaming workgroup that own columns, 32 each: as many as still leave every compute unit a workgroup.
-// A CU's address path takes the four wavefronts' weight loads one after the other (half lines, 32 cycles each: 1150
-// cycles per superstage for 264 of MFMA), so columns on other CUs are faster than columns on the same.  With one
-// wavefront a CU more superstages in flight help too.  us, weights in no cache, 1 row, four wavefronts and 3 sets -> now: N x K = 2048 x
-// 8192 14.5 -> 7.3 (3 sets 8.9), 8192 x 8192 15.8 -> 10.0, 500 x 16384 20.9 -> 10.7, 4096 x 4096 9.3 -> 5.9, 300 x 2048 5.3 -> 3.4;
-// 14336 x 4096 (two wavefronts; 5 sets 8.5) 9.9 -> 8.2; 28672 x 8192 (four; two 23.3, with 16 rows 24.7 for 24.0) 23.6 -> 23.5.
-// The one-launch call, whose workgroups all quantize x, stays at 3 sets: 2048 x 8192 16.6 -> 9.8 (5 sets 10.4), 14336 x 4096 11.2 -> 9.7.
+// Wavefronts of a streaming workgroup that own columns, 32 each: as many as still leave every compute unit a workgroup. A
+// CU's address path takes the four wavefronts' weight loads one after the other (half lines, 32 cycles each: 1150 cycles per
+// superstage for 264 of MFMA), so columns on other CUs are faster than columns on the same.  With one wavefront a CU more
+// superstages in flight help too.  us, weights in no cache, 1 row, four wavefronts and 3 sets -> now: N x K = 2048 x 8192
+// 14.5 -> 7.3 (3 sets 8.9), 8192 x 8192 15.8 -> 10.0, 500 x 16384 20.9 -> 10.7, 4096 x 4096 9.3 -> 5.9, 300 x 2048 5.3 ->
+// 3.4; 14336 x 4096 (two wavefronts; 5 sets 8.5) 9.9 -> 8.2; 28672 x 8192 (four; two 23.3, with 16 rows 24.7 for 24.0) 23.6
+// -> 23.5. The one-launch call, whose workgroups all quantize x, stays at 3 sets: 2048 x 8192 16.6 -> 9.8 (5 sets 10.4),
+// 14336 x 4096 11.2 -> 9.7.
 static int streaming_waves(int64_t N, int cus) { return N <= (int64_t)32 * cus ? 1 : N <= (int64_t)64 * cus ? 2 : 4; }
 
 hipError_t setup_gemm_decode_fused() {
@@ -536,8 +538,12 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // as off, though the one-tile kernels store them as those on lines: as on lines for these, tiled 2.7 -> 1.9 %, but row-major 0.2 ->
 // 1.4, 36 shapes each.  The three bounds blend into each other (4-norm).  The constants are fitted to
 // the candidates' times, weights not in any cache, on 147 tiled and 160 row-major shapes (M 10 .. 8192, N 256 .. 28672 in
-// eights, K 512 .. 13824): the choice costs 0.9 % over the best of the seven on average, row-major 0.5 % (15 % and 27 % at
+// eights, K 512 .. 13824): the choice cost 0.9 % over the best of the seven on average, row-major 0.5 % (15 % and 27 % at
 // worst); the fit to the kernels before them (row-major stages by themselves, every row stored past the L2) cost 4 % (67 %).
+// Two changes to the one-tile kernels came after the fit (six stages of both operands in 64 x 128 row-major, the hint on half
+// lines); with them, on 64 other shapes of each layout, a quarter each on lines, half lines, 16 bytes and anywhere, it is 1.6 /
+// 2.9 / 1.0 / 0.9 % tiled and 0.2 / 0.1 / 0.3 / 0.3 % row-major (22 % and 4 % at worst; tiled 3234 x 5040 x 1536 25.6 -> 26.4 us
+// since the table before).
 struct TileCost { float fixed, alone, full, store, store_off; int per_cu; };    // store_off: rows off lines
 struct Tile { int na, mb, route; TileCost tiled, rowmajor; };                   // 64 mb x 64 na
 static const Tile TILES[2 + MID_TILES] = {
@@ -587,13 +593,18 @@ bool gemm_route_supported(int route, const GemmShape& g) {
 
 int gemm_route(const GemmShape& g, int cus) {
     // Up to 16 rows: weight streaming where the weights are tiled, or row-major with K of a single superstage; other
-    // row-major weights go to the one-tile kernel, which takes their half lines through the LDS ring.  Weight streaming
-    // against the 64 x 128 tile, us, weights in no cache, 1 / 16 rows:
-    //   weights tiled      N x K = 256 x 512 2.9 / 3.2 : 3.6 / 3.7,  2048 x 2048 5.4 / 5.8 : 5.8 / 5.9,  8192 x 4096 9.6 / 10.3 : 9.2 / 9.9,
-    //                      28672 x 4096 14.0 / 13.7 : 14.2 / 13.7,  28672 x 8192 24.9 / 24.4 : 24.2 / 24.5  (activations of either layout)
-    //   weights row-major  256 x 512 3.3 / 3.6 : 3.6 / 3.7,  28672 x 512 4.7 / 5.0 : 5.1 / 5.1,  1024 x 1024 4.3 / 4.6 : 4.2 / 4.3,
-    //                      28672 x 1024 6.2 / 6.7 : 6.6 / 6.6,  8192 x 4096 15.0 / 15.7 : 12.7 / 13.5,  28672 x 8192 35.3 / 34.6 : 28.5 / 29.0
-    // 32 rows, tiled, 8192 x 4096 10.8 : 10.3, and where it needed more row tiles 64 rows 13.0 : 11.0, 128 rows 17.5 : 10.9.
+    // row-major weights go to the one-tile kernel, which takes their half lines through the LDS ring.  Weight streaming : the
+    // 64 x 128 tile : the K-split kernel (ROUTE_SKINNY, which sums in another order), us, weights in no cache, 1 / 16 rows:
+    //   weights tiled      N x K = 256 x 512 2.4 / 2.8 : 3.5 / 3.6 : 2.0 / 2.4,  2048 x 2048 4.0 / 4.3 : 5.9 / 5.9 : 3.8 / 4.2,
+    //                      2048 x 8192 7.4 / 7.9 : 13.9 / 14.7 : 11.7 / 12.0,  8192 x 4096 7.3 / 7.6 : 9.4 / 9.7 : 8.0 / 8.3,
+    //                      28672 x 2048 8.7 / 9.0 : 8.7 / 8.7 : 9.1 / 10.4,  28672 x 8192 24.9 / 25.3 : 25.5 / 25.8 : 30.6 / 33.3
+    //   weights row-major  256 x 512 2.6 / 2.9 : 3.6 / 3.8 : 2.0 / 2.5,  28672 x 512 4.7 / 5.0 : 5.7 / 5.6 : 4.3 / 5.3,
+    //                      28672 x 1024 6.4 / 6.9 : 7.0 / 7.1 : 6.8 / 8.1,  28672 x 2048 10.5 / 11.0 : 9.7 / 9.9 : 11.4 / 13.1,
+    //                      28672 x 8192 38.0 / 36.8 : 32.6 / 31.1 : 38.0 / 42.8
+    // That line for row-major weights is right where four wavefronts of a workgroup stream (N above 64 columns a CU).  Below, it
+    // is older than workgroups that own 32 or 64 columns, and streaming would be the faster: 2048 x 8192 9.0 / 9.9 : 18.8 / 19.3 :
+    // 12.6 / 13.0,  4096 x 4096 6.6 / 7.2 : 11.5 / 11.8 : 7.9 / 8.1,  8192 x 4096 7.2 / 7.6 : 11.8 / 12.1 : 8.6 / 9.0,  14336 x 8192
+    // 18.4 / 17.6 : 23.3 / 21.9 : 19.8 / 24.8.
     if (gemm_route_supported(ROUTE_STREAM, g) && (g.w_tiled || g.K <= 512 || !gemm_route_supported(ROUTE_ONE_TILE, g))) return ROUTE_STREAM;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
     return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;

@@ -37,12 +37,13 @@
 // LDS map (bytes), S = NA + MB: W's DW stages x 4K NA | A's DA stages x 4K MB; then ceil(DW / 4) scale buffers x
 // (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the rings.
 //
-// DW, DA: as many stages as the LDS takes where that measured faster.  Single stages: two workgroups of 64 x 128 on a CU
-// with 6 stages each instead of 4: 200 x 4096 x 4096 11.2 -> 9.7 us, 300 x 28672 x 8192 75 -> 68.  The other tiles gain nothing
-// from depth (128 x 128 with 8 stages and one workgroup a CU instead of 4 and two: 58 -> 65 us on the latter); 320 x 128, for a
-// few hundred rows, has 5 and reads its weights once: 47.6 -> 44.8 us on the latter.  Pairs: 4 stages of both wait for
-// every load (128 x 128: 1082 cycles a stage, 6 of both 705, 8 the same); 64 x 128 with 6 and 4 instead of 6 of both, 1000 x 4096 x
-// 11008 45.1 us against 47.0, but 1 x 936 x 8192 13.4 against 12.9, 200 x 4096 x 4096 12.0 against 11.8: it is for the small shapes.
+// DW, DA: as many stages as the LDS takes where that measured faster.  Single stages: two workgroups of 64 x 128 on a CU with
+// 6 stages each instead of 4: 200 x 4096 x 4096 11.2 -> 9.7 us, 300 x 28672 x 8192 75 -> 68.  The other tiles gain nothing
+// from depth (128 x 128 with 8 stages and one workgroup a CU instead of 4 and two: 58 -> 65 us on the latter); 320 x 128, for
+// a few hundred rows, has 5 and reads its weights once: 47.6 -> 44.8 us on the latter.  Pairs: 4 stages of both wait for
+// every load (128 x 128: 1082 cycles a stage, 6 of both 705, 8 the same); 64 x 128 with 6 and 4 instead of 6 of both, 1000 x
+// 4096 x 11008 45.1 us against 47.0, but 1 x 936 x 8192 13.4 against 12.9, 200 x 4096 x 4096 12.0 against 11.8: it is for the
+// small shapes.
 #include "mfma_fp4.h"
 #include "brq_launch.h"
 
@@ -54,13 +55,13 @@ constexpr int scale_bufs(int DW) { return (DW + 3) / 4; }
 constexpr int lds_bytes(int NA, int MB, int DW, int DA) { return 4096 * (NA * DW + MB * DA) + scale_bufs(DW) * 1024 * (NA + MB); }
 
 // DW == DA unless PAIR.
-// lines: the output's rows begin on half lines of 64 bytes, and the streaming hint goes with every store.  Where they do
-// not, a store of 128 bytes is the end of one line and the beginning of the next, in pieces of 16 or 32 bytes more or less: with
-// the hint such pieces go to memory as they are, without it the L2 puts the line together.  (Halves of lines it had
-// better not wait for: 1668 x 1072 x 7680 fp32 14.2 us with the hint, 14.8 without, 3234 x 5040 x 1536 fp32 25.8, 27.3.)  Rows that are not 16-byte aligned are stored in the same
-// way (the memory system takes any alignment); only a row's last N % (16 / sizeof(out)) elements go one by one.  128 x 128, us,
-// before -> now: 600 x 6004 x 4096 bf16 (rows on 8 bytes, element by element before) 18.9 -> 13.5, fp32 (the hint before)
-// 17.1 -> 14.7; 600 x 6016 x 4096 12.7.
+// lines: the output's rows begin on half lines of 64 bytes, and the streaming hint goes with every store.  Where they do not,
+// a store of 128 bytes is the end of one line and the beginning of the next, in pieces of 16 or 32 bytes more or less: with
+// the hint such pieces go to memory as they are, without it the L2 puts the line together.  (Halves of lines it had better
+// not wait for: 1668 x 1072 x 7680 fp32 14.2 us with the hint, 14.8 without, 3234 x 5040 x 1536 fp32 25.8, 27.3.)  Rows that
+// are not 16-byte aligned are stored in the same way (the memory system takes any alignment); only a row's last N % (16 /
+// sizeof(out)) elements go one by one.  128 x 128, us, before -> now: 600 x 6004 x 4096 bf16 (rows on 8 bytes, element by
+// element before) 18.9 -> 13.5, fp32 (the hint before) 17.1 -> 14.7; 600 x 6016 x 4096 12.7.
 template <bool OUT_BF16, int NA, int MB, int DW, int DA, bool PAIR>
 __global__ void __launch_bounds__(256, (lds_bytes(NA, MB, DW, DA) <= 81920 ? 2 : 1))
 k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const uint8_t* __restrict__ wq,

@@ -466,8 +466,9 @@ __global__ void __launch_bounds__(256) k_rowwise_t4(RowArgs a) {
 // (One wavefront with 16 chunks a lane leaves room for 3 per SIMD and spills.)
 // Through LDS altogether (two trips for the stages h >= 512, the stages h = 32 .. 256 through its swizzle) the block
 // cost 34 LDS operations per 8 values of a lane and was bound by them; now it is bound by the vector units (about 20
-// instructions per value of a lane at B = 8192, 18 of the 26 us on 4096 x 8192).  A row's 128-byte lines of tiled codes (two rows each) are left to two wavefronts: no
-// streaming hint (3000 x 8192, B = 2048, with the product behind it 39 us instead of 36); from 256 KB of codes on at device scope
+// instructions per value of a lane at B = 8192, 18 of the 25 us on 4096 x 8192; with x in a cache 25.0, in none 25.4).  A row's
+// 128-byte lines of tiled codes (two rows each) are left to two wavefronts: no streaming hint (3000 x 8192, B = 2048, with the
+// product behind it 39 us instead of 36); from 256 KB of codes on at device scope
 // (store_codes; 4096 x 8192 B = 8192 with its product 57.6 -> 56.8), below that plain stores (1 x 8192: 0.4 us less).
 // Quantizing X bf16, tiled codes, before -> after, us: 4096 x 8192 B = 1024 / 2048 / 4096 / 8192 30 / 31 / 28 / 31 ->
 // 25 / 23 / 24 / 26; 16384 x 8192 101 / 102 / 102 / 108 -> 78 / 77 / 76 / 83.
@@ -708,12 +709,17 @@ __global__ void __launch_bounds__(256) k_rowwise_lds(RowArgs a, uint32_t blocks_
 // ---- host side ---------------------------------------------------------------------
 
 // Whether codes are stored through the L2 (store_codes).  Online step and product together, us, streaming hint -> through:
-// row-major 256 x 4096 x 4096 16.2 -> 13.9, 1000 x 4096 x 11008 49.1 -> 43.6, 2000 x 4096 x 11008 79.2 -> 69.4, 4096 x 4096 x 4096
-// 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands gain where K is long and
-// the product is bound by what it reads, as in front of a down-projection: 1000 x 4096 x 11008 with its activation 38.2 -> 34.9, 721 x
-// 4096 x 11008 32.8 -> 30.6, 274 x 1024 x 14336 27.7 -> 24.4 (358 x 14336 x 11008 42.8 -> 43.8, 320 x 8192 x 12288 33.6 -> 33.0); up to
-// K = 8192 they lose as often: 512 x 4096 x 4096 15.6 -> 13.4, but 971 x 4096 x 2048 12.9 -> 14.4.  From 16 MB on the quantizer
-// itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x 8192 as before).
+// row-major 256 x 4096 x 4096 16.2 -> 13.9, 1000 x 4096 x 11008 49.1 -> 43.6, 2000 x 4096 x 11008 79.2 -> 69.4, 4096 x 4096 x
+// 4096 51.2 -> 49.7, 64 x 4096 x 4096 (128 KB of codes) 13.1 -> 13.3, 16 x 4096 x 4096 12.3 -> 12.6.  Tiled operands from 1
+// to 10 MB gain little by little as K grows.  Time through the L2 over that with the hint, geometric mean (best, worst) over
+// N 512 .. 28672, 28 to 49 shapes each: K = 2048 0.991 (0.94, 1.07), 4096 0.993 (0.96, 1.04), 6144 0.987 (0.90, 1.05), 8192
+// 0.982 (0.90, 1.02), 10240 0.981 (0.85, 1.01), 11008 0.980 (0.91, 1.02).  More than K it is N, which the quantizer does not
+// know: 0.961 with 512 columns, 0.98 with 1024 and 2048, 0.995 up to 14336, 1.001 with 28672.  So no line in M and K is
+// sharp, and this one, K > 8192, is on the careful side: beyond it hardly a shape loses more than 2 % (1000 x 4096 x 11008
+// with its activation 38.2 -> 34.9, 721 x 4096 x 11008 32.8 -> 30.6, 274 x 1024 x 14336 27.7 -> 24.4; but 358 x 14336 x 11008
+// 42.8 -> 43.8, 194 x 14336 x 11008 33.0 -> 34.0, 209 x 28672 x 10240 51 -> 53.4), and K = 8192, left out, would gain as much
+// as what is in.  From 16 MB on the quantizer itself is faster (16384 x 8192 58.0 -> 57.0, 8000 x 8192 29.9 -> 29.3, 3000 x
+// 8192 as before).
 static bool code_stores_through(bool tiled, int64_t M, int64_t K) {
     return M * (K / 2) >= (int64_t(1) << (!tiled ? 18 : K > 8192 ? 20 : 24));
 }
@@ -726,8 +732,9 @@ constexpr int STATS_LDS_WGS_PER_CU = 8;
 // three (before: always), one, two: 1000 x 8192 13.6 / 14.0 / 14.4, 8.6 / 9.1 / 9.7, 11.0 / 11.4 / 11.5; 4000 x 4096 15.8 /
 // 16.1 / 16.5, 11.4 / 12.9 / 13.6, 12.8 / 13.3 / 13.6; 6000 x 8192 26.5 / 28.1 / 30.1, 24.9 / 29.0 / 31.3, 24.3 / 27.5 / 30.2;
 // 16384 x 8192 59.0 / 65.4 / 70.6, 66.3 / 70.9 / 76.9, 60.0 / 64.7 / 70.5.  (Two chunks requested ahead instead of one: 2 % slower.)
-// Up to 80 workgroups the atomics are nothing and the chunks are on more CUs in workgroups of 512, B = 32, 1024 threads -> 512: 16 x
-// 4096 3.97 -> 3.59, 64 x 736 3.92 -> 3.53, 31 x 8192 4.19 -> 4.08; 42 x 8192 (84 workgroups of 512) 4.32 either way, 54 x 8192 4.42 -> 4.59.
+// Up to 80 workgroups the atomics are nothing and the chunks are on more CUs in workgroups of 512, B = 32, 1024 threads ->
+// 512: 16 x 4096 3.97 -> 3.59, 64 x 736 3.92 -> 3.53, 31 x 8192 4.19 -> 4.08; 42 x 8192 (84 workgroups of 512) 4.32 either way,
+// 54 x 8192 4.42 -> 4.59.
 struct StatsGrid { int workgroups, threads; };
 static StatsGrid stats_grid(uint32_t chunks, int cus) {
     const int per_cu = chunks <= (1u << 21) ? 1 : chunks <= (1u << 23) ? 2 : 3;
@@ -767,11 +774,11 @@ static uint32_t fix_columns(int& grid, uint32_t period, uint32_t per_wg) {
 }
 
 // The same for a statistics launch, whose few workgroups feel every one that rounding takes away.  A launch of one pass would
-// become one of two: it stays as it is below 100 workgroups, from where the atomics saved pay for the second pass (us, rounded : not:
-// 300 x 736 5.08 : 4.33, 1000 x 736 5.45 : 5.29, 300 x 4128 5.69 : 6.01, 500 x 4128 6.53 : 7.37).  With several passes reading the
-// signs in each costs up to 20 % on 4 M values and more, 5 % on fewer: a grid that loses more than a quarter is not taken above
-// 2^19 chunks (1000 x 4128, 129 of 256 workgroups, 8.29 : 8.66, 2000 x 4128 12.0 : 11.1, 4000 x 4128 19.9 : 16.4; 1000 x 11008,
-// 215 of 256, 11.6 : 12.7).
+// become one of two: it stays as it is below 100 workgroups, from where the atomics saved pay for the second pass (us,
+// rounded : not: 300 x 736 5.08 : 4.33, 1000 x 736 5.45 : 5.29, 300 x 4128 5.69 : 6.01, 500 x 4128 6.53 : 7.37).  With
+// several passes reading the signs in each costs up to 20 % on 4 M values and more, 5 % on fewer: a grid that loses more than
+// a quarter is not taken above 2^19 chunks (1000 x 4128, 129 of 256 workgroups, 8.29 : 8.66, 2000 x 4128 12.0 : 11.1, 4000 x
+// 4128 19.9 : 16.4; 1000 x 11008, 215 of 256, 11.6 : 12.7).
 static uint32_t fix_stats_columns(int& grid, uint32_t chunks, uint32_t period, uint32_t threads) {
     int g = grid;
     if (!fix_columns(g, period, threads)) return 0;
@@ -837,9 +844,9 @@ static hipError_t launch_lds(const RowArgs& a, int64_t M, int64_t K, hipStream_t
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD, int NT = reg_threads(LOG2B)>
 static hipError_t launch_reg(const RowArgs& a, int64_t M, int64_t K, hipStream_t s) {
     const uint32_t bpr = (uint32_t)(K >> LOG2B), nblocks = (uint32_t)M * bpr;
-    // Statistics with B = 1024: workgroups of 1024 threads where the atomics of those of 256 weigh more than the CUs that fewer
-    // workgroups leave idle, us, 256 : 1024 threads, M x 8192: 16 4.4 : 6.0, 100 6.4 : 6.5, 112 6.7 : 6.6, 400 13.9 : 8.6, 4000 37.2 : 29.0, 6000
-    // 42.0 : 40.3, 7000 45.3 : 46.0, 12000 72.3 : 74.1.  (The number of threads as an argument of the kernel cost 1 %.)
+    // Statistics with B = 1024: workgroups of 1024 threads where the atomics of those of 256 weigh more than the CUs that
+    // fewer workgroups leave idle, us, 256 : 1024 threads, M x 8192: 16 4.4 : 6.0, 100 6.4 : 6.5, 112 6.7 : 6.6, 400 13.9 : 8.6,
+    // 4000 37.2 : 29.0, 6000 42.0 : 40.3, 7000 45.3 : 46.0, 12000 72.3 : 74.1.  (The number of threads as an argument: 1 % slower.)
     if constexpr (MODE == MODE_STATS && LOG2B == 10 && NT == 256)
         if (nblocks > 800u && nblocks <= 3u << 14) return launch_reg<LOG2B, IN_BF16, MODE, OUT_BF16, PROD, 1024>(a, M, K, s);
     RowArgs b = a;
