@@ -102,6 +102,7 @@ hipError_t launch_gemm_tiled(const Operand& a, const Operand& w, int64_t M, int6
 
 // One output tile per workgroup, the tile one of a family (mxfp4_gemm_mid.hip): any M, N and pitch.
 bool mid_gemm_supported(int tile, const GemmShape& g);
+bool mid_gemm_pairs(int tile, bool both_tiled, int64_t K);       // whether it loads its stages in pairs
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s);
 

@@ -543,17 +543,21 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // Two changes to the one-tile kernels came after the fit (six stages of both operands in 64 x 128 row-major, the hint on half
 // lines); with them, on 64 other shapes of each layout, a quarter each on lines, half lines, 16 bytes and anywhere, it is 1.6 /
 // 2.9 / 1.0 / 0.9 % tiled and 0.2 / 0.1 / 0.3 / 0.3 % row-major (22 % and 4 % at worst; tiled 3234 x 5040 x 1536 25.6 -> 26.4 us
-// since the table before).
+// since the table before).  `singles`, row-major with K up to 1024, is fitted to 1839 shapes (M 1 .. 8192, N 64 .. 28672): 0.8 %
+// over the best (34 % at worst); fitted to one half 0.9 % on the other.
 struct TileCost { float fixed, alone, full, store, store_off; int per_cu; };    // store_off: rows off lines
-struct Tile { int na, mb, route; TileCost tiled, rowmajor; };                   // 64 mb x 64 na
+struct Tile { int na, mb, route; TileCost tiled, rowmajor, singles; };          // 64 mb x 64 na; singles: row-major by single stages
 static const Tile TILES[2 + MID_TILES] = {
-    {4, 4, ROUTE_256x256, {5.984f, 0.535f, 0.758f, 0.292f, 0.481f, 1}, {6.801f, 0.508f, 0.978f, 0.439f, 0.893f, 1}},
-    {4, 2, ROUTE_128x256, {3.696f, 0.280f, 0.474f, 0.377f, 0.649f, 1}, {3.535f, 0.514f, 0.682f, 0.402f, 0.724f, 1}},
-    {2, 1, ROUTE_ONE_TILE, {3.141f, 0.178f, 0.205f, 0.406f, 0.923f, 2}, {3.749f, 0.196f, 0.264f, 0.512f, 0.585f, 2}},
-    {2, 2, ROUTE_ONE_TILE + 1, {3.731f, 0.206f, 0.292f, 0.348f, 0.560f, 2}, {3.585f, 0.261f, 0.356f, 0.889f, 1.014f, 1}},
-    {2, 3, ROUTE_ONE_TILE + 2, {4.774f, 0.268f, 0.313f, 0.568f, 1.091f, 1}, {5.290f, 0.268f, 0.433f, 0.736f, 1.070f, 1}},
-    {4, 3, ROUTE_ONE_TILE + 3, {6.545f, 0.397f, 0.552f, 0.422f, 0.864f, 1}, {5.012f, 0.522f, 0.751f, 0.529f, 1.038f, 1}},
-    {2, 5, ROUTE_ONE_TILE + 4, {6.659f, 0.363f, 0.494f, 0.545f, 0.950f, 1}, {6.735f, 0.399f, 0.639f, 0.624f, 0.976f, 1}},
+    {4, 4, ROUTE_256x256, {5.984f, 0.535f, 0.758f, 0.292f, 0.481f, 1}, {6.801f, 0.508f, 0.978f, 0.439f, 0.893f, 1}, {}},
+    {4, 2, ROUTE_128x256, {3.696f, 0.280f, 0.474f, 0.377f, 0.649f, 1}, {3.535f, 0.514f, 0.682f, 0.402f, 0.724f, 1}, {}},
+    {2, 1, ROUTE_ONE_TILE, {3.141f, 0.178f, 0.205f, 0.406f, 0.923f, 2}, {3.749f, 0.196f, 0.264f, 0.512f, 0.585f, 2},
+     {3.382f, 0.118f, 0.348f, 0.442f, 0.597f, 2}},
+    {2, 2, ROUTE_ONE_TILE + 1, {3.731f, 0.206f, 0.292f, 0.348f, 0.560f, 2}, {3.585f, 0.261f, 0.356f, 0.889f, 1.014f, 1},
+     {3.958f, 0.267f, 0.356f, 0.307f, 0.489f, 2}},
+    {2, 3, ROUTE_ONE_TILE + 2, {4.774f, 0.268f, 0.313f, 0.568f, 1.091f, 1}, {5.290f, 0.268f, 0.433f, 0.736f, 1.070f, 1},
+     {3.629f, 0.362f, 0.359f, 0.619f, 0.950f, 1}},
+    {4, 3, ROUTE_ONE_TILE + 3, {6.545f, 0.397f, 0.552f, 0.422f, 0.864f, 1}, {5.012f, 0.522f, 0.751f, 0.529f, 1.038f, 1}, {}},
+    {2, 5, ROUTE_ONE_TILE + 4, {6.659f, 0.363f, 0.494f, 0.545f, 0.950f, 1}, {6.735f, 0.399f, 0.639f, 0.624f, 0.976f, 1}, {}},
 };
 
 // The cheapest of the LDS-staged kernels that take the shape, or -1.
@@ -569,7 +573,7 @@ static int pick_tile(const GemmShape& g, int cus) {
         const Tile& t = TILES[i];
         if (!gemm_route_supported(t.route, g)) continue;
         const bool one_tile = t.route >= ROUTE_ONE_TILE;
-        const TileCost& c = tiled ? t.tiled : t.rowmajor;
+        const TileCost& c = tiled ? t.tiled : one_tile && !mid_gemm_pairs(t.route - ROUTE_ONE_TILE, tiled, g.K) ? t.singles : t.rowmajor;
         const int64_t tm = (g.M + 64 * t.mb - 1) / (64 * t.mb), T = tm * ((g.N + 64 * t.na - 1) / (64 * t.na)), places = (int64_t)cus * c.per_cu;
         const float filled = one_tile ? 0.5f + 0.5f * (float)g.M / (float)(64 * t.mb * tm) : 1.0f;
         const float alone = stages * c.alone * (float)((T + places - 1) / places);

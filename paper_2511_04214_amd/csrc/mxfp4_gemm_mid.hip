@@ -21,7 +21,7 @@
 // bounds, and the stages that the window shares with the superstage before get scale bytes 0 in BOTH operands
 // (2^-127 * 2^-127 times at most 36 * 32 vanishes in an fp32 sum).
 //
-// Pairs (PAIR: an operand is row-major).  A stage of a row-major operand is half of a 128-byte line of every row.  Taken
+// Pairs (PAIR: an operand is row-major; mid_gemm_pairs).  A stage of a row-major operand is half of a 128-byte line of every row.  Taken
 // stage by stage each line crosses from the L2 to the CU twice, and from HBM its halves come at two times: with
 // 128 x 128 tiles 1000 x 4096 x 11008 ran at 936 cycles a stage (681 with W in the memory-side cache), tiled operands at 490.
 // So two stages are loaded as one: 8 rows x 128 bytes per load, 128-byte rows in LDS, chunk c of row i at c ^ ((i >> 1) & 7)
@@ -33,6 +33,11 @@
 // 28672 x 8192 (320 x 128) 1340 -> 1046, 57.6 -> 50.9; 2000 x 4096 x 11008 1200 -> 1010, 67 -> 58; 1000 x 4096 x 11008 on 64 x 128
 // 56 -> 45.  What is left over tiled operands is the order in which HBM is read (hot: 495 cycles).
 // Both kinds take either layout; tiled operands keep single stages (4 of them in LDS twice a CU: 29.5 against 30.4 us).
+// So do row-major ones with K up to 1024 on the tiles of at most 192 x 128: there the prologue, which loads all the stages there
+// are, and two workgroups a CU weigh more than whole lines.  Pairs : single stages, us: 128 x 128 2000 x 4096 x 512 10.4 : 7.3, 4000
+// x 8192 x 512 35.4 : 23.5, 2000 x 4096 x 1024 11.9 : 10.2; 192 x 128 134 x 64 x 1024 6.9 : 6.2; 64 x 128 16 x 2048 x 512 4.1 : 3.9, 16 x
+// 2048 x 1024 5.0 : 4.7; with K = 2048 64 x 128 2000 x 4096 17.0 : 18.7, 128 x 128 514 x 16064 23.9 : 22.5 but 100 x 8192 x 3072 13.1 :
+// 14.7; 320 x 128 2000 x 4096 x 1024 10.4 : 10.9, 192 x 256 10.8 : 11.1.
 //
 // LDS map (bytes), S = NA + MB: W's DW stages x 4K NA | A's DA stages x 4K MB; then ceil(DW / 4) scale buffers x
 // (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the rings.
@@ -424,13 +429,14 @@ static const Variant singles[MID_TILES] = {BRQ_MID(2, 1, 6, 6, false), BRQ_MID(2
 static const Variant pairs[MID_TILES] = {BRQ_MID(2, 1, 6, 6, true), BRQ_MID(2, 2, 6, 6, true), BRQ_MID(2, 3, 6, 6, true),
                                          BRQ_MID(4, 3, 4, 4, true), BRQ_MID(2, 5, 6, 4, true)};
 #undef BRQ_MID
-static const Variant& variant(int tile, bool both_tiled) { return both_tiled ? singles[tile] : pairs[tile]; }
 
 }  // namespace mid
 
+bool mid_gemm_pairs(int tile, bool both_tiled, int64_t K) { return !both_tiled && (K > 1024 || tile > 2); }
+
 hipError_t setup_gemm_mid() {
     for (int i = 0; i < 2 * MID_TILES; ++i) {
-        const mid::Variant& v = mid::variant(i / 2, i % 2 != 0);
+        const mid::Variant& v = (i % 2 ? mid::singles : mid::pairs)[i / 2];
         for (mid::Kern k : {v.bf16, v.f32})
             if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                    mid::lds_bytes(v.na, v.mb, v.dw, v.da)); e != hipSuccess) return e;
@@ -441,7 +447,7 @@ hipError_t setup_gemm_mid() {
 // Whole superstages, or both operands row-major with K a multiple of 128 and at least one superstage.  A lane's offset
 // inside the tile, below 64 max(NA, MB) rows of Kp / 2 bytes, has 32 bits, and the offset along K 31 (32 Kp bytes).
 bool mid_gemm_supported(int tile, const GemmShape& g) {
-    const mid::Variant& v = mid::variant(tile, g.a_tiled && g.w_tiled);
+    const mid::Variant& v = mid::singles[tile];
     const int64_t Kp = g.padded_k(), slabs = v.na > v.mb ? v.na : v.mb;
     return g.M > 0 && g.N > 0 && (g.whole_k() || (!g.a_tiled && !g.w_tiled && g.K % 128 == 0 && g.K >= 512)) &&
            Kp < (int64_t(1) << 26) && slabs * 32 * Kp <= (int64_t(1) << 32);
@@ -449,7 +455,7 @@ bool mid_gemm_supported(int tile, const GemmShape& g) {
 
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s) {
-    const mid::Variant& v = mid::variant(tile, a.tiled && w.tiled);
+    const mid::Variant& v = (mid_gemm_pairs(tile, a.tiled && w.tiled, K) ? mid::pairs : mid::singles)[tile];
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
     const int es = out_bf16 ? 2 : 4, lines = N * es % 16 == 0 && rows_on(64, reinterpret_cast<uintptr_t>(y), ldy * es);
     hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.dw, v.da), s,

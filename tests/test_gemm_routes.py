@@ -24,6 +24,8 @@ def route(M, N, K, layout="tiled", dtype=BF16, **kw):
     # ragged rows and columns, and K of one superstage, on the persistent kernel
     ((4100, 14344, 4096), "tiled", "256x256"), ((5000, 8200, 4096), "tiled", "256x256"), ((5000, 8200, 4096), "rowmajor", "256x256"),
     ((8192, 14336, 512), "rowmajor", "256x256"),
+    # short K of row-major operands: single stages of 128 x 128, two workgroups a CU
+    ((4000, 8192, 512), "rowmajor", "128x128"), ((787, 17600, 512), "rowmajor", "128x128"), ((1100, 1000, 512), "rowmajor", "64x128"),
     # N or K that no staged kernel takes
     ((300, 520, 96), "rowmajor", "general"), ((40, 70, 256), "rowmajor", "general"), ((4, 70, 1056), "rowmajor", "skinny")])
 def test_route(shape, layout, want):
@@ -75,7 +77,7 @@ def test_long_k_stays_on_a_staged_kernel(layout):
     assert route(300, 130, 2 ** 25 + 512, layout=layout) in ("64x128", "128x128", "192x128")
 
 
-@pytest.mark.parametrize("shape,on,off", [((8108, 6976, 512), "256x256", "128x256"), ((4434, 4224, 2048), "192x256", "320x128")])
+@pytest.mark.parametrize("shape,on,off", [((6812, 3520, 2048), "192x256", "256x256"), ((4434, 4224, 2048), "192x256", "320x128")])
 def test_an_output_that_begins_off_a_line_is_one_off_lines(shape, on, off, tmp_path):
     """The product's rows lie off 128-byte lines by their pitch or by where the output begins: the same choice of tile.
     (The public call has no address: the library's own is compiled against here.)"""
