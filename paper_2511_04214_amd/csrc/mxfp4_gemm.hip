@@ -144,29 +144,93 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 // banks), scales [tile][64 rows][16 bytes].  Output: lane (r, h) holds D[8 q + 4 h + i][r] for
 // weight row n0 + r, so the 32 lanes of a half store 32 consecutive columns of one output row.
 
+// A wavefront's 32 weight rows, a superstage at a time in 8 registers of 16 bytes per lane, and the fragments from them.
+// Tiled weights: a row's 64 bytes of a stage lie between those of its neighbours, so lane (r, h) loads its fragments
+// directly, 2 KB by two instructions.  Plain loads: one instruction takes half of every cache line it touches and the next
+// one the other half, and a streaming load does not leave the line in the cache for it (the weights would cross HBM twice).
+// Row-major weights (ROWS): a fragment is 32 rows x 32 bytes, a quarter of each of 32 lines, and by the time the fourth
+// instruction asks for the last quarter the other wavefronts' lines have pushed it out.  There an instruction loads 8
+// rows x 128 bytes, whole lines and once, and the wavefront turns the four of two stages round in 4 KB of LDS that no other
+// touches (row i's 16-byte chunk c at c ^ (i & 7): 8 lanes write a row, 8 rows' chunks are read, all banks either way).  A
+// wavefront's LDS operations are done in order, so nothing waits there but for the data.  us, weights in no cache, 1 row,
+// each lane its fragments -> now: 28672 x 8192 36.1 -> 28.5 (with the streaming hint; without 30.5), 14336 x 4096 10.0 -> 8.8, 2048 x 8192
+// 8.8 -> 8.4; the one-launch call, 28672 x 8192 36.6 -> 28.1, 21752 x 10240 42.2 -> 27.3.  Tiled weights 24.
+template <bool ROWS>
+struct WeightRows {
+    const uint8_t* codes;                               // tiled: this lane's row.  ROWS: the first row (uniform), `off` from there
+    const uint8_t* scales;                              // this lane's row
+    uint32_t cstep, sstep, off[4];
+    uint8_t *wr, *rd;                                   // ROWS: this lane's place in the 4 KB
+    uint32_t sw;
+    int h;
+    __device__ __forceinline__ WeightRows(const uint8_t* wq, const uint8_t* ws, int n0, int N, int K, int lane, uint8_t* turn_lds) {
+        const int r = lane & 31;
+        h = lane >> 5;
+        const RowView v(wq, ws, !ROWS, min(n0 + r, N - 1), K);
+        scales = v.scales;
+        cstep = v.cstep;
+        sstep = v.sstep;
+        if constexpr (ROWS) {
+            const int first = min(n0, N - 1);           // (uniform; a wavefront without columns of its own reads the last one)
+            codes = wq + (int64_t)first * (K / 2);
+            const int i = lane >> 3, c = lane & 7;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) off[q] = (uint32_t)min(8 * q + i, N - 1 - first) * (uint32_t)(K / 2) + (uint32_t)c * 16;
+            wr = turn_lds + i * 128 + ((c ^ i) << 4);
+            rd = turn_lds + r * 128;
+            sw = (uint32_t)(r & 7);
+        } else {
+            codes = v.codes;
+            // (a 4096 that the compiler sees lets it take a line's two halves apart)
+            asm("" : "+s"(cstep));
+        }
+    }
+    __device__ __forceinline__ void load(int ss, v4i (&c)[8], v4i& sc) const {
+        if constexpr (ROWS) {
+            const uint8_t* b = codes + (int64_t)ss * 256;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) c[i] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(b + off[i & 3] + (i >> 2) * 128));
+            sc = *reinterpret_cast<const v4i*>(scales + (int64_t)ss * 16);   // (a line holds those of 8 superstages)
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) c[i] = *reinterpret_cast<const v4i*>(codes + (int64_t)(4 * ss + (i >> 1)) * cstep + h * 32 + (i & 1) * 16);
+            sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(scales + (int64_t)ss * sstep));
+        }
+    }
+    // ROWS: the fragments of steps 4 half .. 4 half + 3 (stage 2 half + t, step j at 2 t + j).  (Tiled: c[step].)
+    __device__ __forceinline__ void turn(const v4i (&c)[8], int half, v4i (&f)[4]) const {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<v4i*>(wr + q * 1024) = c[4 * half + q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const v4i*>(rd + ((((uint32_t)(4 * (i >> 1) + 2 * h + (i & 1))) ^ sw) << 4));
+    }
+};
+constexpr int turn_bytes(bool rows) { return rows ? 4 * 4096 : 0; }
+
 // Weight register sets = LDS buffers of A; SETS - 1 superstages are in flight.
 constexpr int smallm_buf_bytes = 4096 + 4096;
-constexpr int smallm_lds_bytes(int sets) { return sets * smallm_buf_bytes; }
+constexpr int smallm_lds_bytes(int sets, bool rows) { return sets * smallm_buf_bytes + turn_bytes(rows); }
 
 // TAIL = (K / 512) % SETS: the superstages left after the main loop, which takes them SETS at a time in
 // one basic block (no load behind a branch: the compiler's count of the outstanding weight loads is
 // then exact; with early exits inside the loop it falls back to waiting for all of them).
-template <int SETS, int TAIL>
+template <bool ROWS, int SETS, int TAIL>
 __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as,
                                                      int a_tiled, const uint8_t* __restrict__ wq,
-                                                     const uint8_t* __restrict__ ws, int w_tiled, int M, int N, int K,
+                                                     const uint8_t* __restrict__ ws, int M, int N, int K,
                                                      void* __restrict__ y, int out_bf16, int64_t ldy, int nw) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int STG = 1024;                           // one stage of A codes: 16 rows x 64 bytes
     constexpr int BUF = smallm_buf_bytes;               // codes [4 stages][16 rows][64], then scales, 1 KB per wavefront
     constexpr int NA = 2;                               // LDS-DMA instructions per wavefront and superstage
+    load_args(aq, as, a_tiled, wq, ws, M, N, K, y, out_bf16, ldy, nw);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
     const int n0 = (blockIdx.x * nw + wave) * 32;       // (of the first nw wavefronts)
     const int nss = (K + 511) / 512;                    // tiled operands are zero-padded to whole superstages
     const int64_t Kp = (int64_t)nss * 512;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-    const RowView vw(wq, ws, w_tiled != 0, min(n0 + r, N - 1), K);
+    const WeightRows<ROWS> vw(wq, ws, n0, N, K, lane, lds + SETS * BUF + wave * 4096);
 
     const uint32_t a_cstep = a_tiled ? 4096u : 64u, a_sstep = a_tiled ? 1024u : 16u;
     auto row_off_c = [&](int row) -> uint32_t {
@@ -190,17 +254,6 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
         dma16<0>(lb, cb, voc);
         dma16<0>(lds0 + buf * BUF + 4 * STG + (uint32_t)wave * 1024, uniform_ptr(as + (int64_t)ss * a_sstep), vos);
     };
-    // a superstage of this lane's weight row: per stage t its two steps (32 bytes at 32 h), and the 16 scale bytes.
-    // Plain loads: one instruction takes half of every cache line it touches and the next one the other half,
-    // and a streaming load does not leave the line in the cache for it (the weights would cross HBM twice).
-    auto load_w = [&](int ss, v4i (&c)[8], v4i& sc) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                c[2 * t + j] = *reinterpret_cast<const v4i*>(vw.codes + (int64_t)(4 * ss + t) * vw.cstep + h * 32 + j * 16);
-        sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(vw.scales + (int64_t)ss * vw.sstep));
-    };
     v16f acc = {};
     const uint32_t ra = (uint32_t)r & 15u;              // lanes 16..31 of a half repeat rows 0..15: never stored
     const uint32_t sw = (ra >> 2) & 3u;
@@ -208,7 +261,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     auto superstage = [&](uint32_t buf, const v4i (&c)[8], const v4i& sc) {
         const uint8_t* cb = lds + buf * BUF + ra * 64;
         const v4i asc = *reinterpret_cast<const v4i*>(lds + buf * BUF + 4 * STG + ra * 16);
-        v4i af[2];
+        v4i af[2], wf[4];
         auto read_step = [&](int st) -> v4i {
             return *reinterpret_cast<const v4i*>(cb + (st >> 1) * STG + (((uint32_t)(2 * h + (st & 1)) ^ sw) << 4));
         };
@@ -216,13 +269,15 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
 #pragma unroll
         for (int st = 0; st < 8; ++st) {
             const int t = st >> 1, j = st & 1;
+            if constexpr (ROWS) { if (st % 4 == 0) vw.turn(c, st / 4, wf); }
             if (st + 1 < 8) af[(st + 1) & 1] = read_step(st + 1);
             __builtin_amdgcn_sched_barrier(0);   // keeps the read ahead of this step's MFMA
             // group 4 t + 2 h + j of the superstage: byte 2 h + j of scale dword t
             const int scb = (int)(((uint32_t)sc[t] >> (16 * h + 8 * j)) & 0xffu);
             const int sca = (int)(((uint32_t)asc[t] >> (16 * h + 8 * j)) & 0xffu);
             v8i a = {}, b = {};
-            b[0] = c[st][0]; b[1] = c[st][1]; b[2] = c[st][2]; b[3] = c[st][3];
+            const v4i w = ROWS ? wf[st & 3] : c[st];
+            b[0] = w[0]; b[1] = w[1]; b[2] = w[2]; b[3] = w[3];
             a[0] = af[st & 1][0]; a[1] = af[st & 1][1]; a[2] = af[st & 1][2]; a[3] = af[st & 1][3];
             acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 4, 4, 0, sca, 0, scb);
         }
@@ -252,7 +307,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
 #pragma unroll
     for (int i = 0; i < D; ++i) {
         dma_a(min(i, nss - 1), (uint32_t)i);
-        load_w(min(i, nss - 1), c[i], s4[i]);
+        vw.load(min(i, nss - 1), c[i], s4[i]);
     }
     // k = the turn's register set and LDS buffer (superstage mod SETS), G = superstages in flight behind it
     auto turn = [&](auto Kc, auto Gc, auto Issue, int ss) {
@@ -272,7 +327,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
         if constexpr (decltype(Issue)::value) {
             const int nx = min(ss + D, nss - 1);
             dma_a(nx, (uint32_t)kn);
-            load_w(nx, c[kn], s4[kn]);
+            vw.load(nx, c[kn], s4[kn]);
         }
         __builtin_amdgcn_sched_barrier(0);
         superstage((uint32_t)k, c[k], s4[k]);
@@ -306,12 +361,13 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
 // for bit that of brq_mxfp4_gemm on the output of brq_rotate_quantize_fused.  The first superstages of
 // weights are requested before the prologue and arrive under it.  What this saves is one small launch; what
 // it costs is that every one of the N / (32 nw) workgroups repeats the quantization of the same activations.
-constexpr int decode_fused_lds_bytes(int64_t K) { return (int)(K / 128 * 1024 + K / 512 * 256); }
+constexpr __host__ __device__ int decode_fused_operand_bytes(int64_t K) { return (int)(K / 128 * 1024 + K / 512 * 256); }
+constexpr int decode_fused_lds_bytes(int64_t K, bool rows) { return decode_fused_operand_bytes(K) + turn_bytes(rows); }
 
-template <bool IN_BF16, int SETS, int TAIL>
+template <bool IN_BF16, bool ROWS, int SETS, int TAIL>
 __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restrict__ x, int64_t ldx, const int8_t* __restrict__ signs,
                                                            const uint8_t* __restrict__ wq, const uint8_t* __restrict__ ws,
-                                                           int w_tiled, int M, int N, int K, void* __restrict__ y, int out_bf16,
+                                                           int M, int N, int K, void* __restrict__ y, int out_bf16,
                                                            int64_t ldy, int nw) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -319,15 +375,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
     const int n0 = (blockIdx.x * nw + (wave & (nw - 1))) * 32;      // (from wavefront nw on: another's rows, to no use)
     const int nss = K / 512;
     uint8_t* const scl = lds + (K / 128) * 1024;          // scales behind the codes
-    const RowView vw(wq, ws, w_tiled != 0, min(n0 + r, N - 1), K);
-    auto load_w = [&](int ss, v4i (&c)[8], v4i& sc) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                c[2 * t + j] = *reinterpret_cast<const v4i*>(vw.codes + (int64_t)(4 * ss + t) * vw.cstep + h * 32 + j * 16);
-        sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(vw.scales + (int64_t)ss * vw.sstep));
-    };
+    const WeightRows<ROWS> vw(wq, ws, n0, N, K, lane, lds + decode_fused_operand_bytes(K) + wave * 4096);
     constexpr int D = SETS - 1;
     v4i c[SETS][8], s4[SETS];
     // ---- prologue: the online step on all M rows.  A wavefront takes 64 chunks (512 elements: one
@@ -378,7 +426,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
         fetch((uint32_t)wave * 64u);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < D; ++i) load_w(min(i, nss - 1), c[i], s4[i]);
+        for (int i = 0; i < D; ++i) vw.load(min(i, nss - 1), c[i], s4[i]);
         __builtin_amdgcn_sched_barrier(0);
         quantize((uint32_t)wave * 64u);
         for (uint32_t cb0 = (uint32_t)wave * 64u + 256u * U; cb0 < nchunks; cb0 += 256u * U) quantize(cb0);
@@ -397,17 +445,19 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
     auto superstage = [&](int ss, const v4i (&cw)[8], const v4i& sc) {
         const uint8_t* cbase = lds + (uint32_t)ss * 4096u + ra * 64u;
         const v4i asc = *reinterpret_cast<const v4i*>(scl + (uint32_t)ss * 256u + ra * 16u);
-        v4i af[2];
+        v4i af[2], wf[4];
         af[0] = *reinterpret_cast<const v4i*>(cbase + (((uint32_t)(2 * h) ^ sw) << 4));
 #pragma unroll
         for (int st = 0; st < 8; ++st) {
             const int t = st >> 1, j = st & 1;
+            if constexpr (ROWS) { if (st % 4 == 0) vw.turn(cw, st / 4, wf); }
             if (st + 1 < 8) af[(st + 1) & 1] = *reinterpret_cast<const v4i*>(cbase + ((st + 1) >> 1) * 1024 + (((uint32_t)(2 * h + ((st + 1) & 1)) ^ sw) << 4));
             __builtin_amdgcn_sched_barrier(0);
             const int scb = (int)(((uint32_t)sc[t] >> (16 * h + 8 * j)) & 0xffu);
             const int sca = (int)(((uint32_t)asc[t] >> (16 * h + 8 * j)) & 0xffu);
             v8i a = {}, b = {};
-            b[0] = cw[st][0]; b[1] = cw[st][1]; b[2] = cw[st][2]; b[3] = cw[st][3];
+            const v4i w = ROWS ? wf[st & 3] : cw[st];
+            b[0] = w[0]; b[1] = w[1]; b[2] = w[2]; b[3] = w[3];
             a[0] = af[st & 1][0]; a[1] = af[st & 1][1]; a[2] = af[st & 1][2]; a[3] = af[st & 1][3];
             acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 4, 4, 0, sca, 0, scb);
         }
@@ -416,7 +466,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
     // SETS turns and every load is visible to the compiler, whose wait counts are then exact.
     auto turn = [&](auto Kc, auto Issue, int ss) {
         constexpr int k = decltype(Kc)::value, kn = (k + D) % SETS;
-        if constexpr (decltype(Issue)::value) load_w(min(ss + D, nss - 1), c[kn], s4[kn]);
+        if constexpr (decltype(Issue)::value) vw.load(min(ss + D, nss - 1), c[kn], s4[kn]);
         __builtin_amdgcn_sched_barrier(0);
         superstage(ss, c[k], s4[k]);
         __builtin_amdgcn_sched_barrier(0);
@@ -487,15 +537,20 @@ hipError_t launch_mfma_ceiling(const uint8_t* operands, int iters, int workgroup
     return hipGetLastError();
 }
 
-using SmallmKern = void (*)(const uint8_t*, const uint8_t*, int, const uint8_t*, const uint8_t*, int, int, int, int, void*,
-                            int, int64_t, int);
+using SmallmKern = void (*)(const uint8_t*, const uint8_t*, int, const uint8_t*, const uint8_t*, int, int, int, void*, int, int64_t, int);
 constexpr int FEW = 3, MANY = 5;      // register sets
-static const SmallmKern smallm_few[FEW] = {k_gemm_smallm<FEW, 0>, k_gemm_smallm<FEW, 1>, k_gemm_smallm<FEW, 2>};
-static const SmallmKern smallm_many[MANY] = {k_gemm_smallm<MANY, 0>, k_gemm_smallm<MANY, 1>, k_gemm_smallm<MANY, 2>, k_gemm_smallm<MANY, 3>,
-                                             k_gemm_smallm<MANY, 4>};
-using DecodeKern = void (*)(const void*, int64_t, const int8_t*, const uint8_t*, const uint8_t*, int, int, int, int, void*, int, int64_t, int);
-static const DecodeKern decode_kern[2][FEW] = {{k_gemm_decode_fused<false, FEW, 0>, k_gemm_decode_fused<false, FEW, 1>, k_gemm_decode_fused<false, FEW, 2>},
-                                               {k_gemm_decode_fused<true, FEW, 0>, k_gemm_decode_fused<true, FEW, 1>, k_gemm_decode_fused<true, FEW, 2>}};
+#define BRQ_FEW(ROWS) {k_gemm_smallm<ROWS, FEW, 0>, k_gemm_smallm<ROWS, FEW, 1>, k_gemm_smallm<ROWS, FEW, 2>}
+#define BRQ_MANY(ROWS) {k_gemm_smallm<ROWS, MANY, 0>, k_gemm_smallm<ROWS, MANY, 1>, k_gemm_smallm<ROWS, MANY, 2>, k_gemm_smallm<ROWS, MANY, 3>, \
+                        k_gemm_smallm<ROWS, MANY, 4>}
+static const SmallmKern smallm_few[2][FEW] = {BRQ_FEW(false), BRQ_FEW(true)};          // [weights row-major][K / 512 % sets]
+static const SmallmKern smallm_many[2][MANY] = {BRQ_MANY(false), BRQ_MANY(true)};
+#undef BRQ_FEW
+#undef BRQ_MANY
+using DecodeKern = void (*)(const void*, int64_t, const int8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int, int64_t, int);
+#define BRQ_DECODE(BF16, ROWS) {k_gemm_decode_fused<BF16, ROWS, FEW, 0>, k_gemm_decode_fused<BF16, ROWS, FEW, 1>, k_gemm_decode_fused<BF16, ROWS, FEW, 2>}
+static const DecodeKern decode_kern[2][2][FEW] = {{BRQ_DECODE(false, false), BRQ_DECODE(false, true)},   // [x bf16][weights row-major]
+                                                  {BRQ_DECODE(true, false), BRQ_DECODE(true, true)}};
+#undef BRQ_DECODE
 
 // Wavefronts of a streaming workgroup that own columns, 32 each: as many as still leave every compute unit a workgroup. A
 // CU's address path takes the four wavefronts' weight loads one after the other (half lines, 32 cycles each: 1150 cycles per
@@ -508,10 +563,11 @@ static const DecodeKern decode_kern[2][FEW] = {{k_gemm_decode_fused<false, FEW, 
 static int streaming_waves(int64_t N, int cus) { return N <= (int64_t)32 * cus ? 1 : N <= (int64_t)64 * cus ? 2 : 4; }
 
 hipError_t setup_gemm_decode_fused() {
-    for (const auto& row : decode_kern)
-        for (DecodeKern k : row)
-            if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, decode_fused_lds_bytes(DECODE_FUSED_MAX_K));
-                e != hipSuccess) return e;
+    for (const auto& in : decode_kern)
+        for (int rows = 0; rows < 2; ++rows)
+            for (DecodeKern k : in[rows])
+                if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, decode_fused_lds_bytes(DECODE_FUSED_MAX_K, rows));
+                    e != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -520,8 +576,8 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
     int cus = 0;
     if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
     const int nw = streaming_waves(N, cus);
-    hipLaunchKernelGGL(decode_kern[in_bf16][K / 512 % FEW], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256), decode_fused_lds_bytes(K), s,
-                       x, ldx, signs, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy, nw);
+    hipLaunchKernelGGL(decode_kern[in_bf16][!w.tiled][K / 512 % FEW], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256),
+                       decode_fused_lds_bytes(K, !w.tiled), s, x, ldx, signs, w.codes, w.scales, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy, nw);
     return hipGetLastError();
 }
 
@@ -595,27 +651,28 @@ bool gemm_route_supported(int route, const GemmShape& g) {
     }
 }
 
+// Whether the 64 x 128 tile of this shape is one of the streaming kernel's workgroups: up to 16 rows, row-major weights.
+static bool few_rows(const GemmShape& g) { return !g.w_tiled && gemm_route_supported(ROUTE_STREAM, g); }
+
 int gemm_route(const GemmShape& g, int cus) {
-    // Up to 16 rows: weight streaming where the weights are tiled, or row-major with K of a single superstage; other
-    // row-major weights go to the one-tile kernel, which takes their half lines through the LDS ring.  Weight streaming : the
-    // 64 x 128 tile : the K-split kernel (ROUTE_SKINNY, which sums in another order), us, weights in no cache, 1 / 16 rows:
+    // Up to 16 rows: the weights are streamed (k_gemm_smallm), tiled ones and row-major ones of one superstage under that
+    // name, other row-major ones under the name of the tile that its workgroups then are (few_rows below).  The staged 64 x 128
+    // kernel and the K-split one (ROUTE_SKINNY, which sums in another order) against it, us, weights in no cache, 1 / 16 rows,
+    // streaming : 64 x 128 : K-split:
     //   weights tiled      N x K = 256 x 512 2.4 / 2.8 : 3.5 / 3.6 : 2.0 / 2.4,  2048 x 2048 4.0 / 4.3 : 5.9 / 5.9 : 3.8 / 4.2,
     //                      2048 x 8192 7.4 / 7.9 : 13.9 / 14.7 : 11.7 / 12.0,  8192 x 4096 7.3 / 7.6 : 9.4 / 9.7 : 8.0 / 8.3,
     //                      28672 x 2048 8.7 / 9.0 : 8.7 / 8.7 : 9.1 / 10.4,  28672 x 8192 24.9 / 25.3 : 25.5 / 25.8 : 30.6 / 33.3
-    //   weights row-major  256 x 512 2.6 / 2.9 : 3.6 / 3.8 : 2.0 / 2.5,  28672 x 512 4.7 / 5.0 : 5.7 / 5.6 : 4.3 / 5.3,
-    //                      28672 x 1024 6.4 / 6.9 : 7.0 / 7.1 : 6.8 / 8.1,  28672 x 2048 10.5 / 11.0 : 9.7 / 9.9 : 11.4 / 13.1,
-    //                      28672 x 8192 38.0 / 36.8 : 32.6 / 31.1 : 38.0 / 42.8
-    // That line for row-major weights is right where four wavefronts of a workgroup stream (N above 64 columns a CU).  Below, it
-    // is older than workgroups that own 32 or 64 columns, and streaming would be the faster: 2048 x 8192 9.0 / 9.9 : 18.8 / 19.3 :
-    // 12.6 / 13.0,  4096 x 4096 6.6 / 7.2 : 11.5 / 11.8 : 7.9 / 8.1,  8192 x 4096 7.2 / 7.6 : 11.8 / 12.1 : 8.6 / 9.0,  14336 x 8192
-    // 18.4 / 17.6 : 23.3 / 21.9 : 19.8 / 24.8.
-    if (gemm_route_supported(ROUTE_STREAM, g) && (g.w_tiled || g.K <= 512 || !gemm_route_supported(ROUTE_ONE_TILE, g))) return ROUTE_STREAM;
+    //   weights row-major  64 x 512 2.4 / 2.7 : 3.5 / 3.5,  28672 x 512 4.4 / 4.8 : 5.2 / 5.2 : 4.3 / 5.3,  28672 x 1024 6.2 / 6.6 :
+    //                      6.6 / 6.7 : 6.8 / 8.1,  28672 x 2048 8.7 / 9.1 : 9.7 / 9.9 : 11.4 / 13.1,  28672 x 8192 28.5 / 29.3 : 31.2 /
+    //                      31.3 : 38.0 / 42.8,  2048 x 8192 8.4 / 8.7 : 18.6 / 19.2 : 12.6 / 13.0,  14336 x 4096 8.8 / 9.4 : 12.4 / 12.9
+    if (gemm_route_supported(ROUTE_STREAM, g)) return g.w_tiled || g.K <= 512 || !gemm_route_supported(ROUTE_ONE_TILE, g) ? ROUTE_STREAM : ROUTE_ONE_TILE;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
     return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
 }
 
 hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {
     const int64_t M = g.M, N = g.N, K = g.K;
+    if (route == ROUTE_ONE_TILE && few_rows(g)) route = ROUTE_STREAM;
     switch (route) {
         case ROUTE_GENERAL: {
             const dim3 grid((uint32_t)((N + 63) / 64), (uint32_t)((M + 63) / 64));
@@ -632,9 +689,9 @@ hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, cons
             if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
             const int64_t nss = g.padded_k() / 512;
             const int nw = streaming_waves(N, cus), sets = nw == 1 && nss >= MANY ? MANY : FEW;
-            hipLaunchKernelGGL((sets == MANY ? smallm_many : smallm_few)[nss % sets], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256), smallm_lds_bytes(sets),
-                               s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y,
-                               (int)g.out_bf16, g.ldy, nw);
+            const SmallmKern* const kern = sets == MANY ? smallm_many[!w.tiled] : smallm_few[!w.tiled];
+            hipLaunchKernelGGL(kern[nss % sets], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256), smallm_lds_bytes(sets, !w.tiled),
+                               s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy, nw);
             return hipGetLastError();
         }
         case ROUTE_256x256:
