@@ -153,8 +153,9 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 // rows x 128 bytes, whole lines and once, and the wavefront turns the four of two stages round in 4 KB of LDS that no other
 // touches (row i's 16-byte chunk c at c ^ (i & 7): 8 lanes write a row, 8 rows' chunks are read, all banks either way).  A
 // wavefront's LDS operations are done in order, so nothing waits there but for the data.  us, weights in no cache, 1 row,
-// each lane its fragments -> now: 28672 x 8192 36.1 -> 28.5 (with the streaming hint; without 30.5), 14336 x 4096 10.0 -> 8.8, 2048 x 8192
-// 8.8 -> 8.4; the one-launch call, 28672 x 8192 36.6 -> 28.1, 21752 x 10240 42.2 -> 27.3.  Tiled weights 24.
+// each lane its fragments -> now: 28672 x 8192 36.1 -> 30.5 (tiled weights 24), 14336 x 4096 10.0 -> 9.3; the one-launch call, 28672 x
+// 8192 36.6 -> 30.2, 21752 x 10240 42.2 -> 28.9.  No streaming hint here either: with it 28.5, 8.8, 28.1, 27.3, but weights that lie in the
+// memory-side cache are then fetched past it (both calls, 15 rows against the same 23808 x 4096: 13.4 : 14.9).
 template <bool ROWS>
 struct WeightRows {
     const uint8_t* codes;                               // tiled: this lane's row.  ROWS: the first row (uniform), `off` from there
@@ -189,7 +190,7 @@ struct WeightRows {
         if constexpr (ROWS) {
             const uint8_t* b = codes + (int64_t)ss * 256;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) c[i] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(b + off[i & 3] + (i >> 2) * 128));
+            for (int i = 0; i < 8; ++i) c[i] = *reinterpret_cast<const v4i*>(b + off[i & 3] + (i >> 2) * 128);
             sc = *reinterpret_cast<const v4i*>(scales + (int64_t)ss * 16);   // (a line holds those of 8 superstages)
         } else {
 #pragma unroll
@@ -662,9 +663,9 @@ int gemm_route(const GemmShape& g, int cus) {
     //   weights tiled      N x K = 256 x 512 2.4 / 2.8 : 3.5 / 3.6 : 2.0 / 2.4,  2048 x 2048 4.0 / 4.3 : 5.9 / 5.9 : 3.8 / 4.2,
     //                      2048 x 8192 7.4 / 7.9 : 13.9 / 14.7 : 11.7 / 12.0,  8192 x 4096 7.3 / 7.6 : 9.4 / 9.7 : 8.0 / 8.3,
     //                      28672 x 2048 8.7 / 9.0 : 8.7 / 8.7 : 9.1 / 10.4,  28672 x 8192 24.9 / 25.3 : 25.5 / 25.8 : 30.6 / 33.3
-    //   weights row-major  64 x 512 2.4 / 2.7 : 3.5 / 3.5,  28672 x 512 4.4 / 4.8 : 5.2 / 5.2 : 4.3 / 5.3,  28672 x 1024 6.2 / 6.6 :
-    //                      6.6 / 6.7 : 6.8 / 8.1,  28672 x 2048 8.7 / 9.1 : 9.7 / 9.9 : 11.4 / 13.1,  28672 x 8192 28.5 / 29.3 : 31.2 /
-    //                      31.3 : 38.0 / 42.8,  2048 x 8192 8.4 / 8.7 : 18.6 / 19.2 : 12.6 / 13.0,  14336 x 4096 8.8 / 9.4 : 12.4 / 12.9
+    //   weights row-major  64 x 512 2.4 / 2.7 : 3.5 / 3.5,  28672 x 512 4.6 / 5.0 : 5.2 / 5.2 : 4.3 / 5.3,  28672 x 1024 6.4 / 6.8 :
+    //                      6.6 / 6.7 : 6.8 / 8.1,  28672 x 2048 9.1 / 9.6 : 9.7 / 9.9 : 11.4 / 13.1,  28672 x 8192 30.5 / 31.1 : 31.2 /
+    //                      31.3 : 38.0 / 42.8,  2048 x 8192 8.7 / 9.1 : 18.6 / 19.2 : 12.6 / 13.0,  14336 x 4096 9.3 / 9.8 : 12.4 / 12.9
     if (gemm_route_supported(ROUTE_STREAM, g)) return g.w_tiled || g.K <= 512 || !gemm_route_supported(ROUTE_ONE_TILE, g) ? ROUTE_STREAM : ROUTE_ONE_TILE;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
     return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
