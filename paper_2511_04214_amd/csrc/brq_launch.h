@@ -106,6 +106,10 @@ bool mid_gemm_pairs(int tile, bool both_tiled, int64_t K);       // whether it l
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s);
 
+// The same for any K of at least 256 elements and any mix of layouts, 64 or 128 rows x 128 columns a workgroup.
+hipError_t launch_gemm_any_k(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y, bool out_bf16, int64_t ldy,
+                             hipStream_t s);
+
 // Tiled -> row-major copy of a quantized operand.
 hipError_t launch_to_rowmajor(const uint8_t* codes_t, const uint8_t* scales_t, int64_t rows, int64_t K,
                               uint8_t* codes, uint8_t* scales, hipStream_t s);

@@ -676,6 +676,13 @@ hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, cons
     if (route == ROUTE_ONE_TILE && few_rows(g)) route = ROUTE_STREAM;
     switch (route) {
         case ROUTE_GENERAL: {
+            // Through LDS from where its pairs of stages have something to hide behind: enough of them, or enough tiles.  us,
+            // row-major, weights in no cache, k_gemm_direct : k_gemm_any_k, either side of the line: M x N x K = 1000 x 512 x 2080
+            // 10.9 : 12.3, 300 x 512 x 4000 18.2 : 18.7, 300 x 2048 x 1056 7.2 : 8.7, 128 x 8192 x 1056 10.0 : 9.8, 1000 x 4096 x 288
+            // 8.1 : 7.3, 1000 x 8192 x 544 21.3 : 11.9, 128 x 2048 x 10976 84 : 43; of 64 rows 64 x 1024 x 1056 6.8 : 6.8, 64 x
+            // 1024 x 2080 12.0 : 9.0, 64 x 16384 x 544 6.9 : 6.7.
+            const int64_t tiles = (M + (M <= 64 ? 63 : 127)) / (M <= 64 ? 64 : 128) * ((N + 127) / 128);
+            if (K >= 256 && (K >= (M <= 64 ? 2048 : 4096) || tiles * K >= 65536)) return launch_gemm_any_k(a, w, M, N, K, y, g.out_bf16, g.ldy, s);
             const dim3 grid((uint32_t)((N + 63) / 64), (uint32_t)((M + 63) / 64));
             hipLaunchKernelGGL(k_gemm_direct, grid, dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales,
                                (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);

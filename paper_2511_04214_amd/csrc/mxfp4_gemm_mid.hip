@@ -59,7 +59,6 @@ namespace mid {
 constexpr int scale_bufs(int DW) { return (DW + 3) / 4; }
 constexpr int lds_bytes(int NA, int MB, int DW, int DA) { return 4096 * (NA * DW + MB * DA) + scale_bufs(DW) * 1024 * (NA + MB); }
 
-// DW == DA unless PAIR.
 // lines: the output's rows begin on half lines of 64 bytes, and the streaming hint goes with every store.  Where they do not,
 // a store of 128 bytes is the end of one line and the beginning of the next, in pieces of 16 or 32 bytes more or less: with
 // the hint such pieces go to memory as they are, without it the L2 puts the line together.  (Halves of lines it had better
@@ -67,6 +66,73 @@ constexpr int lds_bytes(int NA, int MB, int DW, int DA) { return 4096 * (NA * DW
 // are not 16-byte aligned are stored in the same way (the memory system takes any alignment); only a row's last N % (16 /
 // sizeof(out)) elements go one by one.  128 x 128, us, before -> now: 600 x 6004 x 4096 bf16 (rows on 8 bytes, element by
 // element before) 18.9 -> 13.5, fp32 (the hint before) 17.1 -> 14.7; 600 x 6016 x 4096 12.7.
+// The output of a workgroup's tile, 64 MB rows from m0 on and 64 NA columns from n0 on.  `lds`: 16 KB that nobody reads any more.
+template <bool OUT_BF16, int NA, int MB>
+__device__ __forceinline__ void store_tile(v16f (&acc)[NA][MB], uint8_t* lds, void* y, int64_t ldy, int64_t m0, int64_t n0, int M, int N, int lines) {
+    constexpr int NM = NA * MB;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5, wn = wave >> 1, wm = wave & 1;
+    // The accumulators were last written by MFMAs hidden in inline assembly: the compiler does not
+    // know to keep the wait states between a 16-pass MFMA and a read of its result.  Each wavefront turns its
+    // 32-row x 128-byte blocks round in 4 KB of the ring (whose last reads are behind the last barrier):
+    // chunk c of row i at i * 128 + ((c ^ (i & 7)) << 4), stored as 8 rows x 128 contiguous bytes.
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    constexpr int ES = OUT_BF16 ? 2 : 4, EPC = 16 / ES, XPB = OUT_BF16 ? 2 : 1;
+    const int64_t pitch = ldy * ES;
+    uint8_t* const ebuf = lds + wave * 4096;
+    uint8_t* const ytile = reinterpret_cast<uint8_t*>(y) + (m0 + wm * 32 * MB) * pitch + (n0 + wn * 32 * NA) * ES;
+    uint8_t* const ewr = ebuf + r * 128;
+    const uint32_t wsw = (uint32_t)((r & 7) ^ h) << 4;
+    const uint8_t* const erd = ebuf + (lane >> 3) * 128 + (((lane & 7) ^ ((lane >> 3) & 7)) << 4);
+    const int64_t mrem = M - m0 - wm * 32 * MB - (lane >> 3), nrem = N - n0 - wn * 32 * NA - (lane & 7) * EPC;
+    static_for([&](auto Xc) __attribute__((always_inline)) {
+        constexpr int X = decltype(Xc)::value, A = PairA<X, MB>::value, B = PairB<X, MB>::value;
+        float c[16];
+        read_acc8(acc[A][B], IC<0>{}, c);
+        read_acc8(acc[A][B], IC<8>{}, c);
+        if constexpr (OUT_BF16) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint32_t x0 = pack_bf16x2(c[8 * p + 0], c[8 * p + 1]), x1 = pack_bf16x2(c[8 * p + 2], c[8 * p + 3]);
+                const uint32_t y0 = pack_bf16x2(c[8 * p + 4], c[8 * p + 5]), y1 = pack_bf16x2(c[8 * p + 6], c[8 * p + 7]);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+                *reinterpret_cast<uint4*>(ewr + (wsw ^ (uint32_t)(((A & 1) * 4 + 2 * p) << 4))) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(ewr + (wsw ^ (uint32_t)(q << 5))) = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+        }
+        if constexpr (X % XPB == XPB - 1) {
+            constexpr int row = B * 32, colbytes = (OUT_BF16 ? A / 2 : A) * 128;
+            uint8_t* const dst = ytile + (row + (lane >> 3)) * pitch + colbytes + (lane & 7) * 16;
+            const int64_t cols = nrem - colbytes / ES;          // columns left from this lane's chunk on
+            typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+            u4 ob[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ob[j] = *reinterpret_cast<const u4*>(erd + j * 1024);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (row + 8 * j < mrem && cols > 0) {
+                    if (lines) {                                // uniform
+                        __builtin_nontemporal_store(ob[j], reinterpret_cast<u4*>(dst + 8 * j * pitch));
+                    } else if (cols >= EPC) {
+                        typedef unsigned int u4_any __attribute__((ext_vector_type(4), aligned(2)));
+                        *reinterpret_cast<u4_any*>(dst + 8 * j * pitch) = ob[j];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < EPC; ++e)
+                            if (e < cols) {
+                                if constexpr (OUT_BF16) reinterpret_cast<uint16_t*>(dst + 8 * j * pitch)[e] = (uint16_t)(ob[j][e >> 1] >> (16 * (e & 1)));
+                                else reinterpret_cast<uint32_t*>(dst + 8 * j * pitch)[e] = ob[j][e];
+                            }
+                    }
+                }
+        }
+    }, IC<NM>{});
+}
+
+// DW == DA unless PAIR.
 template <bool OUT_BF16, int NA, int MB, int DW, int DA, bool PAIR>
 __global__ void __launch_bounds__(256, (lds_bytes(NA, MB, DW, DA) <= 81920 ? 2 : 1))
 k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const uint8_t* __restrict__ wq,
@@ -360,66 +426,131 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     for (int kq = 0; kq < KQ - 1; ++kq) superstage(IC<0>{}, kq);
     superstage(IC<1>{}, KQ - 1);
 
-    // ---- output.  The accumulators were last written by MFMAs hidden in inline assembly: the compiler does not
-    // know to keep the wait states between a 16-pass MFMA and a read of its result.  Each wavefront turns its
-    // 32-row x 128-byte blocks round in 4 KB of the ring (whose last reads are behind the last barrier):
-    // chunk c of row i at i * 128 + ((c ^ (i & 7)) << 4), stored as 8 rows x 128 contiguous bytes.
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    constexpr int ES = OUT_BF16 ? 2 : 4, EPC = 16 / ES, XPB = OUT_BF16 ? 2 : 1;
-    const int64_t pitch = ldy * ES;
-    uint8_t* const ebuf = lds + wave * 4096;
-    uint8_t* const ytile = reinterpret_cast<uint8_t*>(y) + (m0 + wm * 32 * MB) * pitch + (n0 + wn * 32 * NA) * ES;
-    uint8_t* const ewr = ebuf + r * 128;
-    const uint32_t wsw = (uint32_t)((r & 7) ^ h) << 4;
-    const uint8_t* const erd = ebuf + (lane >> 3) * 128 + (((lane & 7) ^ ((lane >> 3) & 7)) << 4);
-    const int64_t mrem = mrows - wm * 32 * MB - (lane >> 3), nrem = nrows - wn * 32 * NA - (lane & 7) * EPC;
-    static_for([&](auto Xc) __attribute__((always_inline)) {
-        constexpr int X = decltype(Xc)::value, A = PairA<X, MB>::value, B = PairB<X, MB>::value;
-        float c[16];
-        read_acc8(acc[A][B], IC<0>{}, c);
-        read_acc8(acc[A][B], IC<8>{}, c);
-        if constexpr (OUT_BF16) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const uint32_t x0 = pack_bf16x2(c[8 * p + 0], c[8 * p + 1]), x1 = pack_bf16x2(c[8 * p + 2], c[8 * p + 3]);
-                const uint32_t y0 = pack_bf16x2(c[8 * p + 4], c[8 * p + 5]), y1 = pack_bf16x2(c[8 * p + 6], c[8 * p + 7]);
-                const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
-                const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
-                *reinterpret_cast<uint4*>(ewr + (wsw ^ (uint32_t)(((A & 1) * 4 + 2 * p) << 4))) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4*>(ewr + (wsw ^ (uint32_t)(q << 5))) = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
-        }
-        if constexpr (X % XPB == XPB - 1) {
-            constexpr int row = B * 32, colbytes = (OUT_BF16 ? A / 2 : A) * 128;
-            uint8_t* const dst = ytile + (row + (lane >> 3)) * pitch + colbytes + (lane & 7) * 16;
-            const int64_t cols = nrem - colbytes / ES;          // columns left from this lane's chunk on
-            typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-            u4 ob[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) ob[j] = *reinterpret_cast<const u4*>(erd + j * 1024);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (row + 8 * j < mrem && cols > 0) {
-                    if (lines) {                                // uniform
-                        __builtin_nontemporal_store(ob[j], reinterpret_cast<u4*>(dst + 8 * j * pitch));
-                    } else if (cols >= EPC) {
-                        typedef unsigned int u4_any __attribute__((ext_vector_type(4), aligned(2)));
-                        *reinterpret_cast<u4_any*>(dst + 8 * j * pitch) = ob[j];
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < EPC; ++e)
-                            if (e < cols) {
-                                if constexpr (OUT_BF16) reinterpret_cast<uint16_t*>(dst + 8 * j * pitch)[e] = (uint16_t)(ob[j][e >> 1] >> (16 * (e & 1)));
-                                else reinterpret_cast<uint32_t*>(dst + 8 * j * pitch)[e] = ob[j][e];
-                            }
-                    }
-                }
-        }
-    }, IC<NM>{});
+    store_tile<OUT_BF16, NA, MB>(acc, lds, y, ldy, m0, n0, M, N, lines);
 }
+
+// ---- any K of at least 256 elements, any mix of layouts: what the kernels above do not take (row-major K that is not a multiple
+// of 128, mixed layouts with K % 512 != 0, K below 512).  A row's scales then begin at any byte and its codes on any 16, which
+// LDS-DMA is not for: tiles of 64 MB x 128 whose operands pass through registers, two pairs of stages ahead, into two halves of LDS (the
+// image of PAIR above), one barrier a pair.  The last pair's groups past K load the last one's codes, in bounds, and have scale
+// byte 0 in both operands.  Same order of summation as everywhere.
+// Bound by the address path, which takes a load by the lines it touches: two stages at once are 8 rows x 128 bytes an instruction,
+// 8 to 16 lines for what takes 32 stage by stage, and a row's scales cost a line whether four or eight are taken.  us, bf16 out,
+// one 32 x 32 tile a wavefront straight from global memory (k_gemm_direct) : stage by stage : now: 2000 x 4096 x 10976 656 : 125 : 88,
+// 300 x 4096 x 4000 32.6 : 20.3 : 19.5, 2629 x 26904 x 832 315 : 104 : 104 (there the tiles' two ends are most of it).
+template <bool OUT_BF16, int MB>
+__global__ void __launch_bounds__(256, 2)
+k_gemm_any_k(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const uint8_t* __restrict__ wq, const uint8_t* __restrict__ ws,
+             int M, int N, int K, void* __restrict__ y, int64_t ldy, int a_tiled, int w_tiled, int lines) {
+    constexpr int NA = 2, TM = 64 * MB, TN = 128, SETS = 2, CODES = 128 * (TN + TM), BUF = CODES + 8 * 256;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];                            // 2 BUF
+    load_args(aq, as, wq, ws, M, N, K, a_tiled, w_tiled);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5, wn = wave >> 1, wm = wave & 1;
+    const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN, T = tiles_m * tiles_n, per_xcd = (T + 7) / 8;
+    TileWalk tw{(int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3)), min((int)((blockIdx.x & 7) + 1) * per_xcd, T), 1, tiles_m, tiles_n};
+    if (tw.first >= tw.end) return;                            // uniform over the workgroup
+    int tm, tn;
+    tw.tile(0, tm, tn);
+    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+    const int groups = K / 32, pairs = (groups + 7) / 8;
+    // codes: thread i brings chunk i & 7 of rows i >> 3, + 32, ..; scales: of row i of the 128 of W and the TM of A
+    const uint8_t *wp[4], *ap[2 * MB];
+    const int64_t Kp = ((int64_t)K + 511) / 512 * 512;
+    auto code_row = [&](const uint8_t* c, bool tiled, int64_t row) { return c + (tiled ? (row >> 6) * (Kp / 128) * 4096 + (row & 63) * 64 : row * (K / 2)); };
+    auto scale_row = [&](const uint8_t* s, bool tiled, int64_t row) { return s + (tiled ? (row >> 6) * (Kp / 512) * 1024 + (row & 63) * 16 : row * (K / 32)); };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wp[q] = code_row(wq, w_tiled, min(n0 + 32 * q + (tid >> 3), (int64_t)N - 1));
+#pragma unroll
+    for (int q = 0; q < 2 * MB; ++q) ap[q] = code_row(aq, a_tiled, min(m0 + 32 * q + (tid >> 3), (int64_t)M - 1));
+    const bool st = wave < 2 ? w_tiled : a_tiled;
+    const uint8_t* const sp = wave < 2 ? scale_row(ws, st, min(n0 + tid, (int64_t)N - 1)) : scale_row(as, st, min(m0 + tid - TN, (int64_t)M - 1));
+    const int64_t wstep = w_tiled ? 4096 : 64, astep = a_tiled ? 4096 : 64;
+    v4i cw[SETS][4], ca[SETS][2 * MB];
+    uint64_t sc[SETS];
+    auto load = [&](int t, v4i (&w)[4], v4i (&a)[2 * MB], uint64_t& s) {
+        t = min(t, pairs - 1);                                 // past the end: the last pair again, which nobody reads
+        const int g = min(8 * t + (tid & 7), groups - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const v4i*>(wp[q] + (g >> 2) * wstep + (g & 3) * 16);
+#pragma unroll
+        for (int q = 0; q < 2 * MB; ++q) a[q] = *reinterpret_cast<const v4i*>(ap[q] + (g >> 2) * astep + (g & 3) * 16);
+        typedef uint64_t any __attribute__((aligned(1)));
+        // eight scale bytes; of a row-major row's last pair the row's last eight.  (One load: none behind a branch.)
+        s = *reinterpret_cast<const any*>(sp + (st ? (t >> 1) * 1024 + (t & 1) * 8 : min(8 * t, groups - 8)));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    uint8_t* const wr = lds + (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+    auto put = [&](int t, uint32_t buf, const v4i (&w)[4], const v4i (&a)[2 * MB], uint64_t s) {
+        const int over = 8 * max(8 * min(t, pairs - 1) - (groups - 8), 0);       // bits of the last pair's scales that are past K
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<v4i*>(wr + buf + q * 4096) = w[q];
+#pragma unroll
+        for (int q = 0; q < 2 * MB; ++q) *reinterpret_cast<v4i*>(wr + buf + (4 + q) * 4096) = a[q];
+        *reinterpret_cast<uint64_t*>(lds + buf + CODES + tid * 8) = st ? s & (~uint64_t(0) >> over) : s >> over;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    v16f acc[NA][MB];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < MB; ++b) acc[a][b] = v16f{};
+    const uint8_t* const wrd = lds + (wn * 64 + r) * 128;
+    const uint8_t* const ard = lds + (TN + wm * 32 * MB + r) * 128;
+    const uint8_t* const wsp = lds + CODES + (wn * 64 + r) * 8;
+    const uint8_t* const asp = lds + CODES + (TN + wm * 32 * MB + r) * 8;
+    const uint32_t sw = (uint32_t)(r >> 1) & 7u;
+    auto multiply = [&](uint32_t buf) {
+        uint64_t sw_[NA], sa_[MB];
+#pragma unroll
+        for (int k = 0; k < NA; ++k) sw_[k] = *reinterpret_cast<const uint64_t*>(wsp + buf + k * 256);
+#pragma unroll
+        for (int k = 0; k < MB; ++k) sa_[k] = *reinterpret_cast<const uint64_t*>(asp + buf + k * 256);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)                            // stage u of the pair, step j
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t c = ((uint32_t)(4 * u + 2 * h + j) ^ sw) << 4;
+                v8i w[NA], a[MB];
+#pragma unroll
+                for (int k = 0; k < NA; ++k) {
+                    const v4i f = *reinterpret_cast<const v4i*>(wrd + buf + k * 4096 + c);
+                    w[k] = v8i{f[0], f[1], f[2], f[3], 0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int k = 0; k < MB; ++k) {
+                    const v4i f = *reinterpret_cast<const v4i*>(ard + buf + k * 4096 + c);
+                    a[k] = v8i{f[0], f[1], f[2], f[3], 0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int x = 0; x < NA * MB; ++x) {
+                    v16f& d = acc[x / MB][x % MB];
+                    const int s0 = (int)((uint32_t)(sw_[x / MB] >> (32 * u)) >> (16 * h)), s1 = (int)((uint32_t)(sa_[x % MB] >> (32 * u)) >> (16 * h));
+                    if (j == 0) d = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w[x / MB], a[x % MB], d, 4, 4, 0, s0, 0, s1);
+                    else d = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w[x / MB], a[x % MB], d, 4, 4, 1, s0, 1, s1);
+                }
+            }
+    };
+    // turn t: pair t + 1 into the half of LDS that pair t - 1 was read from, pair t + 1 + SETS requested, pair t multiplied
+    uint32_t buf = 0;
+    auto turn = [&](auto Kc, int t) __attribute__((always_inline)) {
+        constexpr int k = (decltype(Kc)::value + 1) % SETS;
+        put(t + 1, BUF - buf, cw[k], ca[k], sc[k]);
+        load(t + 1 + SETS, cw[k], ca[k], sc[k]);
+        multiply(buf);
+        lds_wait_and_barrier();
+        buf = BUF - buf;
+    };
+    static_for([&](auto Kc) __attribute__((always_inline)) { load(decltype(Kc)::value, cw[decltype(Kc)::value], ca[decltype(Kc)::value], sc[decltype(Kc)::value]); }, IC<SETS>{});
+    put(0, 0, cw[0], ca[0], sc[0]);
+    load(SETS, cw[0], ca[0], sc[0]);
+    lds_wait_and_barrier();
+    int t = 0;
+    for (; t + SETS <= pairs; t += SETS) static_for([&](auto Kc) __attribute__((always_inline)) { turn(Kc, t + decltype(Kc)::value); }, IC<SETS>{});
+    if (t < pairs) turn(IC<0>{}, t);
+    store_tile<OUT_BF16, NA, MB>(acc, lds, y, ldy, m0, n0, M, N, lines);
+}
+constexpr int any_k_lds_bytes(int mb) { return 2 * (128 * (128 + 64 * mb) + 8 * 256); }
 
 using Kern = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int64_t, int, int, int);
 struct Variant { int na, mb, dw, da; Kern bf16, f32; };
@@ -429,6 +560,8 @@ static const Variant singles[MID_TILES] = {BRQ_MID(2, 1, 6, 6, false), BRQ_MID(2
 static const Variant pairs[MID_TILES] = {BRQ_MID(2, 1, 6, 6, true), BRQ_MID(2, 2, 6, 6, true), BRQ_MID(2, 3, 6, 6, true),
                                          BRQ_MID(4, 3, 4, 4, true), BRQ_MID(2, 5, 6, 4, true)};
 #undef BRQ_MID
+using AnyK = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int64_t, int, int, int);
+static const AnyK any_k[2][2] = {{k_gemm_any_k<false, 1>, k_gemm_any_k<true, 1>}, {k_gemm_any_k<false, 2>, k_gemm_any_k<true, 2>}};    // [MB - 1][bf16 out]
 
 }  // namespace mid
 
@@ -441,6 +574,9 @@ hipError_t setup_gemm_mid() {
             if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                    mid::lds_bytes(v.na, v.mb, v.dw, v.da)); e != hipSuccess) return e;
     }
+    for (int mb = 1; mb <= 2; ++mb)
+        for (mid::AnyK k : mid::any_k[mb - 1])
+            if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, mid::any_k_lds_bytes(mb)); e != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -453,11 +589,25 @@ bool mid_gemm_supported(int tile, const GemmShape& g) {
            Kp < (int64_t(1) << 26) && slabs * 32 * Kp <= (int64_t(1) << 32);
 }
 
+static int on_half_lines(const void* y, int64_t N, int64_t ldy, bool out_bf16) {
+    const int es = out_bf16 ? 2 : 4;
+    return N * es % 16 == 0 && rows_on(64, reinterpret_cast<uintptr_t>(y), ldy * es);
+}
+
+// Tiles of 64 rows where that is all there are.
+hipError_t launch_gemm_any_k(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y, bool out_bf16, int64_t ldy, hipStream_t s) {
+    const int mb = M <= 64 ? 1 : 2;
+    const int64_t T = (M + 64 * mb - 1) / (64 * mb) * ((N + 127) / 128);
+    hipLaunchKernelGGL(mid::any_k[mb - 1][out_bf16], dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::any_k_lds_bytes(mb), s, a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy,
+                       (int)a.tiled, (int)w.tiled, on_half_lines(y, N, ldy, out_bf16));
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s) {
     const mid::Variant& v = (mid_gemm_pairs(tile, a.tiled && w.tiled, K) ? mid::pairs : mid::singles)[tile];
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
-    const int es = out_bf16 ? 2 : 4, lines = N * es % 16 == 0 && rows_on(64, reinterpret_cast<uintptr_t>(y), ldy * es);
+    const int lines = on_half_lines(y, N, ldy, out_bf16);
     hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.dw, v.da), s,
                        a.codes, a.scales, w.codes, w.scales, (int)M, (int)N, (int)K, y, ldy, (int)a.tiled, (int)w.tiled, lines);
     return hipGetLastError();
