@@ -400,8 +400,10 @@ __device__ __forceinline__ void dma16_stream(uint32_t lds_base, const uint8_t* b
 }
 
 // Kernel arguments, all asked for here: left to the compiler each is loaded where it is first used, and the first global load
-// waits for three or four of these one after the other, 0.1 us each (k_gemm_smallm, 28672 x 2048 tiled, 8.9 -> 8.6 us).  Not in
-// the one-launch decode call, whose x loads then wait for the arguments of its product too (9.7 -> 10.0).
+// waits for three or four of these one after the other, 0.1 us each.  us, before -> now: k_gemm_smallm 28672 x 2048 tiled 8.9 -> 8.6;
+// one-tile product 1000 x 4096 x 1024 6.57 -> 6.41, 200 x 4096 x 4096 8.98 -> 8.81; k_rowwise_reg 4096 x 8192, B = 8192 25.9 -> 25.15.
+// Nothing in k_rowwise and k_rowwise_t4, where other workgroups fill the time; the one-launch decode call is slower with it,
+// its x loads then wait for the arguments of its product too (9.7 -> 10.0).
 template <class... T>
 __device__ __forceinline__ void load_args(T... a) { ([](auto v) __attribute__((always_inline)) { asm volatile("" :: "s"(v)); }(a), ...); }
 

@@ -88,6 +88,7 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
                                                      const uint8_t* __restrict__ ws, int w_tiled, int M, int N, int K,
                                                      void* __restrict__ y, int out_bf16, int64_t ldy) {
     __shared__ float part[4][64][4];
+    load_args(aq, as, a_tiled, wq, ws, w_tiled, M, N, K, y, out_bf16, ldy);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, kq = lane >> 4;
     const int n0 = blockIdx.x * 16;

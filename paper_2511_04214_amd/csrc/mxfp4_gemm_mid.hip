@@ -146,6 +146,7 @@ k_gemm_mid(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, const
     static_assert(PAIR ? DW % 2 == 0 && DA % 2 == 0 && PW >= PA && PA >= 2 : DW == DA, "");
     constexpr int SPW = (S + 3) / 4;                           // scale loads per wavefront and superstage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    load_args(aq, as, wq, ws, M, N, K, a_tiled, w_tiled);
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, h = lane >> 5;

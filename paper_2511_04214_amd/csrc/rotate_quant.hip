@@ -479,6 +479,7 @@ constexpr int reg_occ(int log2b, int mode) { return log2b >= 12 ? (mode == MODE_
 template <int LOG2B, bool IN_BF16, int MODE, bool OUT_BF16, bool PROD, int NT>
 __global__ void __launch_bounds__(NT, reg_occ(LOG2B, MODE)) k_rowwise_reg(RowArgs a, uint32_t blocks_per_row, uint32_t nblocks) {
     static_assert(IN_BF16, "fp32 blocks go through LDS");
+    if constexpr (MODE != MODE_STATS) load_args(a.x, a.codes, a.scales, a.ldx, a.cpr, a.through, a.stages, a.sstages, a.signs, blocks_per_row, nblocks);
     constexpr int W = reg_waves(LOG2B), BPW = NT / 64 / W;             // blocks per workgroup
     constexpr int NP = 1 << (LOG2B - 9), NJ = NP / W;                          // pieces per block and per wavefront
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
