@@ -6,7 +6,7 @@ include/brq.h, and returns the output tensors.  No arithmetic of the method happ
 here.  There is no CPU fallback: without the built library, or without a GPU tensor, the
 calls raise.
 
-The five calls that layers are made of are marshalled in csrc/binding.cpp where their arguments are plain; what it leaves
+The five calls that layers are made of, and the two of the analysis, are marshalled in csrc/binding.cpp where their arguments are plain; what it leaves
 (it returns None) goes the way written here, which takes and refuses everything.  So do all calls where that part cannot be
 loaded: it is linked to one torch's C++ interface, libbrq.so to none.
 """
@@ -102,6 +102,7 @@ def _load_native(L):
     _binding.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.brq_rotate_quantize_fused, L.brq_swiglu_rotate_quantize_fused, L.brq_matrix_rotate_quantize_fused, L.brq_mxfp4_gemm,
         L.brq_rotate_quantize_gemm_fused)))
+    _binding.bind_stats(*(ctypes.cast(f, ctypes.c_void_p).value for f in (L.brq_block_stats, L.brq_block_stats_summary)))
     return _binding
 
 
@@ -315,6 +316,12 @@ def block_stats(x, B, thresholds=(), signs=None, counts=None, want_amax=True, wa
     rotation with block B (1 = none, K = global) (brq_block_stats).  `counts` is added to when given;
     `amax` / `sqerr` / `sqerr_bfp4` may be given as output tensors.  With want_bfp4 (or sqerr_bfp4) a fourth
     element is returned: the loss under the FP16-scale counterpart of MXFP4."""
+    if _native is not None and stream is None and sqerr_bfp4 is None and want_bfp4 is False:
+        r = _native.block_stats(x, B, thresholds, signs, counts, want_amax, want_sqerr, amax, sqerr)
+        if r is not None:
+            if type(r) is int:
+                _check(r)
+            return r
     M, K, ldx = _rows(x, "x")
     th = (ctypes.c_float * max(1, len(thresholds)))(*[float(t) for t in thresholds])
     for t, n in ((amax, "amax"), (sqerr, "sqerr"), (sqerr_bfp4, "sqerr_bfp4")):
@@ -345,6 +352,12 @@ def block_stats_summary(amax, sqerr=None, amax_ref=None, outlier_threshold=0.0, 
                         sums=None, stream=None):
     """(hist [len(edges) + 1] int64, counts [4] int64, sums [4] float64) over the per-block arrays of block_stats
     (brq_block_stats_summary).  Outputs given by the caller are added to."""
+    if _native is not None and stream is None:
+        r = _native.block_stats_summary(amax, sqerr, amax_ref, outlier_threshold, edges, hist, counts, sums)
+        if r is not None:
+            if type(r) is int:
+                _check(r)
+            return r
     n = amax.numel()
     for t, nm in ((amax, "amax"), (sqerr, "sqerr"), (amax_ref, "amax_ref")):
         if t is not None and not (t.is_cuda and t.is_contiguous() and t.dtype == torch.float32 and t.numel() == n):

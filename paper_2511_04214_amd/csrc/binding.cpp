@@ -1,4 +1,4 @@
-// The calls that a layer makes, without the interpreter's share of them: arguments are read from the tensors here, checked
+// The calls that a layer and an analysis make, without the interpreter's share of them: arguments are read from the tensors here, checked
 // as __init__.py checks them, and handed to the C ABI.  With Python and ctypes in between a call cost the host 6 to 9 us, of
 // which the launch is 3: a small layer (16 x 256 x 256, two calls and a result tensor) took 15.0 us, the GPU 6.7.
 //
@@ -9,7 +9,9 @@
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
+#include <ATen/ops/_foreach_zero.h>
 #include <ATen/ops/empty.h>
+#include <ATen/ops/zeros.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
@@ -34,6 +36,8 @@ decltype(&brq_swiglu_rotate_quantize_fused) f_swiglu;
 decltype(&brq_matrix_rotate_quantize_fused) f_matrix;
 decltype(&brq_mxfp4_gemm) f_gemm;
 decltype(&brq_rotate_quantize_gemm_fused) f_decode;
+decltype(&brq_block_stats) f_stats;
+decltype(&brq_block_stats_summary) f_summary;
 
 // A tensor of torch's own type, on the GPU, that nothing watches or stands in for: beside the dispatch keys that every such
 // tensor has (autograd's, autocast's) it has the device's alone.
@@ -278,7 +282,146 @@ PyObject* rotate_quantize_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses of the entry points, in the order above)
+// ---- the analysis: the two statistics calls and the summary of a comparison of up to 8 M values took 45 us, all of it the
+// host; 33 now (six launches, seven new tensors).
+
+// Numbers as float32, as ctypes makes them of float(t): up to `most`.
+bool number(PyObject* o, double* v) {
+    if (PyFloat_CheckExact(o)) *v = PyFloat_AS_DOUBLE(o);
+    else if (PyLong_CheckExact(o)) *v = PyLong_AsDouble(o);
+    else return false;
+    if (!PyErr_Occurred()) return true;
+    PyErr_Clear();
+    return false;
+}
+bool numbers(PyObject* o, float* v, int most, int* n) {
+    if (!PyTuple_CheckExact(o) && !PyList_CheckExact(o)) return false;
+    const Py_ssize_t len = PySequence_Fast_GET_SIZE(o);
+    if (len > most) return false;
+    *n = (int)len;
+    for (int i = 0; i < *n; ++i) {
+        double d;
+        if (!number(PySequence_Fast_GET_ITEM(o, i), &d)) return false;
+        v[i] = (float)d;
+    }
+    return true;
+}
+
+// An output or input of one type: None (`*t` stays undefined), or contiguous with its sizes.
+bool array(PyObject* o, at::ScalarType s, at::IntArrayRef sizes, at::Tensor* t) {
+    if (o == Py_None) return true;
+    const at::Tensor* p = plain(o);
+    if (!p || p->scalar_type() != s || !p->is_contiguous() || p->sizes() != sizes) return false;
+    *t = *p;
+    return true;
+}
+bool flat_array(PyObject* o, at::ScalarType s, int64_t n, at::Tensor* t) {
+    if (o == Py_None) return true;
+    const at::Tensor* p = plain(o);
+    if (!p || p->scalar_type() != s || !p->is_contiguous() || p->numel() != n) return false;
+    *t = *p;
+    return true;
+}
+template <class T>
+T* address(const at::Tensor& t) { return t.defined() ? static_cast<T*>(t.data_ptr()) : nullptr; }
+// the caller's own object, or the new tensor, or None
+PyObject* handed(PyObject* given, at::Tensor& t) {
+    if (given == Py_None && t.defined()) return THPVariable_Wrap(std::move(t));
+    Py_INCREF(given);
+    return given;
+}
+PyObject* three(PyObject* a, PyObject* b, PyObject* c) {
+    PyObject* r = a && b && c ? PyTuple_Pack(3, a, b, c) : nullptr;
+    Py_XDECREF(a);
+    Py_XDECREF(b);
+    Py_XDECREF(c);
+    return r;
+}
+
+// block_stats(x, B, thresholds, signs, counts, want_amax, want_sqerr, amax, sqerr)
+PyObject* block_stats(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    Rows x;
+    int64_t B;
+    float th[8];
+    int nt;
+    const int8_t* signs;
+    at::Tensor counts, amax, sqerr;
+    if (n != 9 || !f_stats || !quiet() || !rows(a[0], &x) || x.M <= 0 || x.K <= 0 || x.K % 32 != 0 || !integer(a[1], &B) || !numbers(a[2], th, 8, &nt) ||
+        !signs_arg(a[3], x.K, &signs) || !flat_array(a[4], at::kLong, nt, &counts) || !PyBool_Check(a[5]) || !PyBool_Check(a[6])) Py_RETURN_NONE;
+    const int64_t shape[2] = {x.M, x.K / 32};
+    if (!array(a[7], at::kFloat, shape, &amax) || !array(a[8], at::kFloat, shape, &sqerr)) Py_RETURN_NONE;
+    const at::TensorOptions f32 = at::TensorOptions().dtype(at::kFloat).device(x.t->device());
+    {
+        const Unlocked u;
+        if (!amax.defined() && a[5] == Py_True) amax = at::empty(shape, f32);
+        if (!sqerr.defined() && a[6] == Py_True) sqerr = at::empty(shape, f32);
+        if (!counts.defined() && nt) counts = at::zeros({nt}, f32.dtype(at::kLong));
+    }
+    for (const at::Tensor* t : {&amax, &sqerr, &counts})
+        if (t->defined() && !on_gpu(*t)) Py_RETURN_NONE;
+    const void* p = x.t->const_data_ptr();
+    if (signs) signs = reinterpret_cast<const int8_t*>(data(a[3]));
+    float *pa = address<float>(amax), *ps = address<float>(sqerr);
+    uint64_t* pc = address<uint64_t>(counts);
+    void* s = current_stream();
+    const brq_status st = released([&] { return f_stats(p, x.dt, x.M, x.K, x.ld, B, signs, th, nt, pa, pc, ps, nullptr, s); });
+    return st != BRQ_OK ? status(st) : three(handed(a[7], amax), handed(a[4], counts), handed(a[8], sqerr));
+    END_HANDLE_TH_ERRORS
+}
+
+// block_stats_summary(amax, sqerr, amax_ref, outlier_threshold, edges, hist, counts, sums)
+PyObject* block_stats_summary(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    const at::Tensor* amax = n == 8 && f_summary && quiet() ? plain(a[0]) : nullptr;
+    if (!amax || amax->scalar_type() != at::kFloat || !amax->is_contiguous() || amax->numel() == 0) Py_RETURN_NONE;
+    const int64_t blocks = amax->numel();
+    at::Tensor sqerr, ref, hist, counts, sums;
+    double outlier;
+    float edges[32];
+    int ne;
+    if (!flat_array(a[1], at::kFloat, blocks, &sqerr) || !flat_array(a[2], at::kFloat, blocks, &ref) || !number(a[3], &outlier) || !numbers(a[4], edges, 32, &ne) ||
+        !flat_array(a[5], at::kLong, ne + 1, &hist) || !flat_array(a[6], at::kLong, 4, &counts) || !flat_array(a[7], at::kDouble, 4, &sums)) Py_RETURN_NONE;
+    const at::TensorOptions i64 = at::TensorOptions().dtype(at::kLong).device(amax->device());
+    {
+        const Unlocked u;
+        std::vector<at::Tensor> made;                          // each a tensor of its own, cleared by one launch
+        if (!hist.defined()) made.push_back(hist = at::empty({ne + 1}, i64));
+        if (!counts.defined()) made.push_back(counts = at::empty({4}, i64));
+        if (!sums.defined()) made.push_back((sums = at::empty({4}, i64.dtype(at::kDouble))).view(at::kLong));
+        if (!made.empty()) at::_foreach_zero_(made);
+    }
+    for (const at::Tensor* t : {&hist, &counts, &sums})
+        if (!on_gpu(*t)) Py_RETURN_NONE;
+    const float *pa = static_cast<const float*>(THPVariable_Unpack(a[0]).const_data_ptr()), *pq = address<float>(sqerr), *pr = address<float>(ref);
+    uint64_t *ph = address<uint64_t>(hist), *pc = address<uint64_t>(counts);
+    double* pd = address<double>(sums);
+    void* s = current_stream();
+    const brq_status st = released([&] { return f_summary(pa, pq, pr, blocks, (float)outlier, edges, ne, ph, pc, pd, s); });
+    return st != BRQ_OK ? status(st) : three(handed(a[5], hist), handed(a[6], counts), handed(a[7], sums));
+    END_HANDLE_TH_ERRORS
+}
+
+// bind_stats(addresses of brq_block_stats and brq_block_stats_summary)
+PyObject* bind_stats(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    void* p[2];
+    if (n != 2) {
+        PyErr_SetString(PyExc_TypeError, "bind_stats takes the addresses of two entry points");
+        return nullptr;
+    }
+    for (int i = 0; i < 2; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[i]);
+        if (!p[i]) {
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point's address is NULL");
+            return nullptr;
+        }
+    }
+    f_stats = reinterpret_cast<decltype(f_stats)>(p[0]);
+    f_summary = reinterpret_cast<decltype(f_summary)>(p[1]);
+    Py_RETURN_NONE;
+}
+
+// bind(addresses of the entry points of a layer, in the order above)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* p[5];
     if (n != 5) {
@@ -302,7 +445,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 #define BRQ_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {BRQ_METHOD(bind), BRQ_METHOD(rotate_quantize), BRQ_METHOD(swiglu_rotate_quantize), BRQ_METHOD(matrix_rotate_quantize),
-                         BRQ_METHOD(gemm), BRQ_METHOD(rotate_quantize_gemm), {nullptr, nullptr, 0, nullptr}};
+                         BRQ_METHOD(gemm), BRQ_METHOD(rotate_quantize_gemm), BRQ_METHOD(bind_stats), BRQ_METHOD(block_stats), BRQ_METHOD(block_stats_summary), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
