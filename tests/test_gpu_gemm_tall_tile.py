@@ -1,0 +1,49 @@
+"""The product's tiles of 256 x 128, which it takes for row-major operands in place of 320 x 128 and 192 x 256 where they go round the
+chip as often: rows and columns around a tile's, K with and without an overlapping last window, mixed layouts, pitches on and off
+lines.  All product kernels but one sum in the same order, so the result is that of the kernel it takes the place of, bit for bit."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def brq():
+    import paper_2511_04214_amd as b
+    b.lib()
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    return b
+
+
+def up(a, b):
+    return -(-a // b)
+
+
+# rows left of a tile of 256 (64 of them a wavefront's two MFMA tiles), columns left, K over 512
+SHAPES = [(0, 0, 2688), (250, 6, 2048), (63, 64, 4224), (140, 120, 1152), (255, 16, 3328), (128, 6, 2944), (129, 64, 1664), (192, 1, 2560)]
+
+
+# (mixed layouts take whole superstages)
+@pytest.mark.parametrize("rows,cols,K,layouts", [(*s, (a, w)) for s in SHAPES for a, w in (("rowmajor", "rowmajor"), ("tiled", "rowmajor"), ("rowmajor", "tiled"))
+                                                 if a == w or s[2] % 512 == 0])
+def test_tall_tile(brq, rows, cols, K, layouts):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    g = torch.Generator(device="cuda").manual_seed(rows * 7 + cols + K)
+    found = 0
+    for tm in (1, 2, 4, 7, 8):                                # tiles of 256 x 128 down; as many across as one round has room for
+        M = 256 * (tm - (rows > 0)) + rows
+        N = 128 * (cus // tm - (cols > 0)) + cols
+        for out in (torch.bfloat16, torch.float32):
+            route = brq.diag_mxfp4_gemm_route(M, N, K, *layouts, out, cus=cus) if M > 16 else ""
+            if route not in ("320x128", "192x256") or up(M, 256) * up(N, 128) > cus:
+                continue
+            found += 1
+            print("case", M, N, K, layouts, out, route, flush=True)
+            x, w = (torch.randn((n, K), generator=g, device="cuda") for n in (M, N))
+            a, b = brq.rotate_quantize_fused(x, 32, layout=layouts[0]), brq.rotate_quantize_fused(w, 32, layout=layouts[1])
+            for pad in (0, 3):
+                y, want = (torch.full((M + 1, N + pad), -7.0, dtype=out, device="cuda") for _ in range(2))
+                brq.mxfp4_gemm(*a, *b, out=y[:M, :N], out_dtype=out, a_layout=layouts[0], w_layout=layouts[1], M=M, N=N, K=K)
+                brq.diag_mxfp4_gemm_on("320x128", *a, *b, want[:M, :N], K, a_layout=layouts[0], w_layout=layouts[1])
+                assert torch.equal(y, want)                   # (the cells beside the product too: untouched)
+    assert found, "no such shape goes this way"
