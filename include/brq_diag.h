@@ -79,8 +79,8 @@ enum {
     BRQ_GEMM_128x128 = 6,
     BRQ_GEMM_192x128 = 7,
     BRQ_GEMM_192x256 = 8,
-    BRQ_GEMM_320x128 = 9         /* brq_mxfp4_gemm takes tiles of 256 x 128 instead of this and of 192 x 256 where an operand is
-                                    row-major, K > 1024 and they go round the compute units as often; not so the call below */
+    BRQ_GEMM_320x128 = 9         /* in place of this and of 192 x 256 brq_mxfp4_gemm takes tiles of 256 x 128 where K is long
+                                    enough and they go round the compute units as often; not so brq_diag_mxfp4_gemm_on */
 };
 
 /*

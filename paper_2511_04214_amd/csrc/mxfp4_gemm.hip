@@ -709,17 +709,20 @@ hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, cons
     }
 }
 
-// Where the estimate takes 320 x 128 or 192 x 256 for row-major operands: whether tiles of 256 x 128 go round the chip as
-// often.  Then each is that much shorter and nothing is lost: on all of 133 such shapes (of 2029: M 100 .. 8192, N 512 .. 28672 in
-// eights, K 1152 .. 13824, weights in no cache) faster by 3 to 23 %, 11 % on average; with a round more slower on 94 % (17 % on
-// average).  us: 2000 x 4096 x 11008 fp32 59.1 -> 56.5, 250 x 28672 x 8192 48.0 -> 45.4, 1000 x 8192 x 4096 27.2 -> 23.3,
-// 4642 x 2744 x 8064 92.3 -> 80.3.  Tiled operands have the persistent kernel's 128 x 256 there (2000 x 4096 x 11008 45.1 : 47.8);
-// K up to 1024 was not looked at.  Same order of summation, same bits.
+// Where the estimate takes 320 x 128 or 192 x 256: whether tiles of 256 x 128 go round the chip as often.  Then each is that
+// much shorter and nothing is lost.  Row-major, on all of 133 such shapes (of 2029: M 100 .. 8192, N 512 .. 28672 in eights, K
+// 1152 .. 13824, weights in no cache) faster by 3 to 23 %, 11 % on average; with a round more slower on 94 % (17 % on average).
+// us: 2000 x 4096 x 11008 fp32 59.1 -> 56.5, 250 x 28672 x 8192 48.0 -> 45.4, 1000 x 8192 x 4096 27.2 -> 23.3, 4642 x 2744 x 8064
+// 92.3 -> 80.3.  Tiled, over 320 x 128, 830 shapes, K from 2304: 1 % slower to 14 % faster, 6.5 % on average (6046 x 2568 x 8192 76.8 ->
+// 72.1); over 192 x 256 in two rounds and more, 127 shapes, faster by 2 to 16 %, in one round not always (3776 x 2080 x 4224 fp32 26.0 :
+// 28.6).  K below was not looked at.  Same order of summation, same bits.
 static bool tall_tile(int route, const GemmShape& g, int cus) {
     const int tile = route - ROUTE_ONE_TILE;
-    if ((tile != 3 && tile != 4) || (g.a_tiled && g.w_tiled) || g.K <= 1024) return false;
+    const bool tiled = g.a_tiled && g.w_tiled;
+    if ((tile != 3 && tile != 4) || g.K <= (tiled ? 2048 : 1024)) return false;
     auto rounds = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm * ((g.N + tn - 1) / tn) + cus - 1) / cus; };
-    return rounds(256, 128) == (tile == 3 ? rounds(192, 256) : rounds(320, 128));
+    const int64_t n = rounds(256, 128);
+    return n == (tile == 3 ? rounds(192, 256) : rounds(320, 128)) && !(tiled && tile == 3 && n == 1);
 }
 
 hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {

@@ -1,5 +1,4 @@
-"""The product's tiles of 256 x 128, which it takes for row-major operands in place of 320 x 128 and 192 x 256 where they go round the
-chip as often: rows and columns around a tile's, K with and without an overlapping last window, mixed layouts, pitches on and off
+"""The product's tiles of 256 x 128, which it takes in place of 320 x 128 and 192 x 256 where they go round the chip as often: rows and columns around a tile's, K with and without an overlapping last window, mixed layouts, pitches on and off
 lines.  All product kernels but one sum in the same order, so the result is that of the kernel it takes the place of, bit for bit."""
 import pytest
 import torch
@@ -47,3 +46,18 @@ def test_tall_tile(brq, rows, cols, K, layouts):
                 brq.diag_mxfp4_gemm_on("320x128", *a, *b, want[:M, :N], K, a_layout=layouts[0], w_layout=layouts[1])
                 assert torch.equal(y, want)                   # (the cells beside the product too: untouched)
     assert found, "no such shape goes this way"
+
+
+# over 320 x 128 in one and in two rounds, and over 192 x 256 in two
+@pytest.mark.parametrize("M,N,K", [(3913, 3746, 4224), (6046, 2568, 8192), (1194, 6374, 5504), (2840, 2623, 9344), (4078, 1876, 5248)])
+def test_tall_tile_tiled(brq, M, N, K):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a, b = (brq.rotate_quantize_fused(torch.randn((n, K), generator=g, device="cuda"), 32, layout="tiled") for n in (M, N))
+    for out in (torch.bfloat16, torch.float32):
+        print("case", M, N, K, out, brq.diag_mxfp4_gemm_route(M, N, K, "tiled", "tiled", out, cus=cus), flush=True)
+        for pad in (0, 3):
+            y, want = (torch.full((M + 1, N + pad), -7.0, dtype=out, device="cuda") for _ in range(2))
+            brq.mxfp4_gemm(*a, *b, out=y[:M, :N], out_dtype=out, a_layout="tiled", w_layout="tiled", M=M, N=N, K=K)
+            brq.diag_mxfp4_gemm_on("320x128", *a, *b, want[:M, :N], K, a_layout="tiled", w_layout="tiled")
+            assert torch.equal(y, want)
