@@ -39,6 +39,11 @@
 // 2048 x 1024 5.0 : 4.7; with K = 2048 64 x 128 2000 x 4096 17.0 : 18.7, 128 x 128 514 x 16064 23.9 : 22.5 but 100 x 8192 x 3072 13.1 :
 // 14.7; 320 x 128 2000 x 4096 x 1024 10.4 : 10.9, 192 x 256 10.8 : 11.1.
 //
+// What bounds a stage where one workgroup runs on a CU is what the CU can have on its way: an L2 hit costs it 16 cycles a KB, but of
+// what misses the L2 at most 32 KB (the L1's size) are in flight, some 1000 cycles each, and hits wait behind misses; deeper
+// rings, other orders and wavefronts that only load change nothing or hand the cycles back to the clock (300 x 28672 x 8192: the
+// loads of a stage by themselves 34 us, the product 43).
+//
 // LDS map (bytes), S = NA + MB: W's DW stages x 4K NA | A's DA stages x 4K MB; then ceil(DW / 4) scale buffers x
 // (W 1K NA | A 1K MB), 16 scale bytes (one superstage) per row.  The output is turned round in the rings.
 //
