@@ -107,7 +107,10 @@ bool mid_gemm_pairs(int tile, bool both_tiled, int64_t K);       // whether it l
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s);
 
-// The same for any K of at least 256 elements and any mix of layouts, 64 or 128 rows x 128 columns a workgroup.
+// The same for any K of at least 256 elements and any mix of layouts, 64 or 128 rows x 128 columns a workgroup.  It takes its
+// operands in pairs of stages, 8 groups: where pair t's eight scale bytes begin, from the row's first (of a row-major row's last pair the
+// row's last eight).
+constexpr int64_t pair_scales(bool tiled, int t, int groups) { return tiled ? (int64_t)(t >> 1) * 1024 + (t & 1) * 8 : 8 * t < groups - 8 ? 8 * t : groups - 8; }
 hipError_t launch_gemm_any_k(const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y, bool out_bf16, int64_t ldy,
                              hipStream_t s);
 

@@ -482,8 +482,7 @@ k_gemm_any_k(const uint8_t* __restrict__ aq, const uint8_t* __restrict__ as, con
 #pragma unroll
         for (int q = 0; q < 2 * MB; ++q) a[q] = *reinterpret_cast<const v4i*>(ap[q] + (g >> 2) * astep + (g & 3) * 16);
         typedef uint64_t any __attribute__((aligned(1)));
-        // eight scale bytes; of a row-major row's last pair the row's last eight.  (One load: none behind a branch.)
-        s = *reinterpret_cast<const any*>(sp + (st ? (t >> 1) * 1024 + (t & 1) * 8 : min(8 * t, groups - 8)));
+        s = *reinterpret_cast<const any*>(sp + pair_scales(st, t, groups));      // (one load: none behind a branch)
         __builtin_amdgcn_sched_barrier(0);
     };
     uint8_t* const wr = lds + (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);

@@ -33,3 +33,21 @@ def test_any_k(brq, M, N, Ks):
                 assert torch.equal(buf[:M, :N], want.to(dt))
                 buf[:M, :N] = -7.0
                 assert (buf == -7.0).all(), "wrote outside the M x N block"
+
+
+def test_scales_past_2_gib(brq):
+    """K = 2^30 + 512: the weights' scales of the last superstage lie 2^31 bytes behind their row's first (tiled, one slab of 36 GB).  Codes
+    1 in 32 groups at either end of K and around that place, 0 elsewhere; all sums are exact."""
+    M, N, K = 17, 15, 2 ** 30 + 512
+    ac, as_ = torch.zeros((M, K // 2), dtype=torch.uint8, device="cuda"), torch.full((M, K // 32), 127, dtype=torch.uint8, device="cuda")
+    wc, ws = (torch.full((n,), v, dtype=torch.uint8, device="cuda") for n, v in zip(brq.operand_bytes(N, K, "tiled"), (0, 127)))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    want = torch.zeros((M, N), dtype=torch.float64)
+    for at in (0, 2 ** 25 - 48, 2 ** 25 - 16):              # first of 32 groups, two superstages of the weights
+        ea, ew = (torch.randint(0, 5, (n, 32), generator=g, device="cuda") for n in (M, N))
+        ac[:, 16 * at:16 * at + 512] = 0x22
+        as_[:, at:at + 32] = (125 + ea).to(torch.uint8)
+        wc.view(K // 128, 64, 64)[at // 4:at // 4 + 8, :N] = 0x22
+        ws.view(K // 512, 64, 16)[at // 16:at // 16 + 2, :N] = (125 + ew).to(torch.uint8).view(N, 2, 16).transpose(0, 1)
+        want += 32 * torch.exp2(ea.cpu().double() - 2) @ torch.exp2(ew.cpu().double() - 2).t()
+    assert torch.equal(brq.mxfp4_gemm(ac, as_, wc, ws, w_layout="tiled", N=N).cpu().double(), want)
