@@ -74,8 +74,7 @@ enum {
     BRQ_GEMM_STREAM = 2,         /* M <= 16, K of whole 512-element superstages */
     BRQ_GEMM_256x256 = 3,        /* the persistent kernel and its two output tiles (rows x columns) */
     BRQ_GEMM_128x256 = 4,
-    BRQ_GEMM_64x128 = 5,         /* the one-tile-per-workgroup kernel and its five; 64 x 128 of up to 16 rows and row-major weights
-                                    (K of whole superstages) is a workgroup of the streaming kernel */
+    BRQ_GEMM_64x128 = 5,         /* the one-tile-per-workgroup kernel and its five */
     BRQ_GEMM_128x128 = 6,
     BRQ_GEMM_192x128 = 7,
     BRQ_GEMM_192x256 = 8,

@@ -653,28 +653,22 @@ bool gemm_route_supported(int route, const GemmShape& g) {
     }
 }
 
-// Whether the 64 x 128 tile of this shape is one of the streaming kernel's workgroups: up to 16 rows, row-major weights.
-static bool few_rows(const GemmShape& g) { return !g.w_tiled && gemm_route_supported(ROUTE_STREAM, g); }
-
 int gemm_route(const GemmShape& g, int cus) {
-    // Up to 16 rows: the weights are streamed (k_gemm_smallm), tiled ones and row-major ones of one superstage under that
-    // name, other row-major ones under the name of the tile that its workgroups then are (few_rows below).  The staged 64 x 128
-    // kernel and the K-split one (ROUTE_SKINNY, which sums in another order) against it, us, weights in no cache, 1 / 16 rows,
-    // streaming : 64 x 128 : K-split:
+    // Up to 16 rows: the weights are streamed (k_gemm_smallm).  The staged 64 x 128 kernel and the K-split one (ROUTE_SKINNY, which
+    // sums in another order) against it, us, weights in no cache, 1 / 16 rows, streaming : 64 x 128 : K-split:
     //   weights tiled      N x K = 256 x 512 2.4 / 2.8 : 3.5 / 3.6 : 2.0 / 2.4,  2048 x 2048 4.0 / 4.3 : 5.9 / 5.9 : 3.8 / 4.2,
     //                      2048 x 8192 7.4 / 7.9 : 13.9 / 14.7 : 11.7 / 12.0,  8192 x 4096 7.3 / 7.6 : 9.4 / 9.7 : 8.0 / 8.3,
     //                      28672 x 2048 8.7 / 9.0 : 8.7 / 8.7 : 9.1 / 10.4,  28672 x 8192 24.9 / 25.3 : 25.5 / 25.8 : 30.6 / 33.3
     //   weights row-major  64 x 512 2.4 / 2.7 : 3.5 / 3.5,  28672 x 512 4.6 / 5.0 : 5.2 / 5.2 : 4.3 / 5.3,  28672 x 1024 6.4 / 6.8 :
     //                      6.6 / 6.7 : 6.8 / 8.1,  28672 x 2048 9.1 / 9.6 : 9.7 / 9.9 : 11.4 / 13.1,  28672 x 8192 30.5 / 31.1 : 31.2 /
     //                      31.3 : 38.0 / 42.8,  2048 x 8192 8.7 / 9.1 : 18.6 / 19.2 : 12.6 / 13.0,  14336 x 4096 9.3 / 9.8 : 12.4 / 12.9
-    if (gemm_route_supported(ROUTE_STREAM, g)) return g.w_tiled || g.K <= 512 || !gemm_route_supported(ROUTE_ONE_TILE, g) ? ROUTE_STREAM : ROUTE_ONE_TILE;
+    if (gemm_route_supported(ROUTE_STREAM, g)) return ROUTE_STREAM;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
     return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
 }
 
 hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {
     const int64_t M = g.M, N = g.N, K = g.K;
-    if (route == ROUTE_ONE_TILE && few_rows(g)) route = ROUTE_STREAM;
     switch (route) {
         case ROUTE_GENERAL: {
             // Through LDS from where its pairs of stages have something to hide behind: enough of them, or enough tiles.  us,
