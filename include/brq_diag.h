@@ -74,12 +74,12 @@ enum {
     BRQ_GEMM_STREAM = 2,         /* M <= 16, K of whole 512-element superstages */
     BRQ_GEMM_256x256 = 3,        /* the persistent kernel and its two output tiles (rows x columns) */
     BRQ_GEMM_128x256 = 4,
-    BRQ_GEMM_64x128 = 5,         /* the one-tile-per-workgroup kernel and its five */
+    BRQ_GEMM_64x128 = 5,         /* the one-tile-per-workgroup kernel and its six */
     BRQ_GEMM_128x128 = 6,
     BRQ_GEMM_192x128 = 7,
     BRQ_GEMM_192x256 = 8,
-    BRQ_GEMM_320x128 = 9         /* in place of this and of 192 x 256 brq_mxfp4_gemm takes tiles of 256 x 128 where K is long
-                                    enough and they go round the compute units as often; not so brq_diag_mxfp4_gemm_on */
+    BRQ_GEMM_320x128 = 9,
+    BRQ_GEMM_256x128 = 10
 };
 
 /*

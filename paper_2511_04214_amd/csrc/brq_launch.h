@@ -74,8 +74,7 @@ struct GemmShape {
     bool whole_k() const { return K % 512 == 0 || (a_tiled && w_tiled); }
 };
 enum GemmRoute { ROUTE_GENERAL, ROUTE_SKINNY, ROUTE_STREAM, ROUTE_256x256, ROUTE_128x256, ROUTE_ONE_TILE };   // + a tile's number
-constexpr int MID_TILES = 5;
-constexpr int MID_TALL = MID_TILES;      // 256 x 128: no route of its own, see launch_mxfp4_gemm
+constexpr int MID_TILES = 6;
 constexpr int GEMM_ROUTES = ROUTE_ONE_TILE + MID_TILES;
 bool gemm_route_supported(int route, const GemmShape& g);
 // The route of a product on a device of `cus` compute units: host arithmetic.

@@ -605,7 +605,7 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
 // over the best (34 % at worst); fitted to one half 0.9 % on the other.
 struct TileCost { float fixed, alone, full, store, store_off; int per_cu; };    // store_off: rows off lines
 struct Tile { int na, mb, route; TileCost tiled, rowmajor, singles; };          // 64 mb x 64 na; singles: row-major by single stages
-static const Tile TILES[2 + MID_TILES] = {
+static const Tile TILES[] = {
     {4, 4, ROUTE_256x256, {5.984f, 0.535f, 0.758f, 0.292f, 0.481f, 1}, {6.801f, 0.508f, 0.978f, 0.439f, 0.893f, 1}, {}},
     {4, 2, ROUTE_128x256, {3.696f, 0.280f, 0.474f, 0.377f, 0.649f, 1}, {3.535f, 0.514f, 0.682f, 0.402f, 0.724f, 1}, {}},
     {2, 1, ROUTE_ONE_TILE, {3.141f, 0.178f, 0.205f, 0.406f, 0.923f, 2}, {3.749f, 0.196f, 0.264f, 0.512f, 0.585f, 2},
@@ -618,7 +618,7 @@ static const Tile TILES[2 + MID_TILES] = {
     {2, 5, ROUTE_ONE_TILE + 4, {6.659f, 0.363f, 0.494f, 0.545f, 0.950f, 1}, {6.735f, 0.399f, 0.639f, 0.624f, 0.976f, 1}, {}},
 };
 
-// The cheapest of the LDS-staged kernels that take the shape, or -1.
+// The cheapest of these that take the shape, or -1.  (The one-tile kernels' sixth tile is not among them: see tall_tile.)
 static int pick_tile(const GemmShape& g, int cus) {
     const bool tiled = g.a_tiled && g.w_tiled;
     const float stages = (float)((g.K + 511) / 512 * 4), output = 0.6e-6f * (float)g.M * (float)g.N * (g.out_bf16 ? 1.0f : 2.0f);
@@ -627,8 +627,7 @@ static int pick_tile(const GemmShape& g, int cus) {
     auto pow4 = [](float x) { return x * x * x * x; };
     int best = -1;
     float least = 0.0f;
-    for (int i = 0; i < 2 + MID_TILES; ++i) {
-        const Tile& t = TILES[i];
+    for (const Tile& t : TILES) {
         if (!gemm_route_supported(t.route, g)) continue;
         const bool one_tile = t.route >= ROUTE_ONE_TILE;
         const TileCost& c = tiled ? t.tiled : one_tile && !mid_gemm_pairs(t.route - ROUTE_ONE_TILE, tiled, g.K) ? t.singles : t.rowmajor;
@@ -653,6 +652,23 @@ bool gemm_route_supported(int route, const GemmShape& g) {
     }
 }
 
+// Where the estimate takes 320 x 128 or 192 x 256: whether tiles of 256 x 128 go round the chip as often.  Then each is that
+// much shorter and nothing is lost.  Row-major, on all of 133 such shapes (of 2029: M 100 .. 8192, N 512 .. 28672 in eights, K
+// 1152 .. 13824, weights in no cache) faster by 3 to 23 %, 11 % on average; with a round more slower on 94 % (17 % on average).
+// us: 2000 x 4096 x 11008 fp32 59.1 -> 56.5, 250 x 28672 x 8192 48.0 -> 45.4, 1000 x 8192 x 4096 27.2 -> 23.3, 4642 x 2744 x 8064
+// 92.3 -> 80.3.  Tiled, over 320 x 128, 830 shapes, K from 2304: 1 % slower to 14 % faster, 6.5 % on average (6046 x 2568 x 8192 76.8 ->
+// 72.1); over 192 x 256 in two rounds and more, 127 shapes, faster by 2 to 16 %, in one round not always (3776 x 2080 x 4224 fp32 26.0 :
+// 28.6).  K below was not looked at.  Same order of summation, same bits.
+constexpr int TALL_TILE = ROUTE_ONE_TILE + 5;
+static bool tall_tile(int route, const GemmShape& g, int cus) {
+    constexpr int TILE_192x256 = ROUTE_ONE_TILE + 3, TILE_320x128 = ROUTE_ONE_TILE + 4;
+    const bool tiled = g.a_tiled && g.w_tiled;
+    if ((route != TILE_192x256 && route != TILE_320x128) || g.K <= (tiled ? 2048 : 1024)) return false;
+    auto rounds = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm * ((g.N + tn - 1) / tn) + cus - 1) / cus; };
+    const int64_t n = rounds(256, 128);
+    return n == (route == TILE_192x256 ? rounds(192, 256) : rounds(320, 128)) && !(tiled && route == TILE_192x256 && n == 1);
+}
+
 int gemm_route(const GemmShape& g, int cus) {
     // Up to 16 rows: the weights are streamed (k_gemm_smallm).  The staged 64 x 128 kernel and the K-split one (ROUTE_SKINNY, which
     // sums in another order) against it, us, weights in no cache, 1 / 16 rows, streaming : 64 x 128 : K-split:
@@ -664,6 +680,7 @@ int gemm_route(const GemmShape& g, int cus) {
     //                      31.3 : 38.0 / 42.8,  2048 x 8192 8.7 / 9.1 : 18.6 / 19.2 : 12.6 / 13.0,  14336 x 4096 9.3 / 9.8 : 12.4 / 12.9
     if (gemm_route_supported(ROUTE_STREAM, g)) return ROUTE_STREAM;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
+    if (tall_tile(t, g, cus)) return TALL_TILE;
     return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
 }
 
@@ -703,28 +720,10 @@ hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, cons
     }
 }
 
-// Where the estimate takes 320 x 128 or 192 x 256: whether tiles of 256 x 128 go round the chip as often.  Then each is that
-// much shorter and nothing is lost.  Row-major, on all of 133 such shapes (of 2029: M 100 .. 8192, N 512 .. 28672 in eights, K
-// 1152 .. 13824, weights in no cache) faster by 3 to 23 %, 11 % on average; with a round more slower on 94 % (17 % on average).
-// us: 2000 x 4096 x 11008 fp32 59.1 -> 56.5, 250 x 28672 x 8192 48.0 -> 45.4, 1000 x 8192 x 4096 27.2 -> 23.3, 4642 x 2744 x 8064
-// 92.3 -> 80.3.  Tiled, over 320 x 128, 830 shapes, K from 2304: 1 % slower to 14 % faster, 6.5 % on average (6046 x 2568 x 8192 76.8 ->
-// 72.1); over 192 x 256 in two rounds and more, 127 shapes, faster by 2 to 16 %, in one round not always (3776 x 2080 x 4224 fp32 26.0 :
-// 28.6).  K below was not looked at.  Same order of summation, same bits.
-static bool tall_tile(int route, const GemmShape& g, int cus) {
-    const int tile = route - ROUTE_ONE_TILE;
-    const bool tiled = g.a_tiled && g.w_tiled;
-    if ((tile != 3 && tile != 4) || g.K <= (tiled ? 2048 : 1024)) return false;
-    auto rounds = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm * ((g.N + tn - 1) / tn) + cus - 1) / cus; };
-    const int64_t n = rounds(256, 128);
-    return n == (tile == 3 ? rounds(192, 256) : rounds(320, 128)) && !(tiled && tile == 3 && n == 1);
-}
-
 hipError_t launch_mxfp4_gemm(const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {
     int cus = 0;
     if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;      // (also the per-device kernel set-up)
-    const int route = gemm_route(g, cus);
-    if (tall_tile(route, g, cus)) return launch_gemm_mid(MID_TALL, a, w, g.M, g.N, g.K, y, g.out_bf16, g.ldy, s);
-    return launch_gemm_route(route, a, w, g, y, s);
+    return launch_gemm_route(gemm_route(g, cus), a, w, g, y, s);
 }
 
 }  // namespace brq

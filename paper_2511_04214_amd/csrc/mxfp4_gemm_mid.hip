@@ -561,10 +561,10 @@ using Kern = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint
 struct Variant { int na, mb, dw, da; Kern bf16, f32; };
 #define BRQ_MID(NA, MB, DW, DA, PAIR) {NA, MB, DW, DA, k_gemm_mid<true, NA, MB, DW, DA, PAIR>, k_gemm_mid<false, NA, MB, DW, DA, PAIR>}
 static const Variant singles[MID_TILES] = {BRQ_MID(2, 1, 6, 6, false), BRQ_MID(2, 2, 4, 4, false), BRQ_MID(2, 3, 4, 4, false),
-                                           BRQ_MID(4, 3, 4, 4, false), BRQ_MID(2, 5, 5, 5, false)};
+                                           BRQ_MID(4, 3, 4, 4, false), BRQ_MID(2, 5, 5, 5, false), BRQ_MID(2, 4, 6, 6, false)};
 static const Variant pairs[MID_TILES] = {BRQ_MID(2, 1, 6, 6, true), BRQ_MID(2, 2, 6, 6, true), BRQ_MID(2, 3, 6, 6, true),
-                                         BRQ_MID(4, 3, 4, 4, true), BRQ_MID(2, 5, 6, 4, true)};
-static const Variant tall[2] = {BRQ_MID(2, 4, 6, 6, false), BRQ_MID(2, 4, 6, 4, true)};      // (pairs with 6 stages of A: 0.5 % slower to 1 % faster)
+                                         BRQ_MID(4, 3, 4, 4, true), BRQ_MID(2, 5, 6, 4, true),
+                                         BRQ_MID(2, 4, 6, 4, true)};       // (6 stages of A: 0.5 % slower to 1 % faster)
 #undef BRQ_MID
 using AnyK = void (*)(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int64_t, int, int, int);
 static const AnyK any_k[2][2] = {{k_gemm_any_k<false, 1>, k_gemm_any_k<true, 1>}, {k_gemm_any_k<false, 2>, k_gemm_any_k<true, 2>}};    // [MB - 1][bf16 out]
@@ -574,8 +574,8 @@ static const AnyK any_k[2][2] = {{k_gemm_any_k<false, 1>, k_gemm_any_k<true, 1>}
 bool mid_gemm_pairs(int tile, bool both_tiled, int64_t K) { return !both_tiled && (K > 1024 || tile > 2); }
 
 hipError_t setup_gemm_mid() {
-    for (int i = 0; i < 2 * MID_TILES + 2; ++i) {
-        const mid::Variant& v = i / 2 == MID_TALL ? mid::tall[i % 2] : (i % 2 ? mid::singles : mid::pairs)[i / 2];
+    for (int i = 0; i < 2 * MID_TILES; ++i) {
+        const mid::Variant& v = (i % 2 ? mid::singles : mid::pairs)[i / 2];
         for (mid::Kern k : {v.bf16, v.f32})
             if (hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                    mid::lds_bytes(v.na, v.mb, v.dw, v.da)); e != hipSuccess) return e;
@@ -611,8 +611,7 @@ hipError_t launch_gemm_any_k(const Operand& a, const Operand& w, int64_t M, int6
 
 hipError_t launch_gemm_mid(int tile, const Operand& a, const Operand& w, int64_t M, int64_t N, int64_t K, void* y,
                            bool out_bf16, int64_t ldy, hipStream_t s) {
-    const bool pair = mid_gemm_pairs(tile, a.tiled && w.tiled, K);
-    const mid::Variant& v = tile == MID_TALL ? mid::tall[pair] : (pair ? mid::pairs : mid::singles)[tile];
+    const mid::Variant& v = (mid_gemm_pairs(tile, a.tiled && w.tiled, K) ? mid::pairs : mid::singles)[tile];
     const int64_t tm = (M + 64 * v.mb - 1) / (64 * v.mb), tn = (N + 64 * v.na - 1) / (64 * v.na), T = tm * tn;
     const int lines = on_half_lines(y, N, ldy, out_bf16);
     hipLaunchKernelGGL((out_bf16 ? v.bf16 : v.f32), dim3((uint32_t)((T + 7) / 8 * 8)), dim3(256), mid::lds_bytes(v.na, v.mb, v.dw, v.da), s,

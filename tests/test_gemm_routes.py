@@ -20,7 +20,7 @@ def route(M, N, K, layout="tiled", dtype=BF16, **kw):
     ((16, 28672, 8192), "tiled", "stream"), ((100, 28672, 8192), "tiled", "128x128"), ((300, 28672, 8192), "tiled", "320x128"),
     ((300, 28672, 8192), "rowmajor", "320x128"), ((2048, 8192, 2048), "tiled", "256x256"), ((4096, 2048, 8192), "tiled", "128x256"),
     ((8192, 14336, 4096), "tiled", "256x256"), ((1000, 4096, 11008), "tiled", "128x128"), ((1000, 4096, 11008), "rowmajor", "192x128"),
-    ((2000, 4096, 11008), "rowmajor", "320x128"), ((192, 256, 4096), "tiled", "64x128"),
+    ((2000, 4096, 11008), "rowmajor", "256x128"), ((192, 256, 4096), "tiled", "64x128"),
     # ragged rows and columns, and K of one superstage, on the persistent kernel
     ((4100, 14344, 4096), "tiled", "256x256"), ((5000, 8200, 4096), "tiled", "256x256"), ((5000, 8200, 4096), "rowmajor", "256x256"),
     ((8192, 14336, 512), "rowmajor", "256x256"),
@@ -30,6 +30,20 @@ def route(M, N, K, layout="tiled", dtype=BF16, **kw):
     ((300, 520, 96), "rowmajor", "general"), ((40, 70, 256), "rowmajor", "general"), ((4, 70, 1056), "rowmajor", "skinny")])
 def test_route(shape, layout, want):
     assert route(*shape, layout=layout) == want
+
+
+@pytest.mark.parametrize("shape,layout,dtype,want", [
+    ((250, 28672, 8192), "rowmajor", BF16, "256x128"), ((1000, 8192, 4096), "rowmajor", BF16, "256x128"), ((3769, 2136, 1536), "rowmajor", BF16, "256x128"),
+    ((5924, 2584, 1536), "rowmajor", BF16, "256x128"), ((4642, 2744, 8064), "rowmajor", F32, "256x128"), ((4642, 2744, 8064), "rowmajor", BF16, "256x128"),
+    ((1194, 6374, 5504), "tiled", BF16, "256x128"), ((2840, 2623, 9344), "tiled", F32, "256x128"), ((4078, 1876, 5248), "tiled", BF16, "256x128"),
+    ((3913, 3746, 4224), "tiled", BF16, "256x128"), ((6046, 2568, 8192), "tiled", BF16, "256x128"), ((6046, 2568, 8192), "tiled", F32, "256x128"),
+    ((7459, 2176, 2560), "tiled", BF16, "256x128"),
+    # a round more; tiled, 192 x 256 in one round
+    ((834, 18856, 2048), "rowmajor", BF16, "320x128"), ((2300, 4096, 1536), "rowmajor", BF16, "192x256"), ((300, 28672, 8192), "tiled", BF16, "320x128"),
+    ((3776, 2080, 4224), "tiled", F32, "192x256")])
+def test_tall_tile(shape, layout, dtype, want):
+    """256 x 128 in place of 320 x 128 and 192 x 256 where it goes round the chip as often, in one round and in two."""
+    assert route(*shape, layout=layout, dtype=dtype) == want
 
 
 def test_few_rows():

@@ -1,5 +1,5 @@
 """Parity of every product kernel, by its name, where it can go wrong: the dispatcher sends a shape to the kernel that is
-the fastest there, so tests of small and ragged shapes through it reach two or three of the ten.  Bars as in
+the fastest there, so tests of small and ragged shapes through it reach two or three of the eleven.  Bars as in
 test_gpu_gemm.py; every kernel in every layout and both output types, with a guard right of column N - 1 and below row
 M - 1.  Kernels that take the K groups in the same order must agree bit for bit."""
 import numpy as np
@@ -13,7 +13,7 @@ from test_gpu_layout import to_tiled
 pytestmark = pytest.mark.gpu
 
 LAYOUTS = [("rowmajor", "rowmajor"), ("tiled", "tiled"), ("tiled", "rowmajor"), ("rowmajor", "tiled")]
-TILE = {r: tuple(int(d) for d in r.split("x")) for r in ("256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128")}
+TILE = {r: tuple(int(d) for d in r.split("x")) for r in ("256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128", "256x128")}
 
 
 @pytest.fixture(scope="module")
@@ -56,7 +56,7 @@ def check_route(brq, orc, route, M, N, K, layouts, rows=None, pads=(8, 0)):
 SHAPES = [(1, 3, 512), (-1, -1, 1024), (0, 5, 1536), (17, 128, 2560), (1, 1, 1024)]
 
 
-@pytest.mark.parametrize("route", ["64x128", "128x128", "192x128", "192x256", "320x128"])
+@pytest.mark.parametrize("route", ["64x128", "128x128", "192x128", "192x256", "320x128", "256x128"])
 def test_one_tile_kernels(brq, orc, route):
     tm, tn = TILE[route]
     for dm, dn, K in SHAPES:
@@ -66,7 +66,7 @@ def test_one_tile_kernels(brq, orc, route):
     check_route(brq, orc, route, 2 * tm + 33, 9 * tn + 2, 512, LAYOUTS[:2], pads=(1,))        # more than one tile on an XCD
 
 
-@pytest.mark.parametrize("route", ["64x128", "128x128", "192x128", "192x256", "320x128"])
+@pytest.mark.parametrize("route", ["64x128", "128x128", "192x128", "192x256", "320x128", "256x128"])
 @pytest.mark.parametrize("K", [640, 768, 896, 1152, 2688])   # the last window overlaps by 3, 2, 1, 3 and 3 stages
 def test_one_tile_kernels_k_of_128s(brq, orc, route, K):
     tm, tn = TILE[route]

@@ -1,5 +1,6 @@
-"""The product's tiles of 256 x 128, which it takes in place of 320 x 128 and 192 x 256 where they go round the chip as often: rows and columns around a tile's, K with and without an overlapping last window, mixed layouts, pitches on and off
-lines.  All product kernels but one sum in the same order, so the result is that of the kernel it takes the place of, bit for bit."""
+"""The product's tiles of 256 x 128, which it takes in place of 320 x 128 and 192 x 256 where they go round the chip as often: rows
+and columns around a tile's, K with and without an overlapping last window, mixed layouts, pitches on and off lines.  All product
+kernels but one sum in the same order, so the result is that of the kernel it takes the place of, bit for bit."""
 import pytest
 import torch
 
@@ -12,10 +13,6 @@ def brq():
     b.lib()
     assert torch.cuda.is_available(), "these tests need the GPU"
     return b
-
-
-def up(a, b):
-    return -(-a // b)
 
 
 # rows left of a tile of 256 (64 of them a wavefront's two MFMA tiles), columns left, K over 512
@@ -33,11 +30,10 @@ def test_tall_tile(brq, rows, cols, K, layouts):
         M = 256 * (tm - (rows > 0)) + rows
         N = 128 * (cus // tm - (cols > 0)) + cols
         for out in (torch.bfloat16, torch.float32):
-            route = brq.diag_mxfp4_gemm_route(M, N, K, *layouts, out, cus=cus) if M > 16 else ""
-            if route not in ("320x128", "192x256") or up(M, 256) * up(N, 128) > cus:
+            if M <= 16 or brq.diag_mxfp4_gemm_route(M, N, K, *layouts, out, cus=cus) != "256x128":
                 continue
             found += 1
-            print("case", M, N, K, layouts, out, route, flush=True)
+            print("case", M, N, K, layouts, out, flush=True)
             x, w = (torch.randn((n, K), generator=g, device="cuda") for n in (M, N))
             a, b = brq.rotate_quantize_fused(x, 32, layout=layouts[0]), brq.rotate_quantize_fused(w, 32, layout=layouts[1])
             for pad in (0, 3):
@@ -48,16 +44,19 @@ def test_tall_tile(brq, rows, cols, K, layouts):
     assert found, "no such shape goes this way"
 
 
-# over 320 x 128 in one and in two rounds, and over 192 x 256 in two
-@pytest.mark.parametrize("M,N,K", [(3913, 3746, 4224), (6046, 2568, 8192), (1194, 6374, 5504), (2840, 2623, 9344), (4078, 1876, 5248)])
-def test_tall_tile_tiled(brq, M, N, K):
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
+# tiled over 320 x 128 in one and in two rounds of 256 workgroups and over 192 x 256 in two, row-major over both in two; the route is bf16's
+@pytest.mark.parametrize("M,N,K,layout", [(3913, 3746, 4224, "tiled"), (6046, 2568, 8192, "tiled"), (1194, 6374, 5504, "tiled"), (2840, 2623, 9344, "tiled"),
+                                          (4078, 1876, 5248, "tiled"), (4642, 2744, 8064, "rowmajor"), (5924, 2584, 1536, "rowmajor"), (5063, 3200, 1536, "rowmajor")])
+def test_tall_tile_by_name(brq, M, N, K, layout):
+    assert brq.diag_mxfp4_gemm_route(M, N, K, layout, layout, torch.bfloat16) == "256x128"
+    lay = dict(a_layout=layout, w_layout=layout)
     g = torch.Generator(device="cuda").manual_seed(M + K)
-    a, b = (brq.rotate_quantize_fused(torch.randn((n, K), generator=g, device="cuda"), 32, layout="tiled") for n in (M, N))
+    a, b = (brq.rotate_quantize_fused(torch.randn((n, K), generator=g, device="cuda"), 32, layout=layout) for n in (M, N))
     for out in (torch.bfloat16, torch.float32):
-        print("case", M, N, K, out, brq.diag_mxfp4_gemm_route(M, N, K, "tiled", "tiled", out, cus=cus), flush=True)
+        print("case", M, N, K, layout, out, flush=True)
         for pad in (0, 3):
-            y, want = (torch.full((M + 1, N + pad), -7.0, dtype=out, device="cuda") for _ in range(2))
-            brq.mxfp4_gemm(*a, *b, out=y[:M, :N], out_dtype=out, a_layout="tiled", w_layout="tiled", M=M, N=N, K=K)
-            brq.diag_mxfp4_gemm_on("320x128", *a, *b, want[:M, :N], K, a_layout="tiled", w_layout="tiled")
-            assert torch.equal(y, want)
+            z, y, want = (torch.full((M + 1, N + pad), -7.0, dtype=out, device="cuda") for _ in range(3))
+            brq.mxfp4_gemm(*a, *b, out=z[:M, :N], out_dtype=out, **lay, M=M, N=N, K=K)
+            brq.diag_mxfp4_gemm_on("256x128", *a, *b, y[:M, :N], K, **lay)
+            brq.diag_mxfp4_gemm_on("320x128", *a, *b, want[:M, :N], K, **lay)
+            assert torch.equal(y, want) and torch.equal(z, want)

@@ -15,7 +15,7 @@ def brq():
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("route", ["256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128"])
+@pytest.mark.parametrize("route", ["256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128", "256x128"])
 def test_product_rows_on_and_off_lines(brq, route, dtype):
     """N of whole 128-byte lines, 16-byte chunks, and (one-tile kernels) anything; rows that begin on a line (pitch 512,
     column 0), on a 16-byte chunk (pitch 520, or column 8), on a half line (column 32 of bf16), and anywhere (pitch 517; an
