@@ -69,7 +69,7 @@ brq_status brq_diag_mxfp4_gemm_no_loads(const uint8_t* aq, const uint8_t* as, br
  * faster.
  */
 enum {
-    BRQ_GEMM_GENERAL = 0,        /* any shape */
+    BRQ_GEMM_GENERAL = 0,        /* any shape, straight from global memory */
     BRQ_GEMM_SKINNY = 1,         /* M <= 16, any K */
     BRQ_GEMM_STREAM = 2,         /* M <= 16, K of whole 512-element superstages */
     BRQ_GEMM_256x256 = 3,        /* the persistent kernel and its two output tiles (rows x columns) */
@@ -79,7 +79,8 @@ enum {
     BRQ_GEMM_192x128 = 7,
     BRQ_GEMM_192x256 = 8,
     BRQ_GEMM_320x128 = 9,
-    BRQ_GEMM_256x128 = 10
+    BRQ_GEMM_256x128 = 10,
+    BRQ_GEMM_ANY_K = 11          /* any shape with K of at least 256, through LDS */
 };
 
 /*

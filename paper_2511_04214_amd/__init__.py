@@ -494,7 +494,7 @@ def diag_mxfp4_gemm_no_loads(aq, as_, wq, ws, clock, **kw):
 
 
 # the kernels of mxfp4_gemm (include/brq_diag.h), by their numbers there
-GEMM_ROUTES = ("general", "skinny", "stream", "256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128", "256x128")
+GEMM_ROUTES = ("general", "skinny", "stream", "256x256", "128x256", "64x128", "128x128", "192x128", "192x256", "320x128", "256x128", "any_k")
 
 
 def diag_mxfp4_gemm_route(M, N, K, a_layout="rowmajor", w_layout="rowmajor", out_dtype=torch.float32, ldy=None, cus=256):

@@ -73,9 +73,9 @@ struct GemmShape {
     // K of whole 512-element superstages: tiled operands are zero-padded to that
     bool whole_k() const { return K % 512 == 0 || (a_tiled && w_tiled); }
 };
-enum GemmRoute { ROUTE_GENERAL, ROUTE_SKINNY, ROUTE_STREAM, ROUTE_256x256, ROUTE_128x256, ROUTE_ONE_TILE };   // + a tile's number
 constexpr int MID_TILES = 6;
-constexpr int GEMM_ROUTES = ROUTE_ONE_TILE + MID_TILES;
+enum GemmRoute { ROUTE_GENERAL, ROUTE_SKINNY, ROUTE_STREAM, ROUTE_256x256, ROUTE_128x256, ROUTE_ONE_TILE /* + a tile's number */,
+                 ROUTE_ANY_K = ROUTE_ONE_TILE + MID_TILES };
 bool gemm_route_supported(int route, const GemmShape& g);
 // The route of a product on a device of `cus` compute units: host arithmetic.
 int gemm_route(const GemmShape& g, int cus);

@@ -648,7 +648,8 @@ bool gemm_route_supported(int route, const GemmShape& g) {
         case ROUTE_STREAM: return g.M <= 16 && g.whole_k() && g.padded_k() < (int64_t(1) << 26);
         case ROUTE_256x256:
         case ROUTE_128x256: return tiled_gemm_supported(g.M, g.N, g.K, g.out_bf16, g.ldy, g.a_tiled && g.w_tiled);
-        default: return route >= ROUTE_ONE_TILE && route < GEMM_ROUTES && mid_gemm_supported(route - ROUTE_ONE_TILE, g);
+        case ROUTE_ANY_K: return g.K >= 256;
+        default: return route >= ROUTE_ONE_TILE && route < ROUTE_ANY_K && mid_gemm_supported(route - ROUTE_ONE_TILE, g);
     }
 }
 
@@ -669,6 +670,16 @@ static bool tall_tile(int route, const GemmShape& g, int cus) {
     return n == (route == TILE_192x256 ? rounds(192, 256) : rounds(320, 128)) && !(tiled && route == TILE_192x256 && n == 1);
 }
 
+// What no staged kernel takes: through LDS (k_gemm_any_k) from where its pairs of stages have something to hide behind, enough of
+// them or enough tiles.  us, row-major, weights in no cache, k_gemm_direct : k_gemm_any_k, either side of the line: M x N x K = 1000 x 512 x
+// 2080 10.9 : 12.3, 300 x 512 x 4000 18.2 : 18.7, 300 x 2048 x 1056 7.2 : 8.7, 128 x 8192 x 1056 10.0 : 9.8, 1000 x 4096 x 288 8.1 :
+// 7.3, 1000 x 8192 x 544 21.3 : 11.9, 128 x 2048 x 10976 84 : 43; of 64 rows 64 x 1024 x 1056 6.8 : 6.8, 64 x 1024 x 2080 12.0 : 9.0, 64 x
+// 16384 x 544 6.9 : 6.7.
+static bool any_k(const GemmShape& g) {
+    const int64_t rows = g.M <= 64 ? 64 : 128, tiles = (g.M + rows - 1) / rows * ((g.N + 127) / 128);
+    return g.K >= 256 && (g.K >= (g.M <= 64 ? 2048 : 4096) || tiles * g.K >= 65536);
+}
+
 int gemm_route(const GemmShape& g, int cus) {
     // Up to 16 rows: the weights are streamed (k_gemm_smallm).  The staged 64 x 128 kernel and the K-split one (ROUTE_SKINNY, which
     // sums in another order) against it, us, weights in no cache, 1 / 16 rows, streaming : 64 x 128 : K-split:
@@ -681,25 +692,17 @@ int gemm_route(const GemmShape& g, int cus) {
     if (gemm_route_supported(ROUTE_STREAM, g)) return ROUTE_STREAM;
     const int t = g.M > 16 || g.K % 512 == 0 ? pick_tile(g, cus) : -1;
     if (tall_tile(t, g, cus)) return TALL_TILE;
-    return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : ROUTE_GENERAL;
+    return t >= 0 ? t : g.M <= 16 ? ROUTE_SKINNY : any_k(g) ? ROUTE_ANY_K : ROUTE_GENERAL;
 }
 
 hipError_t launch_gemm_route(int route, const Operand& a, const Operand& w, const GemmShape& g, void* y, hipStream_t s) {
     const int64_t M = g.M, N = g.N, K = g.K;
     switch (route) {
-        case ROUTE_GENERAL: {
-            // Through LDS from where its pairs of stages have something to hide behind: enough of them, or enough tiles.  us,
-            // row-major, weights in no cache, k_gemm_direct : k_gemm_any_k, either side of the line: M x N x K = 1000 x 512 x 2080
-            // 10.9 : 12.3, 300 x 512 x 4000 18.2 : 18.7, 300 x 2048 x 1056 7.2 : 8.7, 128 x 8192 x 1056 10.0 : 9.8, 1000 x 4096 x 288
-            // 8.1 : 7.3, 1000 x 8192 x 544 21.3 : 11.9, 128 x 2048 x 10976 84 : 43; of 64 rows 64 x 1024 x 1056 6.8 : 6.8, 64 x
-            // 1024 x 2080 12.0 : 9.0, 64 x 16384 x 544 6.9 : 6.7.
-            const int64_t tiles = (M + (M <= 64 ? 63 : 127)) / (M <= 64 ? 64 : 128) * ((N + 127) / 128);
-            if (K >= 256 && (K >= (M <= 64 ? 2048 : 4096) || tiles * K >= 65536)) return launch_gemm_any_k(a, w, M, N, K, y, g.out_bf16, g.ldy, s);
-            const dim3 grid((uint32_t)((N + 63) / 64), (uint32_t)((M + 63) / 64));
-            hipLaunchKernelGGL(k_gemm_direct, grid, dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes, w.scales,
-                               (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);
+        case ROUTE_GENERAL:
+            hipLaunchKernelGGL(k_gemm_direct, dim3((uint32_t)((N + 63) / 64), (uint32_t)((M + 63) / 64)), dim3(256), 0, s, a.codes, a.scales,
+                               (int)a.tiled, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);
             return hipGetLastError();
-        }
+        case ROUTE_ANY_K: return launch_gemm_any_k(a, w, M, N, K, y, g.out_bf16, g.ldy, s);
         case ROUTE_SKINNY:
             hipLaunchKernelGGL(k_gemm_skinny, dim3((uint32_t)((N + 15) / 16)), dim3(256), 0, s, a.codes, a.scales, (int)a.tiled, w.codes,
                                w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)g.out_bf16, g.ldy);

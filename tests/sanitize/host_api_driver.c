@@ -49,7 +49,7 @@ int main(void) {
     EXPECT(brq_diag_mxfp4_gemm_route(BRQ_LAYOUT_TILED, BRQ_LAYOUT_TILED, 8192, 14336, 4096, BRQ_BF16, 14336, 256, NULL), BRQ_ERR_NULL);
     EXPECT(brq_diag_mxfp4_gemm_route(BRQ_LAYOUT_TILED, (brq_layout)7, 8192, 14336, 4096, BRQ_BF16, 14336, 256, &route), BRQ_ERR_LAYOUT);
     EXPECT(brq_diag_mxfp4_gemm_on(-1, p, p, BRQ_LAYOUT_ROWMAJOR, p, p, BRQ_LAYOUT_ROWMAJOR, 128, 256, 512, p, BRQ_F32, 256, NULL), BRQ_ERR_SHAPE);
-    EXPECT(brq_diag_mxfp4_gemm_on(BRQ_GEMM_256x128 + 1, p, p, BRQ_LAYOUT_ROWMAJOR, p, p, BRQ_LAYOUT_ROWMAJOR, 128, 256, 512, p, BRQ_F32, 256, NULL), BRQ_ERR_SHAPE);
+    EXPECT(brq_diag_mxfp4_gemm_on(BRQ_GEMM_ANY_K + 1, p, p, BRQ_LAYOUT_ROWMAJOR, p, p, BRQ_LAYOUT_ROWMAJOR, 128, 256, 512, p, BRQ_F32, 256, NULL), BRQ_ERR_SHAPE);
     EXPECT(brq_diag_mxfp4_gemm_on(BRQ_GEMM_STREAM, p, p, BRQ_LAYOUT_ROWMAJOR, p, p, BRQ_LAYOUT_ROWMAJOR, 17, 256, 512, p, BRQ_F32, 256, NULL), BRQ_ERR_SHAPE);
     for (int s = 0; s < 12; ++s)
         if (strlen(brq_strerror((brq_status)s)) == 0) return 1;

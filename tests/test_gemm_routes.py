@@ -26,8 +26,9 @@ def route(M, N, K, layout="tiled", dtype=BF16, **kw):
     ((8192, 14336, 512), "rowmajor", "256x256"),
     # short K of row-major operands: single stages of 128 x 128, two workgroups a CU
     ((4000, 8192, 512), "rowmajor", "128x128"), ((787, 17600, 512), "rowmajor", "128x128"), ((1100, 1000, 512), "rowmajor", "64x128"),
-    # N or K that no staged kernel takes
-    ((300, 520, 96), "rowmajor", "general"), ((40, 70, 256), "rowmajor", "general"), ((4, 70, 1056), "rowmajor", "skinny")])
+    # N or K that no staged kernel takes, on either side of where LDS pays
+    ((300, 520, 96), "rowmajor", "general"), ((40, 70, 256), "rowmajor", "general"), ((4, 70, 1056), "rowmajor", "skinny"),
+    ((300, 2048, 1056), "rowmajor", "general"), ((1000, 8192, 544), "rowmajor", "any_k"), ((64, 1024, 2080), "rowmajor", "any_k")])
 def test_route(shape, layout, want):
     assert route(*shape, layout=layout) == want
 
@@ -61,7 +62,7 @@ def test_every_kernel_is_taken_somewhere():
     for layout in ("rowmajor", "tiled"):
         for M in (1, 16, 40, 130, 200, 300, 500, 600, 1000, 1100, 2048, 4096, 8192):
             for N in (128, 1024, 2048, 4096, 8192, 28672):
-                for K in (96, 512, 2048, 4096, 8192, 11008):
+                for K in (96, 512, 2048, 2080, 4096, 8192, 11008):
                     seen.setdefault(route(M, N, K, layout=layout), set()).add(layout)
     assert set(seen) == set(brq.GEMM_ROUTES)
 
@@ -86,7 +87,7 @@ def test_long_k_stays_on_a_staged_kernel(layout):
     for K in (2 ** 24 + 512, 2 ** 25, 2 ** 26 - 512):
         for M in (17, 100, 128):
             assert route(M, 130, K, layout=layout) in ("64x128", "128x128")
-    assert route(17, 130, 2 ** 26, layout=layout) == "general"
+    assert route(17, 130, 2 ** 26, layout=layout) == "any_k"
     assert route(300, 130, 2 ** 25 + 512, layout=layout) in ("64x128", "128x128", "192x128")
 
 

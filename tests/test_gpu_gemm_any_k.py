@@ -27,7 +27,7 @@ def test_any_k(brq, M, N, Ks):
         for la, lw in (("rowmajor", "rowmajor"), ("tiled", "rowmajor"), ("rowmajor", "tiled")):
             for dt, pad in ((torch.float32, 0), (torch.bfloat16, 3), (torch.bfloat16, 32)):
                 print("case", M, N, K, la, lw, dt, pad, flush=True)
-                assert la != lw or brq.diag_mxfp4_gemm_route(M, N, K, la, lw, dt, ldy=N + pad) == "general"
+                assert la != lw or brq.diag_mxfp4_gemm_route(M, N, K, la, lw, dt, ldy=N + pad) == "any_k"
                 buf = torch.full((M + 1, N + pad), -7.0, dtype=dt, device="cuda")
                 brq.mxfp4_gemm(*q["a", la], *q["w", lw], out=buf[:M, :N], a_layout=la, w_layout=lw, M=M, N=N, K=K)
                 assert torch.equal(buf[:M, :N], want.to(dt))

@@ -1,5 +1,5 @@
 """Parity of every product kernel, by its name, where it can go wrong: the dispatcher sends a shape to the kernel that is
-the fastest there, so tests of small and ragged shapes through it reach two or three of the eleven.  Bars as in
+the fastest there, so tests of small and ragged shapes through it reach two or three of the twelve.  Bars as in
 test_gpu_gemm.py; every kernel in every layout and both output types, with a guard right of column N - 1 and below row
 M - 1.  Kernels that take the K groups in the same order must agree bit for bit."""
 import numpy as np
@@ -109,10 +109,18 @@ def test_kernels_for_any_k(brq, orc):
         check_route(brq, orc, "skinny", 13, 67, K, LAYOUTS, pads=(3,))
 
 
+# 64 and 128 rows a tile; one row or column past, one short of and several tiles; 8 down to 1 groups in the last pair of stages
+@pytest.mark.parametrize("M,N", [(64, 129), (17, 70), (65, 127), (129, 131), (300, 260)])
+def test_any_k_kernel(brq, orc, M, N):
+    for K in (256, 288, 480, 512, 576, 672, 800, 864, 928, 1056):
+        y = check_route(brq, orc, "any_k", M, N, K, LAYOUTS, pads=(8, 3))
+        assert np.array_equal(y, check_route(brq, orc, "general", M, N, K, LAYOUTS[:1], pads=(0,)))
+
+
 def test_staged_kernels_agree_bit_for_bit(brq, orc):
     """One shape on every kernel that sums in the order of the stages."""
     M, N, K = 330, 264, 1536
-    ys = [check_route(brq, orc, r, M, N, K, LAYOUTS[:2], pads=(0,)) for r in ["general"] + sorted(TILE)]
+    ys = [check_route(brq, orc, r, M, N, K, LAYOUTS[:2], pads=(0,)) for r in ["general", "any_k"] + sorted(TILE)]
     for y in ys[1:]:
         assert np.array_equal(y, ys[0])
 
@@ -120,7 +128,7 @@ def test_staged_kernels_agree_bit_for_bit(brq, orc):
 def test_a_kernel_refuses_what_it_does_not_take(brq):
     q = lambda r, K: (torch.zeros((r, K // 2), dtype=torch.uint8, device="cuda"), torch.zeros((r, K // 32), dtype=torch.uint8, device="cuda"))
     for route, M, N, K in (("skinny", 17, 64, 512), ("stream", 17, 64, 512), ("stream", 4, 64, 544), ("256x256", 300, 250, 512),
-                           ("128x256", 300, 256, 544), ("64x128", 64, 64, 544), ("320x128", 64, 64, 256)):
+                           ("128x256", 300, 256, 544), ("64x128", 64, 64, 544), ("320x128", 64, 64, 256), ("any_k", 64, 64, 224)):
         out = torch.full((M, N), -7.0, dtype=torch.float32, device="cuda")
         with pytest.raises(brq.BrqError) as e:
             brq.diag_mxfp4_gemm_on(route, *q(M, K), *q(N, K), out, K)
