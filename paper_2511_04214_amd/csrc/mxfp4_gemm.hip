@@ -670,14 +670,18 @@ static bool tall_tile(int route, const GemmShape& g, int cus) {
     return n == (route == TILE_192x256 ? rounds(192, 256) : rounds(320, 128)) && !(tiled && route == TILE_192x256 && n == 1);
 }
 
-// What no staged kernel takes: through LDS (k_gemm_any_k) from where its pairs of stages have something to hide behind, enough of
-// them or enough tiles.  us, row-major, weights in no cache, k_gemm_direct : k_gemm_any_k, either side of the line: M x N x K = 1000 x 512 x
-// 2080 10.9 : 12.3, 300 x 512 x 4000 18.2 : 18.7, 300 x 2048 x 1056 7.2 : 8.7, 128 x 8192 x 1056 10.0 : 9.8, 1000 x 4096 x 288 8.1 :
-// 7.3, 1000 x 8192 x 544 21.3 : 11.9, 128 x 2048 x 10976 84 : 43; of 64 rows 64 x 1024 x 1056 6.8 : 6.8, 64 x 1024 x 2080 12.0 : 9.0, 64 x
-// 16384 x 544 6.9 : 6.7.
+// What no staged kernel takes: through LDS (k_gemm_any_k) from where its pairs of stages have something to hide behind.  Up to 64 rows
+// that is enough of them or enough tiles; above, enough of them or enough tiles of 32 x 32, of which k_gemm_direct's wavefronts have
+// one each (counted in tiles of 128 x 128 a few columns pass for many).  k_gemm_any_k's time over k_gemm_direct's, 1002 shapes of
+// more than 64 rows, weights in no cache / in the L2, by tiles of 32 x 32 and K, on either side of the line: 256 x 2500 0.89 / 1.28,
+// 256 x 5000 0.66 / 0.93; 512 x 1700 0.83 / 1.19, 512 x 2400 0.74 / 0.85; 1024 x 860 0.90 / 0.97, 1024 x 1200 0.73 / 0.85; 4096 x 300
+// 0.85 / 0.90; K from 4096 below the line 0.71 / 1.07.  us, either kernel, weights in the L2: 15897 x 2 x 672 4.9 : 7.6, 4182 x 5 x 3872 14.0 :
+// 17.5, 141 x 5692 x 1088 7.4 : 9.3; in no cache 2000 x 4096 x 10976 656 : 88, 128 x 2048 x 10976 84 : 43, 1000 x 8192 x 544 21.3 : 11.9.  Of
+// 64 rows (198 shapes, none slower beyond the line) 64 x 1024 x 1056 6.8 : 6.8, 64 x 1024 x 2080 12.0 : 9.0, 64 x 16384 x 544 6.9 : 6.7.
 static bool any_k(const GemmShape& g) {
-    const int64_t rows = g.M <= 64 ? 64 : 128, tiles = (g.M + rows - 1) / rows * ((g.N + 127) / 128);
-    return g.K >= 256 && (g.K >= (g.M <= 64 ? 2048 : 4096) || tiles * g.K >= 65536);
+    if (g.K < 256) return false;
+    if (g.M <= 64) return g.K >= 2048 || (g.N + 127) / 128 * g.K >= 65536;
+    return g.K >= 4096 || (double)((g.M + 31) / 32) * (double)((g.N + 31) / 32) * (double)g.K >= (double)(1 << 20);
 }
 
 int gemm_route(const GemmShape& g, int cus) {

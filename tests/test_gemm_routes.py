@@ -28,7 +28,9 @@ def route(M, N, K, layout="tiled", dtype=BF16, **kw):
     ((4000, 8192, 512), "rowmajor", "128x128"), ((787, 17600, 512), "rowmajor", "128x128"), ((1100, 1000, 512), "rowmajor", "64x128"),
     # N or K that no staged kernel takes, on either side of where LDS pays
     ((300, 520, 96), "rowmajor", "general"), ((40, 70, 256), "rowmajor", "general"), ((4, 70, 1056), "rowmajor", "skinny"),
-    ((300, 2048, 1056), "rowmajor", "general"), ((1000, 8192, 544), "rowmajor", "any_k"), ((64, 1024, 2080), "rowmajor", "any_k")])
+    ((300, 2048, 1056), "rowmajor", "general"), ((1000, 8192, 544), "rowmajor", "any_k"), ((64, 1024, 2080), "rowmajor", "any_k"),
+    ((15897, 2, 672), "rowmajor", "general"), ((4182, 5, 3872), "rowmajor", "general"), ((141, 5692, 1088), "rowmajor", "general"),
+    ((2000, 520, 2080), "rowmajor", "any_k"), ((141, 28672, 1088), "rowmajor", "any_k"), ((300, 7, 4128), "rowmajor", "any_k")])
 def test_route(shape, layout, want):
     assert route(*shape, layout=layout) == want
 
