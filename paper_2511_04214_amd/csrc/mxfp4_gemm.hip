@@ -149,9 +149,9 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 // Tiled weights: a row's 64 bytes of a stage lie between those of its neighbours, so lane (r, h) loads its fragments
 // directly, 2 KB by two instructions.  Plain loads: one instruction takes half of every cache line it touches and the next
 // one the other half, and a streaming load does not leave the line in the cache for it (the weights would cross HBM twice).
-// Row-major weights (ROWS): a fragment is 32 rows x 32 bytes, a quarter of each of 32 lines, and by the time the fourth
-// instruction asks for the last quarter the other wavefronts' lines have pushed it out.  There an instruction loads 8
-// rows x 128 bytes, whole lines and once, and the wavefront turns the four of two stages round in 4 KB of LDS that no other
+// Row-major weights (without ROWS they are loaded like that too): a fragment is 32 rows x 32 bytes, a quarter of each of 32
+// lines, and by the time the fourth instruction asks for the last quarter the other wavefronts' lines have pushed it out.  With
+// ROWS an instruction loads 8 rows x 128 bytes, whole lines and once, and the wavefront turns the four of two stages round in 4 KB of LDS that no other
 // touches (row i's 16-byte chunk c at c ^ (i & 7): 8 lanes write a row, 8 rows' chunks are read, all banks either way).  A
 // wavefront's LDS operations are done in order, so nothing waits there but for the data.  us, weights in no cache, 1 row,
 // each lane its fragments -> now: 28672 x 8192 36.1 -> 30.5 (tiled weights 24), 14336 x 4096 10.0 -> 9.3; the one-launch call, 28672 x
@@ -159,16 +159,16 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 // memory-side cache are then fetched past it (both calls, 15 rows against the same 23808 x 4096: 13.4 : 14.9).
 template <bool ROWS>
 struct WeightRows {
-    const uint8_t* codes;                               // tiled: this lane's row.  ROWS: the first row (uniform), `off` from there
+    const uint8_t* codes;                               // this lane's row.  ROWS: the first row (uniform), `off` from there
     const uint8_t* scales;                              // this lane's row
     uint32_t cstep, sstep, off[4];
     uint8_t *wr, *rd;                                   // ROWS: this lane's place in the 4 KB
     uint32_t sw;
     int h;
-    __device__ __forceinline__ WeightRows(const uint8_t* wq, const uint8_t* ws, int n0, int N, int K, int lane, uint8_t* turn_lds) {
+    __device__ __forceinline__ WeightRows(const uint8_t* wq, const uint8_t* ws, bool tiled, int n0, int N, int K, int lane, uint8_t* turn_lds) {
         const int r = lane & 31;
         h = lane >> 5;
-        const RowView v(wq, ws, !ROWS, min(n0 + r, N - 1), K);
+        const RowView v(wq, ws, tiled, min(n0 + r, N - 1), K);
         scales = v.scales;
         cstep = v.cstep;
         sstep = v.sstep;
@@ -199,7 +199,7 @@ struct WeightRows {
             sc = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(scales + (int64_t)ss * sstep));
         }
     }
-    // ROWS: the fragments of steps 4 half .. 4 half + 3 (stage 2 half + t, step j at 2 t + j).  (Tiled: c[step].)
+    // ROWS: the fragments of steps 4 half .. 4 half + 3 (stage 2 half + t, step j at 2 t + j).  (Without: c[step].)
     __device__ __forceinline__ void turn(const v4i (&c)[8], int half, v4i (&f)[4]) const {
 #pragma unroll
         for (int q = 0; q < 4; ++q) *reinterpret_cast<v4i*>(wr + q * 1024) = c[4 * half + q];
@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(256) k_gemm_smallm(const uint8_t* __restrict__
     const int nss = (K + 511) / 512;                    // tiled operands are zero-padded to whole superstages
     const int64_t Kp = (int64_t)nss * 512;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-    const WeightRows<ROWS> vw(wq, ws, n0, N, K, lane, lds + SETS * BUF + wave * 4096);
+    const WeightRows<ROWS> vw(wq, ws, !ROWS, n0, N, K, lane, lds + SETS * BUF + wave * 4096);
 
     const uint32_t a_cstep = a_tiled ? 4096u : 64u, a_sstep = a_tiled ? 1024u : 16u;
     auto row_off_c = [&](int row) -> uint32_t {
@@ -369,7 +369,7 @@ constexpr int decode_fused_lds_bytes(int64_t K, bool rows) { return decode_fused
 template <bool IN_BF16, bool ROWS, int SETS, int TAIL>
 __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restrict__ x, int64_t ldx, const int8_t* __restrict__ signs,
                                                            const uint8_t* __restrict__ wq, const uint8_t* __restrict__ ws,
-                                                           int M, int N, int K, void* __restrict__ y, int out_bf16,
+                                                           int w_tiled, int M, int N, int K, void* __restrict__ y, int out_bf16,
                                                            int64_t ldy, int nw) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode_fused(const void* __restric
     const int n0 = (blockIdx.x * nw + (wave & (nw - 1))) * 32;      // (from wavefront nw on: another's rows, to no use)
     const int nss = K / 512;
     uint8_t* const scl = lds + (K / 128) * 1024;          // scales behind the codes
-    const WeightRows<ROWS> vw(wq, ws, n0, N, K, lane, lds + decode_fused_operand_bytes(K) + wave * 4096);
+    const WeightRows<ROWS> vw(wq, ws, !ROWS && w_tiled, n0, N, K, lane, lds + decode_fused_operand_bytes(K) + wave * 4096);
     constexpr int D = SETS - 1;
     v4i c[SETS][8], s4[SETS];
     // ---- prologue: the online step on all M rows.  A wavefront takes 64 chunks (512 elements: one
@@ -548,9 +548,9 @@ static const SmallmKern smallm_few[2][FEW] = {BRQ_FEW(false), BRQ_FEW(true)};   
 static const SmallmKern smallm_many[2][MANY] = {BRQ_MANY(false), BRQ_MANY(true)};
 #undef BRQ_FEW
 #undef BRQ_MANY
-using DecodeKern = void (*)(const void*, int64_t, const int8_t*, const uint8_t*, const uint8_t*, int, int, int, void*, int, int64_t, int);
+using DecodeKern = void (*)(const void*, int64_t, const int8_t*, const uint8_t*, const uint8_t*, int, int, int, int, void*, int, int64_t, int);
 #define BRQ_DECODE(BF16, ROWS) {k_gemm_decode_fused<BF16, ROWS, FEW, 0>, k_gemm_decode_fused<BF16, ROWS, FEW, 1>, k_gemm_decode_fused<BF16, ROWS, FEW, 2>}
-static const DecodeKern decode_kern[2][2][FEW] = {{BRQ_DECODE(false, false), BRQ_DECODE(false, true)},   // [x bf16][weights row-major]
+static const DecodeKern decode_kern[2][2][FEW] = {{BRQ_DECODE(false, false), BRQ_DECODE(false, true)},   // [x bf16][row-major weights turned round]
                                                   {BRQ_DECODE(true, false), BRQ_DECODE(true, true)}};
 #undef BRQ_DECODE
 
@@ -578,8 +578,12 @@ hipError_t launch_gemm_decode_fused(const void* x, bool in_bf16, int64_t M, int6
     int cus = 0;
     if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
     const int nw = streaming_waves(N, cus);
-    hipLaunchKernelGGL(decode_kern[in_bf16][!w.tiled][K / 512 % FEW], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256),
-                       decode_fused_lds_bytes(K, !w.tiled), s, x, ldx, signs, w.codes, w.scales, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy, nw);
+    // Up to 32 columns no other wavefront's lines push a row-major line out between its quarters, and turning it round is only in the
+    // way: fragments.  us, whole lines -> fragments: 1 row, 5 x 4096 5.4 -> 4.7, 2 rows, 3 x 9216 10.8 -> 9.4, 8 rows, 8 x 4096 10.1 -> 9.3 (111 shapes
+    // 5 % faster); of 33 to 128 columns (31 shapes) whole lines are 6 % faster.
+    const bool turned = !w.tiled && N > 32;
+    hipLaunchKernelGGL(decode_kern[in_bf16][turned][K / 512 % FEW], dim3((uint32_t)((N + 32 * nw - 1) / (32 * nw))), dim3(256),
+                       decode_fused_lds_bytes(K, turned), s, x, ldx, signs, w.codes, w.scales, (int)w.tiled, (int)M, (int)N, (int)K, y, (int)out_bf16, ldy, nw);
     return hipGetLastError();
 }
 
