@@ -91,18 +91,19 @@ def lib():
 
 
 def _load_native(L):
-    """The compiled marshalling bound to the entry points of L, or None (and a warning) where it does not fit this torch."""
+    """The compiled marshalling bound to the entry points of L, or None (and a warning) where it does not fit this torch or this file."""
     try:
         from . import _binding
         if getattr(_binding, "TORCH", None) != str(torch.__version__):
             raise ImportError("built against another torch than %s" % torch.__version__)
-    except ImportError as e:
+        bind, bind_stats = _binding.bind, _binding.bind_stats
+    except (ImportError, AttributeError) as e:              # (AttributeError: built before the call came)
         warnings.warn("the compiled part of the binding is not used, calls take some us longer: %s" % e, RuntimeWarning, stacklevel=3)
         return None
-    _binding.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+    bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.brq_rotate_quantize_fused, L.brq_swiglu_rotate_quantize_fused, L.brq_matrix_rotate_quantize_fused, L.brq_mxfp4_gemm,
         L.brq_rotate_quantize_gemm_fused)))
-    _binding.bind_stats(*(ctypes.cast(f, ctypes.c_void_p).value for f in (L.brq_block_stats, L.brq_block_stats_summary)))
+    bind_stats(*(ctypes.cast(f, ctypes.c_void_p).value for f in (L.brq_block_stats, L.brq_block_stats_summary)))
     return _binding
 
 

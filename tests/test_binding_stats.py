@@ -1,5 +1,8 @@
 """The statistics' calls through the binding's compiled part and through Python: the same results in the caller's own buffers or new
 ones, the same refusals."""
+import sys
+import types
+
 import pytest
 import torch
 
@@ -16,6 +19,18 @@ def test_left_to_python():
         n.bind_stats(1)
     with pytest.raises(ValueError):
         n.bind_stats(0, 0)
+
+
+def test_the_library_does_without_a_compiled_part_built_before_these_calls(monkeypatch):
+    brq.lib()
+    older = types.SimpleNamespace(TORCH=str(torch.__version__), bind=lambda *a: None)
+    monkeypatch.setattr(brq, "_lib", None)
+    monkeypatch.setattr(brq, "_native", None)
+    monkeypatch.setattr(brq, "_binding", older, raising=False)
+    monkeypatch.setitem(sys.modules, brq.__name__ + "._binding", older)
+    with pytest.warns(RuntimeWarning, match="compiled part"):
+        brq.lib()
+    assert brq._native is None and brq.operand_bytes(64, 512) == (16384, 1024)
 
 
 @pytest.mark.gpu
