@@ -155,8 +155,9 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(const uint8_t* __restrict__
 // touches (row i's 16-byte chunk c at c ^ (i & 7): 8 lanes write a row, 8 rows' chunks are read, all banks either way).  A
 // wavefront's LDS operations are done in order, so nothing waits there but for the data.  us, weights in no cache, 1 row,
 // each lane its fragments -> now: 28672 x 8192 36.1 -> 30.5 (tiled weights 24), 14336 x 4096 10.0 -> 9.3; the one-launch call, 28672 x
-// 8192 36.6 -> 30.2, 21752 x 10240 42.2 -> 28.9.  No streaming hint here either: with it 28.5, 8.8, 28.1, 27.3, but weights that lie in the
-// memory-side cache are then fetched past it (both calls, 15 rows against the same 23808 x 4096: 13.4 : 14.9).
+// 8192 36.6 -> 30.2, 21752 x 10240 42.2 -> 28.9.  No streaming hint here either: it fetches weights past the memory-side cache that lie there.
+// Both calls, 240 shapes of 8 to 230 MB of weights, 1 to 16 rows, the hint's time over that without: weights in no cache, up to 32 MB 0.99,
+// above 0.96 (0.92 to 1.00; the four above 28.5, 8.8, 28.1, 27.3); in the memory-side cache 1.01, above 32 MB 1.08 (0.96 to 1.30).
 template <bool ROWS>
 struct WeightRows {
     const uint8_t* codes;                               // this lane's row.  ROWS: the first row (uniform), `off` from there

@@ -1,4 +1,4 @@
-"""Seeded sweeps over shapes, layouts, types and pitches: the product's dispatcher picks one of ten
+"""Seeded sweeps over shapes, layouts, types and pitches: the product's dispatcher picks one of twelve
 kernels from M, N, K and the operand layouts, the row-wise entry points one of four from B, K and the
 pitches; the hand-picked shapes of the other test files sit on the known boundaries, these draw the
 rest of the space.  Same bars as there: codes and scales bit for bit (by the interval rule where the
